@@ -9,7 +9,7 @@
 //     experts is left to combine's first stage (order-fixed, no float atomics).
 //   Shared experts: the same two kernels over all T rows of x with the shared weights.
 //
-// bf16 path: LDS-tiled MFMA (v_mfma_f32_32x32x16_bf16), f32 accumulation.  Weights are
+// bf16 path: LDS-tiled MFMA, f32 accumulation.  Weights are
 // K-contiguous ([out][in]), activations are K-contiguous rows, so both MFMA operands are read
 // from LDS as 16-byte K-runs and no transpose is needed.
 // f32 path: plain f32 FMA kernel for small parity-sized layers.
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs first, c
 
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA kernel, main variant (prefill-shaped layers).  Block = 256 threads = 4 waves (2 x 2),
-// block tile 256 x 256 x 64, wave tile 128 x 128 = 4 x 4 MFMA tiles of 32 x 32 (256 accumulator
+// block tile 256 x 256 x 64, wave tile 128 x 128 = 8 x 8 MFMA tiles of 16 x 16 (256 accumulator
 // registers per lane, one wave per SIMD, one block per CU).
 //
 // Persistent blocks.  With one block per CU nothing overlaps a tile's fixed costs (finding its
@@ -548,12 +548,16 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs first, c
 // lane's choice of global chunk.  (LDS has 64 banks = 256 bytes per clock: two 128-byte rows share
 // a bank line, so 16 consecutive rows x one chunk must cover the 16 slots of a line.)
 //
-// Schedule.  With one wave per SIMD nothing hides an instruction clump, so a K step (16 MFMAs) is
-// written as 8 groups of {2 MFMAs, 1 LDS fragment read for the next K step, 1 tile load} pinned in
-// source order: the matrix pipe keeps running while the other pipes are fed.  The steps of a K
-// tile are rotated to 1, 2, wait, 3, 0': the block-wide wait for the next K tile sits before step
-// 3, so the barrier and the first fragment reads of that tile run under 16 MFMAs.  Step 0 of an
-// output tile multiplies into a zero constant, so accumulators are never cleared.  No branch sits
+// Matrix instruction.  v_mfma_f32_16x16x32_bf16 rather than 32x32x16: the clock under matrix load is power-limited, and
+// the 16 x 16 form reads and writes half as many accumulator bytes per product.  Measured with nothing but products and
+// fragment reads on normally distributed operands: 1900 TFLOP/s against 1680 (on zeros both 2450).  Here the clock went
+// from 1.70 to 1.95 - 2.05 GHz and the kernel is bound by the operand stream into LDS instead.
+//
+// Schedule.  With one wave per SIMD nothing hides an instruction clump, so a K step of 32 (64 MFMAs) is written as 16
+// groups of {4 MFMAs, up to 2 LDS fragment reads for the next K step, up to 2 tile loads} pinned in source order: the
+// matrix pipe keeps running while the other pipes are fed.  The block-wide wait for the next K tile sits between the two
+// steps of a K tile, whose last fragments have been read by then; the next tile's step-0 fragments are read under
+// step 1.  Step 0 of an output tile multiplies into a zero constant, so accumulators are never cleared.  No branch sits
 // inside a K tile (each would make the register allocator shuffle the 256 accumulators).
 //
 // Epilogue.  The MFMA operands are swapped (weights as the row operand), so a lane holds 4
@@ -561,8 +565,8 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs first, c
 // idle stage (the region its own next loads will fill, so no block barrier is needed), 32 rows x
 // 64 columns at a time, and leave as 16-byte stores of whole 128-byte row segments.  With SWIGLU
 // the 128 B-rows of a wave's half tile are [gate c..c+31 | up c..c+31 | gate c+32..c+63 |
-// up c+32..c+63], so MFMA row blocks (0,1) and (2,3) pair gate with up and the activation is
-// applied in registers.
+// up c+32..c+63], so MFMA row blocks (0,1) and (2,3), (4,5) and (6,7) pair gate with up and the
+// activation is applied in registers.
 namespace t256 {
 constexpr int BM = 256, BN = 256, BK = 64;
 constexpr int A_BYTES = BM * BK * 2;             // 32 KiB
@@ -581,6 +585,17 @@ __device__ __forceinline__ void load_to_lds_16(const char* base, unsigned off, u
 __device__ __forceinline__ void load_to_lds_16(const char* src, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
 }
+// acc (16 x 16) += b (16 weight rows x 32 K) * a (16 token rows x 32 K)^T, accumulators in the accumulation registers.
+// Written as assembly because the compiler, given the builtin, moves the 64 accumulator quads between the two register
+// files; it cannot see that these are matrix instructions, so whoever reads acc has to leave the wait states itself
+// (mfma_results_ready).
+__device__ __forceinline__ void mfma16(f32x4& acc, const bf16x8& b, const bf16x8& a) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
+}
+__device__ __forceinline__ void mfma16_first(f32x4& acc, const bf16x8& b, const bf16x8& a) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(b), "v"(a));
+}
+__device__ __forceinline__ void mfma_results_ready() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 // every load of this wave has landed and its LDS reads have returned; then the same for the block
 __device__ __forceinline__ void wait_all_and_barrier() {
   asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -733,11 +748,11 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
   const char* a_base = static_cast<const char*>(a.A);
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
   const unsigned lds_w = __builtin_amdgcn_readfirstlane(lds0 + wave * 8192);
-  // fragment read offsets inside a 32-row block for the four 16-wide K steps of a tile
-  int foff[4];
+  // fragment read offsets inside a 16-row block for the two 32-wide K steps of a tile
+  int foff[2];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk)
-    foff[kk] = (lane & 31) * 128 + (((2 * kk + (lane >> 5)) ^ ((lane >> 1) & 7)) * 16);
+  for (int kk = 0; kk < 2; ++kk)
+    foff[kk] = (lane & 15) * 128 + (((4 * kk + (lane >> 4)) ^ ((lane >> 1) & 7)) * 16);
   const int nk = a.K / BK;   // host: >= 2
 
   aoff_t a_off[8];
@@ -746,15 +761,18 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
   const char* w_lo = static_cast<const char*>(a.B) + (long long)hd.widx * a.b_group_stride * 2;   // loads 0..3
   const char* w_hi = SWIGLU ? static_cast<const char*>(a.B2) + (long long)hd.widx * a.b_group_stride * 2 : w_lo;
 
-  bf16x8 fa[2][4], fb[2][4];
-  // fragment idx 0..3: token-row blocks, 4..7: weight-row blocks, of K step kk of the tile in `stage`
-  auto read_frag = [&](int set, int stage, int kk, int idx) {
+  bf16x8 fa[2][8], fb[2][8];
+  // read r (0..15) of the fragments of K step kk of the tile in `stage`, in the order in which the products want them:
+  // the first weight-row block, the token-row blocks, the other weight-row blocks
+  auto read_frag = [&](int set, int stage, int kk, int r) {
     const char* As = smem + stage * STAGE_BYTES + wm * 128 * 128;
     const char* Bs = smem + stage * STAGE_BYTES + A_BYTES + wn * 128 * 128;
-    if (idx < 4)
-      fa[set][idx] = *reinterpret_cast<const bf16x8*>(As + idx * 32 * 128 + foff[kk]);
-    else
-      fb[set][idx - 4] = *reinterpret_cast<const bf16x8*>(Bs + (idx - 4) * 32 * 128 + foff[kk]);
+    if (r >= 1 && r <= 8)
+      fa[set][r - 1] = *reinterpret_cast<const bf16x8*>(As + (r - 1) * 16 * 128 + foff[kk]);
+    else {
+      const int ni = r == 0 ? 0 : r - 8;
+      fb[set][ni] = *reinterpret_cast<const bf16x8*>(Bs + ni * 16 * 128 + foff[kk]);
+    }
   };
   // A rows / B rows of a K tile: load g (0..7) of this wave into `stage`
   auto load_a = [&](const aoff_t (&ao)[8], int ktile, int stage, int g) {
@@ -788,12 +806,11 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
   for (int g = 0; g < 8; ++g) load_b(b_off, w_lo, w_hi, 0, 0, g);
   wait_all_and_barrier();
 #pragma unroll
-  for (int idx = 0; idx < 8; ++idx) read_frag(0, 0, 0, idx);
+  for (int r = 0; r < 16; ++r) read_frag(0, 0, 0, r);
 #pragma unroll
   for (int g = 0; g < 8; ++g) load_a(a_off, 1, 1, g);
   __builtin_amdgcn_sched_barrier(0);
 
-  const f32x16 zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   __bf16* C = static_cast<__bf16*>(a.C);
 
   while (true) {
@@ -804,71 +821,80 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
     kb_reset();
     kb_advance();
 
-    f32x16 acc[4][4];   // [weight-row block ni][token-row block mi]
-    auto mfma_pair = [&](int set, int g) {
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int t = 2 * g + q, ni = t >> 2, mi = t & 3;
-        acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][ni], fa[set][mi], acc[ni][mi], 0, 0, 0);
-      }
+    f32x4 acc[8][8];   // [weight-row block ni][token-row block mi]
+    // One K step: 16 groups of {4 products, the fragment reads of the next step, tile loads}, pinned in source order.
+    // A K tile is multiplied in two steps and its successor but one is loaded meanwhile: tile load i (0..7: token rows,
+    // 8..15: weight rows) of a wave goes out in group load_at(i) of the 32 (step 1, then step 0 of the next K tile).
+    // Two loads per group hold up the products behind them (the path into LDS takes about one per group from each
+    // wave), later ones have not landed at the wait: of eight placements (GEMM-1 of the prefill batch) this one is the
+    // fastest, 941 us, against 963 (all in step 1, two per group) and 955 - 965 (8 + 8, or evenly over 28 or 32 groups).
+    auto reads_of_group = [&](int set, int stage, int kk, int g, int half) {
+      if (g < 4) read_frag(set, stage, kk, 2 * g + half);
+      else if (g < 12 && half == 0) read_frag(set, stage, kk, g + 4);
     };
-    // K step 0 of the output tile: B half of K tile 1, fragments of step 1, products into zero
+    auto group = [&](auto first, int set, int g, auto&& load, auto&& reads) {
 #pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      if ((g & 1) == 0) load_b(b_off, w_lo, w_hi, kb_next, par ^ 1, g >> 1);
-      read_frag(1, par, 1, g);
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int t = 2 * g + q, ni = t >> 2, mi = t & 3;
-        acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[0][ni], fa[0][mi], zero16, 0, 0, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-
-    // steps 1 and 2 of K tile kt in stage s
-    auto steps_12 = [&](int s, const unsigned (&bo)[8], const char* lo, const char* hi, long long kb) {
-#pragma unroll
-      for (int g = 0; g < 8; ++g) {
-        if ((g & 1) == 0) load_b(bo, lo, hi, kb, s ^ 1, 4 + (g >> 1));   // second half of the B loads begun in the step before
-        read_frag(0, s, 2, g);
-        mfma_pair(1, g);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int g = 0; g < 8; ++g) {
-        read_frag(1, s, 3, g);
-        mfma_pair(0, g);
+      for (int q = 0; q < 4; ++q) {
+        const int t = 4 * g + q, ni = t >> 3, mi = t & 7;
+        if constexpr (decltype(first)::value) mfma16_first(acc[ni][mi], fb[set][ni], fa[set][mi]);
+        else mfma16(acc[ni][mi], fb[set][ni], fa[set][mi]);
+        if (q == 0) load();
+        if (q == 1) reads(0);
+        if (q == 2) reads(1);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
-
-    // K tiles 0 .. nk-3: steps 1, 2, wait for K tile kt+1, step 3, step 0 of K tile kt+1
+    auto load_at = [](int i) { return i < 12 ? i * 2 / 3 : i + 4; };   // 12 in step 1, groups 0..7; 4 in step 0, groups 0..3
+    // step 0 of K tile kt in stage s: the rest of K tile kt+1 -> stage s^1, fragments of step 1.
+    // head: the first step of an output tile, whose weight half of K tile 1 is all still to be requested
+    auto step0 = [&](int s, const unsigned (&bo)[8], const char* lo, const char* hi, long long kb, auto head) {
+#pragma unroll
+      for (int g = 0; g < 16; ++g) {
+        group(head, 0, g,
+              [&] {
+                if constexpr (decltype(head)::value) {
+                  if (g < 8) load_b(bo, lo, hi, kb, s ^ 1, g);
+                } else {
+#pragma unroll
+                  for (int i = 8; i < 16; ++i)
+                    if (load_at(i) == 16 + g) load_b(bo, lo, hi, kb, s ^ 1, i - 8);
+                }
+              },
+              [&](int half) { reads_of_group(1, s, 1, g, half); });
+      }
+    };
+    // step 1 of K tile kt in stage s, after the wait: first loads of K tile kt+2 -> stage s, step-0 fragments of K tile
+    // kt+1.  tail: the last step of an output tile, whose epilogue uses the weight half of stage s: token half only
+    auto step1 = [&](int s, const aoff_t (&ao)[8], int ktile, const unsigned (&bo)[8], const char* lo, const char* hi,
+                     long long kb, auto tail) {
+#pragma unroll
+      for (int g = 0; g < 16; ++g) {
+        group(std::false_type{}, 1, g,
+              [&] {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                  if (load_at(i) == g) {
+                    if (i < 8) load_a(ao, ktile, s, i);
+                    else if (!decltype(tail)::value) load_b(bo, lo, hi, kb, s, i - 8);
+                  }
+              },
+              [&](int half) { reads_of_group(0, s ^ 1, 0, g, half); });
+      }
+    };
+    step0(par, b_off, w_lo, w_hi, kb_next, std::true_type{});
+    kb_advance();
+    // K tiles 0 .. nk-3
     for (int kt = 0; kt < nk - 2; ++kt) {
       const int s = (par + kt) & 1;
-      steps_12(s, b_off, w_lo, w_hi, kb_next);
-      kb_advance();
       // K tile kt+1 has landed (this wave's loads, then every wave's), and every wave has issued
       // and completed its last reads of stage s, which may therefore be refilled
       wait_all_and_barrier();
-#pragma unroll
-      for (int g = 0; g < 8; ++g) {   // step 3: A half of K tile kt+2 -> stage s, step-0 fragments of kt+1
-        load_a(a_off, kt + 2, s, g);
-        read_frag(0, s ^ 1, 0, g);
-        mfma_pair(1, g);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int g = 0; g < 8; ++g) {   // step 0 of K tile kt+1: B half of K tile kt+2 -> stage s
-        if ((g & 1) == 0) load_b(b_off, w_lo, w_hi, kb_next, s, g >> 1);
-        read_frag(1, s ^ 1, 1, g);
-        mfma_pair(0, g);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      step1(s, a_off, kt + 2, b_off, w_lo, w_hi, kb_next, std::false_type{});
+      step0(s ^ 1, b_off, w_lo, w_hi, kb_next, std::false_type{});
+      kb_advance();
     }
-
-    // K tile nk-2: as above, but the stage it frees receives K tile 0 of the next output tile
+    // K tile nk-2: its stage receives K tile 0 of the next output tile
     const int s = (par + nk - 2) & 1, s1 = s ^ 1;
-    steps_12(s, b_off, w_lo, w_hi, kb_next);
     wait_all_and_barrier();
     aoff_t na_off[8];
     unsigned nb_off[8];
@@ -876,44 +902,24 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
     const char* nw_lo = static_cast<const char*>(a.B) + (long long)hn.widx * a.b_group_stride * 2;
     const char* nw_hi = SWIGLU ? static_cast<const char*>(a.B2) + (long long)hn.widx * a.b_group_stride * 2 : nw_lo;
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      load_a(na_off, 0, s, g);
-      read_frag(0, s1, 0, g);
-      mfma_pair(1, g);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      if ((g & 1) == 0) load_b(nb_off, nw_lo, nw_hi, 0, s, g >> 1);
-      read_frag(1, s1, 1, g);
-      mfma_pair(0, g);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // K tile nk-1 (stage s1): steps 1, 2; then the next tile's K tile 0 is complete in stage s and
-    // stage s1 is free: step 3 sends the A half of the next tile's K tile 1 there and reads the
-    // next tile's first fragments
-    steps_12(s1, nb_off, nw_lo, nw_hi, 0);
+    step1(s, na_off, 0, nb_off, nw_lo, nw_hi, 0, std::false_type{});
+    step0(s1, nb_off, nw_lo, nw_hi, 0, std::false_type{});
+    // K tile nk-1 (stage s1): the next tile's K tile 0 is complete in stage s and stage s1 is free: the token half of
+    // the next tile's K tile 1 goes there
     wait_all_and_barrier();
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      load_a(na_off, 1, s1, g);
-      read_frag(0, s, 0, g);
-      mfma_pair(1, g);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    step1(s1, na_off, 1, nb_off, nw_lo, nw_hi, 0, std::true_type{});
+    mfma_results_ready();
 
-    // epilogue.  acc[ni][mi] element r of lane l: output row (token) mi*32 + l%32, output column
-    // ni*32 + (r/4)*8 + (l/32)*4 + r%4 of the wave tile: 4 consecutive columns per register quad.
+    // epilogue.  acc[ni][mi] element e of lane l: output row (token) mi*16 + l%16, output column
+    // ni*16 + (l/16)*4 + e of the wave tile: 4 consecutive columns per register quad.
     // Chunk c = 32 rows x 64 output columns = 4 KiB (128-byte rows, 16-byte slots swizzled like
     // the operand tiles), two buffers inside this wave's 8 KiB of stage s1's B region.
     {
       char* stg = smem + s1 * STAGE_BYTES + A_BYTES + wave * 8192;
       constexpr int NCH = SWIGLU ? 4 : 8;
       constexpr int W_COLS = SWIGLU ? 64 : 128;   // output columns of a wave tile
-      const int srow = lane & 31;
-      char* wr = stg + srow * 128 + (lane >> 5) * 8;
-      const int wsw = (srow >> 1) & 7;
+      char* wr = stg + (lane & 15) * 128 + ((lane >> 4) & 1) * 8;
+      const int wsw = (lane >> 1) & 7;
       const int rrow = lane >> 3, rch = lane & 7;
       // A chunk sequence number cc alternates the two staging buffers (cc & 1).  Without SAVE chunk cc is
       // output chunk cc.  With SAVE the sequence is, per row block mi: the activated chunk, then the gate
@@ -926,23 +932,28 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
         const int c = SAVE ? cc / 3 : cc;
         const int mi = SWIGLU ? c : (c >> 1), h = SWIGLU ? 0 : (c & 1);
 #pragma unroll
-        for (int nn = 0; nn < 2; ++nn)
+        for (int m2 = 0; m2 < 2; ++m2)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
+          for (int nn = 0; nn < 4; ++nn) {   // 16 output columns
+            const int gi = (nn >> 1) * 4 + (nn & 1);   // SWIGLU: weight-row block of the gate; the up block is gi + 2
+            if (SAVE) {   // read again for every kind: values kept from one chunk to the next would not fit the registers
+              asm volatile("" : "+a"(acc[gi][2 * mi + m2]));
+              asm volatile("" : "+a"(acc[gi + 2][2 * mi + m2]));
+            }
             float v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               if (SWIGLU && kind == 0)
-                v[e] = swiglu_fast(acc[2 * nn][mi][q * 4 + e], acc[2 * nn + 1][mi][q * 4 + e]);
+                v[e] = swiglu_fast(acc[gi][2 * mi + m2][e], acc[gi + 2][2 * mi + m2][e]);
               else if (SWIGLU)
-                v[e] = acc[2 * nn + (kind - 1)][mi][q * 4 + e];   // kind 1: gate, 2: up
+                v[e] = acc[gi + 2 * (kind - 1)][2 * mi + m2][e];   // kind 1: gate, 2: up
               else
-                v[e] = acc[2 * h + nn][mi][q * 4 + e];
+                v[e] = acc[4 * h + nn][2 * mi + m2][e];
             }
             uint2 pk;
             pk.x = pack_bf16(v[0], v[1]);
             pk.y = pack_bf16(v[2], v[3]);
-            *reinterpret_cast<uint2*>(buf + (((nn * 4 + q) ^ wsw) * 16)) = pk;
+            *reinterpret_cast<uint2*>(buf + m2 * 16 * 128 + (((nn * 2 + (lane >> 5)) ^ wsw) * 16)) = pk;
           }
       };
       // Stores go through a buffer descriptor over the wave tile's valid rows, so rows past the
