@@ -434,49 +434,79 @@ __global__ __launch_bounds__(256) void router_f32_kernel(const float* __restrict
   logits[i] = acc;
 }
 
-// Gram matrix of router scores, H^T H in float64.  A block takes a slice of tokens and a 64 x 64
-// tile of the matrix: the two 64-column panels of its tokens go through LDS, every thread keeps a
-// 4 x 4 patch of sums, and the tile is added to the result with double atomics.
-constexpr int kGramTokens = 64;
+// Gram matrix of router scores, H^T H in float64, on v_mfma_f64_16x16x4_f64.  A block takes a slice of tokens and a
+// 64 x 64 tile of the matrix, its wave w the tile's rows w*16 .. +15; four tokens per step go straight from the scores
+// into the operands (a lane holds one score of token lane / 16, converted to double), and the tile is added to the
+// result with double atomics, begun at another row in every block.  Tiles below the diagonal are written by the block
+// of their mirror image.  What bounds it is the chain of 64-cycle products of a block and, with more blocks, the
+// atomics on the few thousand cells.  16384 tokens of 64 experts: 160 us with 16 blocks of scalar double arithmetic,
+// 15 us now; 65536 tokens 169 -> 35 us (clearing launch included).
+constexpr int kGramTokens = 64;   // tokens per block, at least
 __global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ logits, int T, int E,
                                                    int tokens_per_block, double* __restrict__ gram) {
-  __shared__ float pa[kGramTokens][65], pb[kGramTokens][65];
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  // blockIdx.y -> tile (ti, tj), ti <= tj
+  int ti = 0, tj = blockIdx.y;
   const int tiles = (E + 63) / 64;
-  const int ti = blockIdx.y / tiles, tj = blockIdx.y % tiles;
-  const int ty = threadIdx.x / 16, tx = threadIdx.x % 16;   // patch rows ty*4.., columns tx*4..
-  double acc[4][4] = {};
-  const int t_begin = blockIdx.x * tokens_per_block;
-  const int t_end = min(T, t_begin + tokens_per_block);
-  for (int t0 = t_begin; t0 < t_end; t0 += kGramTokens) {
-    for (int i = threadIdx.x; i < kGramTokens * 64; i += 256) {
-      const int tt = i / 64, c = i % 64;
-      const int t = t0 + tt;
-      const int ea = ti * 64 + c, eb = tj * 64 + c;
-      pa[tt][c] = (t < t_end && ea < E) ? logits[(size_t)t * E + ea] : 0.0f;
-      pb[tt][c] = (t < t_end && eb < E) ? logits[(size_t)t * E + eb] : 0.0f;
-    }
-    __syncthreads();
-    for (int tt = 0; tt < kGramTokens; ++tt) {
-      double a[4], b[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        a[q] = (double)pa[tt][ty * 4 + q];
-        b[q] = (double)pb[tt][tx * 4 + q];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = acc[i][j] + a[i] * b[j];
-    }
-    __syncthreads();
+  while (tj >= tiles - ti) {
+    tj -= tiles - ti;
+    ++ti;
   }
+  tj += ti;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tk = lane >> 4, c = lane & 15;
+  const int ea = ti * 64 + wave * 16 + c;
+  const int t_begin = blockIdx.x * tokens_per_block, t_end = min(T, t_begin + tokens_per_block);
+  f64x4 acc[4] = {};
+  constexpr int UN = 8;   // steps of 4 tokens requested together, one such set ahead of the products
+  struct Set {
+    float a[UN], b[UN][4];
+  };
+  auto load = [&](Set& s, int t0) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int u = 0; u < UN; ++u) {
+      const int t = t0 + 4 * u + tk;
+      const float* row = logits + (size_t)t * E;
+      s.a[u] = (t < t_end && ea < E) ? row[ea] : 0.0f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int ei = ti * 64 + ty * 4 + i, ej = tj * 64 + tx * 4 + j;
-      if (ei < E && ej < E) atomicAdd(&gram[(size_t)ei * E + ej], acc[i][j]);
+      for (int j = 0; j < 4; ++j) {
+        const int eb = tj * 64 + j * 16 + c;
+        s.b[u][j] = (t < t_end && eb < E) ? row[eb] : 0.0f;
+      }
     }
+  };
+  auto multiply = [&](const Set& s) {
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)s.a[u], (double)s.b[u][j], acc[j], 0, 0, 0);
+  };
+  Set s0, s1;
+  load(s0, t_begin);
+  for (int t0 = t_begin; t0 < t_end; t0 += 8 * UN) {   // past the end a set is all zeros
+    load(s1, t0 + 4 * UN);
+    multiply(s0);
+    load(s0, t0 + 8 * UN);
+    multiply(s1);
+  }
+  // acc[j] element i of lane l: tile row wave*16 + i*4 + l/16, column j*16 + l%16
+#pragma unroll
+  for (int jj = 0; jj < 4; ++jj) {
+    const int j = (jj + blockIdx.x) & 3;
+    f64x4 v = acc[0];
+#pragma unroll
+    for (int m = 1; m < 4; ++m)
+      if (j == m) v = acc[m];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int ei = ti * 64 + wave * 16 + i * 4 + tk, ej = tj * 64 + j * 16 + c;
+      if (ei < E && ej < E) {
+        atomicAdd(&gram[(size_t)ei * E + ej], v[i]);
+        if (ti != tj) atomicAdd(&gram[(size_t)ej * E + ei], v[i]);
+      }
+    }
+  }
 }
 
 __global__ void fill_f64(double* p, size_t n, double v) {
@@ -503,11 +533,16 @@ extern "C" int occult_similarity_gram(const occult_cfg_t* cfg, const float* logi
   if (c.T == 0) return OCCULT_OK;
   OCC_REQUIRE(logits, OCCULT_ENULLPTR, "logits is NULL");
   const int tiles = (c.E + 63) / 64;
-  int slices = (c.T + 1023) / 1024;          // about 1024 tokens per block
-  if (slices < 1) slices = 1;
-  const int per = ((c.T + slices - 1) / slices + kGramTokens - 1) / kGramTokens * kGramTokens;
+  // as many slices as give a block 64 tokens, within 512 blocks: beyond that the atomics on the tile's cells cost more than
+  // the shorter chains save (measured, us: T = 16384, E = 64: 28 / 18 / 15 / 15 with 64 / 128 / 256 / 512 slices; E = 200,
+  // ten tiles: 66 / 70 / 93 / 147 with 32 / 64 / 128 / 256)
+  const int n_tiles = tiles * (tiles + 1) / 2;
+  int slices = (c.T + kGramTokens - 1) / kGramTokens;
+  const int most = 512 / n_tiles > 32 ? 512 / n_tiles : 32;
+  if (slices > most) slices = most;
+  const int per = ((c.T + slices - 1) / slices + 15) / 16 * 16;
   slices = (c.T + per - 1) / per;
-  hipLaunchKernelGGL(gram_kernel, dim3(slices, tiles * tiles), dim3(256), 0, s, logits, c.T, c.E, per, gram);
+  hipLaunchKernelGGL(gram_kernel, dim3(slices, n_tiles), dim3(256), 0, s, logits, c.T, c.E, per, gram);
   OCC_LAUNCH_CHECK("gram_kernel");
   return OCCULT_OK;
 }
