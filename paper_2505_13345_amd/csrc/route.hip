@@ -1,10 +1,11 @@
 // occult_route: softmax top-k gating with optional collaboration pruning
 // (paper Eq. 1; Section 3.3, routing-score-based pruning).
 //
-// One 64-lane wavefront per token.  Lane l holds the scores of experts l, l+64, l+128, l+192
-// (E <= 256), so a row of scores is read with coalesced loads and a selection round is a
-// per-lane best followed by a 6-step butterfly arg-max over the wave.  Selection compares raw
-// scores (softmax is monotone): larger first, equal -> lower expert index.
+// Sixteen lanes per token, four tokens per wavefront.  Lane r of a token's sixteen holds the scores of experts r, r+16,
+// r+32, ... (E <= 256); a selection round is the lane's best followed by a 4-step arg-max over the sixteen lanes.
+// Selection compares raw scores (softmax is monotone): larger first, equal -> lower expert index.
+// Routing is bound by these vector operations, not by its 300 bytes per token; a whole wavefront per token spent them on
+// one token instead of four (18.5 us at 16384 tokens of 64 experts, k = 8; 40 us pruned).
 //
 // The pruning decision of mode 1 compares per-device sums of exp(score - max); those sums are
 // taken in one fixed float32 sequence (exp_ref below: separately rounded multiplies and adds,
@@ -12,7 +13,6 @@
 #include "common.h"
 
 #include <float.h>
-#include <limits.h>
 #include <math.h>
 
 // every float operation in this file is rounded on its own
@@ -43,126 +43,119 @@ __device__ __forceinline__ float exp_ref(float z) {
   return z < -80.0f ? 0.0f : out;
 }
 
-// Cross-lane steps on the VALU's data-parallel primitives (no LDS crossbar): four symmetric
-// exchanges leave every lane of a 16-lane row with the row's result, two row broadcasts carry it
-// into lane 63, which is read back as a wave-uniform value.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int dpp_i(int own, int v) {
-  return __builtin_amdgcn_update_dpp(own, v, CTRL, ROW_MASK, 0xF, false);   // rows outside the mask keep `own`
+// Cross-lane steps on the VALU's data-parallel primitives (no LDS crossbar): four symmetric exchanges leave every lane of
+// a row of 16 with the row's result.
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
 }
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_f(float own, float v) {
-  return __builtin_bit_cast(float, dpp_i<CTRL, ROW_MASK>(__builtin_bit_cast(int, own), __builtin_bit_cast(int, v)));
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __builtin_bit_cast(float, dpp_i<CTRL>(__builtin_bit_cast(int, v)));
 }
 constexpr int kQuadSwap1 = 0xB1;       // quad_perm [1,0,3,2]
 constexpr int kQuadSwap2 = 0x4E;       // quad_perm [2,3,0,1]
 constexpr int kRowHalfMirror = 0x141;
 constexpr int kRowMirror = 0x140;
-constexpr int kRowBcast15 = 0x142;     // lane 15 of each row into the next row (rows 1 and 3 take it)
-constexpr int kRowBcast31 = 0x143;     // lane 31 into rows 2 and 3
 
 // (value, index) as one 64-bit key whose unsigned order is "larger value first, equal values -> lower index":
 // the value's bits made monotone (negative floats inverted, positive ones offset) in the high word, the
-// complemented index in the low word.  One 64-bit compare per step instead of three compares.
-__device__ __forceinline__ unsigned long long argmax_key(float v, int i) {
+// complemented index in the low word.  One 64-bit compare per step instead of three compares.  The key of a finite
+// value is never 0, which stands for "taken" and "not there".
+typedef unsigned long long key_t64;
+__device__ __forceinline__ key_t64 argmax_key(float v, int i) {
   const unsigned u = __builtin_bit_cast(unsigned, v);
   const unsigned ord = u ^ ((u >> 31) ? 0xFFFFFFFFu : 0x80000000u);
-  return ((unsigned long long)ord << 32) | (unsigned)(~i);
+  return ((key_t64)ord << 32) | (unsigned)(~i);
+}
+__device__ __forceinline__ int key_index(key_t64 key) { return ~(int)(unsigned)key; }
+__device__ __forceinline__ float key_value(key_t64 key) {
+  const unsigned ord = (unsigned)(key >> 32);
+  return __builtin_bit_cast(float, ord ^ ((ord >> 31) ? 0x80000000u : 0xFFFFFFFFu));
 }
 
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void argmax_step(unsigned long long& key) {
-  const int lo = dpp_i<CTRL, ROW_MASK>((int)(unsigned)key, (int)(unsigned)key);
-  const int hi = dpp_i<CTRL, ROW_MASK>((int)(unsigned)(key >> 32), (int)(unsigned)(key >> 32));
-  const unsigned long long other = ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
-  key = other > key ? other : key;
+template <int CTRL>
+__device__ __forceinline__ key_t64 key_max_step(key_t64 key) {
+  const int lo = dpp_i<CTRL>((int)(unsigned)key), hi = dpp_i<CTRL>((int)(unsigned)(key >> 32));
+  const key_t64 other = ((key_t64)(unsigned)hi << 32) | (unsigned)lo;
+  return other > key ? other : key;
+}
+// largest key of a row of 16 lanes, in every one of them
+__device__ __forceinline__ key_t64 row_max(key_t64 key) {
+  key = key_max_step<kQuadSwap1>(key);
+  key = key_max_step<kQuadSwap2>(key);
+  key = key_max_step<kRowHalfMirror>(key);
+  return key_max_step<kRowMirror>(key);
+}
+__device__ __forceinline__ float row_sum(float v) {
+  v += dpp_f<kQuadSwap1>(v);
+  v += dpp_f<kQuadSwap2>(v);
+  v += dpp_f<kRowHalfMirror>(v);
+  v += dpp_f<kRowMirror>(v);
+  return v;
 }
 
-// larger value first, equal values -> lower index; result in every lane
-__device__ __forceinline__ void wave_argmax(float& v, int& i) {
-  unsigned long long key = argmax_key(v, i);
-  argmax_step<kQuadSwap1, 0xF>(key);
-  argmax_step<kQuadSwap2, 0xF>(key);
-  argmax_step<kRowHalfMirror, 0xF>(key);
-  argmax_step<kRowMirror, 0xF>(key);
-  argmax_step<kRowBcast15, 0xA>(key);
-  argmax_step<kRowBcast31, 0xC>(key);
-  const unsigned ord = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(key >> 32), 63);
-  i = ~__builtin_amdgcn_readlane((int)(unsigned)key, 63);
-  v = __builtin_bit_cast(float, ord ^ ((ord >> 31) ? 0x80000000u : 0xFFFFFFFFu));
-}
+constexpr int kRouteTokens = 16;   // tokens per block of 256 threads
 
-__device__ __forceinline__ float wave_sum(float v) {
-  v += dpp_f<kQuadSwap1, 0xF>(v, v);
-  v += dpp_f<kQuadSwap2, 0xF>(v, v);
-  v += dpp_f<kRowHalfMirror, 0xF>(v, v);
-  v += dpp_f<kRowMirror, 0xF>(v, v);
-  v += dpp_f<kRowBcast15, 0xA>(0.0f, v);
-  v += dpp_f<kRowBcast31, 0xC>(0.0f, v);
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
+// EPL = experts per lane, E <= 16 * EPL.  Lane r of a token writes slots r and r + 16.
+template <int EPL, bool PRUNE>
+__global__ __launch_bounds__(256) void route_kernel(
+    const float* __restrict__ logits, int T, int E, int k, int D, int G,
+    const int32_t* __restrict__ expert_pos, int n_d, int prune_mode, int renorm,
+    const int32_t* __restrict__ sim_table, int32_t* __restrict__ ids, float* __restrict__ w) {
+  __shared__ int s_dev[PRUNE ? OCCULT_MAX_E : 1];   // only pruning asks which device an expert is on
+  if (PRUNE) {
+    for (int e = threadIdx.x; e < E; e += blockDim.x) s_dev[e] = (expert_pos ? expert_pos[e] : e) / G;
+    __syncthreads();
+  }
+  const int lane = threadIdx.x & 63, r = lane & 15, row0 = lane & 48;
+  const int t = blockIdx.x * kRouteTokens + (threadIdx.x >> 4);
+  if (t >= T) return;   // all sixteen lanes of a token leave together; no barrier follows
+  const float* row = logits + (size_t)t * E;
 
-constexpr int kRouteWavesPerBlock = 4;
-
-// Routes one token on one wavefront.  `row` points at the token's E scores (global or LDS);
-// s_dev[e] is the device of expert e.  Lane s < k writes slot s.
-template <int EPL>  // experts per lane = ceil(E / 64)
-__device__ __forceinline__ void route_one(const float* row, int lane, int E, int k, int D, const int* s_dev,
-                                          int n_d, int prune_mode, int renorm, const int32_t* sim_table,
-                                          int32_t* ids_t, float* w_t) {
-  const float kNegInf = -INFINITY;
-  float v0[EPL];   // the token's scores as read (with -0.0 folded onto +0.0)
-  float v[EPL];    // working copy: taken / disallowed entries become -inf
+  float v0[EPL];     // the token's scores as read (with -0.0 folded onto +0.0)
+  key_t64 key[EPL];  // 0: taken, not allowed or not there
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    const int e = lane + 64 * i;
-    // NaN and -inf scores are read as the lowest finite value and +inf as the highest: every real
-    // entry then stays above the -inf that marks taken and absent entries, so each round selects a
-    // new index below E whatever the scores hold (ids index other tables downstream), and the
-    // device sums and gates stay finite
-    v0[i] = (e < E) ? fminf(fmaxf(row[e] + 0.0f, -FLT_MAX), FLT_MAX) : kNegInf;
-    v[i] = v0[i];
+    const int e = r + 16 * i;
+    // NaN and -inf scores are read as the lowest finite value and +inf as the highest: each round then selects a new
+    // index below E whatever the scores hold (ids index other tables downstream), and the device sums and gates stay
+    // finite
+    v0[i] = (e < E) ? fminf(fmaxf(row[e] + 0.0f, -FLT_MAX), FLT_MAX) : 0.0f;
+    key[i] = (e < E) ? argmax_key(v0[i], e) : 0ull;
   }
-
-  auto select_round = [&](float& bv, int& bi) {
-    bv = kNegInf;
-    bi = INT_MAX;
+  auto select_round = [&]() {
+    key_t64 best = key[0];
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      const int e = lane + 64 * i;
-      // strictly greater keeps the lower index among a lane's equal scores (i ascending)
-      if (e < E && (v[i] > bv || bi == INT_MAX)) {
-        bv = v[i];
-        bi = e;
-      }
-    }
-    wave_argmax(bv, bi);
+    for (int i = 1; i < EPL; ++i) best = key[i] > best ? key[i] : best;
+    best = row_max(best);
 #pragma unroll
-    for (int i = 0; i < EPL; ++i)
-      if (lane + 64 * i == bi) v[i] = kNegInf;
+    for (int i = 0; i < EPL; ++i) key[i] = key[i] == best ? 0ull : key[i];
+    return best;
   };
 
-  int my_id = 0;       // lane s < k keeps slot s
-  float my_v = 0.0f;
+  key_t64 slot[2] = {0ull, 0ull};   // slots r and r + 16
+  auto keep_slot = [&](int s, key_t64 best) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (r + 16 * h == s) slot[h] = best;
+  };
   float mx = 0.0f;
-  float dev_sum = 0.0f;          // lane j < D: mode-1 score of device j
-  unsigned long long kept = 0;   // mode 2: devices kept so far (wave-uniform)
+  float dev_sum[4] = {};         // mode 1: scores of devices r, r + 16, r + 32, r + 48
+  unsigned long long kept = 0;   // mode 2: devices kept so far (the same in a token's sixteen lanes)
   int n_kept = 0;
 
   for (int s = 0; s < k; ++s) {
-    float bv;
-    int bi;
-    select_round(bv, bi);
-    if (s == 0) mx = bv;
-    if (lane == s) {
-      my_id = bi;
-      my_v = bv;
-    }
-    if (n_d > 0) {
-      const int dev = s_dev[bi];
+    const key_t64 best = select_round();
+    if (s == 0) mx = key_value(best);
+    keep_slot(s, best);
+    if (PRUNE) {
+      const int dev = s_dev[key_index(best)];
       if (prune_mode == 1) {
-        const float q = exp_ref(bv - mx);
-        if (lane == dev) dev_sum = dev_sum + q;   // sequential in slot order
+        const float q = exp_ref(key_value(best) - mx);
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+          if (r + 16 * h == dev) dev_sum[h] = dev_sum[h] + q;   // sequential in slot order
       } else if (!((kept >> dev) & 1ull) && n_kept < n_d) {
         kept |= 1ull << dev;
         ++n_kept;
@@ -170,13 +163,18 @@ __device__ __forceinline__ void route_one(const float* row, int lane, int E, int
     }
   }
 
-  if (n_d > 0 && prune_mode == 3) {
+  if (PRUNE && prune_mode == 3) {
     // Expert-similarity-based pruning: routed experts on kept devices stay in their slots; the
     // others are replaced, in slot (= descending score) order, by the first entry of their table
-    // row that is on a kept device and not taken.  `taken` = one bit per expert, wave-uniform.
+    // row that is on a kept device and not taken.  `taken` = one bit per expert, the same in a token's lanes; the
+    // control flow below differs between the tokens of a wave, never between the lanes of a token.
     unsigned long long taken[4] = {0ull, 0ull, 0ull, 0ull};
+    auto expert_of = [&](int s) {   // expert in slot s
+      const int lo = __shfl(key_index(slot[0]), row0 + (s & 15), 64), hi = __shfl(key_index(slot[1]), row0 + (s & 15), 64);
+      return s < 16 ? lo : hi;
+    };
     for (int s = 0; s < k; ++s) {
-      const int e = __shfl(my_id, s, 64);
+      const int e = expert_of(s);
       if ((kept >> s_dev[e]) & 1ull) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -184,12 +182,12 @@ __device__ __forceinline__ void route_one(const float* row, int lane, int E, int
       }
     }
     for (int s = 0; s < k; ++s) {
-      const int e = __shfl(my_id, s, 64);
-      if ((kept >> s_dev[e]) & 1ull) continue;   // wave-uniform
+      const int e = expert_of(s);
+      if ((kept >> s_dev[e]) & 1ull) continue;
       const int32_t* trow = sim_table + (size_t)e * (E - 1);
       int found = -1;
-      for (int base = 0; base < E - 1 && found < 0; base += 64) {
-        const int q = base + lane;
+      for (int base = 0; base < E - 1 && found < 0; base += 16) {
+        const int q = base + r;
         int c = 0;
         bool ok = false;
         if (q < E - 1) {
@@ -200,88 +198,68 @@ __device__ __forceinline__ void route_one(const float* row, int lane, int E, int
             if ((c >> 6) == m) word = taken[m];
           ok = ((kept >> s_dev[c]) & 1ull) && !((word >> (c & 63)) & 1ull);
         }
-        const unsigned long long hits = __ballot(ok);
-        if (hits) found = __shfl(c, __ffsll((long long)hits) - 1, 64);
+        const unsigned hits = (unsigned)(__ballot(ok) >> row0) & 0xFFFFu;
+        const int c_hit = __shfl(c, row0 + (hits ? __ffs((int)hits) - 1 : 0), 64);
+        if (hits) found = c_hit;
       }
       // host checks n_d * G >= k, so a free expert on a kept device always exists
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         if ((found >> 6) == q) taken[q] |= 1ull << (found & 63);
-      // its score sits in lane found % 64, register found / 64
+      // its score sits in lane found % 16 of the token, register found / 16
       float fv = v0[0];
 #pragma unroll
       for (int i = 1; i < EPL; ++i)
-        if ((found >> 6) == i) fv = v0[i];
-      fv = __shfl(fv, found & 63, 64);
-      if (lane == s) {
-        my_id = found;
-        my_v = fv;
-      }
+        if ((found >> 4) == i) fv = v0[i];
+      fv = __shfl(fv, row0 + (found & 15), 64);
+      keep_slot(s, argmax_key(fv, found));
     }
-  } else if (n_d > 0) {
+  } else if (PRUNE) {
     if (prune_mode == 1) {
-      float sv = (lane < D) ? dev_sum : kNegInf;
+      key_t64 dk[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) dk[h] = r + 16 * h < D ? argmax_key(dev_sum[h], r + 16 * h) : 0ull;
       kept = 0;
-      for (int r = 0; r < n_d; ++r) {
-        float bv = sv;
-        int bi = (lane < D) ? lane : INT_MAX;
-        wave_argmax(bv, bi);
-        kept |= 1ull << bi;
-        if (lane == bi) sv = kNegInf;
+      for (int q = 0; q < n_d; ++q) {
+        key_t64 best = dk[0];
+#pragma unroll
+        for (int h = 1; h < 4; ++h) best = dk[h] > best ? dk[h] : best;
+        best = row_max(best);
+        kept |= 1ull << key_index(best);
+#pragma unroll
+        for (int h = 0; h < 4; ++h) dk[h] = dk[h] == best ? 0ull : dk[h];
       }
     }
     // second pass: the k best experts on the surviving devices
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
-      const int e = lane + 64 * i;
+      const int e = r + 16 * i;
       const bool ok = (e < E) && ((kept >> s_dev[e < E ? e : 0]) & 1ull);
-      v[i] = ok ? v0[i] : kNegInf;
+      key[i] = ok ? argmax_key(v0[i], e) : 0ull;
     }
-    for (int s = 0; s < k; ++s) {
-      float bv;
-      int bi;
-      select_round(bv, bi);
-      if (lane == s) {
-        my_id = bi;
-        my_v = bv;
-      }
-    }
+    for (int s = 0; s < k; ++s) keep_slot(s, select_round());
   }
 
   // gate values: softmax over all E experts at the selected ones
   float part = 0.0f;
 #pragma unroll
   for (int i = 0; i < EPL; ++i)
-    if (lane + 64 * i < E) part += exp_ref(v0[i] - mx);
-  const float denom = wave_sum(part);
-  float g = (lane < k) ? exp_ref(my_v - mx) / denom : 0.0f;
+    if (r + 16 * i < E) part += exp_ref(v0[i] - mx);
+  const float denom = row_sum(part);
+  float g[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) g[h] = r + 16 * h < k ? exp_ref(key_value(slot[h]) - mx) / denom : 0.0f;
   if (renorm) {
-    const float sel = wave_sum(g);
-    g = g / sel;
+    const float sel = row_sum(g[0] + g[1]);
+    g[0] = g[0] / sel;
+    g[1] = g[1] / sel;
   }
-  if (lane < k) {
-    ids_t[lane] = my_id;
-    w_t[lane] = g;
-  }
-}
-
-template <int EPL>
-__global__ __launch_bounds__(kRouteWavesPerBlock * 64) void route_kernel(
-    const float* __restrict__ logits, int T, int E, int k, int D, int G,
-    const int32_t* __restrict__ expert_pos, int n_d, int prune_mode, int renorm,
-    const int32_t* __restrict__ sim_table, int32_t* __restrict__ ids, float* __restrict__ w) {
-  __shared__ int s_dev[OCCULT_MAX_E];
-  if (n_d > 0) {   // uniform; only pruning asks which device an expert is on
-    for (int e = threadIdx.x; e < E; e += blockDim.x)
-      s_dev[e] = (expert_pos ? expert_pos[e] : e) / G;
-    __syncthreads();
-  }
-
-  const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * kRouteWavesPerBlock + (threadIdx.x >> 6);
-  if (t >= T) return;   // whole wave leaves together; no barrier follows
-  route_one<EPL>(logits + (size_t)t * E, lane, E, k, D, s_dev, n_d, prune_mode, renorm, sim_table,
-                 ids + (size_t)t * k, w + (size_t)t * k);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    if (r + 16 * h < k) {
+      ids[(size_t)t * k + r + 16 * h] = key_index(slot[h]);
+      w[(size_t)t * k + r + 16 * h] = g[h];
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -590,17 +568,21 @@ extern "C" int occult_route(const occult_cfg_t* cfg, const float* logits, int32_
     OCC_REQUIRE(c.sim_table != nullptr, OCCULT_ENULLPTR, "prune_mode 3 needs cfg.sim_table");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int G = c.E / c.D;
-  const dim3 grid((c.T + kRouteWavesPerBlock - 1) / kRouteWavesPerBlock), block(kRouteWavesPerBlock * 64);
-  const int epl = (c.E + 63) / 64;
-#define OCC_ROUTE_LAUNCH(N)                                                                     \
-  hipLaunchKernelGGL(route_kernel<N>, grid, block, 0, s, logits, c.T, c.E, c.k, c.D, G,         \
+  const dim3 grid((c.T + kRouteTokens - 1) / kRouteTokens), block(256);
+#define OCC_ROUTE_LAUNCH(N, P)                                                                  \
+  hipLaunchKernelGGL((route_kernel<N, P>), grid, block, 0, s, logits, c.T, c.E, c.k, c.D, G,    \
                      c.expert_pos, c.n_d, c.prune_mode, c.renorm, c.sim_table, ids, w)
-  switch (epl) {
-    case 1: OCC_ROUTE_LAUNCH(1); break;
-    case 2: OCC_ROUTE_LAUNCH(2); break;
-    case 3: OCC_ROUTE_LAUNCH(3); break;
-    default: OCC_ROUTE_LAUNCH(4); break;
-  }
+#define OCC_ROUTE(N)                     \
+  do {                                   \
+    if (c.n_d > 0) OCC_ROUTE_LAUNCH(N, true); \
+    else OCC_ROUTE_LAUNCH(N, false);     \
+  } while (0)
+  if (c.E <= 16) OCC_ROUTE(1);
+  else if (c.E <= 32) OCC_ROUTE(2);
+  else if (c.E <= 64) OCC_ROUTE(4);
+  else if (c.E <= 128) OCC_ROUTE(8);
+  else OCC_ROUTE(16);
+#undef OCC_ROUTE
 #undef OCC_ROUTE_LAUNCH
   OCC_LAUNCH_CHECK("route_kernel");
   return OCCULT_OK;
