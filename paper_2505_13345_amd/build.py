@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(ROOT, "_build", "occult")
 LIB_PATH = os.path.join(HERE, "liboccult.so")
 
-SOURCES = ["api.hip", "route.hip", "plan.hip", "dispatch.hip", "ffn.hip", "combine.hip", "combine_atomic.hip", "coact.hip", "backward.hip",
+SOURCES = ["api.hip", "route.hip", "plan.hip", "dispatch.hip", "ffn.hip", "ffn_tile128.hip", "combine.hip", "combine_atomic.hip", "coact.hip", "backward.hip",
            "ffn_backward.hip", "wgrad.hip"]
 
 HIPCC_FLAGS = [
@@ -43,7 +43,7 @@ def _hipcc() -> str:
 # Kernels that must not touch scratch memory: in the persistent 256-row GEMM every reload of a spilled
 # register waits for all outstanding loads, the next tile's prefetch included (a one-register change in
 # its epilogue has cost 20 % before).  Matched against the mangled kernel names.
-NO_SCRATCH = ("t256",)
+NO_SCRATCH = ("t256", "t128")
 
 
 def _resource_usage(stderr: str):

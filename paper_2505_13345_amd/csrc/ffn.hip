@@ -1101,7 +1101,7 @@ __global__ __launch_bounds__(FM * FN) void grouped_gemm_f32(const GemmArgs a) {
 }
 
 // compute units of the current device (the persistent kernel runs one block on each), cached
-static int device_cu_count(int* out) {
+int device_cu_count(int* out) {
   static int cached[64];
   int dev = 0;
   OCC_HIP(hipGetDevice(&dev));
@@ -1307,6 +1307,33 @@ int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total
   return rc;
 }
 
+// Which products take the 128-row tiles (ffn_tile128.hip).  Rows per group, d = 2048, f = 1024 / 1408, 60 - 64 experts:
+//  - below them stands the weight-streaming kernel, above the 256-row tiles, which need a third fewer operand bytes per
+//    product but waste more on partly filled tiles and on the last round of tiles over the CUs;
+//  - with shared experts one launch does both sets' work, which alone would leave most CUs idle (500 tokens: 118 of
+//    357 us) or add a last round of its own: worth it down to any number of rows and up to about 800 per group
+//    (656 rows: 1116 us against 1057; 768: equal);
+//  - without, from 24 rows (32: 226 us against 220; 20: 215 against 218) up to about 240 (237: 339 against 323 us; 256
+//    and 287: slower, 325: faster, by how the tiles happen to divide over the CUs);
+//  - when the pre-activations are to be stored, from any number: the alternative is two more passes over the weights.
+static bool fits_tile128(const GemmArgs& a) {
+  return a.K >= 192 && a.K % 64 == 0 && a.N % 64 == 0 && (long long)a.a_rows_total * a.lda * 2 < (1ll << 32);
+}
+static bool uses_tile128(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, int total_rows) {
+  if (c.dtype != OCCULT_BF16 || a.grp_offset == nullptr || !fits_tile128(a) || (b != nullptr && !fits_tile128(*b)))
+    return false;
+  const long long lo = b != nullptr || a.C2 != nullptr ? 0 : 24, hi = b != nullptr ? 800 : 240;
+  return total_rows >= lo * a.ngroups && total_rows < hi * a.ngroups;
+}
+
+int launch_gemm_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, int rows_b,
+                     hipStream_t s) {
+  if (total_rows > 0 && uses_tile128(c, a, b, total_rows)) return launch_tile128(a, b, swiglu, total_rows, s);
+  const int rc = launch_gemm(c, a, swiglu, total_rows, s);
+  if (rc || b == nullptr) return rc;
+  return launch_gemm(c, *b, swiglu, rows_b, s);
+}
+
 }  // namespace occult
 
 using namespace occult;
@@ -1322,6 +1349,11 @@ static bool pairs_shared_with_routed(const occult_cfg_t& c) {
          c.f % skinny::BN_OUT == 0 && c.d % skinny::BN_OUT == 0 &&
          (long long)sfd_rows_max(c) * c.d * 2 < (1ll << 32) && (long long)c.T * c.k * c.f * 2 < (1ll << 32) &&
          (long long)c.T * c.S * c.f * 2 < (1ll << 32);
+}
+
+// of those batches, the ones that the 128-row tiles take instead: many rows per routed expert, or stored pre-activations
+static bool uses_tile128_for_few_rows(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs& b) {
+  return (a.C2 != nullptr || c.T * c.k >= 16 * c.E) && uses_tile128(c, a, &b, c.T * c.k);
 }
 
 static size_t ffn_ws_need(const occult_cfg_t& c, int* ksplit_out) {
@@ -1373,126 +1405,62 @@ static int expert_ffn_impl(const occult_cfg_t* cfg, const occult_plan_t* plan, c
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int n_epd = c.T * c.k;
 
-  hipStream_t s_shared = s;
   const bool do1 = c.ffn_phase != 2, do2 = c.ffn_phase != 1;
 
-  auto shared_experts = [&]() -> int {
-    // h_shared[t][s*f .. (s+1)*f) per shared expert, then one product whose K dimension walks
-    // the S down-projection matrices
-    if (do1) {   // the S shared experts as S groups over the same T rows
-      GemmArgs a1{};
-      a1.A = x; a1.lda = c.d; a1.a_rows = nullptr;
-      a1.B = weights->w_gate; a1.B2 = weights->w_up;
-      a1.b_group_stride = (long long)c.f * c.d; a1.ldb = c.d; a1.kseg = c.d;
-      a1.C = h_shared; a1.ldc = c.S * c.f; a1.c_col0 = 0; a1.c_group_cols = c.f;
-      a1.C2 = gu_shared;   // rows of S * 2f: per shared expert [gate | up]
-      a1.grp_offset = nullptr; a1.grp_widx = nullptr; a1.w_base = c.E;
-      a1.ngroups = c.S; a1.M = c.T; a1.N = c.f; a1.K = c.d; a1.a_rows_total = c.T;
-      const int r1 = launch_gemm(c, a1, true, c.T * c.S, s_shared);
-      if (r1) return r1;
+  if (do1) {   // h = silu(x W_gate^T) * (x W_up^T); the S shared experts as S groups over the same T rows
+    GemmArgs g1{}, a1{};
+    g1.A = sfd_x; g1.lda = c.d; g1.a_rows = plan->epd_sfd_row;
+    a1.A = x; a1.lda = c.d;
+    g1.B = a1.B = weights->w_gate; g1.B2 = a1.B2 = weights->w_up;
+    g1.b_group_stride = a1.b_group_stride = (long long)c.f * c.d;
+    g1.ldb = a1.ldb = g1.kseg = a1.kseg = g1.K = a1.K = c.d;
+    g1.Bp = packed; g1.bp_group_stride = a1.bp_group_stride = 4ll * c.f * c.d;
+    g1.N = a1.N = c.f;
+    g1.C = epd_h; g1.ldc = c.f;
+    g1.C2 = epd_gu;      // rows of 2f: [gate | up]
+    a1.C = h_shared; a1.ldc = c.S * c.f; a1.c_group_cols = c.f;
+    a1.C2 = gu_shared;   // rows of S * 2f: per shared expert [gate | up]
+    g1.grp_offset = plan->exp_offset; g1.grp_widx = plan->pos_expert; g1.ngroups = c.E;
+    g1.a_rows_total = sfd_rows_max(c);
+    a1.w_base = c.E; a1.ngroups = c.S; a1.M = c.T; a1.a_rows_total = c.T;
+    if (pairs_shared_with_routed(c) && !uses_tile128_for_few_rows(c, g1, a1)) {
+      a1.Bp = packed;
+      rc = launch_skinny(g1, &a1, true, n_epd, s);
+      if (rc == OCCULT_OK && epd_gu != nullptr) rc = launch_preactivations(c, g1, n_epd, s);
+      if (rc == OCCULT_OK && gu_shared != nullptr) rc = launch_preactivations(c, a1, c.T * c.S, s);
+    } else {
+      rc = launch_gemm_pair(c, g1, c.S > 0 ? &a1 : nullptr, true, n_epd, c.T * c.S, s);
     }
-    if (do2) {
-      GemmArgs a2{};
-      a2.A = h_shared; a2.lda = c.S * c.f; a2.a_rows = nullptr;
-      a2.B = weights->w_down; a2.B2 = nullptr;
-      a2.b_group_stride = (long long)c.d * c.f; a2.ldb = c.f; a2.kseg = c.f;
-      a2.C = y_shared; a2.ldc = c.d; a2.c_col0 = 0;
-      a2.grp_offset = nullptr; a2.grp_widx = nullptr; a2.w_base = c.E;
-      a2.ngroups = 1; a2.M = c.T; a2.N = c.d; a2.K = c.S * c.f; a2.a_rows_total = c.T;
+    if (rc) return rc;
+  }
+  if (do2) {   // y = h W_down^T; the shared experts as one product whose K dimension walks the S down matrices
+    GemmArgs g2{}, a2{};
+    g2.A = epd_h; g2.lda = c.f;
+    a2.A = h_shared; a2.lda = c.S * c.f;
+    g2.B = a2.B = weights->w_down;
+    g2.b_group_stride = a2.b_group_stride = (long long)c.d * c.f;
+    g2.ldb = a2.ldb = g2.kseg = a2.kseg = g2.K = c.f;
+    a2.K = c.S * c.f;
+    if (packed) g2.Bp = static_cast<const char*>(packed) + 4ll * c.f * c.d * (c.E + c.S);
+    g2.bp_group_stride = a2.bp_group_stride = 2ll * c.d * c.f;
+    g2.N = a2.N = c.d;
+    g2.C = epd_y; g2.ldc = c.d;
+    a2.C = y_shared; a2.ldc = c.d;
+    g2.grp_offset = plan->exp_offset; g2.grp_widx = plan->pos_expert; g2.ngroups = c.E;
+    g2.a_rows_total = n_epd;
+    a2.w_base = c.E; a2.ngroups = 1; a2.M = c.T; a2.a_rows_total = c.T;
+    if (pairs_shared_with_routed(c) && !uses_tile128_for_few_rows(c, g2, a2)) {
+      a2.Bp = g2.Bp;
+      rc = launch_skinny(g2, &a2, false, n_epd, s);
+    } else {
       int ks = 0;
       const size_t need = ffn_ws_need(c, &ks);
       if (ks > 1 && ws != nullptr && ws_bytes >= need) {
         a2.ksplit = ks;
         a2.ws = static_cast<float*>(ws);
       }
-      return launch_gemm(c, a2, false, c.T, s_shared);
+      rc = launch_gemm_pair(c, g2, c.S > 0 ? &a2 : nullptr, false, n_epd, c.T, s);
     }
-    return OCCULT_OK;
-  };
-  auto routed_experts = [&]() -> int {
-    if (do1) {
-      GemmArgs g1{};
-      g1.A = sfd_x; g1.lda = c.d; g1.a_rows = plan->epd_sfd_row;
-      g1.B = weights->w_gate; g1.B2 = weights->w_up;
-      g1.b_group_stride = (long long)c.f * c.d; g1.ldb = c.d; g1.kseg = c.d;
-      g1.Bp = packed; g1.bp_group_stride = 4ll * c.f * c.d;
-      g1.C = epd_h; g1.ldc = c.f; g1.c_col0 = 0;
-      g1.C2 = epd_gu;      // rows of 2f: [gate | up]
-      g1.grp_offset = plan->exp_offset; g1.grp_widx = plan->pos_expert; g1.w_base = 0;
-      g1.ngroups = c.E; g1.M = 0; g1.N = c.f; g1.K = c.d;
-      g1.a_rows_total = sfd_rows_max(c);
-      const int r1 = launch_gemm(c, g1, true, n_epd, s);
-      if (r1) return r1;
-    }
-    if (do2) {
-      GemmArgs g2{};
-      g2.A = epd_h; g2.lda = c.f; g2.a_rows = nullptr;
-      g2.B = weights->w_down; g2.B2 = nullptr;
-      g2.b_group_stride = (long long)c.d * c.f; g2.ldb = c.f; g2.kseg = c.f;
-      if (packed) g2.Bp = static_cast<const char*>(packed) + 4ll * c.f * c.d * (c.E + c.S);
-      g2.bp_group_stride = 2ll * c.d * c.f;
-      g2.C = epd_y; g2.ldc = c.d; g2.c_col0 = 0;
-      g2.grp_offset = plan->exp_offset; g2.grp_widx = plan->pos_expert; g2.w_base = 0;
-      g2.ngroups = c.E; g2.M = 0; g2.N = c.d; g2.K = c.f;
-      g2.a_rows_total = n_epd;
-      return launch_gemm(c, g2, false, n_epd, s);
-    }
-    return OCCULT_OK;
-  };
-
-  if (pairs_shared_with_routed(c)) {
-    if (do1) {
-      GemmArgs g1{}, a1{};
-      g1.A = sfd_x; g1.lda = c.d; g1.a_rows = plan->epd_sfd_row;
-      a1.A = x; a1.lda = c.d;
-      g1.B = a1.B = weights->w_gate; g1.B2 = a1.B2 = weights->w_up;
-      g1.b_group_stride = a1.b_group_stride = (long long)c.f * c.d;
-      g1.ldb = a1.ldb = g1.kseg = a1.kseg = g1.K = a1.K = c.d;
-      g1.Bp = a1.Bp = packed; g1.bp_group_stride = a1.bp_group_stride = 4ll * c.f * c.d;
-      g1.N = a1.N = c.f;
-      g1.C = epd_h; g1.ldc = c.f;
-      a1.C = h_shared; a1.ldc = c.S * c.f; a1.c_group_cols = c.f;
-      g1.grp_offset = plan->exp_offset; g1.grp_widx = plan->pos_expert; g1.ngroups = c.E;
-      g1.a_rows_total = sfd_rows_max(c);
-      a1.w_base = c.E; a1.ngroups = c.S; a1.M = c.T; a1.a_rows_total = c.T;
-      rc = launch_skinny(g1, &a1, true, n_epd, s);
-      if (rc) return rc;
-      if (epd_gu != nullptr) {   // a training step keeps the pre-activations: rows of 2f, [gate | up]
-        g1.C2 = epd_gu;
-        rc = launch_preactivations(c, g1, n_epd, s);
-        if (rc) return rc;
-      }
-      if (gu_shared != nullptr) {   // rows of S * 2f: per shared expert [gate | up]
-        a1.C2 = gu_shared;
-        rc = launch_preactivations(c, a1, c.T * c.S, s);
-        if (rc) return rc;
-      }
-    }
-    if (do2) {
-      GemmArgs g2{}, a2{};
-      g2.A = epd_h; g2.lda = c.f;
-      a2.A = h_shared; a2.lda = c.S * c.f;
-      g2.B = a2.B = weights->w_down;
-      g2.b_group_stride = a2.b_group_stride = (long long)c.d * c.f;
-      g2.ldb = a2.ldb = g2.kseg = a2.kseg = g2.K = c.f;
-      a2.K = c.S * c.f;   // one product over the S down matrices
-      if (packed) g2.Bp = a2.Bp = static_cast<const char*>(packed) + 4ll * c.f * c.d * (c.E + c.S);
-      g2.bp_group_stride = a2.bp_group_stride = 2ll * c.d * c.f;
-      g2.N = a2.N = c.d;
-      g2.C = epd_y; g2.ldc = c.d;
-      a2.C = y_shared; a2.ldc = c.d;
-      g2.grp_offset = plan->exp_offset; g2.grp_widx = plan->pos_expert; g2.ngroups = c.E;
-      g2.a_rows_total = n_epd;
-      a2.w_base = c.E; a2.ngroups = 1; a2.M = c.T; a2.a_rows_total = c.T;
-      rc = launch_skinny(g2, &a2, false, n_epd, s);
-      if (rc) return rc;
-    }
-    return OCCULT_OK;
-  }
-  rc = routed_experts();
-  if (rc) return rc;
-  if (c.S > 0) {
-    rc = shared_experts();
     if (rc) return rc;
   }
   return OCCULT_OK;

@@ -201,76 +201,59 @@ extern "C" int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_
   const int n_epd = c.T * c.k;
   const long long mat = (long long)c.f * c.d;
 
-  // ---- routed experts: groups = placement positions over the EPD rows -----------------------
-  GemmArgs base{};
-  base.grp_offset = plan->exp_offset; base.grp_widx = plan->pos_expert; base.w_base = 0;
-  base.ngroups = c.E; base.M = 0;
+  // routed experts: groups = placement positions over the EPD rows; shared experts: S uniform groups over the T rows
+  // of x, every token with weight 1
+  GemmArgs base{}, sh{};
+  base.grp_offset = plan->exp_offset; base.grp_widx = plan->pos_expert; base.ngroups = c.E;
+  sh.w_base = c.E; sh.ngroups = c.S; sh.M = c.T; sh.a_rows_total = c.T;
+  const bool has_shared = c.S > 0;
   OCC_REQUIRE(gu_saved == 0 || gu_saved == 1, OCCULT_EINVAL, "gu_saved=%d must be 0 or 1", gu_saved);
   if (!gu_saved) {   // g | u: the forward's first product without its SwiGLU epilogue, gate then up
-    GemmArgs a = base;
+    GemmArgs a = base, b = sh;
     a.A = sfd_x; a.lda = c.d; a.a_rows = plan->epd_sfd_row; a.a_rows_total = sfd_rows_max(c);
-    a.b_group_stride = mat; a.ldb = c.d; a.kseg = c.d;
-    a.C = epd_gu; a.ldc = 2 * c.f; a.N = c.f; a.K = c.d;
-    a.B = weights->w_gate; a.c_col0 = 0;
-    rc = launch_gemm(c, a, false, n_epd, s);
-    if (rc) return rc;
-    a.B = weights->w_up; a.c_col0 = c.f;
-    rc = launch_gemm(c, a, false, n_epd, s);
-    if (rc) return rc;
+    b.A = x; b.lda = c.d;
+    a.b_group_stride = b.b_group_stride = mat;
+    a.ldb = b.ldb = a.kseg = b.kseg = a.K = b.K = c.d;
+    a.N = b.N = c.f;
+    a.C = epd_gu; a.ldc = 2 * c.f;
+    b.C = gu_shared; b.ldc = c.S * 2 * c.f; b.c_group_cols = 2 * c.f;
+    for (int up = 0; up < 2; ++up) {
+      a.B = b.B = up ? weights->w_up : weights->w_gate;
+      a.c_col0 = b.c_col0 = up ? c.f : 0;
+      rc = launch_gemm_pair(c, a, has_shared ? &b : nullptr, false, n_epd, c.T * c.S, s);
+      if (rc) return rc;
+    }
   }
   {   // dh = epd_dy W_down: contraction over d against the transposed down projection [f][d]
-    GemmArgs a = base;
-    a.A = epd_dy; a.lda = c.d; a.a_rows = nullptr; a.a_rows_total = n_epd;
-    a.B = w_down_t; a.b_group_stride = mat; a.ldb = c.d; a.kseg = c.d;
-    a.C = epd_dh; a.ldc = c.f; a.c_col0 = 0; a.N = c.f; a.K = c.d;
-    rc = launch_gemm(c, a, false, n_epd, s);
+    GemmArgs a = base, b = sh;
+    a.A = epd_dy; a.a_rows_total = n_epd;
+    b.A = dy;
+    a.lda = b.lda = a.ldb = b.ldb = a.kseg = b.kseg = a.K = b.K = c.d;
+    a.B = b.B = w_down_t; a.b_group_stride = b.b_group_stride = mat;
+    a.N = b.N = c.f;
+    a.C = epd_dh; a.ldc = c.f;
+    b.C = dh_shared; b.ldc = c.S * c.f; b.c_group_cols = c.f;
+    rc = launch_gemm_pair(c, a, has_shared ? &b : nullptr, false, n_epd, c.T * c.S, s);
     if (rc) return rc;
   }
   rc = launch_swiglu_bwd(c, epd_gu, epd_dh, n_epd, s);
   if (rc) return rc;
-  {   // epd_dx = [dg | du] [W_gate^T | W_up^T]^T: one product over K = 2f
-    GemmArgs a = base;
-    a.A = epd_gu; a.lda = 2 * c.f; a.a_rows = nullptr; a.a_rows_total = n_epd;
-    a.B = w_gu_t; a.b_group_stride = 2 * mat; a.ldb = 2 * c.f; a.kseg = 2 * c.f;
-    a.C = epd_dx; a.ldc = c.d; a.c_col0 = 0; a.N = c.d; a.K = 2 * c.f;
-    rc = launch_gemm(c, a, false, n_epd, s);
+  if (has_shared) {
+    rc = launch_swiglu_bwd(c, gu_shared, dh_shared, (long long)c.T * c.S, s);
     if (rc) return rc;
   }
-  if (c.S == 0) return OCCULT_OK;
-
-  // ---- shared experts: S uniform groups over the T rows of x; every token with weight 1 ------
-  GemmArgs sh{};
-  sh.grp_offset = nullptr; sh.grp_widx = nullptr; sh.w_base = c.E; sh.ngroups = c.S; sh.M = c.T;
-  sh.a_rows = nullptr; sh.a_rows_total = c.T;
-  if (!gu_saved) {
-    GemmArgs a = sh;
-    a.A = x; a.lda = c.d;
-    a.b_group_stride = mat; a.ldb = c.d; a.kseg = c.d;
-    a.C = gu_shared; a.ldc = c.S * 2 * c.f; a.c_group_cols = 2 * c.f; a.N = c.f; a.K = c.d;
-    a.B = weights->w_gate; a.c_col0 = 0;
-    rc = launch_gemm(c, a, false, c.T * c.S, s);
-    if (rc) return rc;
-    a.B = weights->w_up; a.c_col0 = c.f;
-    rc = launch_gemm(c, a, false, c.T * c.S, s);
-    if (rc) return rc;
-  }
-  {
-    GemmArgs a = sh;
-    a.A = dy; a.lda = c.d;
-    a.B = w_down_t; a.b_group_stride = mat; a.ldb = c.d; a.kseg = c.d;
-    a.C = dh_shared; a.ldc = c.S * c.f; a.c_col0 = 0; a.c_group_cols = c.f; a.N = c.f; a.K = c.d;
-    rc = launch_gemm(c, a, false, c.T * c.S, s);
-    if (rc) return rc;
-  }
-  rc = launch_swiglu_bwd(c, gu_shared, dh_shared, (long long)c.T * c.S, s);
-  if (rc) return rc;
-  {   // one product whose K dimension walks the S transposed gate | up matrices
-    GemmArgs a = sh;
-    a.ngroups = 1;
-    a.A = gu_shared; a.lda = c.S * 2 * c.f;
-    a.B = w_gu_t; a.b_group_stride = 2 * mat; a.ldb = 2 * c.f; a.kseg = 2 * c.f;
-    a.C = dx_shared; a.ldc = c.d; a.c_col0 = 0; a.N = c.d; a.K = c.S * 2 * c.f;
-    rc = launch_gemm(c, a, false, c.T, s);
+  {   // epd_dx = [dg | du] [W_gate^T | W_up^T]^T: one product over K = 2f; the shared experts' K walks their S matrices
+    GemmArgs a = base, b = sh;
+    a.A = epd_gu; a.lda = 2 * c.f; a.a_rows_total = n_epd;
+    b.A = gu_shared; b.lda = c.S * 2 * c.f;
+    b.ngroups = 1;
+    a.B = b.B = w_gu_t; a.b_group_stride = b.b_group_stride = 2 * mat;
+    a.ldb = b.ldb = a.kseg = b.kseg = a.K = 2 * c.f;
+    b.K = c.S * 2 * c.f;
+    a.N = b.N = c.d;
+    a.C = epd_dx; b.C = dx_shared;
+    a.ldc = b.ldc = c.d;
+    rc = launch_gemm_pair(c, a, has_shared ? &b : nullptr, false, n_epd, c.T, s);
     if (rc) return rc;
   }
   return OCCULT_OK;

@@ -1,0 +1,380 @@
+// Grouped expert GEMM, 128-row tiles: groups of a few dozen to a few hundred rows (a prompt chunk, a training
+// micro-batch), where every expert's weights have to come from HBM for few rows each, and where 256-row tiles would
+// be mostly padding.  Same products as ffn.hip (argument block in gemm.h), bf16 only.
+#include "common.h"
+#include "gemm.h"
+
+#include <type_traits>
+
+namespace occult {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// Block = 256 threads = 4 waves (2 x 2), block tile 128 token rows x 256 weight rows, wave tile 64 x 128 = 4 x 8
+// v_mfma_f32_16x16x32_bf16 tiles (128 accumulator registers per lane), one persistent block per CU.
+//
+// What bounds it: the weights' way from HBM while groups are small, the operand stream from L2 into LDS (48 KiB per K
+// tile of 64 and 1024 matrix-pipe cycles) when they are not.  The operands go through a ring of three 48 KiB stages
+// (global_load_lds), K tile j+3 requested as soon as every wave has read the last fragments of K tile j, so two K tiles
+// are in flight at any time; a block walks its output tiles as one stream of K tiles, so the loads go on through the
+// end of a tile and its epilogue.  Rows of a K tile are whole 128-byte lines: a first version with two blocks per CU and
+// 64-byte rows (K tiles of 32) made twice the L2 requests and was bound by them.  16-byte chunk c of row r lives in slot
+// c ^ ((r >> 1) & 7) of its LDS row: conflict-free for the fragment reads (ffn.hip).
+//
+// Order of the tiles: group by group, weight columns outside, row tiles inside, cut into eight equal runs, one per
+// XCD (workgroups go to the XCDs round-robin).  The row tiles of one expert and weight block so run next to each
+// other on one XCD and the weights leave HBM once; and no XCD gets more than one tile above its share.
+//
+// One launch carries two problems of the same N: `second` (uniform groups: the shared experts) has its tiles at the
+// front of every XCD's run because its K can be longer (the shared down projection walks S matrices).
+namespace t128 {
+constexpr int BM = 128, BN = 256, BK = 64, NST = 3;
+constexpr int A_BYTES = BM * BK * 2;                // 16 KiB
+constexpr int STAGE_BYTES = A_BYTES + BN * BK * 2;  // 48 KiB: token rows, then weight rows
+constexpr int OUT_BYTES = 2048;                     // per wave: 16 rows x 64 output columns on their way out
+
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void load_to_lds_16(const char* base, unsigned off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+               : "memory", "m0");
+}
+__device__ __forceinline__ void load_to_lds_4(const char* src, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads_and_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+#pragma clang diagnostic pop
+
+__device__ __forceinline__ float swiglu_fast(float g, float u) {
+  const float e = __builtin_amdgcn_exp2f(g * -1.4426950408889634f);
+  return g * u * __builtin_amdgcn_rcpf(1.0f + e);
+}
+
+// one output tile; every field is wave-uniform
+struct Tile {
+  int valid, is_second, group, m0, n0, rows, row_base, widx;
+};
+
+// SAVE (with SWIGLU): the gate and up pre-activations are stored too (C2).
+template <bool SWIGLU, bool SAVE>
+__global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first, const GemmArgs second) {
+  static_assert(SWIGLU || !SAVE, "pre-activations exist only with the fused activation");
+  __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE_BYTES];
+  __shared__ __attribute__((aligned(16))) char s_out[4][OUT_BYTES];
+  __shared__ int s_idx[4][64];               // source rows of the next tile's token rows, per loading wave
+  __shared__ int s_goff[OCCULT_MAX_E + 1];   // first's row offsets and, before each group, its tile count
+  __shared__ int s_tpre[OCCULT_MAX_E + 1];
+  constexpr int BN_OUT = SWIGLU ? BN / 2 : BN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int n_tiles = (first.N + BN_OUT - 1) / BN_OUT;
+
+  for (int i = tid; i <= first.ngroups; i += 256) s_goff[i] = first.grp_offset[i];
+  if (wave == 0) {
+    int before = 0;
+    for (int c0 = 0; c0 < first.ngroups; c0 += 64) {
+      const int g = c0 + lane;
+      const int nt = g < first.ngroups ? (first.grp_offset[g + 1] - first.grp_offset[g] + BM - 1) / BM * n_tiles : 0;
+      int incl = nt;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+      }
+      if (g < first.ngroups) s_tpre[g] = before + incl - nt;
+      before += __shfl(incl, 63, 64);
+    }
+    if (lane == 0) s_tpre[first.ngroups] = before;
+  }
+  __syncthreads();
+
+  // this XCD's runs of the two problems' tiles
+  const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3;
+  const int mt2 = (second.M + BM - 1) / BM;
+  const long long total1 = s_tpre[first.ngroups], total2 = (long long)second.ngroups * mt2 * n_tiles;
+  const int lo1 = __builtin_amdgcn_readfirstlane((int)(total1 * xcd / 8));
+  const int cnt1 = __builtin_amdgcn_readfirstlane((int)(total1 * (xcd + 1) / 8)) - lo1;
+  const int lo2 = (int)(total2 * xcd / 8), cnt2 = (int)(total2 * (xcd + 1) / 8) - lo2;
+  auto tile_at = [&](int slot) {
+    Tile t{};
+    if (slot < cnt2) {
+      const int n = lo2 + slot, per_group = mt2 * n_tiles, within = n % per_group;
+      t.valid = t.is_second = 1;
+      t.group = n / per_group;
+      t.m0 = within % mt2 * BM; t.n0 = within / mt2 * BN_OUT;
+      t.rows = second.M;
+      t.widx = second.w_base + t.group;
+    } else if (slot - cnt2 < cnt1) {
+      const int n = lo1 + slot - cnt2;
+      for (int c0 = 0; c0 < first.ngroups; c0 += 64) {
+        const int g = c0 + lane;
+        const unsigned long long hit = __ballot(g < first.ngroups && n >= s_tpre[g] && n < s_tpre[g + 1]);
+        if (hit) {   // wave-uniform
+          t.group = c0 + __builtin_ctzll(hit);
+          break;
+        }
+      }
+      t.valid = 1;
+      t.row_base = s_goff[t.group];
+      t.rows = s_goff[t.group + 1] - t.row_base;
+      const int mt = (t.rows + BM - 1) / BM, within = n - s_tpre[t.group];
+      t.m0 = within % mt * BM; t.n0 = within / mt * BN_OUT;
+      t.widx = first.grp_widx ? first.grp_widx[t.group] : first.w_base + t.group;
+    }
+    t.group = __builtin_amdgcn_readfirstlane(t.group);
+    t.m0 = __builtin_amdgcn_readfirstlane(t.m0);
+    t.n0 = __builtin_amdgcn_readfirstlane(t.n0);
+    t.rows = __builtin_amdgcn_readfirstlane(t.rows);
+    t.row_base = __builtin_amdgcn_readfirstlane(t.row_base);
+    t.widx = __builtin_amdgcn_readfirstlane(t.widx);
+    return t;
+  };
+#define OCC_PICK(t, field) ((t).is_second ? second.field : first.field)
+
+  int slot = blockIdx.x >> 3;
+  Tile cur = tile_at(slot);
+  if (!cur.valid) return;   // uniform over the block, and so are its later tiles
+
+  // loader role: a load covers 8 rows of 128 bytes, lane -> row lane/8, slot lane%8; four loads of token rows and eight
+  // of weight rows per wave and K tile.  Token row i of this wave: tile row wave*32 + i*8 + lane/8.
+  struct {
+    const char *a, *w_even, *w_odd;   // scalar bases; w_odd: the up matrix
+    unsigned a_off[4], b_off[8];      // per-lane byte offsets, constant over K
+    long long kb;                     // byte offset of the K tile inside a token row (kt) and a weight row
+    int kin, kseg;                    // K > kseg walks consecutive weight matrices
+    long long ka, seg_step;
+  } ld;
+  // tile row of this lane for index slot `lane` (0..31) of s_idx, clamped to the group
+  auto idx_row = [&](const Tile& t, int r) { return t.row_base + min(t.m0 + r, t.rows - 1); };
+  auto request_rows = [&](const Tile& t) {   // source rows of tile t's token rows -> s_idx (nothing without a gather)
+    const int32_t* a_rows = OCC_PICK(t, a_rows);
+    if (a_rows)
+      load_to_lds_4(reinterpret_cast<const char*>(a_rows + idx_row(t, wave * 32 + (lane & 31))),
+                    __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) int*)&s_idx[wave][0]));
+  };
+  auto start_loading = [&](const Tile& t) {   // the rows requested for t have landed
+    const bool gather = OCC_PICK(t, a_rows) != nullptr;
+    const unsigned lda = OCC_PICK(t, lda), ldb = OCC_PICK(t, ldb);
+    const int lrow = lane >> 3;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned chunk = (lane & 7) ^ ((i * 4 + (lane >> 4)) & 7);
+      const unsigned src = gather ? s_idx[wave][i * 8 + lrow] : idx_row(t, wave * 32 + i * 8 + lrow);
+      ld.a_off[i] = (src * lda + chunk * 8) * 2;   // host: A is below 4 GiB
+    }
+    // with SWIGLU a wave tile's 128 weight rows are [gate 16 | up 16] x 4, so MFMA row blocks 2j and 2j + 1 hold gate
+    // and up of the same 16 output columns
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const unsigned chunk = (lane & 7) ^ ((i * 4 + (lane >> 4)) & 7);
+      const int blk = wave * 4 + (i >> 1);
+      int ncol = t.n0 + (SWIGLU ? (blk >> 1) * 16 : blk * 16) + (i & 1) * 8 + lrow;
+      if (ncol >= first.N) ncol = first.N - 1;
+      ld.b_off[i] = ((unsigned)ncol * ldb + chunk * 8) * 2;   // host: a weight matrix is below 4 GiB
+    }
+    const long long stride_b = OCC_PICK(t, b_group_stride);
+    ld.a = static_cast<const char*>(OCC_PICK(t, A));
+    ld.w_even = static_cast<const char*>(OCC_PICK(t, B)) + t.widx * stride_b * 2;
+    ld.w_odd = SWIGLU ? static_cast<const char*>(OCC_PICK(t, B2)) + t.widx * stride_b * 2 : ld.w_even;
+    ld.ka = ld.kb = 0;
+    ld.kin = 0;
+    ld.kseg = OCC_PICK(t, kseg);
+    ld.seg_step = (stride_b - ld.kseg) * 2;
+  };
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+  const unsigned lds_a = __builtin_amdgcn_readfirstlane(lds0 + wave * 4096);
+  const unsigned lds_b = __builtin_amdgcn_readfirstlane(lds0 + A_BYTES + wave * 8192);
+  constexpr int LOADS = 12;
+  // load i (0..11) of the K tile being requested, into the stage at byte st; the last one moves on to the next K tile
+  auto issue = [&](unsigned st, int i) {
+    if (i < 8) load_to_lds_16((SWIGLU && (i & 2) ? ld.w_odd : ld.w_even) + ld.kb, ld.b_off[i], lds_b + st + i * 1024);
+    else load_to_lds_16(ld.a + ld.ka, ld.a_off[i - 8], lds_a + st + (i - 8) * 1024);
+    if (i == LOADS - 1) {
+      ld.ka += BK * 2;
+      ld.kb += BK * 2;
+      ld.kin += BK;
+      if (ld.kin >= ld.kseg) {
+        ld.kin = 0;
+        ld.kb += ld.seg_step;
+      }
+    }
+  };
+  auto next = [](unsigned st) { return st == (NST - 1) * STAGE_BYTES ? 0u : st + STAGE_BYTES; };
+
+  // fragments of the two K steps of 32: lane l holds row l%16, K group l/16 of a 16-row block
+  int foff[2];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) foff[kk] = (lane & 15) * 128 + (((4 * kk + (lane >> 4)) ^ ((lane >> 1) & 7)) * 16);
+  const char* frag_a = smem + wm * 8192;
+  const char* frag_b = smem + A_BYTES + wn * 16384;
+  bf16x8 fa[2][4], fb[8];
+  auto read_a = [&](int kk, unsigned st, int i) {
+    fa[kk][i] = *reinterpret_cast<const bf16x8*>(frag_a + st + foff[kk] + i * 2048);
+  };
+  auto read_b = [&](int kk, unsigned st, int i) {
+    fb[i] = *reinterpret_cast<const bf16x8*>(frag_b + st + foff[kk] + i * 2048);
+  };
+
+  f32x4 acc[8][4];   // [weight-row block][token-row block]
+  // K step kk of the K tile in stage st: 8 groups of {4 products with, between them, one tile load into stage st_load
+  // and up to two fragment reads of the next step (out of stage st_next)}, pinned in source order.  A fragment takes the registers of one
+  // multiplied before; fb[7] follows in group 0 of its own step.  Step 1 has the block-wide wait between groups 1 and 2,
+  // when the K tile's last fragments have been read: the next K tile has landed (for every wave) and stage st is free.
+  // Its first six loads go out behind the wait, the other six in step 0 of the next K tile.
+  auto step = [&](auto kk_, unsigned st, unsigned st_next, unsigned st_load) {
+    constexpr int kk = decltype(kk_)::value;
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+      if (kk == 1 && g == 2) wait_loads_and_barrier<LOADS>();
+#pragma unroll
+      for (int mi = 0; mi < 4; ++mi) {
+        acc[g][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[g], fa[kk][mi], acc[g][mi], 0, 0, 0);
+        // (fb[g] itself is free after the fourth product)
+        if (mi == 0 && g >= 2) issue(st_load, kk == 1 ? g - 2 : g + 4);
+        if (g == 2 || g == 3) {
+          if (mi == 1) read_a(kk ^ 1, st_next, 2 * g - 4);
+          if (mi == 2) read_a(kk ^ 1, st_next, 2 * g - 3);
+        }
+        if (g >= 4 && mi == 1) read_b(kk ^ 1, st_next, g - 4);
+        if (g >= 5 && mi == 2) read_b(kk ^ 1, st_next, g - 1);
+        if (g == 0 && mi == 3) read_b(kk, st, 7);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  const std::integral_constant<int, 0> k0{};
+  const std::integral_constant<int, 1> k1{};
+
+  // first tile: rows, K tiles 0 and 1, half of K tile 2
+  request_rows(cur);
+  wait_loads();   // a wave reads back only its own indices
+  start_loading(cur);
+  int nk = OCC_PICK(cur, K) / BK;   // host: >= 3
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int i = 0; i < (k < 2 ? LOADS : LOADS / 2); ++i) issue(k * STAGE_BYTES, i);
+  wait_loads_and_barrier<LOADS + LOADS / 2>();
+  unsigned st = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) read_a(0, 0, i);
+#pragma unroll
+  for (int i = 0; i < 7; ++i) read_b(0, 0, i);
+  __builtin_amdgcn_sched_barrier(0);
+
+  while (true) {
+    slot += stride;
+    Tile nxt = tile_at(slot);
+    const bool more = nxt.valid;
+    if (!more) nxt = cur;   // keeps everything derived from it addressable
+    request_rows(nxt);
+#pragma unroll
+    for (int ni = 0; ni < 8; ++ni)
+#pragma unroll
+      for (int mi = 0; mi < 4; ++mi) acc[ni][mi] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // step 0 of a K tile requests the second half of the K tile two ahead, step 1 the first half of the one three ahead
+    step(k0, st, st, next(next(st)));
+    for (int kt = 0; kt < nk - 3; ++kt) {
+      const unsigned sn = next(st);
+      step(k1, st, sn, st);
+      step(k0, sn, sn, st);
+      st = sn;
+    }
+    if (nk < 5) wait_loads();   // the rows requested above have landed: two block-wide waits lie behind otherwise
+    start_loading(nxt);
+    {
+      const unsigned s1 = next(st), s2 = next(s1);
+      step(k1, st, s1, st);
+      step(k0, s1, s1, st);
+      step(k1, s1, s2, s1);
+      step(k0, s2, s2, s1);
+      step(k1, s2, st, s2);
+    }
+
+    // epilogue.  acc[ni][mi] element e of lane l: token row mi*16 + l%16, weight row ni*16 + (l/16)*4 + e of the wave
+    // tile.  bf16 results pass through the wave's 2 KiB of LDS, 16 rows x 64 columns at a time (16-byte slots swizzled by
+    // the row), and leave as row segments of 128 bytes.
+    {
+      char* stg = s_out[wave];
+      constexpr int W_COLS = SWIGLU ? 64 : 128;      // output columns of a wave tile
+      const int rows_left = cur.rows - cur.m0 - wm * 64;
+      const int col_w = cur.n0 + wn * W_COLS;
+      const int ccol = OCC_PICK(cur, c_col0) + cur.group * OCC_PICK(cur, c_group_cols);
+      const int ldc = OCC_PICK(cur, ldc);
+      const int scol = (lane & 7) * 8, srow = lane >> 3;
+      constexpr int CHUNKS = SAVE ? 3 : W_COLS / 64;   // per 16-row block; SAVE: outputs, gate, up
+#pragma unroll
+      for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+        for (int ch = 0; ch < CHUNKS; ++ch) {
+#pragma unroll
+          for (int nn = 0; nn < 4; ++nn) {   // 16 output columns
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              if (SWIGLU && ch == 0) v[e] = swiglu_fast(acc[2 * nn][mi][e], acc[2 * nn + 1][mi][e]);
+              else if (SWIGLU) v[e] = acc[2 * nn + ch - 1][mi][e];
+              else v[e] = acc[4 * ch + nn][mi][e];
+            }
+            uint2 pk;
+            pk.x = pack_bf16(v[0], v[1]);
+            pk.y = pack_bf16(v[2], v[3]);
+            const int row = lane & 15;
+            *reinterpret_cast<uint2*>(stg + row * 128 + (((nn * 2 + (lane >> 5)) ^ ((row >> 1) & 7)) * 16) +
+                                      ((lane >> 4) & 1) * 8) = pk;
+          }
+          const bool pre = SAVE && ch > 0;
+          const int col = col_w + (SWIGLU ? 0 : ch * 64) + scol;
+          __bf16* C = static_cast<__bf16*>(pre ? OCC_PICK(cur, C2) : OCC_PICK(cur, C));
+          const long long pitch = pre ? 2ll * ldc : ldc;
+          const int c0 = pre ? 2 * ccol + (ch - 1) * first.N : ccol;
+          __bf16* dst = C + (cur.row_base + cur.m0 + wm * 64 + mi * 16) * pitch + c0 + col;
+#pragma unroll
+          for (int it = 0; it < 2; ++it) {
+            const int row = it * 8 + srow;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(stg + row * 128 + (((lane & 7) ^ ((row >> 1) & 7)) * 16));
+            if (mi * 16 + row < rows_left && col < first.N) *reinterpret_cast<u32x4*>(dst + row * pitch) = v;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if (!more) break;   // uniform over the block
+    cur = nxt;
+    nk = OCC_PICK(cur, K) / BK;
+  }
+#undef OCC_PICK
+  wait_loads();   // the loads issued for a tile that does not exist must land before the block's LDS is released
+}
+}  // namespace t128
+
+int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, hipStream_t s) {
+  const int bn_out = swiglu ? t128::BN / 2 : t128::BN;
+  const long long n_tiles = (a.N + bn_out - 1) / bn_out;
+  GemmArgs second{};
+  if (b != nullptr) second = *b;
+  OCC_REQUIRE(a.grp_offset != nullptr && a.K >= 3 * t128::BK && a.K % 64 == 0 && a.N % 64 == 0 &&
+                  (b == nullptr || (b->grp_offset == nullptr && b->N == a.N && b->K >= 3 * t128::BK && b->K % 64 == 0)),
+              OCCULT_EINVAL, "grouped GEMM shape outside the 128-row tiles' range");
+  const long long t1 = (total_rows / t128::BM + a.ngroups) * n_tiles;   // at most one partial tile per group
+  const long long t2 = (long long)second.ngroups * ((second.M + t128::BM - 1) / t128::BM) * n_tiles;
+  OCC_REQUIRE(t1 + t2 < (1ll << 28), OCCULT_EINVAL, "grouped GEMM grid too large");
+  int cus = 0;
+  const int rc = device_cu_count(&cus);
+  if (rc) return rc;
+  long long blocks = ((t1 + 7) / 8 + (t2 + 7) / 8) * 8;   // one block per CU, a multiple of 8 so a block keeps its XCD
+  const long long resident = cus >= 8 ? cus / 8 * 8 : 8;
+  if (blocks > resident) blocks = resident;
+  const bool save = swiglu && a.C2 != nullptr;
+  const dim3 grid((unsigned)blocks), block(256);
+  if (save) hipLaunchKernelGGL((t128::grouped_gemm_bf16<true, true>), grid, block, 0, s, a, second);
+  else if (swiglu) hipLaunchKernelGGL((t128::grouped_gemm_bf16<true, false>), grid, block, 0, s, a, second);
+  else hipLaunchKernelGGL((t128::grouped_gemm_bf16<false, false>), grid, block, 0, s, a, second);
+  OCC_LAUNCH_CHECK("grouped_gemm");
+  return OCCULT_OK;
+}
+
+}  // namespace occult

@@ -43,4 +43,15 @@ struct GemmArgs {
 // rows over all groups.  Picks the tile shape from the rows per group.  Returns an OCCULT_* code.
 int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total_rows, hipStream_t s);
 
+// The same product for the routed experts (`a`, grouped rows) and, unless b is NULL, for the shared ones (`b`,
+// uniform groups, rows_b rows over all of them, same N): one launch where the 128-row tiles take `a`, two otherwise.
+int launch_gemm_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, int rows_b,
+                     hipStream_t s);
+
+// compute units of the current device
+int device_cu_count(int* out);
+
+// 128-row tiles (ffn_tile128.hip): `a` grouped, `b` NULL or uniform; bf16.
+int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, hipStream_t s);
+
 }  // namespace occult

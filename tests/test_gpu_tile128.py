@@ -1,0 +1,75 @@
+"""The 128-row tiles of the grouped expert products (routed and shared experts in one launch), at the sizes where they
+can go wrong: rows around a tile, half-filled column tiles, the shortest K (three and four K tiles), more than 64 groups,
+empty groups, a shared down projection whose K walks several matrices.  Every stored tensor against the float64
+product of its own stored operands, element by element."""
+import numpy as np
+import pytest
+import torch
+
+from inputs import workloads as wl
+from paper_2505_13345_amd.layer import OccultLayer
+from tests.helpers import assert_one_rounding, require_gpu, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # T, d, f, E, S, k, D
+    (128, 192, 192, 4, 1, 4, 2),      # exactly one row tile per expert (k = E), three K tiles everywhere
+    (129, 192, 320, 4, 2, 4, 2),      # one row more; half-filled column tiles; shared K of 2 x 320
+    (127, 256, 448, 2, 3, 2, 1),      # one row less; four K tiles
+    (640, 320, 192, 132, 1, 4, 2),    # more than 64 groups, a few rows each
+    (300, 192, 256, 96, 1, 1, 4),     # some groups empty
+    (900, 512, 704, 8, 0, 2, 4),      # no shared experts; two row tiles per group
+    (700, 1088, 192, 12, 1, 4, 3),    # column tiles of 1088 outputs: 4 whole and a quarter
+]
+
+
+@pytest.mark.parametrize("T,d,f,E,S,k,D", CASES)
+def test_tile128_products(T, d, f, E, S, k, D):
+    say(f"128-row tiles T={T} d={d} f={f} E={E} S={S} k={k}")
+    dev = require_gpu()
+    wk = wl.make_workload(wl.LayerShape("t128", T=T, d=d, f=f, E=E, S=S, k=k, D=D, dtype="bf16", components=4), seed=T + d)
+    layer = OccultLayer(T, d, f, E, S, k, D, "bf16")
+    x = to_dev(wk.x, "bf16", dev)
+    wg, wu, wd = (to_dev(a, "bf16", dev) for a in (wk.w_gate, wk.w_up, wk.w_down))
+    layer.forward(torch.from_numpy(wk.logits).to(dev), x, wg, wu, wd, train=True)
+    layer.transpose_weights(wg, wu, wd)
+    dy = wl.round_to_bf16(np.random.default_rng(T).standard_normal((T, d)).astype(np.float32))
+    _, epd_dy, _ = layer.combine_backward(to_dev(dy, "bf16", dev))
+    gu_fwd = layer.epd_gu.double().cpu().numpy()
+    gu_sh_fwd = layer.gu_shared.double().cpu().numpy() if S else None
+    layer.expert_ffn_backward(x, wg, wu, epd_dy, to_dev(dy, "bf16", dev))
+    torch.cuda.synchronize()
+    f64 = lambda t: t.double().cpu().numpy()
+    tab = layer.tables()
+    off, expert = tab["exp_offset"].cpu().numpy(), tab["pos_expert"].cpu().numpy()
+    src = tab["epd_sfd_row"].cpu().numpy()
+    sfd_x, h, y, dh, dgu, dx, dyq = (f64(t) for t in (layer.sfd_x, layer.epd_h, layer.epd_y, layer.epd_dh, layer.epd_gu,
+                                                     layer.epd_dx, epd_dy))
+    W = [np.asarray(a, dtype=np.float64) for a in (wk.w_gate, wk.w_up, wk.w_down)]
+
+    def check(tag, e, rows_x, rows_gu, rows_h, rows_dy, rows_dh):
+        g, u = rows_x @ W[0][e].T, rows_x @ W[1][e].T
+        assert_one_rounding(rows_gu, np.concatenate([g, u], axis=1), f"pre-activations {tag}")
+        assert_one_rounding(rows_h, g / (1.0 + np.exp(-g)) * u, f"h {tag}")
+        assert_one_rounding(rows_dh, rows_dy @ W[2][e], f"dh {tag}")
+
+    for P in range(E):
+        r = slice(off[P], off[P + 1])
+        if off[P + 1] == off[P]:
+            continue
+        e = int(expert[P])
+        check(f"expert {e}", e, sfd_x[src[r]], gu_fwd[r], h[r], dyq[r], dh[r])
+        assert_one_rounding(y[r], h[r] @ W[2][e].T, f"y expert {e}")
+        assert_one_rounding(dx[r], dgu[r, :f] @ W[0][e] + dgu[r, f:] @ W[1][e], f"dx expert {e}")
+    if S:
+        hs, ys, dhs, dgus, dxs = (f64(t) for t in (layer.h_shared, layer.y_shared, layer.dh_shared, layer.gu_shared,
+                                                   layer.dx_shared))
+        y_ref, dx_ref = np.zeros((T, d)), np.zeros((T, d))
+        for s in range(S):
+            c, c2 = slice(s * f, (s + 1) * f), slice(s * 2 * f, (s + 1) * 2 * f)
+            check(f"shared {s}", E + s, wk.x.astype(np.float64), gu_sh_fwd[:, c2], hs[:, c], dy.astype(np.float64), dhs[:, c])
+            y_ref += hs[:, c] @ W[2][E + s].T
+            dx_ref += dgus[:, c2][:, :f] @ W[0][E + s] + dgus[:, c2][:, f:] @ W[1][E + s]
+        assert_one_rounding(ys, y_ref, "y shared")
+        assert_one_rounding(dxs, dx_ref, "dx shared")
