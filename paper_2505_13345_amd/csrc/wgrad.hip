@@ -10,16 +10,17 @@
 // operands are both contiguous along the contracted index).
 //
 // bf16 kernel (namespace wgd below).  Block = 256 threads = 4 waves (2 x 2), block tile 256 x 256
-// outputs, wave tile 128 x 128 = 4 x 4 v_mfma_f32_32x32x16_bf16 tiles (256 accumulator registers, one
+// outputs, wave tile 128 x 128 = 8 x 8 v_mfma_f32_16x16x32_bf16 tiles (256 accumulator registers, one
 // block per CU).  Outputs are f32 (gradient accumulation across calls is exact to f32), stored
-// straight from the accumulators: 32 lanes cover 128 contiguous bytes.  With 8 groups or more a
+// straight from the accumulators: four lanes cover 64 contiguous bytes.  With 8 groups or more a
 // group's tiles are launched on one XCD (workgroup id % 8), so its rows are fetched into one L2.
 #include "common.h"
+
+#include <type_traits>
 
 namespace occult {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 struct WgradArgs {
   const void* A;             // [rows][lda]: its columns index the output rows (M of them)
@@ -50,18 +51,24 @@ struct WgradArgs {
 // (64 KiB per CU) in flight, which covers a step's products but not the latency of memory under
 // load (measured: products alone 985 TFLOP/s, with the loads 480).  Here a step is 32 rows, the raw
 // row-major tiles go from global memory straight into a ring of NST LDS stages
-// (global_load_lds_dwordx4: no registers held while a load is in flight), NST - 1 steps ahead, and
+// (global_load_lds_dwordx4: no registers held while a load is in flight), NST steps ahead, and
 // the transposition happens in the fragment reads: ds_read_b64_tr_b16 gives every lane
 // of a 16-lane block the 4 contracted elements of its own column out of 4 rows x 16 columns that the
 // block's lanes address (lanes 4e..4e+3 address row e).  Two such reads make one MFMA operand.
 // One load instruction fills 1 KiB = 2 tile rows; 16-byte chunk c of tile row k sits at chunk
-// c ^ ((k & 3) << 2) (realised by the loading lane's choice of source chunk), so that the 4 rows x
-// 64 bytes a block reads fall on different banks.  Rows past the group's end: the A side reads a
-// page of zeros, the B side repeats the group's last row (0 * finite = 0).  Gathered row indices
-// take the same road two steps ahead of the rows they address: one 4-byte-per-lane LDS-directed
-// load per wave and step into a small ring, read back with ordinary LDS reads.  Every step issues
+// c ^ ((k & 3) << 2) ^ ((k >> 3 & 1) << 1) (realised by the loading lane's choice of source chunk), so that
+// the 2 x 4 rows x 32 bytes which two of a read's blocks address fall on different banks.  Rows past the
+// group's end: the A side reads a page of zeros, the B side repeats the group's last row (0 * finite = 0).
+// Gathered row indices take the same road two steps ahead of the rows they address: one 4-byte-per-lane
+// LDS-directed load per wave and step into a small ring, read back with ordinary LDS reads.  Every step issues
 // the same number of loads (steps past the end are clamped like rows past the end), so one
-// constant vmcnt tells that the current step's tiles, and the indices about to be used, have landed.
+// constant vmcnt tells that the next step's tiles, and the indices about to be used, have landed.
+//
+// A step's fragments are read into registers under the products of the step before (two register sets), so a stage is
+// free again one step earlier: four steps are in flight, and the LDS pipe (a step's 128 transposing reads at 64 B/clk
+// and 32 KiB of writes, about 1130 cycles per CU) and the matrix pipe (1024) can work side by side.  Before, a
+// step read its first fragments behind its barrier with nothing to multiply, and 32x32x16 products drew more power
+// (ffn.hip).  Training step of 16384 tokens (64 experts, d = 2048, f = 1024) about 115 us less of 6000.
 namespace wgd {
 constexpr int BM = 256, BN = 256, BK = 32;
 constexpr int NST = 4;   // the index ring below assumes 4
@@ -90,6 +97,12 @@ __device__ __forceinline__ void wait_loads_and_barrier() {
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 #pragma clang diagnostic pop
+
+// acc (16 output rows x 16 columns) += A block^T * B block over 32 rows; assembly for the reason given in ffn.hip: the
+// compiler, given the builtin, moves the 64 accumulator quads between the register files
+__device__ __forceinline__ void mfma16(f32x4& acc, const bf16x8& b, const bf16x8& a) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
+}
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
@@ -133,13 +146,14 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
   const long long widx = a.grp_widx ? a.grp_widx[group] : (a.w_base + group);
   const int nk = (r1 - r0 + BK - 1) / BK;
 
-  f32x16 acc[4][4];
+  f32x4 acc[8][8];   // [output-row block][output-column block] of 16 x 16
 #pragma unroll
-  for (int mi = 0; mi < 4; ++mi)
+  for (int mi = 0; mi < 8; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.0f;
+    for (int ni = 0; ni < 8; ++ni) {
+      acc[mi][ni] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      asm volatile("" : "+a"(acc[mi][ni]));   // cleared here, long before the first product reads it
+    }
 
   if (nk > 0) {
     // loader role: a load instruction covers tile rows kb, kb + 1; lane = (row rr, chunk position p)
@@ -156,7 +170,7 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int k = wave * 8 + i * 2 + rr;           // tile row of this lane
-      int ca = p ^ ((k & 3) << 2), cb = ca;          // source chunk of this lane's position
+      int ca = p ^ ((k & 3) << 2) ^ (((k >> 3) & 1) << 1), cb = ca;   // source chunk of this lane's position
       if (ca >= a_chunks) ca = 0;                     // columns past M or N: any valid chunk (never stored)
       if (cb >= b_chunks) cb = 0;
       off_a[i] = (unsigned)(k * a_pitch + ca * 16);
@@ -202,37 +216,27 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
       }
     };
 
-    // fragment reads: lane l = 16 b + j, j = 4 e + q: block b covers columns 16 (b & 1) .. + 16 and rows
-    // 8 (b >> 1) + e (first read), + 4 (second read); the lane addresses 4 columns (8 bytes) of row e
+    // fragment reads: lane l = 16 b + j, j = 4 e + q: block b covers rows 8 b + e (first read), + 4 (second read) of 16
+    // columns; the lane addresses 4 columns (8 bytes) of row e
     const int fb = lane >> 4, fe = (lane >> 2) & 3, fq = lane & 3;
-    const int f_row = 8 * (fb >> 1) + fe;                       // + 16 * ks, + 4 for the second read
-    const int f_col4 = 4 * (fb & 1) + fq;                       // 8-byte unit inside the 32-column block
     typedef __attribute__((address_space(3))) char lds_char;
-    auto frag = [&](const lds_char* op, int col0, int ks) -> bf16x8 {   // col0: first column of the 32-column block
-      const int row = ks * 16 + f_row;
-      const int unit = (col0 >> 2) + f_col4;                    // 8-byte unit inside the tile row
-      const int pos = ((unit >> 1) ^ (fe << 2)) * 16 + (unit & 1) * 8;
-      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-          (bf16x4 __attribute__((address_space(3)))*)(op + row * 512 + pos));
-      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-          (bf16x4 __attribute__((address_space(3)))*)(op + (row + 4) * 512 + pos));
+    const int f_sw = (fe << 2) ^ ((fb & 1) << 1);
+    int f_off[8];   // byte offset of 16-column block i (0..7) of a wave tile
+#pragma unroll
+    for (int i = 0; i < 8; ++i) f_off[i] = (8 * fb + fe) * 512 + (((2 * i + (fq >> 1)) ^ f_sw) * 16) + (fq & 1) * 8;
+    bf16x8 fa[2][8], fbv[2][8];
+    auto frag = [&](const lds_char* op, int i) -> bf16x8 {
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)(op + f_off[i]));
+      const bf16x4 hi =
+          __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)(op + f_off[i] + 4 * 512));
       return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
-    auto read_frags = [&](int s, int ks, bf16x8 (&fa)[4], bf16x8 (&fbv)[4]) {
-      const lds_char* As = (const lds_char*)smem + (s % NST) * STAGE_BYTES;
-      const lds_char* Bs = As + OP_BYTES;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        fa[i] = frag(As, wm * 128 + i * 32, ks);
-        fbv[i] = frag(Bs, wn * 128 + i * 32, ks);
-      }
-    };
-    auto mma = [&](const bf16x8 (&fa)[4], const bf16x8 (&fbv)[4]) {
-#pragma unroll
-      for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
-          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[mi], fbv[ni], acc[mi][ni], 0, 0, 0);
+    // fragment r (0..15) of step s, in the order in which the products want them: the first block of A, the blocks of B,
+    // the other blocks of A
+    auto read_frag = [&](int set, int s, int r) {
+      const lds_char* st = (const lds_char*)smem + (s % NST) * STAGE_BYTES;
+      if (r >= 1 && r <= 8) fbv[set][r - 1] = frag(st + OP_BYTES + wn * 256, r - 1);
+      else fa[set][r == 0 ? 0 : r - 8] = frag(st + wm * 256, r == 0 ? 0 : r - 8);
     };
 
     // source rows of this wave's 8 tile rows of step s (clamped to the group) -> its ring slot s % 4
@@ -247,77 +251,79 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
       for (int s = 0; s < 4; ++s) issue_idx(s);          // one ring of indices
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // a wave reads only its own indices: no barrier
     }
-    // The prologue issues in the order the loop continues: indices of step NST go into the slot step 0 has just
-    // been read from (its reads have returned: the tile loads' addresses depend on them), BEFORE the tiles of
-    // steps 1 and 2, so that the constant count below covers them when step 1 reads them.
+    // Loads complete in order.  Per step a wave issues [indices of step s + 6,] 8 tile loads of step s + 4.  At the start
+    // of step s the tiles of step s + 1 and the indices of step s + 4 have to have landed: behind them stand the tiles of
+    // steps s + 2 and s + 3 and the indices of step s + 5.  The prologue issues in the order the loop continues; an index
+    // slot is refilled once it has been read (the tile loads' addresses depend on the reads).
     issue(0);
-    if (GATHER) issue_idx(NST);
+    issue(1);
+    if (GATHER) issue_idx(4);
+    issue(2);
+    if (GATHER) issue_idx(5);
+    issue(3);
+    wait_loads_and_barrier<3 * OPS - (GATHER ? 1 : 0)>();   // tiles of step 0
 #pragma unroll
-    for (int s = 1; s < NST - 1; ++s) issue(s);
-    // Loads complete in order.  Per step a wave issues [indices of step s + NST + 1,] 8 tile loads of step
-    // s + NST - 1.  The tiles of step s are older than the (NST - 2) * OPS loads of the last NST - 2 steps;
-    // the indices used (step s + NST - 1, issued first two steps ago) are older than all but one of them.
-    // After the barrier every wave's tiles of step s are in LDS, and every wave is done with the stage that
-    // step s + NST - 1 overwrites.
-    // Two loops, so that neither has a branch inside (one would make the register allocator move the 256
-    // accumulators around): first the steps whose prefetched step lies wholly inside the group.
-    const int n_main = max(0, (r1 - r0) / BK - (NST - 1));
-    int s = 0;
-    for (; s < n_main; ++s) {
-      wait_loads_and_barrier<(NST - 2) * OPS - (GATHER ? 1 : 0)>();
-      bf16x8 fa[2][4], fbv[2][4];
-      read_frags(s, 0, fa[0], fbv[0]);
-      __builtin_amdgcn_sched_barrier(0);
-      const int sn = s + NST - 1;
-      if (GATHER) issue_idx(s + NST + 1);
-      // With one wave per SIMD nothing hides an instruction clump: the first half's 16 products are issued as
-      // 8 groups of {2 MFMAs, 1 tile load, 1 fragment read for the second half}, pinned in source order.
-      const unsigned st = smem_base + (unsigned)(sn % NST) * STAGE_BYTES;
+    for (int r = 0; r < 16; ++r) read_frag(0, 0, r);
+    // One step: 16 groups of {4 products, fragment reads of the next step, a tile load}, pinned in source order (one wave
+    // per SIMD: nothing else hides an instruction clump).  After its barrier the tiles of step s + 1 are in LDS, and every
+    // wave has the fragments of step s in registers, so that step s + 4 may overwrite its stage.
+    // full: all rows of step s + 4 lie inside the group
+    auto step = [&](int set, int s, auto full) {
+      wait_loads_and_barrier<2 * OPS - (GATHER ? 1 : 0)>();
+      const int sn = s + NST;
+      if (GATHER) issue_idx(s + NST + 2);
+      const unsigned st = smem_base + (unsigned)(s % NST) * STAGE_BYTES + wave * 4096u;
       const char* a_step = a_cols + (long long)(r0 + sn * BK) * a_pitch;
       const char* b_step = b_cols + (long long)(r0 + sn * BK) * b_pitch;
-      const lds_char* As = (const lds_char*)smem + (s % NST) * STAGE_BYTES;
-      const lds_char* Bs = As + OP_BYTES;
+      int rb[4];
 #pragma unroll
-      for (int g = 0; g < 8; ++g) {
-        const int mi = g >> 1, nj = (g & 1) * 2;
-        acc[mi][nj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][mi], fbv[0][nj], acc[mi][nj], 0, 0, 0);
-        acc[mi][nj + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][mi], fbv[0][nj + 1], acc[mi][nj + 1], 0, 0, 0);
-        const int i = g & 3;
-        const unsigned kb = (unsigned)(wave * 8 + i * 2);
-        if (g < 4) {
-          load_to_lds_16(a_step, off_a[i], st + kb * 512u);
-          fa[1][g] = frag(As, wm * 128 + g * 32, 1);
+      for (int i = 0; i < 4; ++i) rb[i] = GATHER ? s_idx[wave][sn & 3][i * 2 + rr] : 0;   // fetched two steps ago
+      auto tile_load = [&](int i) {   // 0..3: A, 4..7: B
+        const int j = i & 3, row = r0 + sn * BK + wave * 8 + j * 2 + rr;
+        const unsigned dst = st + (unsigned)j * 1024u;
+        if (i < 4) {
+          if constexpr (decltype(full)::value) load_to_lds_16(a_step, off_a[j], dst);
+          else load_to_lds_16(row < r1 ? a_step + off_a[j] : zeros, dst);
+        } else if (GATHER) {
+          asm volatile("" : "+v"(rb[j]));   // nothing of the address is computed, and so waited for, before this place
+          load_to_lds_16(b_cols + (long long)rb[j] * b_pitch + chunk_b[j], dst + (unsigned)OP_BYTES);
         } else {
-          if (GATHER) {
-            const long long rb = s_idx[wave][sn & 3][i * 2 + rr];   // fetched two steps ago
-            load_to_lds_16(b_cols + rb * b_pitch + chunk_b[i], st + (unsigned)OP_BYTES + kb * 512u);
-          } else {
-            load_to_lds_16(b_step, off_b[i], st + (unsigned)OP_BYTES + kb * 512u);
-          }
-          fbv[1][g - 4] = frag(Bs, wn * 128 + (g - 4) * 32, 1);
+          if constexpr (decltype(full)::value) load_to_lds_16(b_step, off_b[j], dst + (unsigned)OP_BYTES);
+          else load_to_lds_16(b_cols + (long long)min(row, r1 - 1) * b_pitch + chunk_b[j], dst + (unsigned)OP_BYTES);
         }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      mma(fa[1], fbv[1]);
+      };
+#pragma unroll
+      for (int g = 0; g < 16; ++g)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int t = 4 * g + q, mi = t >> 3, ni = t & 7;
+          mfma16(acc[mi][ni], fbv[set][ni], fa[set][mi]);
+          if (q == 0 && (g & 1) == 0) tile_load(g / 2);
+          if (q == 1 && g < 12) read_frag(set ^ 1, s + 1, g < 4 ? 2 * g : g + 4);
+          if (q == 2 && g < 4) read_frag(set ^ 1, s + 1, 2 * g + 1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // two loops, so that the first has no clamping: pairs of steps whose prefetched steps lie wholly inside the group
+    const int n_main = max(0, (r1 - r0) / BK - NST) & ~1;
+    int s = 0;
+    for (; s < n_main; s += 2) {
+      step(0, s, std::true_type{});
+      step(1, s + 1, std::true_type{});
     }
     // then the steps that prefetch the group's last rows or past them
-    for (; s < nk; ++s) {
-      wait_loads_and_barrier<(NST - 2) * OPS - (GATHER ? 1 : 0)>();
-      bf16x8 fa[2][4], fbv[2][4];
-      read_frags(s, 0, fa[0], fbv[0]);
-      if (GATHER) issue_idx(s + NST + 1);
-      issue_tail(s + NST - 1);
-      read_frags(s, 1, fa[1], fbv[1]);
-      mma(fa[0], fbv[0]);
-      mma(fa[1], fbv[1]);
+    for (; s < nk; s += 2) {
+      step(0, s, std::false_type{});
+      if (s + 1 >= nk) break;   // block-uniform
+      step(1, s + 1, std::false_type{});
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the clamped loads past the end, before the block's LDS is released
   }
 
-  // accumulator element e of lane l: output row (e / 4) * 8 + (l / 32) * 4 + e % 4, column l % 32 of its 32 x 32 tile.
+  // accumulator element e of lane l: output row l % 16, column (l / 16) * 4 + e of its 16 x 16 tile (the operands are
+  // swapped), so 16-byte stores of four lanes cover 64 contiguous bytes.
   // Stores (and, when accumulating, loads) go through a buffer descriptor over the wave tile's valid rows: rows
   // past M lie beyond its range and are dropped by the hardware, columns past N are sent there: no branches.
-  const int frow = lane & 31, fk = lane >> 5;
   const int rows_left = min(a.M - (m0 + wm * 128), 128);
   const int cols_left = min(a.N - (n0 + wn * 128), 128);
   // a row slice writes its partial product densely into the scratch tensor [slice][group][M][N] instead
@@ -332,31 +338,33 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
       (unsigned)__builtin_amdgcn_readfirstlane((unsigned)c_tile);
   const __amdgpu_buffer_rsrc_t c_rsrc = __builtin_amdgcn_make_buffer_rsrc(
       reinterpret_cast<void*>(c_tile_u), 0, __builtin_amdgcn_readfirstlane((int)n_rec), 0x00020000);
+  const int orow = lane & 15, ocol = (lane >> 4) * 4;
+  // wait states of the last products' results (the compiler does not see that they are matrix instructions)
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 #pragma unroll
-  for (int mi = 0; mi < 4; ++mi)
+  for (int mi = 0; mi < 8; ++mi) {
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni) {
-      const int nl = ni * 32 + frow;
-      unsigned off[16];
+    for (int ni = 0; ni < 8; ++ni) asm volatile("" : "+a"(acc[mi][ni]));   // read from here on, not all of them at once
+    unsigned off[8];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int ml = mi * 32 + (e >> 2) * 8 + fk * 4 + (e & 3);
-        off[e] = nl < cols_left ? (unsigned)(ml * ldc + nl) * 4u : n_rec;
-      }
-      if (accumulate) {   // block-uniform; the 16 loads of a tile are in flight together
-        float old[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          old[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(c_rsrc, (int)off[e], 0, 0));
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[mi][ni][e] += old[e];
-      }
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float v = acc[mi][ni][e];   // (a bit cast applied to the vector element itself stores element 0 sixteen times)
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), c_rsrc, (int)off[e], 0, 0);
-      }
+    for (int ni = 0; ni < 8; ++ni) {   // host: N % 8 == 0, so four columns are inside together
+      const int nl = ni * 16 + ocol;
+      off[ni] = nl < cols_left ? (unsigned)((mi * 16 + orow) * ldc + nl) * 4u : n_rec;
     }
+    f32x4 v[8];
+#pragma unroll
+    for (int ni = 0; ni < 8; ++ni) v[ni] = acc[mi][ni];
+    if (accumulate) {   // block-uniform; the 8 loads of a row block are in flight together
+      u32x4 old[8];
+#pragma unroll
+      for (int ni = 0; ni < 8; ++ni) old[ni] = __builtin_amdgcn_raw_buffer_load_b128(c_rsrc, (int)off[ni], 0, 0);
+#pragma unroll
+      for (int ni = 0; ni < 8; ++ni) v[ni] += __builtin_bit_cast(f32x4, old[ni]);
+    }
+#pragma unroll
+    for (int ni = 0; ni < 8; ++ni)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[ni]), c_rsrc, (int)off[ni], 0, 0);
+  }
 }
 }  // namespace wgd
 
