@@ -1,8 +1,9 @@
 // occult_route: softmax top-k gating with optional collaboration pruning
 // (paper Eq. 1; Section 3.3, routing-score-based pruning).
 //
-// Sixteen lanes per token, four tokens per wavefront.  Lane r of a token's sixteen holds the scores of experts r, r+16,
-// r+32, ... (E <= 256); a selection round is the lane's best followed by a 4-step arg-max over the sixteen lanes.
+// Sixteen lanes per token, four tokens per wavefront (a whole wavefront per token in small batches).  Lane r of a token's
+// sixteen holds the scores of experts r, r+16, r+32, ... (E <= 256); a selection round is the lane's best followed by a
+// 4-step arg-max over the sixteen lanes.
 // Selection compares raw scores (softmax is monotone): larger first, equal -> lower expert index.
 // Routing is bound by these vector operations, not by its 300 bytes per token; a whole wavefront per token spent them on
 // one token instead of four (18.5 us at 16384 tokens of 64 experts, k = 8; 40 us pruned).
@@ -45,18 +46,21 @@ __device__ __forceinline__ float exp_ref(float z) {
 
 // Cross-lane steps on the VALU's data-parallel primitives (no LDS crossbar): four symmetric exchanges leave every lane of
 // a row of 16 with the row's result.
-template <int CTRL>
-__device__ __forceinline__ int dpp_i(int v) {
-  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
+// Two row broadcasts carry it on into lane 63 where a token has the whole wavefront.
+template <int CTRL, int ROW_MASK = 0xF>
+__device__ __forceinline__ int dpp_i(int own, int v) {   // rows outside the mask keep `own`
+  return __builtin_amdgcn_update_dpp(own, v, CTRL, ROW_MASK, 0xF, false);
 }
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v) {
-  return __builtin_bit_cast(float, dpp_i<CTRL>(__builtin_bit_cast(int, v)));
+template <int CTRL, int ROW_MASK = 0xF>
+__device__ __forceinline__ float dpp_f(float own, float v) {
+  return __builtin_bit_cast(float, dpp_i<CTRL, ROW_MASK>(__builtin_bit_cast(int, own), __builtin_bit_cast(int, v)));
 }
 constexpr int kQuadSwap1 = 0xB1;       // quad_perm [1,0,3,2]
 constexpr int kQuadSwap2 = 0x4E;       // quad_perm [2,3,0,1]
 constexpr int kRowHalfMirror = 0x141;
 constexpr int kRowMirror = 0x140;
+constexpr int kRowBcast15 = 0x142;     // lane 15 of each row into the next row (rows 1 and 3 take it)
+constexpr int kRowBcast31 = 0x143;     // lane 31 into rows 2 and 3
 
 // (value, index) as one 64-bit key whose unsigned order is "larger value first, equal values -> lower index":
 // the value's bits made monotone (negative floats inverted, positive ones offset) in the high word, the
@@ -74,31 +78,41 @@ __device__ __forceinline__ float key_value(key_t64 key) {
   return __builtin_bit_cast(float, ord ^ ((ord >> 31) ? 0x80000000u : 0xFFFFFFFFu));
 }
 
-template <int CTRL>
+template <int CTRL, int ROW_MASK = 0xF>
 __device__ __forceinline__ key_t64 key_max_step(key_t64 key) {
-  const int lo = dpp_i<CTRL>((int)(unsigned)key), hi = dpp_i<CTRL>((int)(unsigned)(key >> 32));
+  const int klo = (int)(unsigned)key, khi = (int)(unsigned)(key >> 32);
+  const int lo = dpp_i<CTRL, ROW_MASK>(klo, klo), hi = dpp_i<CTRL, ROW_MASK>(khi, khi);
   const key_t64 other = ((key_t64)(unsigned)hi << 32) | (unsigned)lo;
   return other > key ? other : key;
 }
-// largest key of a row of 16 lanes, in every one of them
-__device__ __forceinline__ key_t64 row_max(key_t64 key) {
+// largest key of a token's LANES lanes, in every one of them
+template <int LANES>
+__device__ __forceinline__ key_t64 token_max(key_t64 key) {
   key = key_max_step<kQuadSwap1>(key);
   key = key_max_step<kQuadSwap2>(key);
   key = key_max_step<kRowHalfMirror>(key);
-  return key_max_step<kRowMirror>(key);
+  key = key_max_step<kRowMirror>(key);
+  if (LANES == 16) return key;
+  key = key_max_step<kRowBcast15, 0xA>(key);
+  key = key_max_step<kRowBcast31, 0xC>(key);
+  return ((key_t64)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(key >> 32), 63) << 32) |
+         (unsigned)__builtin_amdgcn_readlane((int)(unsigned)key, 63);
 }
-__device__ __forceinline__ float row_sum(float v) {
-  v += dpp_f<kQuadSwap1>(v);
-  v += dpp_f<kQuadSwap2>(v);
-  v += dpp_f<kRowHalfMirror>(v);
-  v += dpp_f<kRowMirror>(v);
-  return v;
+template <int LANES>
+__device__ __forceinline__ float token_sum(float v) {
+  v += dpp_f<kQuadSwap1>(v, v);
+  v += dpp_f<kQuadSwap2>(v, v);
+  v += dpp_f<kRowHalfMirror>(v, v);
+  v += dpp_f<kRowMirror>(v, v);
+  if (LANES == 16) return v;
+  v += dpp_f<kRowBcast15, 0xA>(0.0f, v);
+  v += dpp_f<kRowBcast31, 0xC>(0.0f, v);
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
-constexpr int kRouteTokens = 16;   // tokens per block of 256 threads
-
-// EPL = experts per lane, E <= 16 * EPL.  Lane r of a token writes slots r and r + 16.
-template <int EPL, bool PRUNE>
+// LANES = lanes per token, 16 or 64; EPL = experts per lane, E <= LANES * EPL.  Lane r of a token writes slots r and,
+// with 16 lanes, r + 16.
+template <int LANES, int EPL, bool PRUNE>
 __global__ __launch_bounds__(256) void route_kernel(
     const float* __restrict__ logits, int T, int E, int k, int D, int G,
     const int32_t* __restrict__ expert_pos, int n_d, int prune_mode, int renorm,
@@ -108,16 +122,17 @@ __global__ __launch_bounds__(256) void route_kernel(
     for (int e = threadIdx.x; e < E; e += blockDim.x) s_dev[e] = (expert_pos ? expert_pos[e] : e) / G;
     __syncthreads();
   }
-  const int lane = threadIdx.x & 63, r = lane & 15, row0 = lane & 48;
-  const int t = blockIdx.x * kRouteTokens + (threadIdx.x >> 4);
-  if (t >= T) return;   // all sixteen lanes of a token leave together; no barrier follows
+  const int lane = threadIdx.x & 63, r = lane & (LANES - 1), row0 = lane & (64 - LANES);
+  constexpr int SLOTS = OCCULT_MAX_K > LANES ? OCCULT_MAX_K / LANES : 1, DEVS = OCCULT_MAX_D / LANES;   // per lane
+  const int t = blockIdx.x * (256 / LANES) + threadIdx.x / LANES;
+  if (t >= T) return;   // all lanes of a token leave together; no barrier follows
   const float* row = logits + (size_t)t * E;
 
   float v0[EPL];     // the token's scores as read (with -0.0 folded onto +0.0)
   key_t64 key[EPL];  // 0: taken, not allowed or not there
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    const int e = r + 16 * i;
+    const int e = r + LANES * i;
     // NaN and -inf scores are read as the lowest finite value and +inf as the highest: each round then selects a new
     // index below E whatever the scores hold (ids index other tables downstream), and the device sums and gates stay
     // finite
@@ -128,21 +143,21 @@ __global__ __launch_bounds__(256) void route_kernel(
     key_t64 best = key[0];
 #pragma unroll
     for (int i = 1; i < EPL; ++i) best = key[i] > best ? key[i] : best;
-    best = row_max(best);
+    best = token_max<LANES>(best);
 #pragma unroll
     for (int i = 0; i < EPL; ++i) key[i] = key[i] == best ? 0ull : key[i];
     return best;
   };
 
-  key_t64 slot[2] = {0ull, 0ull};   // slots r and r + 16
+  key_t64 slot[SLOTS] = {};
   auto keep_slot = [&](int s, key_t64 best) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-      if (r + 16 * h == s) slot[h] = best;
+    for (int h = 0; h < SLOTS; ++h)
+      if (r + LANES * h == s) slot[h] = best;
   };
   float mx = 0.0f;
-  float dev_sum[4] = {};         // mode 1: scores of devices r, r + 16, r + 32, r + 48
-  unsigned long long kept = 0;   // mode 2: devices kept so far (the same in a token's sixteen lanes)
+  float dev_sum[DEVS] = {};      // mode 1: scores of devices r, r + LANES, ...
+  unsigned long long kept = 0;   // mode 2: devices kept so far (the same in a token's lanes)
   int n_kept = 0;
 
   for (int s = 0; s < k; ++s) {
@@ -154,8 +169,8 @@ __global__ __launch_bounds__(256) void route_kernel(
       if (prune_mode == 1) {
         const float q = exp_ref(key_value(best) - mx);
 #pragma unroll
-        for (int h = 0; h < 4; ++h)
-          if (r + 16 * h == dev) dev_sum[h] = dev_sum[h] + q;   // sequential in slot order
+        for (int h = 0; h < DEVS; ++h)
+          if (r + LANES * h == dev) dev_sum[h] = dev_sum[h] + q;   // sequential in slot order
       } else if (!((kept >> dev) & 1ull) && n_kept < n_d) {
         kept |= 1ull << dev;
         ++n_kept;
@@ -170,8 +185,10 @@ __global__ __launch_bounds__(256) void route_kernel(
     // control flow below differs between the tokens of a wave, never between the lanes of a token.
     unsigned long long taken[4] = {0ull, 0ull, 0ull, 0ull};
     auto expert_of = [&](int s) {   // expert in slot s
-      const int lo = __shfl(key_index(slot[0]), row0 + (s & 15), 64), hi = __shfl(key_index(slot[1]), row0 + (s & 15), 64);
-      return s < 16 ? lo : hi;
+      const int lo = __shfl(key_index(slot[0]), row0 + (s & (LANES - 1)), 64);
+      if (SLOTS == 1) return lo;
+      const int hi = __shfl(key_index(slot[SLOTS - 1]), row0 + (s & (LANES - 1)), 64);
+      return s < LANES ? lo : hi;
     };
     for (int s = 0; s < k; ++s) {
       const int e = expert_of(s);
@@ -186,7 +203,7 @@ __global__ __launch_bounds__(256) void route_kernel(
       if ((kept >> s_dev[e]) & 1ull) continue;
       const int32_t* trow = sim_table + (size_t)e * (E - 1);
       int found = -1;
-      for (int base = 0; base < E - 1 && found < 0; base += 16) {
+      for (int base = 0; base < E - 1 && found < 0; base += LANES) {
         const int q = base + r;
         int c = 0;
         bool ok = false;
@@ -198,42 +215,42 @@ __global__ __launch_bounds__(256) void route_kernel(
             if ((c >> 6) == m) word = taken[m];
           ok = ((kept >> s_dev[c]) & 1ull) && !((word >> (c & 63)) & 1ull);
         }
-        const unsigned hits = (unsigned)(__ballot(ok) >> row0) & 0xFFFFu;
-        const int c_hit = __shfl(c, row0 + (hits ? __ffs((int)hits) - 1 : 0), 64);
+        const unsigned long long hits = (__ballot(ok) >> row0) & (~0ull >> (64 - LANES));
+        const int c_hit = __shfl(c, row0 + (hits ? __ffsll((long long)hits) - 1 : 0), 64);
         if (hits) found = c_hit;
       }
       // host checks n_d * G >= k, so a free expert on a kept device always exists
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         if ((found >> 6) == q) taken[q] |= 1ull << (found & 63);
-      // its score sits in lane found % 16 of the token, register found / 16
+      // its score sits in lane found % LANES of the token, register found / LANES
       float fv = v0[0];
 #pragma unroll
       for (int i = 1; i < EPL; ++i)
-        if ((found >> 4) == i) fv = v0[i];
-      fv = __shfl(fv, row0 + (found & 15), 64);
+        if (found / LANES == i) fv = v0[i];
+      fv = __shfl(fv, row0 + (found & (LANES - 1)), 64);
       keep_slot(s, argmax_key(fv, found));
     }
   } else if (PRUNE) {
     if (prune_mode == 1) {
-      key_t64 dk[4];
+      key_t64 dk[DEVS];
 #pragma unroll
-      for (int h = 0; h < 4; ++h) dk[h] = r + 16 * h < D ? argmax_key(dev_sum[h], r + 16 * h) : 0ull;
+      for (int h = 0; h < DEVS; ++h) dk[h] = r + LANES * h < D ? argmax_key(dev_sum[h], r + LANES * h) : 0ull;
       kept = 0;
       for (int q = 0; q < n_d; ++q) {
         key_t64 best = dk[0];
 #pragma unroll
-        for (int h = 1; h < 4; ++h) best = dk[h] > best ? dk[h] : best;
-        best = row_max(best);
+        for (int h = 1; h < DEVS; ++h) best = dk[h] > best ? dk[h] : best;
+        best = token_max<LANES>(best);
         kept |= 1ull << key_index(best);
 #pragma unroll
-        for (int h = 0; h < 4; ++h) dk[h] = dk[h] == best ? 0ull : dk[h];
+        for (int h = 0; h < DEVS; ++h) dk[h] = dk[h] == best ? 0ull : dk[h];
       }
     }
     // second pass: the k best experts on the surviving devices
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
-      const int e = r + 16 * i;
+      const int e = r + LANES * i;
       const bool ok = (e < E) && ((kept >> s_dev[e < E ? e : 0]) & 1ull);
       key[i] = ok ? argmax_key(v0[i], e) : 0ull;
     }
@@ -244,21 +261,21 @@ __global__ __launch_bounds__(256) void route_kernel(
   float part = 0.0f;
 #pragma unroll
   for (int i = 0; i < EPL; ++i)
-    if (r + 16 * i < E) part += exp_ref(v0[i] - mx);
-  const float denom = row_sum(part);
-  float g[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) g[h] = r + 16 * h < k ? exp_ref(key_value(slot[h]) - mx) / denom : 0.0f;
+    if (r + LANES * i < E) part += exp_ref(v0[i] - mx);
+  const float denom = token_sum<LANES>(part);
+  const bool second = SLOTS > 1 && k > LANES;   // uniform
+  float g[2] = {r < k ? exp_ref(key_value(slot[0]) - mx) / denom : 0.0f, 0.0f};
+  if (second) g[1] = r + LANES < k ? exp_ref(key_value(slot[SLOTS - 1]) - mx) / denom : 0.0f;
   if (renorm) {
-    const float sel = row_sum(g[0] + g[1]);
+    const float sel = token_sum<LANES>(g[0] + g[1]);
     g[0] = g[0] / sel;
-    g[1] = g[1] / sel;
+    if (second) g[1] = g[1] / sel;
   }
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
-    if (r + 16 * h < k) {
-      ids[(size_t)t * k + r + 16 * h] = key_index(slot[h]);
-      w[(size_t)t * k + r + 16 * h] = g[h];
+  for (int h = 0; h < SLOTS; ++h)
+    if (r + LANES * h < k) {
+      ids[(size_t)t * k + r + LANES * h] = key_index(slot[h]);
+      w[(size_t)t * k + r + LANES * h] = g[h];
     }
 }
 
@@ -568,20 +585,29 @@ extern "C" int occult_route(const occult_cfg_t* cfg, const float* logits, int32_
     OCC_REQUIRE(c.sim_table != nullptr, OCCULT_ENULLPTR, "prune_mode 3 needs cfg.sim_table");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int G = c.E / c.D;
-  const dim3 grid((c.T + kRouteTokens - 1) / kRouteTokens), block(256);
-#define OCC_ROUTE_LAUNCH(N, P)                                                                  \
-  hipLaunchKernelGGL((route_kernel<N, P>), grid, block, 0, s, logits, c.T, c.E, c.k, c.D, G,    \
+  // A wavefront per token while every token can have a SIMD of a 256-CU chip to itself: the call is then one token's
+  // chain of dependent steps, shortest with few experts per lane (3.5 us with sixteen lanes, 2.4 with 64, at 128 tokens
+  // of 60 experts).  Beyond that the steps are shared by four tokens (16384 tokens: 18 us with 64 lanes, 8 with sixteen).
+  const bool few = c.T <= 1024;
+  const int per_block = few ? 4 : 16;
+  const dim3 grid((c.T + per_block - 1) / per_block), block(256);
+#define OCC_ROUTE_LAUNCH(L, N, P)                                                                  \
+  hipLaunchKernelGGL((route_kernel<L, N, P>), grid, block, 0, s, logits, c.T, c.E, c.k, c.D, G,    \
                      c.expert_pos, c.n_d, c.prune_mode, c.renorm, c.sim_table, ids, w)
-#define OCC_ROUTE(N)                     \
-  do {                                   \
-    if (c.n_d > 0) OCC_ROUTE_LAUNCH(N, true); \
-    else OCC_ROUTE_LAUNCH(N, false);     \
+#define OCC_ROUTE(L, N)                        \
+  do {                                         \
+    if (c.n_d > 0) OCC_ROUTE_LAUNCH(L, N, true); \
+    else OCC_ROUTE_LAUNCH(L, N, false);          \
   } while (0)
-  if (c.E <= 16) OCC_ROUTE(1);
-  else if (c.E <= 32) OCC_ROUTE(2);
-  else if (c.E <= 64) OCC_ROUTE(4);
-  else if (c.E <= 128) OCC_ROUTE(8);
-  else OCC_ROUTE(16);
+  if (few) {
+    if (c.E <= 64) OCC_ROUTE(64, 1);
+    else if (c.E <= 128) OCC_ROUTE(64, 2);
+    else OCC_ROUTE(64, 4);
+  } else if (c.E <= 16) OCC_ROUTE(16, 1);
+  else if (c.E <= 32) OCC_ROUTE(16, 2);
+  else if (c.E <= 64) OCC_ROUTE(16, 4);
+  else if (c.E <= 128) OCC_ROUTE(16, 8);
+  else OCC_ROUTE(16, 16);
 #undef OCC_ROUTE
 #undef OCC_ROUTE_LAUNCH
   OCC_LAUNCH_CHECK("route_kernel");

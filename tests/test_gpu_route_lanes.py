@@ -1,4 +1,4 @@
-"""Routing with sixteen lanes per token and the score Gram matrix in tiles of 16 x 16, at the expert and token counts
+"""Routing with a wavefront per token (up to 1024 tokens) and with sixteen lanes per token, and the score Gram matrix in tiles of 16 x 16, at the expert and token counts
 where their lanes, registers and slices end."""
 import numpy as np
 import pytest
@@ -15,9 +15,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("E", [1, 2, 15, 16, 17, 31, 33, 63, 65, 127, 129, 255, 256])
 @pytest.mark.parametrize("k", [1, 16, 17, 32])
-def test_route_at_lane_edges(E, k):
-    k, T = min(k, E), 19
-    say(f"route E={E} k={k}")
+@pytest.mark.parametrize("T", [19, 1024, 1025])
+def test_route_at_lane_edges(E, k, T):
+    k = min(k, E)
+    say(f"route E={E} k={k} T={T}")
     dev = require_gpu()
     lg = wl.random_logits(T, E, seed=E, scale=1.3)
     lg[::3] = np.round(lg[::3])   # ties
