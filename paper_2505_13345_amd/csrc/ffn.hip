@@ -1213,6 +1213,9 @@ static int launch_skinny(const GemmArgs& a, const GemmArgs* b, bool swiglu, int 
   return OCCULT_OK;
 }
 
+// rows per group from which a product takes the 256-row tiles: uniform groups; grouped rows of the gate/up product
+constexpr long long kBigRowsUniform = 192, kBigRowsSwiglu = 129;
+
 // *fused_save: the pre-activations asked for through a.C2 were written by the launch itself
 static int launch_gemm_main(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total_rows, hipStream_t s,
                             bool* fused_save_out) {
@@ -1224,7 +1227,7 @@ static int launch_gemm_main(const occult_cfg_t& c, const GemmArgs& a, bool swigl
     // (measured on 60 experts, d = 2048, f = 1408: the gate/up product is weight-bound on the
     // 128-row tiles until an expert's rows no longer fit one of them; the down projection is
     // faster on the 256-row tiles from about 64 rows per expert)
-    const long long big_rows = a.grp_offset == nullptr ? 192 : (swiglu ? 129 : 64);
+    const long long big_rows = a.grp_offset == nullptr ? kBigRowsUniform : (swiglu ? kBigRowsSwiglu : 64);
     const bool use_big =
         (long long)total_rows >= big_rows * groups && a.ksplit <= 1 && a.K >= 2 * t256::BK && a.N % 64 == 0;
     const bool wide = (long long)a.a_rows_total * a.lda * 2 >= (1ll << 32);
@@ -1328,7 +1331,13 @@ static bool uses_tile128(const occult_cfg_t& c, const GemmArgs& a, const GemmArg
 
 int launch_gemm_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, int rows_b,
                      hipStream_t s) {
-  if (total_rows > 0 && uses_tile128(c, a, b, total_rows)) return launch_tile128(a, b, swiglu, total_rows, s);
+  if (total_rows > 0 && uses_tile128(c, a, b, total_rows)) {
+    GemmArgs p = a, q{};
+    if (b != nullptr) q = *b;
+    p.silu_rcp = total_rows >= kBigRowsSwiglu * p.ngroups;   // as launch_gemm_main would choose
+    q.silu_rcp = rows_b >= kBigRowsUniform * q.ngroups;
+    return launch_tile128(p, b ? &q : nullptr, swiglu, total_rows, s);
+  }
   const int rc = launch_gemm(c, a, swiglu, total_rows, s);
   if (rc || b == nullptr) return rc;
   return launch_gemm(c, *b, swiglu, rows_b, s);

@@ -49,10 +49,13 @@ __device__ __forceinline__ void wait_loads_and_barrier() {
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 #pragma clang diagnostic pop
 
-__device__ __forceinline__ float swiglu_fast(float g, float u) {
+// silu(g) * u in the form of the kernel that the rows of a group would otherwise take (silu_rcp, wave-uniform): with the
+// 256-row tiles' hardware reciprocal, or with the f32 division of the weight-streaming and small-tile kernels
+__device__ __forceinline__ float swiglu_rcp(float g, float u) {
   const float e = __builtin_amdgcn_exp2f(g * -1.4426950408889634f);
   return g * u * __builtin_amdgcn_rcpf(1.0f + e);
 }
+__device__ __forceinline__ float swiglu_div(float g, float u) { return g / (1.0f + __expf(-g)) * u; }
 
 // one output tile; every field is wave-uniform
 struct Tile {
@@ -314,11 +317,18 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
 #pragma unroll
           for (int nn = 0; nn < 4; ++nn) {   // 16 output columns
             float v[4];
+            if (SWIGLU && ch == 0) {
+              const f32x4 g = acc[2 * nn][mi], u = acc[2 * nn + 1][mi];
+              if (OCC_PICK(cur, silu_rcp)) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              if (SWIGLU && ch == 0) v[e] = swiglu_fast(acc[2 * nn][mi][e], acc[2 * nn + 1][mi][e]);
-              else if (SWIGLU) v[e] = acc[2 * nn + ch - 1][mi][e];
-              else v[e] = acc[4 * ch + nn][mi][e];
+                for (int e = 0; e < 4; ++e) v[e] = swiglu_rcp(g[e], u[e]);
+              } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = swiglu_div(g[e], u[e]);
+              }
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = SWIGLU ? acc[2 * nn + ch - 1][mi][e] : acc[4 * ch + nn][mi][e];
             }
             uint2 pk;
             pk.x = pack_bf16(v[0], v[1]);

@@ -31,9 +31,11 @@ struct GemmArgs {
   int M;                    // rows when grp_offset == NULL
   int a_rows_total;         // rows of the A buffer that may be addressed (bounds 32-bit offsets)
   int plain_map;            // small-tile kernel: workgroup id = m-tile * n_tiles + n-tile (tiny grids)
-  int ksplit;               // small-tile kernel, one group, no SWIGLU: blockIdx.y takes K tiles
-                            // [y*nk/ksplit, (y+1)*nk/ksplit) and writes f32 sums to ws; 0 or 1 = off
-  float* ws;                // [ksplit][M][N] partial sums
+  int ksplit;               // K in consecutive parts, K tiles [y*nk/ksplit, (y+1)*nk/ksplit), whose f32 sums are added in
+                            // order; 0 or 1 = one sum.  Small-tile kernel (one group, no SWIGLU): blockIdx.y takes part
+                            // y and writes its sums to ws; 128-row tiles: a block adds the parts in registers
+  float* ws;                // small-tile kernel: [ksplit][M][N] partial sums
+  int silu_rcp;             // 128-row tiles, SWIGLU: activation as the 256-row tiles compute it (hardware reciprocal)
   int N;                    // output columns (for SWIGLU: columns of h)
   int K;
 };

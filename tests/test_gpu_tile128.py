@@ -73,3 +73,34 @@ def test_tile128_products(T, d, f, E, S, k, D):
             dx_ref += dgus[:, c2][:, :f] @ W[0][E + s] + dgus[:, c2][:, f:] @ W[1][E + s]
         assert_one_rounding(ys, y_ref, "y shared")
         assert_one_rounding(dxs, dx_ref, "dx shared")
+
+
+def test_activation_of_groups_of_a_few_rows_divides_first():
+    """50 routed rows per group and 100 shared ones: silu(g) * u is g / (1 + exp(-g)) first, with the f32 division, and
+    then times u, so a large negative gate beside a large up value gives -0 (g * u alone overflows f32); the other
+    values are the f64 activation rounded once."""
+    T, d, f, E, S, k, D = 100, 192, 192, 4, 1, 2, 2
+    say(f"activation T={T} E={E} S={S} k={k}")
+    dev = require_gpu()
+    wk = wl.make_workload(wl.LayerShape("silu", T=T, d=d, f=f, E=E, S=S, k=k, D=D, dtype="bf16", components=4), seed=3)
+    x, wg, wu = wk.x.copy(), wk.w_gate.copy(), wk.w_up.copy()
+    wg[:, :32, 0], wu[:, :32, 0] = -2.0 ** 33, 2.0 ** 33
+    x[::3] = 0.0
+    x[::3, 0] = 2.0 ** 33          # gate -2^66, up 2^66 in the first 32 columns of these tokens
+    x[1::3, 0] = x[2::3, 0] = 0.0
+    layer = OccultLayer(T, d, f, E, S, k, D, "bf16")
+    layer.forward(torch.from_numpy(wk.logits).to(dev), *(to_dev(a, "bf16", dev) for a in (x, wg, wu, wk.w_down)))
+    torch.cuda.synchronize()
+    tab = layer.tables()
+    off, expert = tab["exp_offset"].cpu().numpy(), tab["pos_expert"].cpu().numpy()
+    src = tab["epd_sfd_row"].cpu().numpy()
+    sfd_x = layer.sfd_x.double().cpu().numpy()
+    groups = [(int(expert[P]), sfd_x[src[off[P]:off[P + 1]]], layer.epd_h[off[P]:off[P + 1]]) for P in range(E)]
+    for e, rows, h in groups + [(E, x.astype(np.float64), layer.h_shared)]:
+        h = h.float().cpu().numpy()
+        g, u = rows @ wg[e].astype(np.float64).T, rows @ wu[e].astype(np.float64).T
+        far = g < -100.0           # exp(-g) overflows f32 well before: the activation is 0
+        assert far[:, :32].any() and np.array_equal(h[far], np.zeros(far.sum(), dtype=np.float32)), f"expert {e}"
+        near = np.abs(u).max(axis=1) < 1e6
+        g, u = g[near], u[near]
+        assert_one_rounding(h[near], g / (1.0 + np.exp(-g)) * u, f"h of expert {e}")
