@@ -1213,23 +1213,27 @@ static int launch_skinny(const GemmArgs& a, const GemmArgs* b, bool swiglu, int 
   return OCCULT_OK;
 }
 
+constexpr int kStreamParts = 4;   // parts of K of that kernel where its waves split K: one per wave
+
 // rows per group from which a product takes the 256-row tiles: uniform groups; grouped rows of the gate/up product
 constexpr long long kBigRowsUniform = 192, kBigRowsSwiglu = 129;
+
+static bool uses_tile256(const GemmArgs& a, bool swiglu, int total_rows) {
+  // 256-row tiles once groups average enough rows and there are at least two K tiles to pipeline
+  // (measured on 60 experts, d = 2048, f = 1408: the gate/up product is weight-bound on the
+  // 128-row tiles until an expert's rows no longer fit one of them; the down projection is
+  // faster on the 256-row tiles from about 64 rows per expert)
+  const long long big_rows = a.grp_offset == nullptr ? kBigRowsUniform : (swiglu ? kBigRowsSwiglu : 64);
+  return (long long)total_rows >= big_rows * a.ngroups && a.ksplit <= 1 && a.K >= 2 * t256::BK && a.N % 64 == 0;
+}
 
 // *fused_save: the pre-activations asked for through a.C2 were written by the launch itself
 static int launch_gemm_main(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total_rows, hipStream_t s,
                             bool* fused_save_out) {
   *fused_save_out = false;
   if (c.dtype == OCCULT_BF16) {
-    const int groups = a.ngroups;
-    // 256-row tiles once groups average enough rows and there are at least two K tiles to pipeline
-    // (an A operand of 4 GiB or more takes the variant with 64-bit row offsets)
-    // (measured on 60 experts, d = 2048, f = 1408: the gate/up product is weight-bound on the
-    // 128-row tiles until an expert's rows no longer fit one of them; the down projection is
-    // faster on the 256-row tiles from about 64 rows per expert)
-    const long long big_rows = a.grp_offset == nullptr ? kBigRowsUniform : (swiglu ? kBigRowsSwiglu : 64);
-    const bool use_big =
-        (long long)total_rows >= big_rows * groups && a.ksplit <= 1 && a.K >= 2 * t256::BK && a.N % 64 == 0;
+    const bool use_big = uses_tile256(a, swiglu, total_rows);
+    // an A operand of 4 GiB or more takes the variant of the 256-row tiles with 64-bit row offsets
     const bool wide = (long long)a.a_rows_total * a.lda * 2 >= (1ll << 32);
     // only the 256-row tiles store the pre-activations themselves (not built with 64-bit offsets: registers)
     const bool fused_save = swiglu && a.C2 != nullptr && use_big && !wide;
@@ -1288,17 +1292,14 @@ static int launch_gemm_main(const occult_cfg_t& c, const GemmArgs& a, bool swigl
   return OCCULT_OK;
 }
 
-// The two pre-activations of a gate/up product `a` (a.C2) as two more products without the activation: only the
-// 256-row tiles store them from the product's own launch.
-static int launch_preactivations(const occult_cfg_t& c, const GemmArgs& a, int total_rows, hipStream_t s) {
-  bool fused_save = false;
+// one pre-activation (gate or up) of a gate/up product `a`, stored where a.C2 asks for it, as a product of its own
+static GemmArgs preactivation(const GemmArgs& a, bool up) {
   GemmArgs p = a;
   p.C = a.C2; p.ldc = 2 * a.ldc; p.c_group_cols = 2 * a.c_group_cols; p.C2 = nullptr; p.B2 = nullptr; p.Bp = nullptr;
-  p.c_col0 = 2 * a.c_col0;
-  int rc = launch_gemm_main(c, p, false, total_rows, s, &fused_save);
-  if (rc) return rc;
-  p.B = a.B2; p.c_col0 = 2 * a.c_col0 + a.N;
-  return launch_gemm_main(c, p, false, total_rows, s, &fused_save);
+  p.B = up ? a.B2 : a.B;
+  p.c_col0 = 2 * a.c_col0 + (up ? a.N : 0);
+  p.ksplit = 0;
+  return p;
 }
 
 int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total_rows, hipStream_t s) {
@@ -1306,7 +1307,9 @@ int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total
   bool fused_save = false;
   int rc = launch_gemm_main(c, a, swiglu, total_rows, s, &fused_save);
   if (rc) return rc;
-  if (swiglu && a.C2 != nullptr && !fused_save) rc = launch_preactivations(c, a, total_rows, s);
+  if (!swiglu || a.C2 == nullptr || fused_save) return rc;
+  for (int up = 0; up < 2 && rc == OCCULT_OK; ++up)
+    rc = launch_gemm_main(c, preactivation(a, up != 0), false, total_rows, s, &fused_save);
   return rc;
 }
 
@@ -1317,16 +1320,35 @@ int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total
 //    357 us) or add a last round of its own: worth it down to any number of rows and up to about 800 per group
 //    (656 rows: 1116 us against 1057; 768: equal);
 //  - without, from 24 rows (32: 226 us against 220; 20: 215 against 218) up to about 240 (237: 339 against 323 us; 256
-//    and 287: slower, 325: faster, by how the tiles happen to divide over the CUs);
-//  - when the pre-activations are to be stored, from any number: the alternative is two more passes over the weights.
+//    and 287: slower, 325: faster, by how the tiles happen to divide over the CUs).
 static bool fits_tile128(const GemmArgs& a) {
   return a.K >= 192 && a.K % 64 == 0 && a.N % 64 == 0 && (long long)a.a_rows_total * a.lda * 2 < (1ll << 32);
 }
 static bool uses_tile128(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, int total_rows) {
   if (c.dtype != OCCULT_BF16 || a.grp_offset == nullptr || !fits_tile128(a) || (b != nullptr && !fits_tile128(*b)))
     return false;
-  const long long lo = b != nullptr || a.C2 != nullptr ? 0 : 24, hi = b != nullptr ? 800 : 240;
+  const long long lo = b != nullptr ? 0 : 24, hi = b != nullptr ? 800 : 240;
   return total_rows >= lo * a.ngroups && total_rows < hi * a.ngroups;
+}
+
+// Parts of K, summed one by one, of the kernel that would otherwise take a product: the 128-row tiles sum the same parts,
+// so that a row's result does not depend on which of the two takes its batch.  The weight-streaming kernel's four waves
+// take a quarter each of the gate/up product; a.ksplit: parts asked for.
+static int k_parts(const GemmArgs& a, bool swiglu, int total_rows) {
+  if (a.ksplit > 1) return a.ksplit;
+  return swiglu && !uses_tile256(a, swiglu, total_rows) && streams_weights(a, total_rows) ? kStreamParts : 1;
+}
+
+static int launch_preactivation_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, int total_rows, int rows_b,
+                                     hipStream_t s) {
+  int rc = OCCULT_OK;
+  for (int up = 0; up < 2 && rc == OCCULT_OK; ++up) {
+    const GemmArgs p = preactivation(a, up != 0);
+    GemmArgs q{};
+    if (b != nullptr) q = preactivation(*b, up != 0);
+    rc = launch_gemm_pair(c, p, b ? &q : nullptr, false, total_rows, rows_b, s);
+  }
+  return rc;
 }
 
 int launch_gemm_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, int rows_b,
@@ -1336,7 +1358,13 @@ int launch_gemm_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b
     if (b != nullptr) q = *b;
     p.silu_rcp = total_rows >= kBigRowsSwiglu * p.ngroups;   // as launch_gemm_main would choose
     q.silu_rcp = rows_b >= kBigRowsUniform * q.ngroups;
-    return launch_tile128(p, b ? &q : nullptr, swiglu, total_rows, s);
+    p.ksplit = k_parts(a, swiglu, total_rows);
+    if (b != nullptr) q.ksplit = k_parts(*b, swiglu, rows_b);
+    // pre-activations are stored as one sum over K: by the launch itself unless it sums the activation's in parts
+    const bool apart = a.C2 != nullptr && (p.ksplit > 1 || q.ksplit > 1);
+    if (apart) p.C2 = q.C2 = nullptr;
+    const int rc = launch_tile128(p, b ? &q : nullptr, swiglu, total_rows, s);
+    return rc || !apart ? rc : launch_preactivation_pair(c, a, b, total_rows, rows_b, s);
   }
   const int rc = launch_gemm(c, a, swiglu, total_rows, s);
   if (rc || b == nullptr) return rc;
@@ -1360,9 +1388,9 @@ static bool pairs_shared_with_routed(const occult_cfg_t& c) {
          (long long)c.T * c.S * c.f * 2 < (1ll << 32);
 }
 
-// of those batches, the ones that the 128-row tiles take instead: many rows per routed expert, or stored pre-activations
+// of those batches, the ones with so many rows per routed expert that the 128-row tiles take them instead
 static bool uses_tile128_for_few_rows(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs& b) {
-  return (a.C2 != nullptr || c.T * c.k >= 16 * c.E) && uses_tile128(c, a, &b, c.T * c.k);
+  return c.T * c.k >= 16 * c.E && uses_tile128(c, a, &b, c.T * c.k);
 }
 
 static size_t ffn_ws_need(const occult_cfg_t& c, int* ksplit_out) {
@@ -1432,12 +1460,13 @@ static int expert_ffn_impl(const occult_cfg_t* cfg, const occult_plan_t* plan, c
     g1.grp_offset = plan->exp_offset; g1.grp_widx = plan->pos_expert; g1.ngroups = c.E;
     g1.a_rows_total = sfd_rows_max(c);
     a1.w_base = c.E; a1.ngroups = c.S; a1.M = c.T; a1.a_rows_total = c.T;
-    if (pairs_shared_with_routed(c) && !uses_tile128_for_few_rows(c, g1, a1)) {
+    const bool paired = pairs_shared_with_routed(c);
+    if (paired && !uses_tile128_for_few_rows(c, g1, a1)) {
       a1.Bp = packed;
       rc = launch_skinny(g1, &a1, true, n_epd, s);
-      if (rc == OCCULT_OK && epd_gu != nullptr) rc = launch_preactivations(c, g1, n_epd, s);
-      if (rc == OCCULT_OK && gu_shared != nullptr) rc = launch_preactivations(c, a1, c.T * c.S, s);
+      if (rc == OCCULT_OK && epd_gu != nullptr) rc = launch_preactivation_pair(c, g1, &a1, n_epd, c.T * c.S, s);
     } else {
+      if (paired) a1.ksplit = kStreamParts;
       rc = launch_gemm_pair(c, g1, c.S > 0 ? &a1 : nullptr, true, n_epd, c.T * c.S, s);
     }
     if (rc) return rc;
@@ -1458,11 +1487,13 @@ static int expert_ffn_impl(const occult_cfg_t* cfg, const occult_plan_t* plan, c
     g2.grp_offset = plan->exp_offset; g2.grp_widx = plan->pos_expert; g2.ngroups = c.E;
     g2.a_rows_total = n_epd;
     a2.w_base = c.E; a2.ngroups = 1; a2.M = c.T; a2.a_rows_total = c.T;
-    if (pairs_shared_with_routed(c) && !uses_tile128_for_few_rows(c, g2, a2)) {
+    const bool paired = pairs_shared_with_routed(c);
+    if (paired && !uses_tile128_for_few_rows(c, g2, a2)) {
       a2.Bp = g2.Bp;
       rc = launch_skinny(g2, &a2, false, n_epd, s);
     } else {
       int ks = 0;
+      if (paired) a2.ksplit = kStreamParts;
       const size_t need = ffn_ws_need(c, &ks);
       if (ks > 1 && ws != nullptr && ws_bytes >= need) {
         a2.ksplit = ks;

@@ -63,9 +63,14 @@ struct Tile {
 };
 
 // SAVE (with SWIGLU): the gate and up pre-activations are stored too (C2).
-template <bool SWIGLU, bool SAVE>
+// PARTS: a problem's K may be summed in parts (GemmArgs.ksplit), whose sums are added in order: a result so has the bits
+// that the weight-streaming or small-tile kernel gives the same rows.  The finished parts' sums have registers of
+// their own (one wave per SIMD: there is room) and cost one addition per accumulator and part (500 tokens of 64 + 2 experts,
+// shared down projection in parts: 312 -> 318 us; 300 of 60 + 4, gate/up in quarters as well: 305 -> 325 us).
+template <bool SWIGLU, bool SAVE, bool PARTS>
 __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first, const GemmArgs second) {
   static_assert(SWIGLU || !SAVE, "pre-activations exist only with the fused activation");
+  static_assert(!SAVE || !PARTS, "stored pre-activations are one sum over K");
   __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE_BYTES];
   __shared__ __attribute__((aligned(16))) char s_out[4][OUT_BYTES];
   __shared__ int s_idx[4][64];               // source rows of the next tile's token rows, per loading wave
@@ -223,6 +228,26 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
   };
 
   f32x4 acc[8][4];   // [weight-row block][token-row block]
+  f32x4 tot[PARTS ? 8 : 1][4];   // PARTS: sums of the finished parts
+  int nk = 0, parts = 1, edge = 0;   // of the current output tile: K tiles, parts, end of the part being summed
+  auto part_after = [&](int done) {   // end of the part that K tile `done` is in: the smallest p * nk / parts above it
+    const int p = ((done + 1) * parts + nk - 1) / nk;
+    return __builtin_amdgcn_readfirstlane(p * nk / parts);
+  };
+  auto finish_part = [&](int done) {   // `done` < nk K tiles have been multiplied; the last part is added by sum()
+    if constexpr (PARTS) {
+      if (done != edge) return;   // wave-uniform
+#pragma unroll
+      for (int ni = 0; ni < 8; ++ni)
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi) {
+          tot[ni][mi] += acc[ni][mi];
+          acc[ni][mi] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+      edge = part_after(done);
+    }
+  };
+  auto sum = [&](int ni, int mi) { return PARTS ? tot[PARTS ? ni : 0][mi] + acc[ni][mi] : acc[ni][mi]; };
   // K step kk of the K tile in stage st: 8 groups of {4 products with, between them, one tile load into stage st_load
   // and up to two fragment reads of the next step (out of stage st_next)}, pinned in source order.  A fragment takes the registers of one
   // multiplied before; fb[7] follows in group 0 of its own step.  Step 1 has the block-wide wait between groups 1 and 2,
@@ -256,7 +281,6 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
   request_rows(cur);
   wait_loads();   // a wave reads back only its own indices
   start_loading(cur);
-  int nk = OCC_PICK(cur, K) / BK;   // host: >= 3
 #pragma unroll
   for (int k = 0; k < 3; ++k)
 #pragma unroll
@@ -275,15 +299,21 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
     const bool more = nxt.valid;
     if (!more) nxt = cur;   // keeps everything derived from it addressable
     request_rows(nxt);
+    nk = OCC_PICK(cur, K) / BK;   // host: >= 3
+    if (PARTS) {
+      parts = OCC_PICK(cur, ksplit);   // host: >= 1
+      edge = part_after(0);
+    }
 #pragma unroll
     for (int ni = 0; ni < 8; ++ni)
 #pragma unroll
-      for (int mi = 0; mi < 4; ++mi) acc[ni][mi] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int mi = 0; mi < 4; ++mi) acc[ni][mi] = tot[PARTS ? ni : 0][mi] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     // step 0 of a K tile requests the second half of the K tile two ahead, step 1 the first half of the one three ahead
     step(k0, st, st, next(next(st)));
     for (int kt = 0; kt < nk - 3; ++kt) {
       const unsigned sn = next(st);
       step(k1, st, sn, st);
+      finish_part(kt + 1);
       step(k0, sn, sn, st);
       st = sn;
     }
@@ -292,13 +322,15 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
     {
       const unsigned s1 = next(st), s2 = next(s1);
       step(k1, st, s1, st);
+      finish_part(nk - 2);
       step(k0, s1, s1, st);
       step(k1, s1, s2, s1);
+      finish_part(nk - 1);
       step(k0, s2, s2, s1);
       step(k1, s2, st, s2);
     }
 
-    // epilogue.  acc[ni][mi] element e of lane l: token row mi*16 + l%16, weight row ni*16 + (l/16)*4 + e of the wave
+    // epilogue.  sum(ni, mi) element e of lane l: token row mi*16 + l%16, weight row ni*16 + (l/16)*4 + e of the wave
     // tile.  bf16 results pass through the wave's 2 KiB of LDS, 16 rows x 64 columns at a time (16-byte slots swizzled by
     // the row), and leave as row segments of 128 bytes.
     {
@@ -318,7 +350,7 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
           for (int nn = 0; nn < 4; ++nn) {   // 16 output columns
             float v[4];
             if (SWIGLU && ch == 0) {
-              const f32x4 g = acc[2 * nn][mi], u = acc[2 * nn + 1][mi];
+              const f32x4 g = sum(2 * nn, mi), u = sum(2 * nn + 1, mi);
               if (OCC_PICK(cur, silu_rcp)) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = swiglu_rcp(g[e], u[e]);
@@ -328,7 +360,7 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
               }
             } else {
 #pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = SWIGLU ? acc[2 * nn + ch - 1][mi][e] : acc[4 * ch + nn][mi][e];
+              for (int e = 0; e < 4; ++e) v[e] = SWIGLU ? sum(2 * nn + ch - 1, mi)[e] : sum(4 * ch + nn, mi)[e];
             }
             uint2 pk;
             pk.x = pack_bf16(v[0], v[1]);
@@ -354,7 +386,6 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
     }
     if (!more) break;   // uniform over the block
     cur = nxt;
-    nk = OCC_PICK(cur, K) / BK;
   }
 #undef OCC_PICK
   wait_loads();   // the loads issued for a tile that does not exist must land before the block's LDS is released
@@ -378,11 +409,15 @@ int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_
   long long blocks = ((t1 + 7) / 8 + (t2 + 7) / 8) * 8;   // one block per CU, a multiple of 8 so a block keeps its XCD
   const long long resident = cus >= 8 ? cus / 8 * 8 : 8;
   if (blocks > resident) blocks = resident;
-  const bool save = swiglu && a.C2 != nullptr;
+  const bool save = swiglu && a.C2 != nullptr, parts = a.ksplit > 1 || second.ksplit > 1;
+  OCC_REQUIRE(!(save && parts) && (!parts || (a.ksplit >= 1 && (b == nullptr || second.ksplit >= 1))), OCCULT_EINVAL,
+              "grouped GEMM: parts of K outside the 128-row tiles' range");
   const dim3 grid((unsigned)blocks), block(256);
-  if (save) hipLaunchKernelGGL((t128::grouped_gemm_bf16<true, true>), grid, block, 0, s, a, second);
-  else if (swiglu) hipLaunchKernelGGL((t128::grouped_gemm_bf16<true, false>), grid, block, 0, s, a, second);
-  else hipLaunchKernelGGL((t128::grouped_gemm_bf16<false, false>), grid, block, 0, s, a, second);
+  if (save) hipLaunchKernelGGL((t128::grouped_gemm_bf16<true, true, false>), grid, block, 0, s, a, second);
+  else if (swiglu && parts) hipLaunchKernelGGL((t128::grouped_gemm_bf16<true, false, true>), grid, block, 0, s, a, second);
+  else if (swiglu) hipLaunchKernelGGL((t128::grouped_gemm_bf16<true, false, false>), grid, block, 0, s, a, second);
+  else if (parts) hipLaunchKernelGGL((t128::grouped_gemm_bf16<false, false, true>), grid, block, 0, s, a, second);
+  else hipLaunchKernelGGL((t128::grouped_gemm_bf16<false, false, false>), grid, block, 0, s, a, second);
   OCC_LAUNCH_CHECK("grouped_gemm");
   return OCCULT_OK;
 }

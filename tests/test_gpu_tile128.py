@@ -104,3 +104,64 @@ def test_activation_of_groups_of_a_few_rows_divides_first():
         near = np.abs(u).max(axis=1) < 1e6
         g, u = g[near], u[near]
         assert_one_rounding(h[near], g / (1.0 + np.exp(-g)) * u, f"h of expert {e}")
+
+
+def _rows_by_token_and_expert(layer):
+    """EPD row of every (token, expert) pair of the layer's last plan."""
+    tab = layer.tables()
+    off, expert = tab["exp_offset"].cpu().numpy(), tab["pos_expert"].cpu().numpy()
+    token = tab["sfd_token"].cpu().numpy()[tab["epd_sfd_row"].cpu().numpy()]
+    return {(int(token[r]), int(expert[P])): r for P in range(len(expert)) for r in range(off[P], off[P + 1])}
+
+
+def _bits(t):
+    return t.view(torch.int16).cpu().numpy()
+
+
+@pytest.mark.parametrize("T,part,d,f,E,S,k", [
+    (80, 40, 512, 320, 16, 2, 4),     # 20 and 10 rows per expert: both batches' shared experts beside the routed ones
+    (200, 100, 320, 448, 40, 1, 4),   # above the batch sizes whose shared experts are streamed with the routed ones
+    (128, 60, 192, 192, 16, 3, 2),    # three K tiles: the quarters of K have none or one
+])
+def test_few_rows_have_the_bits_of_smaller_batches(T, part, d, f, E, S, k):
+    """The weight-streaming kernel, which takes the first `part` tokens alone, sums the gate/up product in quarters of K
+    (and with shared experts beside the routed ones, their products too); the 128-row tiles, which take all T, sum the same
+    quarters.  The stored activations and products of a token are the same bits, and a training step's are too."""
+    say(f"rows of {part} and {T} tokens E={E} S={S} k={k} d={d} f={f}")
+    dev = require_gpu()
+    wk = wl.make_workload(wl.LayerShape("few", T=T, d=d, f=f, E=E, S=S, k=k, D=2, dtype="bf16", components=4), seed=T)
+    lg, x = torch.from_numpy(wk.logits).to(dev), to_dev(wk.x, "bf16", dev)
+    w = [to_dev(a, "bf16", dev) for a in (wk.w_gate, wk.w_up, wk.w_down)]
+    small, whole = (OccultLayer(n, d, f, E, S, k, 2, "bf16") for n in (part, T))
+    small.forward(lg[:part].contiguous(), x[:part].contiguous(), *w)
+    for train in (False, True):
+        whole.forward(lg, x, *w, train=train)
+        torch.cuda.synchronize()
+        at, ref = _rows_by_token_and_expert(whole), _rows_by_token_and_expert(small)
+        rows = np.array([(at[key], r) for key, r in ref.items()])
+        for name in ("epd_h", "epd_y"):
+            got, want = _bits(getattr(whole, name))[rows[:, 0]], _bits(getattr(small, name))[rows[:, 1]]
+            assert np.array_equal(got, want), (name, train, np.mean(got != want))
+        for name in ("h_shared", "y_shared") if T <= 128 else ():
+            got, want = _bits(getattr(whole, name))[:part], _bits(getattr(small, name))
+            assert np.array_equal(got, want), (name, train, np.mean(got != want))
+
+
+def test_shared_down_projection_has_the_bits_of_the_split_product():
+    """With scratch the shared down projection is summed in three parts of K: by the small tiles into the scratch where a
+    single routed expert has all 1000 rows, in registers by the 128-row tiles where four share them."""
+    T, d, f, S = 1000, 256, 192, 4
+    say(f"shared down projection in parts T={T} d={d} f={f} S={S}")
+    dev = require_gpu()
+    wk = wl.make_workload(wl.LayerShape("parts", T=T, d=d, f=f, E=4, S=S, k=1, D=1, dtype="bf16", components=4), seed=8)
+    x = to_dev(wk.x, "bf16", dev)
+    w4 = [to_dev(a, "bf16", dev) for a in (wk.w_gate, wk.w_up, wk.w_down)]
+    out = []
+    for E, w in ((4, w4), (1, [t[3:].contiguous() for t in w4])):
+        layer = OccultLayer(T, d, f, E, S, 1, 1, "bf16")
+        assert layer.ffn_ws is not None
+        layer.forward(torch.from_numpy(wk.logits[:, :E].copy()).to(dev), x, *w)
+        torch.cuda.synchronize()
+        out.append((_bits(layer.h_shared), _bits(layer.y_shared)))
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.array_equal(out[0][1], out[1][1]), np.mean(out[0][1] != out[1][1])
