@@ -98,16 +98,29 @@ __device__ __forceinline__ key_t64 token_max(key_t64 key) {
   return ((key_t64)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(key >> 32), 63) << 32) |
          (unsigned)__builtin_amdgcn_readlane((int)(unsigned)key, 63);
 }
-template <int LANES>
-__device__ __forceinline__ float token_sum(float v) {
-  v += dpp_f<kQuadSwap1>(v, v);
-  v += dpp_f<kQuadSwap2>(v, v);
-  v += dpp_f<kRowHalfMirror>(v, v);
-  v += dpp_f<kRowMirror>(v, v);
-  if (LANES == 16) return v;
-  v += dpp_f<kRowBcast15, 0xA>(0.0f, v);
-  v += dpp_f<kRowBcast31, 0xC>(0.0f, v);
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+// Sum over a token's experts (or slots) in one order for both lane counts, so that a token's gates do not depend on the
+// size of its batch: v[q] holds a lane's share of the columns of residue 16 q + lane % 16 modulo 64 (with 64 lanes: q = 0,
+// the columns of residue `lane`).  Each sixteen are added up on their own, then the four sums as (3 + 2) + (1 + 0).
+template <int LANES, int N>
+__device__ __forceinline__ float token_sum(float (&v)[N]) {
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    v[q] += dpp_f<kQuadSwap1>(v[q], v[q]);
+    v[q] += dpp_f<kQuadSwap2>(v[q], v[q]);
+    v[q] += dpp_f<kRowHalfMirror>(v[q], v[q]);
+    v[q] += dpp_f<kRowMirror>(v[q], v[q]);
+  }
+  if constexpr (LANES == 16) {
+    static_assert(N == 1 || N == 2 || N == 4, "sixteen columns per sum");
+    if constexpr (N == 4) return (v[3] + v[2]) + (v[1] + v[0]);
+    return N == 2 ? v[N - 1] + v[0] : v[0];
+  } else {
+    static_assert(N == 1, "a lane per column");
+    float s = v[0];
+    s += dpp_f<kRowBcast15, 0xA>(0.0f, s);
+    s += dpp_f<kRowBcast31, 0xC>(0.0f, s);
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, s), 63));
+  }
 }
 
 // LANES = lanes per token, 16 or 64; EPL = experts per lane, E <= LANES * EPL.  Lane r of a token writes slots r and,
@@ -258,18 +271,22 @@ __global__ __launch_bounds__(256) void route_kernel(
   }
 
   // gate values: softmax over all E experts at the selected ones
-  float part = 0.0f;
+  constexpr int ROWS = 64 / LANES < EPL ? 64 / LANES : EPL;   // sums of sixteen columns that a lane takes part in: 1, 2 or 4
+  float part[ROWS] = {};
 #pragma unroll
   for (int i = 0; i < EPL; ++i)
-    if (r + LANES * i < E) part += exp_ref(v0[i] - mx);
+    if (r + LANES * i < E) part[i % ROWS] += exp_ref(v0[i] - mx);
   const float denom = token_sum<LANES>(part);
   const bool second = SLOTS > 1 && k > LANES;   // uniform
-  float g[2] = {r < k ? exp_ref(key_value(slot[0]) - mx) / denom : 0.0f, 0.0f};
-  if (second) g[1] = r + LANES < k ? exp_ref(key_value(slot[SLOTS - 1]) - mx) / denom : 0.0f;
+  float g[SLOTS] = {r < k ? exp_ref(key_value(slot[0]) - mx) / denom : 0.0f};
+  if (second) g[SLOTS - 1] = r + LANES < k ? exp_ref(key_value(slot[SLOTS - 1]) - mx) / denom : 0.0f;
   if (renorm) {
-    const float sel = token_sum<LANES>(g[0] + g[1]);
-    g[0] = g[0] / sel;
-    if (second) g[1] = g[1] / sel;
+    float sel[1] = {g[0]}, sel2[SLOTS];
+#pragma unroll
+    for (int h = 0; h < SLOTS; ++h) sel2[h] = g[h];
+    const float sum = second ? token_sum<LANES>(sel2) : token_sum<LANES>(sel);
+    g[0] = g[0] / sum;
+    if (second) g[SLOTS - 1] = g[SLOTS - 1] / sum;
   }
 #pragma unroll
   for (int h = 0; h < SLOTS; ++h)

@@ -40,3 +40,20 @@ def test_gram_at_slice_edges(E, T):
     want = routing.gram(lg)
     got = gram.cpu().numpy()
     assert np.max(np.abs(got - want)) <= 1e-11 * np.max(np.abs(want))   # T sums of doubles: T * 2^-53 < 1e-11
+
+
+@pytest.mark.parametrize("E", [7, 16, 24, 32, 60, 64, 100, 128, 200, 256])
+@pytest.mark.parametrize("k", [2, 16, 20, 32])
+@pytest.mark.parametrize("renorm", [0, 1])
+def test_gates_do_not_depend_on_the_batch_size(E, k, renorm):
+    """A token's gates are the same bits whether sixteen lanes or a wavefront route it: their sums run in one order."""
+    k = min(k, E)
+    say(f"gates E={E} k={k} renorm={renorm}")
+    dev = require_gpu()
+    T, part = 1500, 700
+    lg = torch.from_numpy(wl.random_logits(T, E, seed=E + k, scale=1.7)).to(dev)
+    large, small = (OccultLayer(n, 64, 64, E, 0, k, 1, "bf16", 0, 1, renorm, with_ffn=False) for n in (T, part))
+    large.route(lg)
+    small.route(lg[:part].contiguous())
+    assert torch.equal(large.ids[:part], small.ids)
+    assert torch.equal(large.w[:part].view(torch.int32), small.w.view(torch.int32))
