@@ -1317,8 +1317,8 @@ int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total
 //  - below them stands the weight-streaming kernel, above the 256-row tiles, which need a third fewer operand bytes per
 //    product but waste more on partly filled tiles and on the last round of tiles over the CUs;
 //  - with shared experts one launch does both sets' work, which alone would leave most CUs idle (500 tokens: 118 of
-//    357 us) or add a last round of its own: worth it down to any number of rows and up to about 800 per group
-//    (656 rows: 1116 us against 1057; 768: equal);
+//    357 us) or add a last round of its own: up to about 800 rows per group (656 rows: 1116 us against 1057; 768: equal),
+//    and down to any number where shares_launch() says so;
 //  - without, from 24 rows (32: 226 us against 220; 20: 215 against 218) up to about 240 (237: 339 against 323 us; 256
 //    and 287: slower, 325: faster, by how the tiles happen to divide over the CUs).
 static bool fits_tile128(const GemmArgs& a) {
@@ -1339,6 +1339,30 @@ static int k_parts(const GemmArgs& a, bool swiglu, int total_rows) {
   return swiglu && !uses_tile256(a, swiglu, total_rows) && streams_weights(a, total_rows) ? kStreamParts : 1;
 }
 
+// Whether the shared experts' product `b` runs in one launch of 128-row tiles with the routed experts' `a`, where those
+// take it.  Apart, `a` goes to the kernel that takes it alone and `b` to its own.  What decides it (1000 pairs of times over
+// 4 - 128 experts, 1 - 4 shared ones, d = 512 - 4096, f = 384 - 1536):
+//  - a gate/up product that would stream its weights: the tiles spend a fixed time per expert, and gain the time that the
+//    shared rows would take alone.  Joined from 6144 shared rows x K per expert, twice that where the weights are packed:
+//    of 127 batches below 24 rows per expert 0.81 of the time apart on average (at worst 1.16), packed 0.88 (1.15).
+//    (64 + 4 experts, 155 tokens, d = 1024, f = 512: 46 us against 43; 60 + 1, 169 tokens, the same widths: 27 against 37.)
+//  - a down projection with scratch: apart, its K (S matrices long) is split over workgroups, joined it is one block's chain
+//    of about 0.75 us per K tile of 64.  Joined while that chain is at most 9 K tiles (4 where `a` streams its weights) longer
+//    than a block's share of all tiles and the work of `b` alone, spread over 256 CUs, together.
+//    (60 + 4 experts, 180 tokens, d = 512, f = 1088: 62 us against 36; 32 + 2, 517 tokens, 2048, 1408: 49 against 76.)
+static bool shares_launch(const GemmArgs& a, const GemmArgs& b, bool swiglu, int total_rows) {
+  const bool streams = streams_weights(a, total_rows);
+  if (swiglu && streams)
+    return (long long)b.ngroups * b.M * a.K > (a.Bp != nullptr ? 2 : 1) * 6144ll * a.ngroups;
+  if (b.ksplit <= 1) return true;
+  const long long n_tiles = (a.N + 255) / 256;
+  const long long tiles_a = a.ngroups * ((total_rows / a.ngroups + 127) / 128) * n_tiles;   // of evenly loaded experts
+  const long long tiles_b = (b.M + 127) / 128 * n_tiles;
+  const long long blocks = tiles_a + tiles_b < 256 ? tiles_a + tiles_b : 256;
+  const long long share = (tiles_a * a.K + tiles_b * b.K) / blocks;
+  return b.K - share - tiles_b * b.K / 256 <= (streams ? 4 : 9) * 64;
+}
+
 static int launch_preactivation_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, int total_rows, int rows_b,
                                      hipStream_t s) {
   int rc = OCCULT_OK;
@@ -1353,6 +1377,10 @@ static int launch_preactivation_pair(const occult_cfg_t& c, const GemmArgs& a, c
 
 int launch_gemm_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, int rows_b,
                      hipStream_t s) {
+  if (b != nullptr && !shares_launch(a, *b, swiglu, total_rows)) {
+    const int rc = launch_gemm_pair(c, a, nullptr, swiglu, total_rows, 0, s);
+    return rc ? rc : launch_gemm(c, *b, swiglu, rows_b, s);
+  }
   if (total_rows > 0 && uses_tile128(c, a, b, total_rows)) {
     GemmArgs p = a, q{};
     if (b != nullptr) q = *b;
@@ -1386,11 +1414,6 @@ static bool pairs_shared_with_routed(const occult_cfg_t& c) {
          c.f % skinny::BN_OUT == 0 && c.d % skinny::BN_OUT == 0 &&
          (long long)sfd_rows_max(c) * c.d * 2 < (1ll << 32) && (long long)c.T * c.k * c.f * 2 < (1ll << 32) &&
          (long long)c.T * c.S * c.f * 2 < (1ll << 32);
-}
-
-// of those batches, the ones with so many rows per routed expert that the 128-row tiles take them instead
-static bool uses_tile128_for_few_rows(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs& b) {
-  return c.T * c.k >= 16 * c.E && uses_tile128(c, a, &b, c.T * c.k);
 }
 
 static size_t ffn_ws_need(const occult_cfg_t& c, int* ksplit_out) {
@@ -1460,13 +1483,11 @@ static int expert_ffn_impl(const occult_cfg_t* cfg, const occult_plan_t* plan, c
     g1.grp_offset = plan->exp_offset; g1.grp_widx = plan->pos_expert; g1.ngroups = c.E;
     g1.a_rows_total = sfd_rows_max(c);
     a1.w_base = c.E; a1.ngroups = c.S; a1.M = c.T; a1.a_rows_total = c.T;
-    const bool paired = pairs_shared_with_routed(c);
-    if (paired && !uses_tile128_for_few_rows(c, g1, a1)) {
+    if (pairs_shared_with_routed(c)) {
       a1.Bp = packed;
       rc = launch_skinny(g1, &a1, true, n_epd, s);
       if (rc == OCCULT_OK && epd_gu != nullptr) rc = launch_preactivation_pair(c, g1, &a1, n_epd, c.T * c.S, s);
     } else {
-      if (paired) a1.ksplit = kStreamParts;
       rc = launch_gemm_pair(c, g1, c.S > 0 ? &a1 : nullptr, true, n_epd, c.T * c.S, s);
     }
     if (rc) return rc;
@@ -1487,13 +1508,11 @@ static int expert_ffn_impl(const occult_cfg_t* cfg, const occult_plan_t* plan, c
     g2.grp_offset = plan->exp_offset; g2.grp_widx = plan->pos_expert; g2.ngroups = c.E;
     g2.a_rows_total = n_epd;
     a2.w_base = c.E; a2.ngroups = 1; a2.M = c.T; a2.a_rows_total = c.T;
-    const bool paired = pairs_shared_with_routed(c);
-    if (paired && !uses_tile128_for_few_rows(c, g2, a2)) {
+    if (pairs_shared_with_routed(c)) {
       a2.Bp = g2.Bp;
       rc = launch_skinny(g2, &a2, false, n_epd, s);
     } else {
       int ks = 0;
-      if (paired) a2.ksplit = kStreamParts;
       const size_t need = ffn_ws_need(c, &ks);
       if (ks > 1 && ws != nullptr && ws_bytes >= need) {
         a2.ksplit = ks;

@@ -15,7 +15,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("name,T,d,f,E,S,k,D", [
-    ("decode_like", 96, 256, 192, 16, 2, 4, 4),      # weight-streaming + small-tile kernels, split-K scratch
+    ("decode_like", 96, 256, 192, 16, 2, 4, 4),      # 128-row tiles, routed and shared experts in one launch
+    ("split_k", 140, 512, 256, 16, 4, 4, 4),         # the shared down projection split over K into scratch
+    ("few_rows", 90, 256, 192, 16, 2, 4, 4),         # weight-streaming kernel with the shared experts inside
     ("prefill_like", 1300, 256, 128, 4, 0, 2, 2),    # persistent 256-row tiles
 ])
 def test_step_replays_from_a_graph(name, T, d, f, E, S, k, D):

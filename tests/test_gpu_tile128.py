@@ -119,14 +119,15 @@ def _bits(t):
 
 
 @pytest.mark.parametrize("T,part,d,f,E,S,k", [
-    (80, 40, 512, 320, 16, 2, 4),     # 20 and 10 rows per expert: both batches' shared experts beside the routed ones
-    (200, 100, 320, 448, 40, 1, 4),   # above the batch sizes whose shared experts are streamed with the routed ones
-    (128, 60, 192, 192, 16, 3, 2),    # three K tiles: the quarters of K have none or one
+    (160, 100, 512, 320, 8, 2, 1),    # 20 rows per expert, two K tiles per quarter
+    (200, 100, 320, 448, 10, 2, 1),   # five K tiles: quarters of one and two
+    (150, 100, 192, 192, 8, 3, 1),    # three K tiles: the quarters of K have none or one
+    (300, 100, 512, 256, 40, 2, 3),
 ])
 def test_few_rows_have_the_bits_of_smaller_batches(T, part, d, f, E, S, k):
-    """The weight-streaming kernel, which takes the first `part` tokens alone, sums the gate/up product in quarters of K
-    (and with shared experts beside the routed ones, their products too); the 128-row tiles, which take all T, sum the same
-    quarters.  The stored activations and products of a token are the same bits, and a training step's are too."""
+    """The weight-streaming kernel, which takes the first `part` tokens alone, sums the gate/up product in quarters of K; the
+    128-row tiles, which take all T beside their shared experts, sum the same quarters.  The stored activations and
+    products of a token are the same bits, and a training step's are too."""
     say(f"rows of {part} and {T} tokens E={E} S={S} k={k} d={d} f={f}")
     dev = require_gpu()
     wk = wl.make_workload(wl.LayerShape("few", T=T, d=d, f=f, E=E, S=S, k=k, D=2, dtype="bf16", components=4), seed=T)
@@ -142,9 +143,29 @@ def test_few_rows_have_the_bits_of_smaller_batches(T, part, d, f, E, S, k):
         for name in ("epd_h", "epd_y"):
             got, want = _bits(getattr(whole, name))[rows[:, 0]], _bits(getattr(small, name))[rows[:, 1]]
             assert np.array_equal(got, want), (name, train, np.mean(got != want))
-        for name in ("h_shared", "y_shared") if T <= 128 else ():
-            got, want = _bits(getattr(whole, name))[:part], _bits(getattr(small, name))
-            assert np.array_equal(got, want), (name, train, np.mean(got != want))
+
+
+@pytest.mark.parametrize("T,d,f,E,S,k,apart", [
+    (140, 512, 256, 16, 4, 4, True),     # four K tiles of its own against the sixteen of the shared down projection
+    (160, 1024, 512, 60, 4, 4, True),    # below 24 rows per expert
+    (1000, 256, 192, 4, 4, 1, False),
+    (1000, 1024, 512, 60, 1, 6, False),
+])
+def test_long_shared_down_projection_is_split_in_scratch(T, d, f, E, S, k, apart):
+    """A shared down projection whose K, as one block's chain of tiles, would outlast the launch is split over workgroups
+    into the scratch; one that the routed experts' launch covers leaves the scratch alone."""
+    say(f"scratch of the shared down projection T={T} d={d} f={f} E={E} S={S} k={k}")
+    dev = require_gpu()
+    wk = wl.make_workload(wl.LayerShape("scratch", T=T, d=d, f=f, E=E, S=S, k=k, D=2, dtype="bf16", components=4), seed=S)
+    w = [to_dev(a, "bf16", dev) for a in (wk.w_gate, wk.w_up, wk.w_down)]
+    layer = OccultLayer(T, d, f, E, S, k, 2, "bf16")
+    layer.ffn_ws.fill_(float("nan"))
+    layer.forward(torch.from_numpy(wk.logits).to(dev), to_dev(wk.x, "bf16", dev), *w)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(layer.ffn_ws).all()) != apart
+    h, wd = layer.h_shared.double().cpu().numpy(), wk.w_down[E:].astype(np.float64)
+    ref = sum(h[:, s * f:(s + 1) * f] @ wd[s].T for s in range(S))
+    assert_one_rounding(layer.y_shared.double().cpu().numpy(), ref, "y shared")
 
 
 def test_shared_down_projection_has_the_bits_of_the_split_product():
