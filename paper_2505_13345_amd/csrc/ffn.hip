@@ -588,7 +588,7 @@ __device__ __forceinline__ void load_to_lds_16(const char* src, unsigned lds) {
 // acc (16 x 16) += b (16 weight rows x 32 K) * a (16 token rows x 32 K)^T, accumulators in the accumulation registers.
 // Written as assembly because the compiler, given the builtin, moves the 64 accumulator quads between the two register
 // files; it cannot see that these are matrix instructions, so whoever reads acc has to leave the wait states itself
-// (mfma_results_ready).
+// (mfma_results_ready, with acc named in an assembly statement behind it: that alone keeps the reads there).
 __device__ __forceinline__ void mfma16(f32x4& acc, const bf16x8& b, const bf16x8& a) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
 }
@@ -936,9 +936,13 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
 #pragma unroll
           for (int nn = 0; nn < 4; ++nn) {   // 16 output columns
             const int gi = (nn >> 1) * 4 + (nn & 1);   // SWIGLU: weight-row block of the gate; the up block is gi + 2
-            if (SAVE) {   // read again for every kind: values kept from one chunk to the next would not fit the registers
+            // Read from here on, which is behind the wait states above.  With SAVE again for every kind: values kept from
+            // one chunk to the next would not fit the registers.
+            if (SWIGLU) {
               asm volatile("" : "+a"(acc[gi][2 * mi + m2]));
               asm volatile("" : "+a"(acc[gi + 2][2 * mi + m2]));
+            } else {
+              asm volatile("" : "+a"(acc[4 * h + nn][2 * mi + m2]));
             }
             float v[4];
 #pragma unroll
