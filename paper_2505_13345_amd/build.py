@@ -42,8 +42,10 @@ def _hipcc() -> str:
 
 # Kernels that must not touch scratch memory: in the persistent 256-row GEMM every reload of a spilled
 # register waits for all outstanding loads, the next tile's prefetch included (a one-register change in
-# its epilogue has cost 20 % before).  Matched against the mangled kernel names.
-NO_SCRATCH = ("t256", "t128")
+# its epilogue has cost 20 % before); there and in the weight gradients (wgd) the accumulators are written by
+# assembly statements, whose results a spill inside the loop would read too early.  Matched against the mangled
+# kernel names.
+NO_SCRATCH = ("t256", "t128", "wgd")
 
 
 def _resource_usage(stderr: str):

@@ -1,5 +1,6 @@
 """The matrix instructions that the kernels issue as assembly statements: the compiler leaves no wait states behind those,
-so no accumulator may be read between a kernel's last one and the wait that the source puts there."""
+so no accumulator may be read between a kernel's last one and the wait that the source puts there, and none of these
+kernels may spill registers."""
 import os
 import re
 import subprocess
@@ -35,3 +36,23 @@ def test_accumulators_are_read_behind_the_wait_states(source, tag, tmp_path):
             last = max(j for j in range(i) if lines[j].startswith("v_mfma"))
             early = [l for l in lines[last + 1:i] if not l.startswith(";") and re.search(r"\ba(\d|\[)", l)]
             assert not early, (name, early[:3])
+
+
+@pytest.mark.parametrize("tag", ["t256", "t128", "wgd"])
+def test_build_refuses_kernels_that_spill(tag, tmp_path, monkeypatch):
+    """A kernel of that name whose registers do not suffice does not build."""
+    (tmp_path / "spills.hip").write_text("""
+        #include <hip/hip_runtime.h>
+        namespace %s {
+        __global__ __launch_bounds__(1024) void kernel(const float* in, float* out, int n) {
+          float v[300];
+          for (int i = 0; i < 300; ++i) v[i] = in[i * n];
+          for (int r = 0; r < n; ++r)
+            for (int i = 0; i < 300; ++i) v[i] += v[(i + r) %% 300];
+          for (int i = 0; i < 300; ++i) out[i * n] = v[i];
+        }
+        }""" % tag)
+    monkeypatch.setattr(build, "CSRC", str(tmp_path))
+    monkeypatch.setattr(build, "OBJ_DIR", str(tmp_path))
+    with pytest.raises(RuntimeError, match="scratch"):
+        build._compile("spills.hip")
