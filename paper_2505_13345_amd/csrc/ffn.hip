@@ -1222,13 +1222,17 @@ constexpr int kStreamParts = 4;   // parts of K of that kernel where its waves s
 // rows per group from which a product takes the 256-row tiles: uniform groups; grouped rows of the gate/up product
 constexpr long long kBigRowsUniform = 192, kBigRowsSwiglu = 129;
 
+// the large-tile kernels address a weight matrix's rows with 32-bit byte offsets
+static bool weights_below_4gib(const GemmArgs& a) { return (long long)a.N * a.ldb * 2 < (1ll << 32); }
+
 static bool uses_tile256(const GemmArgs& a, bool swiglu, int total_rows) {
   // 256-row tiles once groups average enough rows and there are at least two K tiles to pipeline
   // (measured on 60 experts, d = 2048, f = 1408: the gate/up product is weight-bound on the
   // 128-row tiles until an expert's rows no longer fit one of them; the down projection is
   // faster on the 256-row tiles from about 64 rows per expert)
   const long long big_rows = a.grp_offset == nullptr ? kBigRowsUniform : (swiglu ? kBigRowsSwiglu : 64);
-  return (long long)total_rows >= big_rows * a.ngroups && a.ksplit <= 1 && a.K >= 2 * t256::BK && a.N % 64 == 0;
+  return (long long)total_rows >= big_rows * a.ngroups && a.ksplit <= 1 && a.K >= 2 * t256::BK && a.N % 64 == 0 &&
+         weights_below_4gib(a);
 }
 
 // *fused_save: the pre-activations asked for through a.C2 were written by the launch itself
@@ -1326,7 +1330,8 @@ int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total
 //  - without, from 24 rows (32: 226 us against 220; 20: 215 against 218) up to about 240 (237: 339 against 323 us; 256
 //    and 287: slower, 325: faster, by how the tiles happen to divide over the CUs).
 static bool fits_tile128(const GemmArgs& a) {
-  return a.K >= 192 && a.K % 64 == 0 && a.N % 64 == 0 && (long long)a.a_rows_total * a.lda * 2 < (1ll << 32);
+  return a.K >= 192 && a.K % 64 == 0 && a.N % 64 == 0 && (long long)a.a_rows_total * a.lda * 2 < (1ll << 32) &&
+         weights_below_4gib(a);
 }
 static bool uses_tile128(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, int total_rows) {
   if (c.dtype != OCCULT_BF16 || a.grp_offset == nullptr || !fits_tile128(a) || (b != nullptr && !fits_tile128(*b)))

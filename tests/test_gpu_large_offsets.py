@@ -13,7 +13,7 @@ import torch
 from inputs import workloads as wl
 from oracle import backward, moe_std, occult_ref, routing
 from paper_2505_13345_amd.layer import OccultLayer
-from tests.helpers import bf16_errors, check_plan_against_trace, expand_plan, f32_rel_error, require_gpu, say
+from tests.helpers import BF16_U, bf16_errors, check_plan_against_trace, expand_plan, f32_rel_error, require_gpu, say
 
 pytestmark = pytest.mark.gpu
 
@@ -175,3 +175,31 @@ def test_expert_ffn_past_4gib_forward_and_backward():
     shape.f, shape.S, shape.E = f, S, E
     say("  weight gradients on the stored operands")
     _check_weight_grads_on_stored_operands(layer, shape, None, None, [0, 3, E - 1], x_dev=x_d, dy_dev=dy_d)
+
+
+@pytest.mark.parametrize("T", [64, 192])
+def test_weight_matrices_past_4gib(T):
+    """Weight matrices just above 4 GiB, at row counts that 128-row and 256-row tiles would take: the last 64 weight rows
+    of the gate/up product and the last columns of the down projection lie past what a 32-bit byte offset reaches."""
+    d, f = 16384, 131136
+    say(f"weight matrices of {d * f * 2 / 2**30:.3f} GiB, T={T}")
+    dev = require_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(T)
+    rand = lambda *shape, std: torch.randn(shape, device=dev, generator=gen, dtype=torch.bfloat16).mul_(std)
+    x, wg, wu, wd = rand(T, d, std=1.0), rand(1, f, d, std=d ** -0.5), rand(1, f, d, std=d ** -0.5), rand(1, d, f, std=f ** -0.5)
+    layer = OccultLayer(T, d, f, 1, 0, 1, 1, "bf16")
+    layer.forward(torch.zeros((T, 1), device=dev), x, wg, wu, wd)
+    torch.cuda.synchronize()
+    assert torch.equal(layer.sfd_x[:T], x)   # one expert: every row once, in token order
+
+    def check(got, want, K, what):   # one bf16 rounding of f32 sums, whose error grows with the root of their K products
+        excess = (got - want).abs() - (BF16_U * (1 + 2.0 ** -10) * want.abs() + 2e-5 * (K / 2048) ** 0.5 * want.square().mean().sqrt())
+        assert excess.max().item() <= 0.0, (what, excess.max().item())
+
+    x64, h64 = x.double(), layer.epd_h.double()
+    for w0 in range(0, f, 8192):
+        g, u = (x64 @ w[0, w0:w0 + 8192].double().t() for w in (wg, wu))
+        check(h64[:, w0:w0 + 8192], g / (1.0 + torch.exp(-g)) * u, d, f"h from column {w0}")
+    for w0 in range(0, d, 1024):
+        check(layer.epd_y[:, w0:w0 + 1024].double(), h64 @ wd[0, w0:w0 + 1024].double().t(), f, f"y from column {w0}")
