@@ -23,7 +23,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 //
 // Order of the tiles: group by group, weight columns outside, row tiles inside, cut into eight equal runs, one per
 // XCD (workgroups go to the XCDs round-robin).  The row tiles of one expert and weight block so run next to each
-// other on one XCD and the weights leave HBM once; and no XCD gets more than one tile above its share.
+// other on one XCD and the weights leave HBM once; and no XCD gets a whole tile more than an eighth of both problems'.
 //
 // One launch carries two problems of the same N: `second` (uniform groups: the shared experts) has its tiles at the
 // front of every XCD's run because its K can be longer (the shared down projection walks S matrices).
@@ -100,13 +100,15 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
   }
   __syncthreads();
 
-  // this XCD's runs of the two problems' tiles
+  // this XCD's runs of the two problems' tiles: an eighth of each, the tiles left over of `second` one each to the first XCDs
+  // and those of `first` to the last ones
   const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3;
   const int mt2 = (second.M + BM - 1) / BM;
-  const long long total1 = s_tpre[first.ngroups], total2 = (long long)second.ngroups * mt2 * n_tiles;
-  const int lo1 = __builtin_amdgcn_readfirstlane((int)(total1 * xcd / 8));
-  const int cnt1 = __builtin_amdgcn_readfirstlane((int)(total1 * (xcd + 1) / 8)) - lo1;
-  const int lo2 = (int)(total2 * xcd / 8), cnt2 = (int)(total2 * (xcd + 1) / 8) - lo2;
+  const int total1 = s_tpre[first.ngroups], total2 = second.ngroups * mt2 * n_tiles;   // host: their sum is below 2^28
+  const int over1 = total1 & 7, over2 = total2 & 7;
+  const int cnt1 = __builtin_amdgcn_readfirstlane((total1 >> 3) + (xcd >= 8 - over1));
+  const int lo1 = __builtin_amdgcn_readfirstlane(xcd * (total1 >> 3) + max(0, xcd - (8 - over1)));
+  const int cnt2 = (total2 >> 3) + (xcd < over2), lo2 = xcd * (total2 >> 3) + min(xcd, over2);
   auto tile_at = [&](int slot) {
     Tile t{};
     if (slot < cnt2) {
