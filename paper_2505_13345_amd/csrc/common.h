@@ -64,6 +64,35 @@ __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));   // one packed conversion
 }
 
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// Loads straight into LDS, counted by vmcnt: 64 lanes x 16 bytes from per-lane global addresses to LDS [lds, lds + 1024)
+__device__ __forceinline__ void load_to_lds_16(const char* src, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
+}
+// the same with a wave-uniform base and a 32-bit byte offset per lane
+__device__ __forceinline__ void load_to_lds_16(const char* base, unsigned off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+               : "memory", "m0");
+}
+// 64 lanes x 4 bytes to LDS [lds, lds + 256)
+__device__ __forceinline__ void load_to_lds_4(const char* src, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
+}
+// all but the last N of this wave's loads have landed and its LDS reads have returned; then the same for the block
+template <int N>
+__device__ __forceinline__ void wait_loads_and_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+#pragma clang diagnostic pop
+
+// silu(g) * u with the hardware exp2 and reciprocal (about 1 ulp each: far inside bf16 rounding);
+// the IEEE division would cost more VALU time per 256-row tile than the epilogue's stores
+__device__ __forceinline__ float swiglu_rcp(float g, float u) {
+  const float e = __builtin_amdgcn_exp2f(g * -1.4426950408889634f);
+  return g * u * __builtin_amdgcn_rcpf(1.0f + e);
+}
+
 // One 16-byte vector of a hidden row as floats: load, and store with the rounding of the storage type.
 template <bool BF16>
 struct Row;

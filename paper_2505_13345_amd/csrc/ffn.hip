@@ -565,26 +565,14 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs first, c
 // idle stage (the region its own next loads will fill, so no block barrier is needed), 32 rows x
 // 64 columns at a time, and leave as 16-byte stores of whole 128-byte row segments.  With SWIGLU
 // the 128 B-rows of a wave's half tile are [gate c..c+31 | up c..c+31 | gate c+32..c+63 |
-// up c+32..c+63], so MFMA row blocks (0,1) and (2,3), (4,5) and (6,7) pair gate with up and the
-// activation is applied in registers.
+// up c+32..c+63], so the MFMA row blocks 0, 1 (4, 5) hold the gates to the up values in 2, 3 (6, 7)
+// and the activation is applied in registers.
 namespace t256 {
 constexpr int BM = 256, BN = 256, BK = 64;
 constexpr int A_BYTES = BM * BK * 2;             // 32 KiB
 constexpr int STAGE_BYTES = 2 * A_BYTES;         // 64 KiB: A tile then B tile
 constexpr int SMEM_BYTES = 2 * STAGE_BYTES;
 
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-// 64 lanes x 16 bytes from global addresses base + off (base wave-uniform, off per lane, bytes)
-// to LDS [lds, lds + 1024), asynchronously; completion is counted by vmcnt
-__device__ __forceinline__ void load_to_lds_16(const char* base, unsigned off, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
-               : "memory", "m0");
-}
-// the same from one 64-bit address per lane
-__device__ __forceinline__ void load_to_lds_16(const char* src, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
-}
 // acc (16 x 16) += b (16 weight rows x 32 K) * a (16 token rows x 32 K)^T, accumulators in the accumulation registers.
 // Written as assembly because the compiler, given the builtin, moves the 64 accumulator quads between the two register
 // files; it cannot see that these are matrix instructions, so whoever reads acc has to leave the wait states itself
@@ -596,18 +584,6 @@ __device__ __forceinline__ void mfma16_first(f32x4& acc, const bf16x8& b, const 
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(b), "v"(a));
 }
 __device__ __forceinline__ void mfma_results_ready() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
-// every load of this wave has landed and its LDS reads have returned; then the same for the block
-__device__ __forceinline__ void wait_all_and_barrier() {
-  asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-#pragma clang diagnostic pop
-
-// silu(g) * u with the hardware exp2 and reciprocal (about 1 ulp each: far inside bf16 rounding);
-// the IEEE division would cost more VALU time per tile than the epilogue's stores
-__device__ __forceinline__ float swiglu_fast(float g, float u) {
-  const float e = __builtin_amdgcn_exp2f(g * -1.4426950408889634f);
-  return g * u * __builtin_amdgcn_rcpf(1.0f + e);
-}
 
 // One output tile before its row gather has come back.  All fields but raw are wave-uniform.
 struct Head {
@@ -804,7 +780,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
   for (int g = 0; g < 8; ++g) load_a(a_off, 0, 0, g);
 #pragma unroll
   for (int g = 0; g < 8; ++g) load_b(b_off, w_lo, w_hi, 0, 0, g);
-  wait_all_and_barrier();
+  wait_loads_and_barrier<0>();
 #pragma unroll
   for (int r = 0; r < 16; ++r) read_frag(0, 0, 0, r);
 #pragma unroll
@@ -888,14 +864,14 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
       const int s = (par + kt) & 1;
       // K tile kt+1 has landed (this wave's loads, then every wave's), and every wave has issued
       // and completed its last reads of stage s, which may therefore be refilled
-      wait_all_and_barrier();
+      wait_loads_and_barrier<0>();
       step1(s, a_off, kt + 2, b_off, w_lo, w_hi, kb_next, std::false_type{});
       step0(s ^ 1, b_off, w_lo, w_hi, kb_next, std::false_type{});
       kb_advance();
     }
     // K tile nk-2: its stage receives K tile 0 of the next output tile
     const int s = (par + nk - 2) & 1, s1 = s ^ 1;
-    wait_all_and_barrier();
+    wait_loads_and_barrier<0>();
     aoff_t na_off[8];
     unsigned nb_off[8];
     offsets_of(hn, na_off, nb_off);   // the gather has long landed: nothing is outstanding here
@@ -906,7 +882,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
     step0(s1, nb_off, nw_lo, nw_hi, 0, std::false_type{});
     // K tile nk-1 (stage s1): the next tile's K tile 0 is complete in stage s and stage s1 is free: the token half of
     // the next tile's K tile 1 goes there
-    wait_all_and_barrier();
+    wait_loads_and_barrier<0>();
     step1(s1, na_off, 1, nb_off, nw_lo, nw_hi, 0, std::true_type{});
     mfma_results_ready();
 
@@ -948,7 +924,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               if (SWIGLU && kind == 0)
-                v[e] = swiglu_fast(acc[gi][2 * mi + m2][e], acc[gi + 2][2 * mi + m2][e]);
+                v[e] = swiglu_rcp(acc[gi][2 * mi + m2][e], acc[gi + 2][2 * mi + m2][e]);
               else if (SWIGLU)
                 v[e] = acc[gi + 2 * (kind - 1)][2 * mi + m2][e];   // kind 1: gate, 2: up
               else
@@ -1047,7 +1023,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
     par = s;
   }
   // the loads issued for a tile that does not exist must land before the block's LDS is released
-  wait_all_and_barrier();
+  wait_loads_and_barrier<0>();
 }
 }  // namespace t256
 

@@ -33,28 +33,10 @@ constexpr int A_BYTES = BM * BK * 2;                // 16 KiB
 constexpr int STAGE_BYTES = A_BYTES + BN * BK * 2;  // 48 KiB: token rows, then weight rows
 constexpr int OUT_BYTES = 2048;                     // per wave: 16 rows x 64 output columns on their way out
 
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void load_to_lds_16(const char* base, unsigned off, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
-               : "memory", "m0");
-}
-__device__ __forceinline__ void load_to_lds_4(const char* src, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
-}
-template <int N>
-__device__ __forceinline__ void wait_loads_and_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-#pragma clang diagnostic pop
 
 // silu(g) * u in the form of the kernel that the rows of a group would otherwise take (silu_rcp, wave-uniform): with the
-// 256-row tiles' hardware reciprocal, or with the f32 division of the weight-streaming and small-tile kernels
-__device__ __forceinline__ float swiglu_rcp(float g, float u) {
-  const float e = __builtin_amdgcn_exp2f(g * -1.4426950408889634f);
-  return g * u * __builtin_amdgcn_rcpf(1.0f + e);
-}
+// 256-row tiles' hardware reciprocal (swiglu_rcp), or with the f32 division of the weight-streaming and small-tile kernels
 __device__ __forceinline__ float swiglu_div(float g, float u) { return g / (1.0f + __expf(-g)) * u; }
 
 // one output tile; every field is wave-uniform

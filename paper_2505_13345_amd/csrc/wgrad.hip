@@ -77,27 +77,6 @@ constexpr int STAGE_BYTES = 2 * OP_BYTES;   // 32 KiB
 
 __device__ __attribute__((aligned(16))) const unsigned zero_page[4] = {0u, 0u, 0u, 0u};
 
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-// 64 lanes x 16 bytes from per-lane global addresses to LDS [lds, lds + 1024); counted by vmcnt
-__device__ __forceinline__ void load_to_lds_16(const char* src, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
-}
-// the same with a wave-uniform base and a 32-bit byte offset per lane
-__device__ __forceinline__ void load_to_lds_16(const char* base, unsigned off, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
-               : "memory", "m0");
-}
-// 64 lanes x 4 bytes to LDS [lds, lds + 256)
-__device__ __forceinline__ void load_to_lds_4(const char* src, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
-}
-template <int N>
-__device__ __forceinline__ void wait_loads_and_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-#pragma clang diagnostic pop
-
 // acc (16 output rows x 16 columns) += A block^T * B block over 32 rows; assembly for the reason given in ffn.hip: the
 // compiler, given the builtin, moves the 64 accumulator quads between the register files
 __device__ __forceinline__ void mfma16(f32x4& acc, const bf16x8& b, const bf16x8& a) {
