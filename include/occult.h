@@ -144,7 +144,7 @@ int occult_plan_bind(const occult_cfg_t* cfg, void* plan_mem, size_t plan_bytes,
 /* Router (paper Eq. 1; Sec. 3.3 routing-score-based pruning).
  * logits [T][E] f32 device ptr (router scores g(x)); outputs ids [T][k] i32 (slot 0 = highest
  * score; equal scores -> lower expert index first) and w [T][k] f32 (softmax over all E experts
- * at the selected ones, divided by their sum if cfg.renorm).  With cfg.n_d > 0 the selection is
+ * at the selected ones, divided by their sum if cfg.renorm).  A token's ids and gates do not depend on T.  With cfg.n_d > 0 the selection is
  * restricted to n_d devices as described at occult_cfg.  cfg.expert_pos is read when n_d > 0. */
 int occult_route(const occult_cfg_t* cfg, const float* logits, int32_t* ids, float* w,
                  occult_stream_t stream);
@@ -217,16 +217,18 @@ int occult_expert_ffn(const occult_cfg_t* cfg, const occult_plan_t* plan, const 
                       const void* x, const occult_weights_t* weights, void* epd_h, void* epd_y,
                       void* h_shared, void* y_shared, occult_stream_t stream);
 
-/* occult_expert_ffn with a scratch buffer, for small batches with shared experts whose down
- * projection alone (few output tiles, K = S*f) leaves most of the chip idle: 24 <= T < 192, unless
- * the batch is one whose shared experts are computed inside the routed experts' two launches
- * anyway (bf16, T <= 128 and fewer than 24 rows per routed expert on average: no scratch, ws_bytes
- * = 0).  Given `ws` (device ptr, 16-byte aligned, >= occult_expert_ffn_ws_bytes() bytes) that
- * product is split over K into f32 partial sums in ws, which a second kernel adds in slice order and
- * rounds once: y_shared then differs from occult_expert_ffn's only by the order of f32 additions;
- * epd_h and epd_y are the same bits.  With ws == NULL, too few bytes, or a layer that does not need
- * it (ws_bytes == 0), identical to occult_expert_ffn.  The contents of ws are not kept between
- * calls and need no initialisation. */
+/* occult_expert_ffn with a scratch buffer, for batches with shared experts whose down projection
+ * alone (few output tiles, K = S*f) leaves most of the chip idle: T >= 24, S*f >= 512 and fewer than
+ * 384 output tiles of 128 x 128, unless the batch is one whose shared experts are computed inside the
+ * routed experts' two weight-streaming launches anyway (bf16, T <= 128 and fewer than 24 rows per
+ * routed expert on average: no scratch, ws_bytes = 0).  Given `ws` (device ptr, 16-byte aligned, >=
+ * occult_expert_ffn_ws_bytes() bytes) the K of that product is summed in up to eight parts, which are
+ * added in their order and rounded once: y_shared then differs from occult_expert_ffn's only by the
+ * order of f32 additions; epd_h and epd_y are the same bits.  The parts go through ws and a second
+ * kernel, or, where the product runs in one launch of 128-row tiles with the routed experts', stay in
+ * registers (ws is not touched; the same bits).  With ws == NULL, too few bytes, or a layer that does
+ * not need it (ws_bytes == 0), identical to occult_expert_ffn.  The contents of ws are not kept
+ * between calls and need no initialisation. */
 int occult_expert_ffn_ws_bytes(const occult_cfg_t* cfg, size_t* ws_bytes);
 int occult_expert_ffn_ws(const occult_cfg_t* cfg, const occult_plan_t* plan, const void* sfd_x,
                          const void* x, const occult_weights_t* weights, void* epd_h, void* epd_y,
@@ -235,8 +237,9 @@ int occult_expert_ffn_ws(const occult_cfg_t* cfg, const occult_plan_t* plan, con
 
 /* Optional repacked weights for decode-shaped batches (paper Sec. 4, decoding: few rows per expert, the
  * expert computation is streaming every active expert's weights once).  Below 24 rows per expert
- * on average the bf16 products run a kernel in which a wave streams its 32 output columns' weights;
- * in the layout of occult_weights_t that is 32 or 64 rows 4 KiB apart, 128 bytes at a time.
+ * on average the bf16 products run a kernel in which a wave streams its 32 output columns' weights
+ * (with shared experts and T > 128 only where joining theirs in one launch of 128-row tiles, which read
+ * `weights`, would be the slower way); in the layout of occult_weights_t that is 32 or 64 rows 4 KiB apart, 128 bytes at a time.
  * occult_pack_weights writes the same numbers once (again after every weight update) in the order
  * that kernel reads them, one contiguous stream per wave: `packed` is a device ptr of
  * occult_pack_weights_bytes() bytes (3*(E+S)*d*f elements; 0 for f32, where the call does nothing),
@@ -333,8 +336,9 @@ int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_plan_t* pla
 
 /* Forward pass of a training step: occult_expert_ffn_ws that also keeps the pre-activations, so that
  * the backward pass need not recompute them: epd_gu [N_epd][2f] = [g | u] per EPD row and, with shared
- * experts, gu_shared [T][S*2f] = per shared expert [g | u] (rounded to cfg.dtype).  On 256-row tiles
- * the first product stores them from the same accumulators; the other kernels add two products.
+ * experts, gu_shared [T][S*2f] = per shared expert [g | u] (rounded to cfg.dtype).  On 128- and 256-row
+ * tiles the first product stores them from the same accumulators; where it is summed in parts of K, and
+ * on the other kernels, they are two products more.
  * Pass gu_saved = 1 to occult_expert_ffn_backward afterwards (it overwrites both with [dg | du]);
  * gu_saved = 0 recomputes g and u there (0.5 GB less memory held between the passes at the prefill
  * size, for about a fifth more backward time). */
@@ -347,7 +351,7 @@ int occult_expert_ffn_train(const occult_cfg_t* cfg, const occult_plan_t* plan, 
  * dw_gate, dw_up [E+S][f][d], dw_down [E+S][d][f], device ptrs).  For the expert at position P with
  * EPD rows q in [exp_offset[P], exp_offset[P+1]) and x_q = sfd_x[epd_sfd_row[q]]:
  *   dw_down = sum_q epd_dy[q] (x) epd_h[q],  dw_gate = sum_q dg[q] (x) x_q,  dw_up = sum_q du[q] (x) x_q,
- * rows summed in f32 (bf16: MFMA, rows in blocks of 64 in ascending order; order-fixed, no atomics).
+ * rows summed in f32 (bf16: MFMA, rows in blocks of 32 in ascending order; order-fixed, no atomics).
  * Inputs: epd_h (and h_shared) as left by occult_expert_ffn, epd_dy by occult_combine_backward,
  * epd_gu = [dg | du] (and gu_shared) by occult_expert_ffn_backward; dy [T][d] serves the shared
  * experts.  accumulate = 0 overwrites the three outputs (experts without rows get zeros), 1 adds to

@@ -1118,7 +1118,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_bf16(const float* __restric
 
 // K slices for a product whose tiles alone would leave most of the chip idle (0 = do not split)
 static int choose_ksplit(long long tiles, int nk) {
-  if (tiles >= 384 || nk < 8) return 0;   // beyond that the 256-row tiles fill the chip by themselves
+  if (tiles >= 384 || nk < 8) return 0;   // beyond that the tiles fill the chip by themselves
   long long ks = 1024 / tiles;   // about two rounds of 512 resident workgroups
   if (ks > nk / 4) ks = nk / 4;
   if (ks > 8) ks = 8;
@@ -1219,7 +1219,7 @@ static int launch_gemm_main(const occult_cfg_t& c, const GemmArgs& a, bool swigl
     const bool use_big = uses_tile256(a, swiglu, total_rows);
     // an A operand of 4 GiB or more takes the variant of the 256-row tiles with 64-bit row offsets
     const bool wide = (long long)a.a_rows_total * a.lda * 2 >= (1ll << 32);
-    // only the 256-row tiles store the pre-activations themselves (not built with 64-bit offsets: registers)
+    // of these kernels only the 256-row tiles store the pre-activations themselves (not with 64-bit offsets: registers)
     const bool fused_save = swiglu && a.C2 != nullptr && use_big && !wide;
     *fused_save_out = fused_save;
     const bool use_skinny = !use_big && streams_weights(a, total_rows);
@@ -1389,8 +1389,6 @@ int launch_gemm_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b
 using namespace occult;
 
 
-// Scratch that lets the shared experts' down projection of a small batch be split over K: the
-// product has T/128 x d/128 tiles only (16 for T = 128, d = 2048) with a long K = S*f.
 // Small batches whose routed experts take the weight-streaming kernel: the shared experts ride in the same two
 // launches, the down projection as one product whose K walks the S matrices (no scratch, no extra launch).
 constexpr int kPairMaxT = 128;   // a shared expert's weights are requested once per 32 tokens (from L2 after the first)
@@ -1401,6 +1399,11 @@ static bool pairs_shared_with_routed(const occult_cfg_t& c) {
          (long long)c.T * c.S * c.f * 2 < (1ll << 32);
 }
 
+// Scratch that lets the shared experts' down projection of a small batch be split over K: the
+// product has T/128 x d/128 tiles only (32 for T = 160, d = 2048) with a long K = S*f.
+// Asked for by shape alone, also where the shared product then joins the routed experts' launch and sums its parts in
+// registers: scratch sized for a server's largest batch serves the smaller ones, and a caller that gives it gets the sums
+// in the same parts either way.
 static size_t ffn_ws_need(const occult_cfg_t& c, int* ksplit_out) {
   *ksplit_out = 0;
   if (c.S == 0 || c.dtype != OCCULT_BF16 || c.T == 0) return 0;

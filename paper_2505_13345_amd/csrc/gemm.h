@@ -46,7 +46,7 @@ struct GemmArgs {
 int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total_rows, hipStream_t s);
 
 // The same product for the routed experts (`a`, grouped rows) and, unless b is NULL, for the shared ones (`b`,
-// uniform groups, rows_b rows over all of them, same N): one launch where the 128-row tiles take `a`, two otherwise.
+// uniform groups, rows_b rows over all of them, same N): one launch where the 128-row tiles take both, two otherwise.
 int launch_gemm_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, int rows_b,
                      hipStream_t s);
 

@@ -302,9 +302,10 @@ __global__ __launch_bounds__(256) void route_kernel(
 // dimension each and multiply it with all E expert rows on v_mfma_f32_16x16x32_bf16 (operands
 // loaded straight into fragment registers: 16 rows x one 64-byte sector per load; the expert
 // rows come from cache).  The four partial products are added in LDS in wave order (a fixed
-// order, so scores are reproducible) and written out as float32.  Routing runs as its own launch:
-// one token per wave is a chain of dependent cross-lane steps, which many resident waves hide and
-// eight tokens in sequence on one wave do not (measured: fused 75 us, separate 40 us at T = 2^14).
+// order, so scores are reproducible) and written out as float32.  Routing runs as its own launch: a token
+// is a chain of dependent cross-lane steps, which many resident waves hide and eight tokens in sequence on
+// one wave of this kernel do not (measured with a wave per token: fused 75 us, separate 40 us at T = 2^14;
+// the routing launch alone is 8 us there with sixteen lanes per token).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 constexpr int kRouterTokens = 32;
@@ -453,7 +454,7 @@ __global__ __launch_bounds__(256) void router_f32_kernel(const float* __restrict
 // of their mirror image.  What bounds it is the chain of 64-cycle products of a block and, with more blocks, the
 // atomics on the few thousand cells.  16384 tokens of 64 experts: 160 us with 16 blocks of scalar double arithmetic,
 // 15 us now; 65536 tokens 169 -> 35 us (clearing launch included).
-constexpr int kGramTokens = 64;   // tokens per block, at least
+constexpr int kGramTokens = 64;   // tokens per block, about (the slices are evened out to multiples of 16)
 __global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ logits, int T, int E,
                                                    int tokens_per_block, double* __restrict__ gram) {
   typedef double f64x4 __attribute__((ext_vector_type(4)));
