@@ -576,14 +576,21 @@ constexpr int SMEM_BYTES = 2 * STAGE_BYTES;
 // acc (16 x 16) += b (16 weight rows x 32 K) * a (16 token rows x 32 K)^T, accumulators in the accumulation registers.
 // Written as assembly because the compiler, given the builtin, moves the 64 accumulator quads between the two register
 // files; it cannot see that these are matrix instructions, so whoever reads acc has to leave the wait states itself
-// (mfma_results_ready, with acc named in an assembly statement behind it: that alone keeps the reads there).
+// (mfma_results_ready) and keep the reads behind them (behind).
 __device__ __forceinline__ void mfma16(f32x4& acc, const bf16x8& b, const bf16x8& a) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
 }
 __device__ __forceinline__ void mfma16_first(f32x4& acc, const bf16x8& b, const bf16x8& a) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(b), "v"(a));
 }
-__device__ __forceinline__ void mfma_results_ready() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+// The wait states, and what ties acc to them: a value that the one leaves and the other takes.  (A volatile statement per
+// accumulator would tie it as well, and hold the epilogue's LDS accesses in source order: prefill step 1673 -> 1688 us.)
+__device__ __forceinline__ int mfma_results_ready() {
+  int ready;
+  asm volatile("s_nop 15\n\ts_nop 15" : "=s"(ready)::"memory");
+  return ready;
+}
+__device__ __forceinline__ void behind(int ready, f32x4& acc) { asm("" : "+a"(acc) : "s"(ready)); }
 
 // One output tile before its row gather has come back.  All fields but raw are wave-uniform.
 struct Head {
@@ -884,7 +891,11 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
     // the next tile's K tile 1 goes there
     wait_loads_and_barrier<0>();
     step1(s1, na_off, 1, nb_off, nw_lo, nw_hi, 0, std::true_type{});
-    mfma_results_ready();
+    const int ready = mfma_results_ready();
+#pragma unroll
+    for (int ni = 0; ni < 8; ++ni)
+#pragma unroll
+      for (int mi = 0; mi < 8; ++mi) behind(ready, acc[ni][mi]);
 
     // epilogue.  acc[ni][mi] element e of lane l: output row (token) mi*16 + l%16, output column
     // ni*16 + (l/16)*4 + e of the wave tile: 4 consecutive columns per register quad.
@@ -912,13 +923,9 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
 #pragma unroll
           for (int nn = 0; nn < 4; ++nn) {   // 16 output columns
             const int gi = (nn >> 1) * 4 + (nn & 1);   // SWIGLU: weight-row block of the gate; the up block is gi + 2
-            // Read from here on, which is behind the wait states above.  With SAVE again for every kind: values kept from
-            // one chunk to the next would not fit the registers.
-            if (SWIGLU) {
+            if (SAVE) {   // read again for every kind: values kept from one chunk to the next would not fit the registers
               asm volatile("" : "+a"(acc[gi][2 * mi + m2]));
               asm volatile("" : "+a"(acc[gi + 2][2 * mi + m2]));
-            } else {
-              asm volatile("" : "+a"(acc[4 * h + nn][2 * mi + m2]));
             }
             float v[4];
 #pragma unroll
