@@ -549,9 +549,9 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs first, c
 // a bank line, so 16 consecutive rows x one chunk must cover the 16 slots of a line.)
 //
 // Matrix instruction.  v_mfma_f32_16x16x32_bf16 rather than 32x32x16: the clock under matrix load is power-limited, and
-// the 16 x 16 form reads and writes half as many accumulator bytes per product.  Measured with nothing but products and
-// fragment reads on normally distributed operands: 1900 TFLOP/s against 1680 (on zeros both 2450).  Here the clock went
-// from 1.70 to 1.95 - 2.05 GHz and the kernel is bound by the operand stream into LDS instead.
+// the 16 x 16 form reads and writes half as many accumulator bytes per product.  Under the counters (GEMM-1 of the prefill
+// batch) 941 us at 1697 MHz with the matrix pipe 70 % busy went to 905 us at 1888 MHz and 65 %: bound by the operand
+// stream into LDS instead.
 //
 // Schedule.  With one wave per SIMD nothing hides an instruction clump, so a K step of 32 (64 MFMAs) is written as 16
 // groups of {4 MFMAs, up to 2 LDS fragment reads for the next K step, up to 2 tile loads} pinned in source order: the
@@ -1339,20 +1339,23 @@ static int k_parts(const GemmArgs& a, bool swiglu, int total_rows) {
 //    of 127 batches below 24 rows per expert 0.81 of the time apart on average (at worst 1.16), packed 0.88 (1.15).
 //    (64 + 4 experts, 155 tokens, d = 1024, f = 512: 46 us against 43; 60 + 1, 169 tokens, the same widths: 27 against 37.)
 //  - a down projection with scratch: apart, its K (S matrices long) is split over workgroups, joined it is one block's chain
-//    of about 0.75 us per K tile of 64.  Joined while that chain is at most 9 K tiles (4 where `a` streams its weights) longer
-//    than a block's share of all tiles and the work of `b` alone, spread over 256 CUs, together.
+//    of about 0.75 us per K tile of 64.  Joined while what that costs (the chain's excess over a block's share of all tiles,
+//    or half the excess of the block with the most tiles, which runs on with more of the memory to itself) stays within 6 K
+//    tiles of what it saves, twice the work of `b` spread over 256 CUs: of 687 pairs it takes 272 of the 304 that gain 3 %
+//    or more and 20 that lose as much, at worst 1.13.
 //    (60 + 4 experts, 180 tokens, d = 512, f = 1088: 62 us against 36; 32 + 2, 517 tokens, 2048, 1408: 49 against 76.)
 static bool shares_launch(const GemmArgs& a, const GemmArgs& b, bool swiglu, int total_rows) {
-  const bool streams = streams_weights(a, total_rows);
-  if (swiglu && streams)
+  if (swiglu && streams_weights(a, total_rows))
     return (long long)b.ngroups * b.M * a.K > (a.Bp != nullptr ? 2 : 1) * 6144ll * a.ngroups;
   if (b.ksplit <= 1) return true;
   const long long n_tiles = (a.N + 255) / 256;
   const long long tiles_a = a.ngroups * ((total_rows / a.ngroups + 127) / 128) * n_tiles;   // of evenly loaded experts
-  const long long tiles_b = (b.M + 127) / 128 * n_tiles;
-  const long long blocks = tiles_a + tiles_b < 256 ? tiles_a + tiles_b : 256;
-  const long long share = (tiles_a * a.K + tiles_b * b.K) / blocks;
-  return b.K - share - tiles_b * b.K / 256 <= (streams ? 4 : 9) * 64;
+  const long long tiles_b = (b.M + 127) / 128 * n_tiles, tiles = tiles_a + tiles_b;
+  const long long share = (tiles_a * a.K + tiles_b * b.K) / (tiles < 256 ? tiles : 256);
+  const long long most_b = (tiles_b + 255) / 256;   // tiles of the fullest block, those of `b` first
+  const long long fullest = most_b * b.K + ((tiles + 255) / 256 - most_b) * a.K;
+  const long long chain = b.K - share, last = (fullest - share) / 2;
+  return (chain > last ? chain : last) - tiles_b * b.K / 128 <= 6 * 64;
 }
 
 static int launch_preactivation_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, int total_rows, int rows_b,
