@@ -1349,7 +1349,8 @@ static bool shares_launch(const GemmArgs& a, const GemmArgs& b, bool swiglu, int
     return (long long)b.ngroups * b.M * a.K > (a.Bp != nullptr ? 2 : 1) * 6144ll * a.ngroups;
   if (b.ksplit <= 1) return true;
   const long long n_tiles = (a.N + 255) / 256;
-  const long long tiles_a = a.ngroups * ((total_rows / a.ngroups + 127) / 128) * n_tiles;   // of evenly loaded experts
+  const long long groups = a.ngroups < total_rows ? a.ngroups : total_rows;
+  const long long tiles_a = groups > 0 ? groups * ((total_rows / groups + 127) / 128) * n_tiles : 0;   // evenly loaded experts
   const long long tiles_b = (b.M + 127) / 128 * n_tiles, tiles = tiles_a + tiles_b;
   const long long share = (tiles_a * a.K + tiles_b * b.K) / (tiles < 256 ? tiles : 256);
   const long long most_b = (tiles_b + 255) / 256;   // tiles of the fullest block, those of `b` first

@@ -148,6 +148,7 @@ def test_few_rows_have_the_bits_of_smaller_batches(T, part, d, f, E, S, k):
 @pytest.mark.parametrize("T,d,f,E,S,k,apart", [
     (140, 512, 256, 16, 4, 4, True),     # four K tiles of its own against the sixteen of the shared down projection
     (160, 1024, 512, 60, 4, 4, True),    # below 24 rows per expert
+    (150, 512, 256, 256, 4, 1, True),    # more experts than rows
     (1000, 256, 192, 4, 4, 1, False),
     (1000, 1024, 512, 60, 1, 6, False),
 ])
