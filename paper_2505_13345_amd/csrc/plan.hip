@@ -10,11 +10,14 @@
 //                        sets' sizes;
 //   pass 2  plan_scan  : one block turns the [blocks][D+E] counts into exclusive bases
 //                        (column scan over blocks, then a scan over devices / positions);
-//   pass 3  plan_fill  : every block rebuilds its sets; a token's rank in a column is the block's
-//                        base plus the number of set bits below its own, and every token writes
-//                        its own entries of the rank-addressed tables.
+//   pass 3  plan_fill  : every workgroup rebuilds the sets of its block of tokens; a token's rank in a
+//                        column is the block's base plus the number of set bits below its own, and
+//                        every token writes its own entries of the rank-addressed tables.
 // Ranks are token-ascending, which is the order the sequential counters would visit: every table
-// is bit-reproducible.  A batch of one block (T <= 256) runs the three passes in one launch.
+// is bit-reproducible.  What bounds the planner is the chain of launches and of dependent steps in each,
+// so the third pass does the work of the others where every workgroup can afford it: it adds the counts of all
+// blocks itself (no scan launch) up to kCountsMaxBlocks blocks, and counts all tokens itself (one launch) up
+// to kSingleMaxTokens tokens.
 #include "common.h"
 
 #include <mutex>
@@ -39,24 +42,19 @@ __device__ __forceinline__ int bits_below(const unsigned long long* col, int tl)
   return n;
 }
 
-// A token's selected placement positions (a position named by several slots counts once, with the gate of the
-// last), their devices and gates; -1 / 0 in unused slots.  k <= KMAX.
+// A token's selected placement positions (a position named by several slots counts once, in the last of them) and their
+// devices; -1 in unused slots.  k <= KMAX.
 template <int KMAX>
 struct TokenSlots {
   int pos[KMAX], dev[KMAX];
-  float gate[KMAX];
   unsigned long long devmask;
 };
 
-template <int KMAX, bool GATES>
-__device__ __forceinline__ void load_token(TokenSlots<KMAX>& ts, const int32_t* __restrict__ ids,
-                                           const float* __restrict__ w, int t, int T, int k, int G, const int* s_pos) {
+template <int KMAX>
+__device__ __forceinline__ void load_token(TokenSlots<KMAX>& ts, const int32_t* __restrict__ ids, int t, int T, int k, int G,
+                                           const int* s_pos) {
 #pragma unroll
-  for (int s = 0; s < KMAX; ++s) {
-    const bool live = (t < T) && (s < k);
-    ts.pos[s] = live ? s_pos[ids[(size_t)t * k + s]] : -1;
-    ts.gate[s] = (GATES && live) ? w[(size_t)t * k + s] : 0.0f;
-  }
+  for (int s = 0; s < KMAX; ++s) ts.pos[s] = (t < T) && (s < k) ? s_pos[ids[(size_t)t * k + s]] : -1;
 #pragma unroll
   for (int s = 0; s < KMAX; ++s)
 #pragma unroll
@@ -82,41 +80,6 @@ __device__ __forceinline__ void join_sets(TokenSet* s_set, int D, int tl, const 
     }
 }
 
-// Token t (bit tl of its block) writes its own entries of every table: base[c] = rank of its block's first token in
-// column c.  The merge list of an SFD row is position-ascending.
-template <int KMAX>
-__device__ __forceinline__ void fill_token(const TokenSlots<KMAX>& ts, int t, int tl, int D, int M1, const TokenSet* s_set,
-                                           const int* base, int32_t* __restrict__ tok_sfd_row,
-                                           int32_t* __restrict__ sfd_token, int32_t* __restrict__ epd_sfd_row,
-                                           float* __restrict__ epd_gate, int32_t* __restrict__ sfd_epd_rows) {
-  for (int j = 0; j < D; ++j) {
-    const bool on = (ts.devmask >> j) & 1ull;
-    const int r = on ? base[j] + bits_below(s_set[j], tl) : -1;
-    tok_sfd_row[(size_t)t * D + j] = r;
-    if (on) {
-      sfd_token[r] = t;
-      int filled = 0;
-#pragma unroll
-      for (int s = 0; s < KMAX; ++s) filled += ts.dev[s] == j ? 1 : 0;
-      for (int i = filled; i < M1; ++i) sfd_epd_rows[(size_t)r * M1 + i] = -1;
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < KMAX; ++s) {
-    const int P = ts.pos[s];
-    if (P < 0) continue;
-    const int j = ts.dev[s];
-    const int r = base[j] + bits_below(s_set[j], tl);
-    const int q = base[D + P] + bits_below(s_set[D + P], tl);
-    int before = 0;   // this token's other positions on the same device below P
-#pragma unroll
-    for (int s2 = 0; s2 < KMAX; ++s2) before += (ts.dev[s2] == j && ts.pos[s2] < P) ? 1 : 0;
-    epd_sfd_row[q] = r;
-    epd_gate[q] = ts.gate[s];
-    sfd_epd_rows[(size_t)r * M1 + before] = q;
-  }
-}
-
 // pass 1: per block of 256 tokens, how many of them touch each device and each placement position
 template <int KMAX>
 __global__ __launch_bounds__(kTPB) void plan_count(const int32_t* __restrict__ ids, int T, int k, int E, int D, int G,
@@ -130,7 +93,7 @@ __global__ __launch_bounds__(kTPB) void plan_count(const int32_t* __restrict__ i
   for (int i = tl; i < C * 4; i += kTPB) (&s_set[0][0])[i] = 0ull;
   __syncthreads();
   TokenSlots<KMAX> ts;
-  load_token<KMAX, false>(ts, ids, nullptr, t, T, k, G, s_pos);
+  load_token<KMAX>(ts, ids, t, T, k, G, s_pos);
   join_sets<KMAX>(s_set, D, tl, ts);
   if (t < T) tok_devmask[t] = ts.devmask;
   __syncthreads();
@@ -217,68 +180,39 @@ __global__ __launch_bounds__(kScanThreads) void plan_scan(
   }
 }
 
-// pass 3: every block rebuilds its token sets and its tokens write the rank-addressed tables; blk_base holds, per
-// block and column, the rank of the block's first token (pass 2)
-template <int KMAX>
-__global__ __launch_bounds__(kTPB) void plan_fill(
-    const int32_t* __restrict__ ids, const float* __restrict__ w, int T, int k, int E, int D, int G,
-    int M1, const int32_t* __restrict__ expert_pos, const int32_t* __restrict__ blk_base,
-    int32_t* __restrict__ tok_sfd_row, int32_t* __restrict__ sfd_token,
-    int32_t* __restrict__ epd_sfd_row, float* __restrict__ epd_gate,
-    int32_t* __restrict__ sfd_epd_rows) {
-  __shared__ int s_pos[OCCULT_MAX_E];
-  __shared__ TokenSet s_set[kMaxCols];
-  __shared__ int s_base[kMaxCols];
-  const int tl = threadIdx.x, t = blockIdx.x * kTPB + tl, C = D + E;
-  for (int e = tl; e < E; e += kTPB) s_pos[e] = expert_pos ? expert_pos[e] : e;
-  for (int i = tl; i < C * 4; i += kTPB) (&s_set[0][0])[i] = 0ull;
-  for (int c = tl; c < C; c += kTPB) s_base[c] = blk_base[(size_t)blockIdx.x * C + c];
-  __syncthreads();
-  TokenSlots<KMAX> ts;
-  load_token<KMAX, true>(ts, ids, w, t, T, k, G, s_pos);
-  join_sets<KMAX>(s_set, D, tl, ts);
-  __syncthreads();
-  if (t < T) fill_token<KMAX>(ts, t, tl, D, M1, s_set, s_base, tok_sfd_row, sfd_token, epd_sfd_row, epd_gate, sfd_epd_rows);
-}
+// pass 3.  A workgroup owns FT tokens of a block of 256 and gives every (token, device) and every (token, slot)
+// entry a thread of its own: with a token per thread the D + k entries of a token were one thread's chain of LDS reads and
+// scattered stores (15 us at any T).  Where the bases come from:
+enum class Bases {
+  kIds,      // the batch's own ids: every workgroup counts all tokens (T <= kSingleMaxTokens; the only launch)
+  kCounts,   // blk holds pass 1's counts: every workgroup adds them up (at most kCountsMaxBlocks blocks)
+  kScanned   // blk holds pass 2's ranks of each block's first token
+};
+// Where the lines lie (us for the whole planner, 64 experts, k = 8, D = 8, calls back to back):
+//  - one launch, tokens x workgroups of counting: 256 tokens 7 against 12 with a counting launch, 500 9.6 / 11.9, 1000 14.6 / 12.0;
+//  - adding the counts up, blocks x workgroups of reading: 2048 tokens 12.4 against 15.1 with a scan launch, 262144 81 / 98;
+//    it grows with the square of the blocks, so the scan keeps what is beyond;
+//  - 32 tokens per workgroup against 256, which build a block's sets once instead of eight times: 16384 tokens 17 / 22,
+//    32768 21.5 / 23, 65536 33 / 30, 131072 57 / 47.
+// (Three launches with a token per thread in the last: 256 tokens 12 (in one launch of one workgroup), 500 19.6, 16384 23,
+// 65536 37, 262144 114.)
+constexpr int kSingleMaxTokens = 512;
+constexpr int kSmallMaxBlocks = 128;
+constexpr int kCountsMaxBlocks = 1024;
 
-// A batch of at most one block of tokens (T <= 256: decode steps): the three passes in one launch of one block,
-// the column counts and their scans held in LDS.  Tables bit-identical to the three-kernel path.
-template <int KMAX>
-__global__ __launch_bounds__(kTPB) void plan_single(
-    const int32_t* __restrict__ ids, const float* __restrict__ w, int T, int k, int E, int D, int G, int M1,
-    const int32_t* __restrict__ expert_pos, uint64_t* __restrict__ tok_devmask, int32_t* __restrict__ dev_count,
-    int32_t* __restrict__ dev_offset, int32_t* __restrict__ exp_count, int32_t* __restrict__ exp_offset,
-    int32_t* __restrict__ pos_expert, uint64_t* __restrict__ counters, int32_t* __restrict__ tok_sfd_row,
-    int32_t* __restrict__ sfd_token, int32_t* __restrict__ epd_sfd_row, float* __restrict__ epd_gate,
-    int32_t* __restrict__ sfd_epd_rows) {
-  __shared__ int s_pos[OCCULT_MAX_E];
-  __shared__ TokenSet s_set[kMaxCols];
-  __shared__ int s_n[kMaxCols];       // column counts
-  __shared__ int s_start[kMaxCols];   // exclusive scans: devices, then positions
-  const int t = threadIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int C = D + E;
-  for (int e = t; e < E; e += kTPB) s_pos[e] = expert_pos ? expert_pos[e] : e;
-  for (int i = t; i < C * 4; i += kTPB) (&s_set[0][0])[i] = 0ull;
-  __syncthreads();
-  TokenSlots<KMAX> ts;
-  load_token<KMAX, true>(ts, ids, w, t, T, k, G, s_pos);
-  join_sets<KMAX>(s_set, D, t, ts);
-  if (t < T) tok_devmask[t] = ts.devmask;
-  __syncthreads();
-
-  for (int c = t; c < C; c += kTPB)
-    s_n[c] = __popcll(s_set[c][0]) + __popcll(s_set[c][1]) + __popcll(s_set[c][2]) + __popcll(s_set[c][3]);
-  __syncthreads();
-
-  // wave 0: devices; wave 1: positions (64 at a time, carrying the running total); waves 2, 3: inverse placement
+// Exclusive scan of the columns' totals and, from one workgroup, the tables that hold them: wave 0 devices, wave 1 positions (64
+// at a time, carrying the running total), waves 2 and 3 the inverse placement.
+__device__ __forceinline__ void scan_columns(const int* s_total, int* s_start, const int* s_pos, bool write, int T, int k, int E,
+                                             int D, const occult_plan_t& p) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (wave < 2) {
     const int n_cols = wave == 0 ? D : E, col0 = wave == 0 ? 0 : D;
-    int32_t* cnt_out = wave == 0 ? dev_count : exp_count;
-    int32_t* off_out = wave == 0 ? dev_offset : exp_offset;
+    int32_t* cnt_out = wave == 0 ? p.dev_count : p.exp_count;
+    int32_t* off_out = wave == 0 ? p.dev_offset : p.exp_offset;
     int run = 0, mx = 0;
     for (int c0 = 0; c0 < n_cols; c0 += 64) {
       const int c = c0 + lane;
-      const int n = c < n_cols ? s_n[col0 + c] : 0;
+      const int n = c < n_cols ? s_total[col0 + c] : 0;
       int incl = n;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
@@ -287,81 +221,186 @@ __global__ __launch_bounds__(kTPB) void plan_single(
       }
       if (c < n_cols) {
         s_start[col0 + c] = run + incl - n;
-        cnt_out[c] = n;
-        off_out[c] = run + incl - n;
+        if (write) {
+          cnt_out[c] = n;
+          off_out[c] = run + incl - n;
+        }
       }
-      int m = n;
+      if (write) {   // uniform over the workgroup
+        int m = n;
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-      mx = max(mx, m);
+        for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+        mx = max(mx, m);
+      }
       run += __shfl(incl, 63, 64);
     }
-    if (lane == 0) {
+    if (write && lane == 0) {
       off_out[n_cols] = run;
       if (wave == 0) {
-        counters[0] = (uint64_t)run;
-        counters[3] = (uint64_t)mx;
+        p.counters[0] = (uint64_t)run;
+        p.counters[3] = (uint64_t)mx;
       } else {
-        counters[1] = (uint64_t)run;
-        counters[2] = (uint64_t)T * (uint64_t)k;
-        counters[4] = (uint64_t)mx;
-        counters[5] = counters[6] = counters[7] = 0;
+        p.counters[1] = (uint64_t)run;
+        p.counters[2] = (uint64_t)T * (uint64_t)k;
+        p.counters[4] = (uint64_t)mx;
+        p.counters[5] = p.counters[6] = p.counters[7] = 0;
       }
     }
-  } else {
-    for (int e = t - 128; e < E; e += kTPB - 128) pos_expert[s_pos[e]] = e;
+  } else if (write) {
+    for (int e = threadIdx.x - 128; e < E; e += kTPB - 128) p.pos_expert[s_pos[e]] = e;
+  }
+}
+
+// FT: tokens of a workgroup
+template <int KMAX, Bases FROM, int FT>
+__global__ __launch_bounds__(kTPB) void plan_fill(const int32_t* __restrict__ ids, const float* __restrict__ w, int T, int k,
+                                                  int E, int D, int G, int M1, int nblk, const int32_t* __restrict__ expert_pos,
+                                                  const int32_t* __restrict__ blk, const occult_plan_t p) {
+  constexpr int PER_BLOCK = kTPB / FT;   // workgroups that share a block of 256 tokens
+  __shared__ int s_pos[OCCULT_MAX_E];
+  __shared__ TokenSet s_set[kMaxCols];
+  __shared__ int s_before[kMaxCols];   // tokens of the blocks before mine in each column
+  __shared__ int s_total[kMaxCols];    // all tokens
+  __shared__ int s_base[kMaxCols];     // rank of my block's first token
+  __shared__ int s_slot[FT][KMAX];   // my tokens' slots: device << 16 | position, or -1
+  const int tl = threadIdx.x, C = D + E;
+  const int block = blockIdx.x / PER_BLOCK, first = (blockIdx.x % PER_BLOCK) * FT;   // first: my first bit
+  const int t0 = block * kTPB;
+  for (int e = tl; e < E; e += kTPB) s_pos[e] = expert_pos ? expert_pos[e] : e;
+  for (int i = tl; i < C * 4; i += kTPB) (&s_set[0][0])[i] = 0ull;
+  for (int c = tl; c < C; c += kTPB) {
+    s_before[c] = s_total[c] = 0;
+    if (FROM == Bases::kScanned) s_base[c] = blk[(size_t)block * C + c];
   }
   __syncthreads();
-  if (t < T) fill_token<KMAX>(ts, t, t, D, M1, s_set, s_start, tok_sfd_row, sfd_token, epd_sfd_row, epd_gate, sfd_epd_rows);
+  {
+    TokenSlots<KMAX> ts;
+    load_token<KMAX>(ts, ids, t0 + tl, T, k, G, s_pos);
+    join_sets<KMAX>(s_set, D, tl, ts);
+    if (tl >= first && tl < first + FT) {
+#pragma unroll
+      for (int s = 0; s < KMAX; ++s) s_slot[tl - first][s] = ts.pos[s] >= 0 ? ts.dev[s] << 16 | ts.pos[s] : -1;
+      if (FROM == Bases::kIds && t0 + tl < T) p.tok_devmask[t0 + tl] = ts.devmask;
+    }
+  }
+  if constexpr (FROM == Bases::kIds) {
+    for (int b = 0; b < nblk; ++b) {   // the other blocks' tokens, before mine and after
+      if (b == block) continue;
+      TokenSlots<KMAX> ts;
+      load_token<KMAX>(ts, ids, b * kTPB + tl, T, k, G, s_pos);
+      int* into = b < block ? s_before : s_total;
+#pragma unroll
+      for (int s = 0; s < KMAX; ++s)
+        if (ts.pos[s] >= 0) atomicAdd(&into[D + ts.pos[s]], 1);
+      for (unsigned long long m = ts.devmask; m != 0; m &= m - 1) atomicAdd(&into[__ffsll((long long)m) - 1], 1);
+    }
+    __syncthreads();
+    for (int c = tl; c < C; c += kTPB)
+      s_total[c] += s_before[c] + __popcll(s_set[c][0]) + __popcll(s_set[c][1]) + __popcll(s_set[c][2]) + __popcll(s_set[c][3]);
+  }
+  if constexpr (FROM == Bases::kCounts) {
+    const int parts = max(1, kTPB / C), rpp = (nblk + parts - 1) / parts;
+    for (int i = tl; i < C * parts; i += kTPB) {
+      const int c = i % C, r0 = i / C * rpp, r1 = min(nblk, r0 + rpp);
+      int before = 0, total = 0;
+#pragma unroll 8
+      for (int r = r0; r < r1; ++r) {
+        const int v = blk[(size_t)r * C + c];
+        total += v;
+        before += r < block ? v : 0;
+      }
+      atomicAdd(&s_total[c], total);   // integer sums: any order
+      atomicAdd(&s_before[c], before);
+    }
+  }
+  if constexpr (FROM != Bases::kScanned) {
+    __syncthreads();
+    scan_columns(s_total, s_base, s_pos, blockIdx.x == 0, T, k, E, D, p);
+    __syncthreads();
+    for (int c = tl; c < C; c += kTPB) s_base[c] += s_before[c];
+  }
+  __syncthreads();
+
+  // (token, device): the token's row of destinations, the row's token, the unused end of the row's merge list
+  const int mine = min(FT, T - t0 - first);   // may be <= 0
+  for (int i = tl; i < mine * D; i += kTPB) {
+    const int m = i / D, j = i - m * D;
+    int filled = 0;
+#pragma unroll
+    for (int s = 0; s < KMAX; ++s) filled += s_slot[m][s] >> 16 == j ? 1 : 0;   // (unused slots: -1 >> 16 = -1)
+    const int r = filled > 0 ? s_base[j] + bits_below(s_set[j], first + m) : -1;
+    p.tok_sfd_row[(size_t)(t0 + first) * D + i] = r;
+    if (filled > 0) {
+      p.sfd_token[r] = t0 + first + m;
+      for (int e = filled; e < M1; ++e) p.sfd_epd_rows[(size_t)r * M1 + e] = -1;
+    }
+  }
+  // (token, slot): the EPD row's source and gate, its entry of the merge list (position-ascending)
+  for (int i = tl; i < mine * k; i += kTPB) {
+    const int m = i / k, s = i - m * k, slot = s_slot[m][s];
+    if (slot < 0) continue;
+    const int j = slot >> 16, P = slot & 0xFFFF;
+    const int r = s_base[j] + bits_below(s_set[j], first + m);
+    const int q = s_base[D + P] + bits_below(s_set[D + P], first + m);
+    int before = 0;   // this token's other positions on the same device below P
+#pragma unroll
+    for (int s2 = 0; s2 < KMAX; ++s2) {
+      const int other = s_slot[m][s2];
+      before += (other >> 16 == j && other < slot) ? 1 : 0;
+    }
+    p.epd_sfd_row[q] = r;
+    p.epd_gate[q] = w[(size_t)(t0 + first) * k + i];
+    p.sfd_epd_rows[(size_t)r * M1 + before] = q;
+  }
 }
 
 size_t plan_workspace_bytes(const occult_cfg_t& c);
 
-// The three launches of the planner on a block-count buffer `blk` of >= nblk * (D + E) ints.  plan_count
-// writes every entry of the first nblk rows before plan_scan reads them: the buffer need not be cleared.
+// The launches of the planner on a block-count buffer `blk` of >= nblk * (D + E) ints.  plan_count writes every entry of the
+// first nblk rows before they are read: the buffer need not be cleared.
 static int launch_plan(const occult_cfg_t& c, const int32_t* ids, const float* w, const occult_plan_t& p,
                        int32_t* blk, hipStream_t s) {
   const int G = c.E / c.D;
   const int nblk = (c.T + kTPB - 1) / kTPB;
-  if (nblk == 1) {   // one block of tokens: the three passes in one launch (blk stays unused)
-#define OCC_PLAN_SINGLE(KM)                                                                                     \
-  hipLaunchKernelGGL(plan_single<KM>, dim3(1), dim3(kTPB), 0, s, ids, w, c.T, c.k, c.E, c.D, G, merge_width(c),  \
-                     c.expert_pos, p.tok_devmask, p.dev_count, p.dev_offset, p.exp_count, p.exp_offset,          \
-                     p.pos_expert, p.counters, p.tok_sfd_row, p.sfd_token, p.epd_sfd_row, p.epd_gate,            \
-                     p.sfd_epd_rows)
-    if (c.k <= 8) OCC_PLAN_SINGLE(8);
-    else if (c.k <= 16) OCC_PLAN_SINGLE(16);
-    else OCC_PLAN_SINGLE(32);
-#undef OCC_PLAN_SINGLE
-    OCC_LAUNCH_CHECK("plan_single");
-    return OCCULT_OK;
-  }
-  if (nblk > 0) {
+  const Bases from = c.T <= kSingleMaxTokens ? Bases::kIds : nblk <= kCountsMaxBlocks ? Bases::kCounts : Bases::kScanned;
+#define OCC_PLAN_KMAX(LAUNCH) \
+  do {                        \
+    if (c.k <= 8) LAUNCH(8);  \
+    else if (c.k <= 16) LAUNCH(16); \
+    else LAUNCH(32);          \
+  } while (0)
+  if (from != Bases::kIds) {
 #define OCC_PLAN_COUNT(KM)                                                                               \
   hipLaunchKernelGGL(plan_count<KM>, dim3(nblk), dim3(kTPB), 0, s, ids, c.T, c.k, c.E, c.D, G, c.expert_pos, \
                      p.tok_devmask, blk)
-    if (c.k <= 8) OCC_PLAN_COUNT(8);
-    else if (c.k <= 16) OCC_PLAN_COUNT(16);
-    else OCC_PLAN_COUNT(32);
+    OCC_PLAN_KMAX(OCC_PLAN_COUNT);
 #undef OCC_PLAN_COUNT
     OCC_LAUNCH_CHECK("plan_count");
   }
-  // with T == 0 the scan still writes zero counts and offsets
-  hipLaunchKernelGGL(plan_scan, dim3(1), dim3(kScanThreads), 0, s, blk, nblk, c.T, c.k, c.E, c.D, G,
-                     c.expert_pos, p.dev_count, p.dev_offset, p.exp_count, p.exp_offset, p.pos_expert,
-                     p.counters);
-  OCC_LAUNCH_CHECK("plan_scan");
-  if (nblk > 0) {
-#define OCC_PLAN_FILL(KM)                                                                              \
-  hipLaunchKernelGGL(plan_fill<KM>, dim3(nblk), dim3(kTPB), 0, s, ids, w, c.T, c.k, c.E, c.D, G,         \
-                     merge_width(c), c.expert_pos, blk, p.tok_sfd_row, p.sfd_token, p.epd_sfd_row,       \
-                     p.epd_gate, p.sfd_epd_rows)
-    if (c.k <= 8) OCC_PLAN_FILL(8);
-    else if (c.k <= 16) OCC_PLAN_FILL(16);
-    else OCC_PLAN_FILL(32);
-#undef OCC_PLAN_FILL
-    OCC_LAUNCH_CHECK("plan_fill");
+  if (from == Bases::kScanned) {
+    hipLaunchKernelGGL(plan_scan, dim3(1), dim3(kScanThreads), 0, s, blk, nblk, c.T, c.k, c.E, c.D, G,
+                       c.expert_pos, p.dev_count, p.dev_offset, p.exp_count, p.exp_offset, p.pos_expert,
+                       p.counters);
+    OCC_LAUNCH_CHECK("plan_scan");
   }
+#define OCC_PLAN_FILL(KM, FROM, FT)                                                                                      \
+  hipLaunchKernelGGL((plan_fill<KM, FROM, FT>), dim3((unsigned)(c.T > 0 ? ((long long)c.T + FT - 1) / FT : 1)), dim3(kTPB), 0, \
+                     s, ids, w, c.T, c.k, c.E, c.D, G, merge_width(c), nblk, c.expert_pos, blk, p)
+#define OCC_PLAN_FILL_IDS(KM) OCC_PLAN_FILL(KM, Bases::kIds, 32)   // T = 0: one workgroup writes zero counts and offsets
+#define OCC_PLAN_FILL_COUNTS(KM) OCC_PLAN_FILL(KM, Bases::kCounts, 32)
+#define OCC_PLAN_FILL_MANY(KM) OCC_PLAN_FILL(KM, Bases::kCounts, kTPB)
+#define OCC_PLAN_FILL_SCANNED(KM) OCC_PLAN_FILL(KM, Bases::kScanned, kTPB)
+  if (from == Bases::kIds) OCC_PLAN_KMAX(OCC_PLAN_FILL_IDS);
+  else if (from == Bases::kScanned) OCC_PLAN_KMAX(OCC_PLAN_FILL_SCANNED);
+  else if (nblk <= kSmallMaxBlocks) OCC_PLAN_KMAX(OCC_PLAN_FILL_COUNTS);
+  else OCC_PLAN_KMAX(OCC_PLAN_FILL_MANY);
+#undef OCC_PLAN_FILL_IDS
+#undef OCC_PLAN_FILL_COUNTS
+#undef OCC_PLAN_FILL_MANY
+#undef OCC_PLAN_FILL_SCANNED
+#undef OCC_PLAN_FILL
+#undef OCC_PLAN_KMAX
+  OCC_LAUNCH_CHECK("plan_fill");
   return OCCULT_OK;
 }
 

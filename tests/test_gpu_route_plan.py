@@ -115,7 +115,50 @@ PLAN_CASES = [
     (256, 4, 3, 191, "random"),
     (8, 2, 8, 100, "contig"),         # k = E
     (32, 4, 16, 77, "random"),
+    # workgroups of 32 tokens at their edges; every workgroup counts all tokens up to 512, adds pass 1's counts beyond
+    (64, 8, 8, 31, "random"),
+    (60, 4, 4, 33, "contig"),
+    (256, 64, 32, 511, "random"),
+    (64, 16, 6, 512, "random"),
+    (64, 16, 6, 513, "random"),
+    (256, 64, 32, 545, "contig"),     # more columns than threads in a workgroup
 ]
+
+
+@pytest.mark.parametrize("E,D,k,T", [(64, 8, 8, 32768), (64, 16, 6, 32769), (12, 3, 4, 262144), (12, 3, 4, 262145)])
+def test_plan_tables_of_many_tokens(E, D, k, T):
+    """Both sides of the lines between the planner's forms for many tokens: the tables against their definition."""
+    say(f"plan tables E={E} D={D} k={k} T={T}")
+    dev = require_gpu()
+    gen = torch.Generator().manual_seed(T)
+    score = torch.rand((T, E), generator=gen) + 0.5 * torch.rand(E, generator=gen)
+    ids = torch.topk(score, k).indices.to(torch.int32)
+    w = torch.rand((T, k), generator=gen)
+    pos = torch.from_numpy(wl.random_placement(E, D, seed=T).astype(np.int64))
+    layer = OccultLayer(T, 64, 64, E, 0, k, D, "bf16", expert_pos=pos.numpy(), with_ffn=False)
+    layer.make_plan(ids.to(dev), w.to(dev))
+    torch.cuda.synchronize()
+    tab = {n: v.cpu() for n, v in layer.tables().items()}
+    P = pos[ids.long()]                                       # [T, k] placement positions
+    on = torch.zeros((T, E), dtype=torch.bool).scatter_(1, P, True)
+    on_dev = on.view(T, D, E // D).any(2)
+    assert torch.equal(tab["dev_count"].long(), on_dev.sum(0)) and torch.equal(tab["exp_count"].long(), on.sum(0))
+    rows = on_dev.t().flatten().long().cumsum(0) - 1          # device-major, token-ascending
+    rows = torch.where(on_dev, rows.view(D, T).t(), -1)
+    assert torch.equal(tab["tok_sfd_row"].long(), rows)
+    n_sfd = int(on_dev.sum())
+    assert torch.equal(tab["sfd_token"][:n_sfd].long(), on_dev.t().nonzero()[:, 1])
+    where = on.t().nonzero()                                  # position-major, token-ascending
+    assert torch.equal(tab["epd_sfd_row"].long(), rows[where[:, 1], where[:, 0] // (E // D)])
+    gate = torch.zeros((T, E)).scatter_(1, P, w)
+    assert torch.equal(tab["epd_gate"], gate[where[:, 1], where[:, 0]])
+    q = torch.where(on, (on.t().flatten().long().cumsum(0) - 1).view(E, T).t(), 1 << 40).view(T, D, E // D)
+    m1 = min(k, E // D)
+    lists = torch.empty((n_sfd, m1), dtype=torch.long)
+    lists[rows[on_dev]] = q[on_dev].sort(1).values[:, :m1]    # position-ascending, -1 behind
+    assert torch.equal(tab["sfd_epd_rows"][:n_sfd].long(), torch.where(lists == 1 << 40, -1, lists))
+    assert torch.equal(tab["tok_devmask"], (on_dev.long() << torch.arange(D)).sum(1))
+    assert tab["counters"][:5].tolist() == [n_sfd, T * k, T * k, int(on_dev.sum(0).max()), int(on.sum(0).max())]
 
 
 @pytest.mark.parametrize("E,D,k,T,placement", PLAN_CASES)
