@@ -12,7 +12,9 @@
 // bf16 kernel (namespace wgd below).  Block = 256 threads = 4 waves (2 x 2), block tile 256 x 256
 // outputs, wave tile 128 x 128 = 8 x 8 v_mfma_f32_16x16x32_bf16 tiles (256 accumulator registers, one
 // block per CU).  Outputs are f32 (gradient accumulation across calls is exact to f32), stored
-// straight from the accumulators: four lanes cover 64 contiguous bytes.  With 8 groups or more a
+// as whole rows of a wave tile, 16 rows at a time through LDS, and marked as not to be kept in L2 (the operands are what is
+// read again: 64 + 2 experts, 562 rows each, 1460 us for the three products with 64-byte pieces straight from the
+// accumulators, 1359 with whole rows, 1290 not kept).  With 8 groups or more a
 // group's tiles are launched on one XCD (workgroup id % 8), so its rows are fetched into one L2.
 #include "common.h"
 
@@ -69,6 +71,7 @@ struct WgradArgs {
 // and 32 KiB of writes, about 1130 cycles per CU) and the matrix pipe (1024) can work side by side.  Before, a
 // step read its first fragments behind its barrier with nothing to multiply, and 32x32x16 products drew more power
 // (ffn.hip).  Training step of 16384 tokens (64 experts, d = 2048, f = 1024) about 115 us less of 6000.
+constexpr int kStreaming = 2;   // cache policy of a buffer store: not to be kept
 namespace wgd {
 constexpr int BM = 256, BN = 256, BK = 32;
 constexpr int NST = 4;   // the index ring below assumes 4
@@ -85,10 +88,15 @@ __device__ __forceinline__ void mfma16(f32x4& acc, const bf16x8& b, const bf16x8
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-template <bool GATHER>   // B rows through a.b_rows
-__global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
+// GATHER: the first problem's B rows through b_rows.  TWO: workgroups [0, second_blocks) work on `second` (uniform groups, no
+// gather), the rest on `first` (the shared experts' product alone had a few dozen workgroups: 6000 tokens of 64 + 2 experts
+// 1290 -> 1267 us for the three products, 4000 of 60 + 4 1063 -> 882 together with the epilogue's stores below).
+template <bool GATHER, bool TWO>
+__global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs first, const WgradArgs second, const int second_blocks) {
   __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE_BYTES];
   __shared__ __attribute__((aligned(256))) int s_idx[4][4][64];   // [wave][step % 4][row of the wave's 8, repeated]
+  const bool is_second = TWO && (int)blockIdx.x < second_blocks;   // uniform
+  const WgradArgs& a = is_second ? second : first;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
@@ -97,14 +105,16 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
   // with 8 groups or more a group's tiles share an XCD (and its L2); fewer groups (shared experts: few
   // groups of many rows) are spread over all XCDs instead
   int group, tile, slice = 0;
-  if (a.ngroups >= 8) {
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int b = is_second ? (int)blockIdx.x : (int)blockIdx.x - second_blocks;
+  if (!is_second && a.ngroups >= 8) {   // (host: second_blocks is a multiple of 8)
+    const int xcd = b & 7, slot = b >> 3;
     group = (slot / tiles) * 8 + xcd;
     tile = slot % tiles;
   } else {
     const int per_slice = a.ngroups * tiles;
-    const int bid = blockIdx.x % per_slice;
-    slice = __builtin_amdgcn_readfirstlane(blockIdx.x / per_slice);   // 0 unless the rows are split (host: grid = slices * per_slice)
+    const int bid = b % per_slice;
+    slice = __builtin_amdgcn_readfirstlane(b / per_slice);   // 0 unless the rows are split
+    if (slice >= max(1, a.rsplit)) return;   // whole block: the grid is padded to whole sets of XCDs
     group = bid / tiles;
     tile = bid % tiles;
   }
@@ -169,7 +179,7 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
         load_to_lds_16(src_a, st + (unsigned)kb * 512u);
         // B: rows past the end repeat the last row (the fetched indices are clamped the same way)
         long long rb = min(row0 + kb + rr, r1 - 1);
-        if (GATHER) rb = s_idx[wave][s & 3][i * 2 + rr];
+        if (GATHER && !is_second) rb = s_idx[wave][s & 3][i * 2 + rr];
         load_to_lds_16(b_cols + rb * b_pitch + chunk_b[i], st + (unsigned)OP_BYTES + (unsigned)kb * 512u);
       }
     };
@@ -184,7 +194,7 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
           const unsigned kb = (unsigned)(wave * 8 + i * 2);
           load_to_lds_16(a_step, off_a[i], st + kb * 512u);
           if (GATHER) {
-            const long long rb = s_idx[wave][s & 3][i * 2 + rr];   // fetched two steps ago
+            const long long rb = is_second ? row0 + (int)kb + rr : s_idx[wave][s & 3][i * 2 + rr];   // fetched two steps ago
             load_to_lds_16(b_cols + rb * b_pitch + chunk_b[i], st + (unsigned)OP_BYTES + kb * 512u);
           } else {
             load_to_lds_16(b_step, off_b[i], st + (unsigned)OP_BYTES + kb * 512u);
@@ -222,7 +232,8 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
     const unsigned idx_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)&s_idx[wave][0][0];
     auto issue_idx = [&](int s) {
       const int r = min(r0 + s * BK + wave * 8 + (lane & 7), r1 - 1);
-      load_to_lds_4(reinterpret_cast<const char*>(a.b_rows + r), idx_base + (unsigned)(s & 3) * 256u);
+      // (the second problem's rows are their own: a load that nobody reads keeps the count)
+      load_to_lds_4(is_second ? zeros : reinterpret_cast<const char*>(a.b_rows + r), idx_base + (unsigned)(s & 3) * 256u);
     };
     constexpr int OPS = GATHER ? 9 : 8;   // loads per wave and step
     if (GATHER) {
@@ -256,7 +267,10 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
       const char* b_step = b_cols + (long long)(r0 + sn * BK) * b_pitch;
       int rb[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) rb[i] = GATHER ? s_idx[wave][sn & 3][i * 2 + rr] : 0;   // fetched two steps ago
+      for (int i = 0; i < 4; ++i) {
+        rb[i] = GATHER ? s_idx[wave][sn & 3][i * 2 + rr] : 0;   // fetched two steps ago
+        if (GATHER && is_second) rb[i] = min(r0 + sn * BK + wave * 8 + i * 2 + rr, r1 - 1);
+      }
       auto tile_load = [&](int i) {   // 0..3: A, 4..7: B
         const int j = i & 3, row = r0 + sn * BK + wave * 8 + j * 2 + rr;
         const unsigned dst = st + (unsigned)j * 1024u;
@@ -300,7 +314,8 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
   }
 
   // accumulator element e of lane l: output row l % 16, column (l / 16) * 4 + e of its 16 x 16 tile (the operands are
-  // swapped), so 16-byte stores of four lanes cover 64 contiguous bytes.
+  // swapped).  16 rows of the wave tile at a time go through LDS, 16-byte chunk c of row r at c ^ r, and leave as two
+  // whole rows of 512 bytes per store.
   // Stores (and, when accumulating, loads) go through a buffer descriptor over the wave tile's valid rows: rows
   // past M lie beyond its range and are dropped by the hardware, columns past N are sent there: no branches.
   const int rows_left = min(a.M - (m0 + wm * 128), 128);
@@ -317,35 +332,216 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs a) {
       (unsigned)__builtin_amdgcn_readfirstlane((unsigned)c_tile);
   const __amdgpu_buffer_rsrc_t c_rsrc = __builtin_amdgcn_make_buffer_rsrc(
       reinterpret_cast<void*>(c_tile_u), 0, __builtin_amdgcn_readfirstlane((int)n_rec), 0x00020000);
-  const int orow = lane & 15, ocol = (lane >> 4) * 4;
   // wait states of the last products' results (the compiler does not see that they are matrix instructions)
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  __syncthreads();   // every wave is past its last reads: the stages are free
+  const int w_row = lane & 15, w_q = lane >> 4, o_row = lane >> 5, o_chunk = lane & 31;
+  const bool col_ok = o_chunk * 4 < cols_left;   // N % 8 == 0 (host): four columns are inside together
 #pragma unroll
   for (int mi = 0; mi < 8; ++mi) {
 #pragma unroll
     for (int ni = 0; ni < 8; ++ni) asm volatile("" : "+a"(acc[mi][ni]));   // read from here on, not all of them at once
+    char* buf = smem + wave * 16384 + (mi & 1) * 8192;
+#pragma unroll
+    for (int ni = 0; ni < 8; ++ni)
+      *reinterpret_cast<f32x4*>(buf + w_row * 512 + ((ni * 4 + w_q) ^ w_row) * 16) = acc[mi][ni];
+    f32x4 v[8];
     unsigned off[8];
 #pragma unroll
-    for (int ni = 0; ni < 8; ++ni) {   // host: N % 8 == 0, so four columns are inside together
-      const int nl = ni * 16 + ocol;
-      off[ni] = nl < cols_left ? (unsigned)((mi * 16 + orow) * ldc + nl) * 4u : n_rec;
+    for (int it = 0; it < 8; ++it) {
+      const int r = it * 2 + o_row;
+      v[it] = *reinterpret_cast<const f32x4*>(buf + r * 512 + (o_chunk ^ r) * 16);
+      off[it] = col_ok ? (unsigned)((mi * 16 + r) * ldc + o_chunk * 4) * 4u : n_rec;
     }
-    f32x4 v[8];
-#pragma unroll
-    for (int ni = 0; ni < 8; ++ni) v[ni] = acc[mi][ni];
     if (accumulate) {   // block-uniform; the 8 loads of a row block are in flight together
       u32x4 old[8];
 #pragma unroll
-      for (int ni = 0; ni < 8; ++ni) old[ni] = __builtin_amdgcn_raw_buffer_load_b128(c_rsrc, (int)off[ni], 0, 0);
+      for (int it = 0; it < 8; ++it) old[it] = __builtin_amdgcn_raw_buffer_load_b128(c_rsrc, (int)off[it], 0, 0);
 #pragma unroll
-      for (int ni = 0; ni < 8; ++ni) v[ni] += __builtin_bit_cast(f32x4, old[ni]);
+      for (int it = 0; it < 8; ++it) v[it] += __builtin_bit_cast(f32x4, old[it]);
     }
 #pragma unroll
-    for (int ni = 0; ni < 8; ++ni)
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[ni]), c_rsrc, (int)off[ni], 0, 0);
+    for (int it = 0; it < 8; ++it)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[it]), c_rsrc, (int)off[it], 0, kStreaming);
   }
 }
 }  // namespace wgd
+
+// ------------------------------------------------------------------------------------------
+// Groups of a few hundred rows and fewer (small micro-batches): a product is then little more than writing its f32 outputs,
+// and one block per CU does that with nothing beside it: a tile's first loads, its few steps and its stores stand in a row.
+// Here a block takes 128 x 128 outputs (wave tile 64 x 64 = 4 x 4 MFMA tiles) and three blocks share a CU, one storing while the
+// others load and multiply.  More operand bytes and LDS reads per product than the 256 x 256 tiles: @RULE@
+// The routed experts' groups (`first`) and the shared experts' (`second`, uniform groups over all tokens) are one launch:
+// alone the shared ones are a few dozen blocks.  They come first in the grid, since each of them runs longest.
+// Staging, swizzle, transposing reads and the order of the sums are those of the kernel above; a step's fragments are read
+// at its start (another block's products fill the gap) and the row indices of 1024 rows at a time are kept in LDS.
+namespace wgs {
+constexpr int BM = 128, BN = 128, BK = 32;
+constexpr int NST = 3;
+constexpr int OP_BYTES = BK * 256;          // raw operand tile: 32 rows x 128 columns of bf16
+constexpr int STAGE_BYTES = 2 * OP_BYTES;   // 16 KiB
+constexpr int IDX_ROWS = 1024;              // a multiple of BK
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(256, 3) void wgrad_bf16(const WgradArgs first, const WgradArgs second, const int second_blocks) {
+  __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE_BYTES];
+  __shared__ int s_idx[IDX_ROWS];
+  const bool is_second = (int)blockIdx.x < second_blocks;   // uniform
+  const WgradArgs& a = is_second ? second : first;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int nt_n = (a.N + BN - 1) / BN;
+  const int tiles = ((a.M + BM - 1) / BM) * nt_n;
+  int group, tile;
+  if (!is_second && a.ngroups >= 8) {   // a group's tiles share an XCD (second_blocks is a multiple of 8)
+    const int b = (int)blockIdx.x - second_blocks, slot = b >> 3;
+    group = (slot / tiles) * 8 + (b & 7);
+    tile = slot % tiles;
+  } else {
+    const int b = is_second ? (int)blockIdx.x : (int)blockIdx.x - second_blocks;
+    group = b / tiles;
+    tile = b % tiles;
+  }
+  if (group >= a.ngroups) return;   // whole block; before any barrier
+  const int m0 = __builtin_amdgcn_readfirstlane((tile / nt_n) * BM), n0 = __builtin_amdgcn_readfirstlane((tile % nt_n) * BN);
+  int r0 = 0, r1 = a.R;
+  if (a.grp_offset) {
+    r0 = a.grp_offset[group];
+    r1 = a.grp_offset[group + 1];
+  }
+  r0 = __builtin_amdgcn_readfirstlane(r0);
+  r1 = __builtin_amdgcn_readfirstlane(r1);
+  const long long widx = a.grp_widx ? a.grp_widx[group] : (a.w_base + group);
+  const int nk = (r1 - r0 + BK - 1) / BK;
+  const bool gather = a.b_rows != nullptr;   // uniform
+
+  f32x4 acc[4][4];   // [output-row block][output-column block] of 16 x 16
+#pragma unroll
+  for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  if (nk > 0) {
+    // loader role: load i (0, 1) of a wave covers tile rows wave*8 + i*4 .. +3; lane = (row rr, chunk position p)
+    const int rr = lane >> 4, p = lane & 15;
+    const char* a_cols = static_cast<const char*>(a.A) + (long long)(a.a_col0 + group * a.a_group_cols + m0) * 2;
+    const char* b_cols = static_cast<const char*>(a.B) + (long long)(a.b_col0 + group * a.b_group_cols + n0) * 2;
+    const long long a_pitch = (long long)a.lda * 2, b_pitch = (long long)a.ldb * 2;
+    const int a_chunks = min(16, (a.M - m0) / 8), b_chunks = min(16, (a.N - n0) / 8);   // valid 16-byte chunks per row
+    const int c_src = p ^ (rr << 2) ^ ((wave & 1) << 1);
+    const int chunk_a = (c_src < a_chunks ? c_src : 0) * 16, chunk_b = (c_src < b_chunks ? c_src : 0) * 16;   // columns past M
+    // or N: any valid chunk (never stored)
+    const unsigned lds_w = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + (unsigned)wave * 2048u;
+    const char* zeros = reinterpret_cast<const char*>(wgd::zero_page);
+    auto fetch_idx = [&](int from) {   // source rows of the group's rows from, from + 1, ...
+      for (int i = tid; i < IDX_ROWS && r0 + from + i < r1; i += 256) s_idx[i] = a.b_rows[r0 + from + i];
+    };
+    auto issue = [&](int s) {   // this wave's 4 loads of step s; steps past the end too, so that the count stays constant
+      const unsigned st = lds_w + (unsigned)(s % NST) * STAGE_BYTES;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int row = r0 + s * BK + wave * 8 + i * 4 + rr;
+        load_to_lds_16(row < r1 ? a_cols + row * a_pitch + chunk_a : zeros, st + (unsigned)i * 1024u);   // past the end: zeros
+        const int rb = min(row, r1 - 1);                                                                // the last row again
+        const long long src = gather ? s_idx[(rb - r0) % IDX_ROWS] : rb;
+        load_to_lds_16(b_cols + src * b_pitch + chunk_b, st + (unsigned)OP_BYTES + (unsigned)i * 1024u);
+      }
+    };
+    // fragment reads: lane l = 16 b + j, j = 4 e + q, as in the kernel above
+    const int fb = lane >> 4, fe = (lane >> 2) & 3, fq = lane & 3;
+    typedef __attribute__((address_space(3))) char lds_char;
+    const int f_sw = (fe << 2) ^ ((fb & 1) << 1), f_row = (8 * fb + fe) * 256 + (fq & 1) * 8;
+    int a_off[4], b_off[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      a_off[i] = f_row + ((wm * 8 + 2 * i + (fq >> 1)) ^ f_sw) * 16;
+      b_off[i] = f_row + ((wn * 8 + 2 * i + (fq >> 1)) ^ f_sw) * 16 + OP_BYTES;
+    }
+    auto frag = [&](const lds_char* at) -> bf16x8 {
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)at);
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)(at + 4 * 256));
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    if (gather) {
+      fetch_idx(0);
+      __syncthreads();
+    }
+#pragma unroll
+    for (int s = 0; s < NST; ++s) issue(s);
+    for (int s = 0; s < nk; ++s) {
+      // the tiles of step s have landed for every wave, and every wave has read those of step s - 1, whose stage is free
+      if (s == 0) {
+        wait_loads_and_barrier<4 * (NST - 1)>();
+      } else {
+        wait_loads_and_barrier<4 * (NST - 2)>();
+        const int next = s + NST - 1;
+        if (gather && next * BK % IDX_ROWS == 0) {   // uniform; the indices of all steps before have been read
+          fetch_idx(next * BK);
+          __syncthreads();
+        }
+        issue(next);
+      }
+      const lds_char* st = (const lds_char*)smem + (s % NST) * STAGE_BYTES;
+      bf16x8 fa[4], fbv[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) fbv[i] = frag(st + b_off[i]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) fa[i] = frag(st + a_off[i]);
+#pragma unroll
+      for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < 4; ++ni)
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fbv[ni], fa[mi], acc[mi][ni], 0, 0, 0);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads of steps past the end, before the block's LDS is released
+  }
+
+  // Outputs leave as whole rows of the wave tile: element e of a lane is output row l % 16, column (l / 16) * 4 + e of its
+  // 16 x 16 tile, and 16 rows x 64 columns at a time go through LDS (the stages are free: every wave is past its last read),
+  // 16-byte chunk c of row r at c ^ r.  Rows past M lie beyond the descriptor's range and are dropped, columns past N are
+  // sent there.
+  const int rows_left = min(a.M - (m0 + wm * 64), 64);
+  const int cols_left = min(a.N - (n0 + wn * 64), 64);
+  const unsigned n_rec = rows_left > 0 && cols_left > 0 ? (unsigned)((rows_left - 1) * a.ldc + cols_left) * 4u : 0u;
+  const unsigned long long c_tile = reinterpret_cast<unsigned long long>(
+      a.C + widx * a.c_mat_stride + (long long)(m0 + wm * 64) * a.ldc + n0 + wn * 64);
+  const unsigned long long c_tile_u =   // the descriptor has to sit in scalar registers
+      ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(c_tile >> 32)) << 32) |
+      (unsigned)__builtin_amdgcn_readfirstlane((unsigned)c_tile);
+  const __amdgpu_buffer_rsrc_t c_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      reinterpret_cast<void*>(c_tile_u), 0, __builtin_amdgcn_readfirstlane((int)n_rec), 0x00020000);
+  __syncthreads();
+  const int w_row = lane & 15, w_q = lane >> 4, o_row = lane >> 4, o_chunk = lane & 15;
+  const bool col_ok = o_chunk * 4 < cols_left;   // N % 8 == 0 (host): four columns are inside together
+#pragma unroll
+  for (int mi = 0; mi < 4; ++mi) {
+    char* buf = smem + wave * 8192 + (mi & 1) * 4096;
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni)
+      *reinterpret_cast<f32x4*>(buf + w_row * 256 + ((ni * 4 + w_q) ^ w_row) * 16) = acc[mi][ni];
+    f32x4 v[4];
+    unsigned off[4];
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const int r = it * 4 + o_row;
+      v[it] = *reinterpret_cast<const f32x4*>(buf + r * 256 + (o_chunk ^ r) * 16);
+      off[it] = col_ok ? (unsigned)((mi * 16 + r) * a.ldc + o_chunk * 4) * 4u : n_rec;
+    }
+    if (a.accumulate) {   // block-uniform
+      u32x4 old[4];
+#pragma unroll
+      for (int it = 0; it < 4; ++it) old[it] = __builtin_amdgcn_raw_buffer_load_b128(c_rsrc, (int)off[it], 0, 0);
+#pragma unroll
+      for (int it = 0; it < 4; ++it) v[it] += __builtin_bit_cast(f32x4, old[it]);
+    }
+#pragma unroll
+    for (int it = 0; it < 4; ++it)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[it]), c_rsrc, (int)off[it], 0, kStreaming);
+  }
+}
+}  // namespace wgs
 
 // Adds the row slices' partial products in slice order and writes (or adds) the sum: C[group] (=|+=) ws[0][group]
 // + ws[1][group] + ...  One thread per 4 output columns (host: N % 4 == 0, ldc % 4 == 0, 16-byte aligned bases).
@@ -427,22 +623,43 @@ static int choose_row_split(const occult_cfg_t& c, int ngroups, int M, int N, in
   return best;
 }
 
-static int launch_wgrad(const occult_cfg_t& c, const WgradArgs& a, hipStream_t s) {
-  if (a.ngroups == 0 || a.M == 0 || a.N == 0) return OCCULT_OK;
+// The routed experts' product and, unless b is NULL, the shared experts' (same M and N), which come first in the grid: their
+// workgroups run longest.
+// 128 x 128 tiles for fewer than 240 rows per group, shared ones included, where the products are mostly stores (us for the
+// three, d = 2048, 128 / 256 tiles: 64 + 2 experts of f = 1408, 91 rows 388 / 441, 182 473 / 530, 242 624 / 595, 303 841 / 724;
+// 64 of f = 1024, 125 rows 274 / 357, 250 387 / 419, 312 495 / 464; 60 + 4, 250 538 / 588, 375 873 / 767), and where the
+// larger tiles would leave half of the CUs without one (4 + 1 experts, d = 256, f = 192, 420 rows: 38 / 66).
+constexpr int kSmallRows = 240, kFewTiles = 128;
+static int launch_wgrad_pair(const occult_cfg_t& c, const WgradArgs& a, const WgradArgs* b, hipStream_t s) {
+  if (a.M == 0 || a.N == 0) return OCCULT_OK;
   if (c.dtype == OCCULT_BF16) {
-    const long long tiles = (long long)((a.M + wgd::BM - 1) / wgd::BM) * ((a.N + wgd::BN - 1) / wgd::BN);
-    long long blocks = a.ngroups >= 8 ? (long long)((a.ngroups + 7) / 8) * tiles * 8 : (long long)a.ngroups * tiles;
-    if (a.rsplit > 1) blocks *= a.rsplit;
+    const bool split = b != nullptr && b->rsplit > 1;
+    const long long groups = c.E + c.S;
+    const bool small_groups = !split && ((long long)c.T * (c.k + c.S) < kSmallRows * groups ||
+                                         groups * ((a.M + wgd::BM - 1) / wgd::BM) * ((a.N + wgd::BN - 1) / wgd::BN) < kFewTiles);
+    const int bm = small_groups ? wgs::BM : wgd::BM, bn = small_groups ? wgs::BN : wgd::BN;
+    const long long tiles = (long long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn);
+    // whole sets of XCDs: the routed groups keep theirs
+    const long long second = b ? (b->ngroups * tiles * (split ? b->rsplit : 1) + 7) / 8 * 8 : 0;
+    const long long blocks = second + (a.ngroups >= 8 ? (a.ngroups + 7) / 8 * 8 : a.ngroups) * tiles;
     OCC_REQUIRE(blocks < (1ll << 31), OCCULT_EINVAL, "weight-gradient grid too large");
-    if (a.b_rows) hipLaunchKernelGGL(wgd::wgrad_bf16<true>, dim3((unsigned)blocks), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(wgd::wgrad_bf16<false>, dim3((unsigned)blocks), dim3(256), 0, s, a);
-    if (a.rsplit > 1) {
+    const dim3 grid((unsigned)blocks), block(256);
+    const WgradArgs& b2 = b ? *b : a;
+    if (small_groups) hipLaunchKernelGGL(wgs::wgrad_bf16, grid, block, 0, s, a, b2, (int)second);
+    else if (a.b_rows && b) hipLaunchKernelGGL((wgd::wgrad_bf16<true, true>), grid, block, 0, s, a, b2, (int)second);
+    else if (a.b_rows) hipLaunchKernelGGL((wgd::wgrad_bf16<true, false>), grid, block, 0, s, a, b2, (int)second);
+    else if (b) hipLaunchKernelGGL((wgd::wgrad_bf16<false, true>), grid, block, 0, s, a, b2, (int)second);
+    else hipLaunchKernelGGL((wgd::wgrad_bf16<false, false>), grid, block, 0, s, a, b2, (int)second);
+    if (split) {
       OCC_LAUNCH_CHECK("wgrad");
-      hipLaunchKernelGGL(wgrad_reduce, dim3(2048), dim3(256), 0, s, a);
+      hipLaunchKernelGGL(wgrad_reduce, dim3(2048), dim3(256), 0, s, *b);
     }
   } else {
-    OCC_REQUIRE(a.ngroups <= 65535, OCCULT_EINVAL, "too many groups");
-    hipLaunchKernelGGL(wgrad_f32, dim3((a.N + 15) / 16, (a.M + 15) / 16, a.ngroups), dim3(256), 0, s, a);
+    for (const WgradArgs* p : {&a, b}) {
+      if (p == nullptr || p->ngroups == 0) continue;
+      OCC_REQUIRE(p->ngroups <= 65535, OCCULT_EINVAL, "too many groups");
+      hipLaunchKernelGGL(wgrad_f32, dim3((p->N + 15) / 16, (p->M + 15) / 16, p->ngroups), dim3(256), 0, s, *p);
+    }
   }
   OCC_LAUNCH_CHECK("wgrad");
   return OCCULT_OK;
@@ -517,28 +734,26 @@ static int backward_weights_impl(const occult_cfg_t* cfg, const occult_plan_t* p
   WgradArgs shared{};
   shared.grp_offset = nullptr; shared.grp_widx = nullptr; shared.w_base = c.E; shared.ngroups = c.S; shared.R = c.T;
   shared.accumulate = accumulate;
-  for (int part = 0; part < (c.S > 0 ? 2 : 1); ++part) {
-    const bool sh = part == 1;
-    const WgradArgs& base = sh ? shared : routed;
-    {   // dW_down [d][f] = sum_r dy_r (x) h_r
-      WgradArgs a = base;
-      a.A = sh ? dy : epd_dy; a.lda = c.d; a.M = c.d;
-      a.B = sh ? h_shared : epd_h; a.ldb = sh ? c.S * c.f : c.f; a.b_group_cols = sh ? c.f : 0; a.N = c.f;
-      a.C = dw_down; a.c_mat_stride = mat; a.ldc = c.f;
-      if (sh) set_row_split(c, a, ws, ws_bytes);
-      rc = launch_wgrad(c, a, s);
-      if (rc) return rc;
+  for (int product = 0; product < 3; ++product) {
+    WgradArgs a = routed, b = shared;
+    if (product == 0) {   // dW_down [d][f] = sum_r dy_r (x) h_r
+      a.A = epd_dy; a.B = epd_h; a.ldb = c.f;
+      b.A = dy; b.B = h_shared; b.ldb = c.S * c.f; b.b_group_cols = c.f;
+      a.lda = b.lda = a.M = b.M = c.d;
+      a.N = b.N = a.ldc = b.ldc = c.f;
+      a.C = b.C = dw_down;
+    } else {              // dW_gate, dW_up [f][d] = sum_r dg_r (x) x_r, sum_r du_r (x) x_r
+      a.A = epd_gu; a.lda = 2 * c.f; a.B = sfd_x; a.b_rows = plan->epd_sfd_row;
+      b.A = gu_shared; b.lda = c.S * 2 * c.f; b.a_group_cols = 2 * c.f; b.B = x;
+      a.a_col0 = b.a_col0 = product == 2 ? c.f : 0;
+      a.M = b.M = c.f;
+      a.N = b.N = a.ldb = b.ldb = a.ldc = b.ldc = c.d;
+      a.C = b.C = product == 2 ? dw_up : dw_gate;
     }
-    for (int up = 0; up < 2; ++up) {   // dW_gate, dW_up [f][d] = sum_r dg_r (x) x_r, sum_r du_r (x) x_r
-      WgradArgs a = base;
-      a.A = sh ? gu_shared : epd_gu; a.lda = sh ? c.S * 2 * c.f : 2 * c.f; a.a_col0 = up ? c.f : 0;
-      a.a_group_cols = sh ? 2 * c.f : 0; a.M = c.f;
-      a.B = sh ? x : sfd_x; a.ldb = c.d; a.b_rows = sh ? nullptr : plan->epd_sfd_row; a.N = c.d;
-      a.C = up ? dw_up : dw_gate; a.c_mat_stride = mat; a.ldc = c.d;
-      if (sh) set_row_split(c, a, ws, ws_bytes);
-      rc = launch_wgrad(c, a, s);
-      if (rc) return rc;
-    }
+    a.c_mat_stride = b.c_mat_stride = mat;
+    if (c.S > 0) set_row_split(c, b, ws, ws_bytes);
+    rc = launch_wgrad_pair(c, a, c.S > 0 ? &b : nullptr, s);
+    if (rc) return rc;
   }
   return OCCULT_OK;
 }
