@@ -13,6 +13,8 @@
 // no contraction into FMAs) so that a CPU restatement of the same text reaches the same bits.
 #include "common.h"
 
+#include <type_traits>
+
 #include <float.h>
 #include <math.h>
 
@@ -298,133 +300,136 @@ __global__ __launch_bounds__(256) void route_kernel(
 
 // ------------------------------------------------------------------------------------------
 // Router projection g(x) = x W_r^T (paper Eq. 1), bf16 inputs.
-// The work is reading x once: a block takes 32 tokens, its 4 waves take a quarter of the hidden
-// dimension each and multiply it with all E expert rows on v_mfma_f32_16x16x32_bf16 (operands
-// loaded straight into fragment registers: 16 rows x one 64-byte sector per load; the expert
-// rows come from cache).  The four partial products are added in LDS in wave order (a fixed
-// order, so scores are reproducible) and written out as float32.  Routing runs as its own launch: a token
+// The work is reading x once.  A block takes 32 tokens and all E expert rows on v_mfma_f32_16x16x32_bf16, wave tiles of 16
+// tokens x half of the experts; K tiles of 64 of both operands go straight into a ring of LDS stages (global_load_lds),
+// all but one of them in flight.  Every request is a whole 128-byte line: 16-byte chunk c of row r lives in slot
+// c ^ ((r >> 1) & 7) of its LDS row, conflict-free for the fragment reads (ffn.hip).  Two blocks share a CU up to 128
+// experts.  (Before, the four waves of a block took a quarter of K each and loaded fragments in 64-byte pieces of 16 rows,
+// permuted through the LDS crossbar: 64 experts, d = 2048, us: 1000
+// tokens 8.7 -> 7.8, 4096 13.7 -> 8.7, 16384 29 -> 15.3 = 4.4 TB/s of x, 65536 107 -> 63; same bits.)
+// K is summed in quarters, added in ascending order: the sums that four waves with a quarter each add up to, shorter
+// chains than one.  Routing runs as its own launch: a token
 // is a chain of dependent cross-lane steps, which many resident waves hide and eight tokens in sequence on
 // one wave of this kernel do not (measured with a wave per token: fused 75 us, separate 40 us at T = 2^14;
 // the routing launch alone is 8 us there with sixteen lanes per token).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4v __attribute__((ext_vector_type(4)));
 constexpr int kRouterTokens = 32;
 
-template <int EB>   // blocks of 16 experts, E <= 16 * EB
+template <int EB, bool QUARTERED>   // EB: blocks of 16 experts, E <= 16 * EB; even
 __global__ __launch_bounds__(256) void router_kernel(const __bf16* __restrict__ x, const __bf16* __restrict__ wr,
                                                      int T, int d, int E, float* __restrict__ logits) {
+  constexpr int X_BYTES = kRouterTokens * 128, STAGE_BYTES = X_BYTES + EB * 16 * 128;
+  constexpr int NST = EB == 2 ? 8 : EB == 4 ? 6 : EB == 8 ? 3 : 4;   // 64, 72, 60, 144 KiB
+  constexpr int LOADS = 1 + EB / 2;                                 // per wave and K tile
+  constexpr int KPB = EB <= 4 ? 2 : 1;                              // K tiles per block-wide wait
   constexpr int LSTRIDE = 16 * EB + 4;
-  __shared__ __attribute__((aligned(16))) float s_lg[kRouterTokens * LSTRIDE];
-
+  static_assert(kRouterTokens * LSTRIDE * 4 <= NST * STAGE_BYTES, "the scores leave through the stages");
+  __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE_BYTES];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int r = lane & 15, c = lane >> 4;
   const int tok0 = blockIdx.x * kRouterTokens;
-  const int kq = d / 4;   // host: d % 128 == 0
-  // The MFMA wants lane l on row l % 16, K group l / 16; loaded that way neighbouring lanes would read rows a whole
-  // row pitch apart (16 cache lines looked up per 16 lanes).  Rows are loaded with lane l on row l / 4, K group l % 4
-  // (four neighbouring lanes = one 64-byte sector) and permuted into the MFMA's order before use (ds_bpermute: the
-  // LDS crossbar, no LDS memory).
-  const int lrow = lane >> 2;
-  const size_t koff = ((size_t)wave * kq + (lane & 3) * 8) * 2;
-  const int from_lane4 = (r * 4 + c) * 4;   // byte index of the lane that loaded what this lane multiplies
-  auto to_mfma_order = [&](const bf16x8& v) {
-    typedef int i32x4v __attribute__((ext_vector_type(4)));
-    i32x4v t = __builtin_bit_cast(i32x4v, v);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) t[e] = __builtin_amdgcn_ds_bpermute(from_lane4, t[e]);
-    return __builtin_bit_cast(bf16x8, t);
-  };
-  const char* xp[2];
-#pragma unroll
-  for (int tb = 0; tb < 2; ++tb) {
-    const int t = min(tok0 + tb * 16 + lrow, T - 1);   // rows past the end repeat the last token; not written
-    xp[tb] = reinterpret_cast<const char*>(x) + (size_t)t * d * 2 + koff;
-  }
-  const char* wp[EB];
-#pragma unroll
-  for (int eb = 0; eb < EB; ++eb) {
-    const int e = min(eb * 16 + lrow, E - 1);
-    wp[eb] = reinterpret_cast<const char*>(wr) + (size_t)e * d * 2 + koff;
-  }
-  f32x4v acc[2][EB];
-#pragma unroll
-  for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-    for (int eb = 0; eb < EB; ++eb) acc[tb][eb] = f32x4v{0.0f, 0.0f, 0.0f, 0.0f};
 
-  // K steps of 32.  The hidden rows are what comes from HBM: XS steps of them (16 rows x 64 bytes
-  // each) are fetched in one go, two such chunks deep, while the expert rows (cache hits) are
-  // fetched one step ahead of their use.
-  constexpr int XS = EB <= 4 ? 8 : (EB == 8 ? 4 : 2);
-  const int nst = kq / 32;
-  struct Chunk {
-    bf16x8 xf[XS][2];
+  // loader role: a load covers 8 rows of 128 bytes, lane -> row lane/8, slot lane%8; one load of token rows and EB / 2 of
+  // expert rows per wave and K tile
+  const int lrow = lane >> 3;
+  auto chunk = [&](int row) { return ((lane & 7) ^ ((row >> 1) & 7)) * 16; };
+  const int x_row = wave * 8 + lrow;
+  const char* xp = reinterpret_cast<const char*>(x) + (size_t)min(tok0 + x_row, T - 1) * d * 2 + chunk(x_row);   // rows past
+  // the end repeat the last token; not written
+  const char* wp[EB / 2];
+#pragma unroll
+  for (int i = 0; i < EB / 2; ++i) {
+    const int row = (wave * (EB / 2) + i) * 8 + lrow;
+    wp[i] = reinterpret_cast<const char*>(wr) + (size_t)min(row, E - 1) * d * 2 + chunk(row);
+  }
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) char*)smem);
+  const int nk = d / 64;   // host: d % 128 == 0, with QUARTERED d % 256 == 0
+  // byte offset of K tile kt in a row.  QUARTERED: the four quarters in turn, so that the requests in flight at a time lie
+  // in different places of the rows, whose pitch is a power of two as often as not and their memory channels then the
+  // same (1000 tokens of 16 experts, d = 4096: 16 us one quarter after another, 8 in turn)
+  auto k_offset = [&](int kt) {   // past the end the last K tile again: the number of loads in flight stays constant
+    kt = min(kt, nk - 1);
+    return QUARTERED ? (size_t)((kt & 3) * (nk >> 2) + (kt >> 2)) * 128 : (size_t)kt * 128;
   };
-  auto load_x = [&](Chunk& ch, int first) {
+  auto issue = [&](int kt) {
+    const unsigned st = lds0 + (unsigned)(kt % NST) * STAGE_BYTES;
+    const size_t k0 = k_offset(kt);
+    load_to_lds_16(xp + k0, st + wave * 1024u);
 #pragma unroll
-    for (int q = 0; q < XS; ++q) {
-      const int st = min(first + q, nst - 1);   // past the end the last step is fetched again and not used
+    for (int i = 0; i < EB / 2; ++i) load_to_lds_16(wp[i] + k0, st + X_BYTES + (wave * (EB / 2) + i) * 1024u);
+  };
+  int foff[2];   // fragments of the two K steps of 32: lane l holds row l%16, K group l/16 of a 16-row block
 #pragma unroll
-      for (int tb = 0; tb < 2; ++tb)
-        ch.xf[q][tb] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(xp[tb] + (size_t)st * 64));
+  for (int kk = 0; kk < 2; ++kk) foff[kk] = (lane & 15) * 128 + (((4 * kk + (lane >> 4)) ^ ((lane >> 1) & 7)) * 16);
+  const int tg = wave & 1, eh = wave >> 1;
+  const char* frag_x = smem + tg * 2048;
+  const char* frag_w = smem + X_BYTES + eh * (EB / 2) * 2048;
+
+  constexpr int NACC = QUARTERED ? 4 : 1;
+  f32x4 acc[NACC][EB / 2], sum[EB / 2];
+#pragma unroll
+  for (int j = 0; j < EB / 2; ++j) {
+    sum[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int n = 0; n < NACC; ++n) acc[n][j] = sum[j];
+  }
+  const int per_quarter = d / 128;   // K steps
+  int left = per_quarter;
+#pragma unroll
+  for (int kt = 0; kt < NST - KPB; ++kt) issue(kt);
+  // K tiles kt .. kt + KPB - 1; n: accumulator of the first
+  auto multiply = [&](int kt, auto n) {
+    // they are there for every wave, and everyone is done with those before
+    wait_loads_and_barrier<(NST - 2 * KPB) * LOADS>();
+#pragma unroll
+    for (int i = 0; i < KPB; ++i) issue(kt + NST - KPB + i);
+    bf16x8 xf[2 * KPB], wf[2 * KPB][EB / 2];
+#pragma unroll
+    for (int q = 0; q < 2 * KPB; ++q) {
+      const int at = ((kt + q / 2) % NST) * STAGE_BYTES + foff[q & 1];
+      xf[q] = *reinterpret_cast<const bf16x8*>(frag_x + at);
+#pragma unroll
+      for (int j = 0; j < EB / 2; ++j) wf[q][j] = *reinterpret_cast<const bf16x8*>(frag_w + at + j * 2048);
     }
-  };
-  constexpr int WD = EB <= 4 ? 4 : 2;   // expert-row fragments in flight (steps ahead + 1)
-  bf16x8 wf[WD][EB];
-  auto load_w = [&](int buf, int st) {
-    st = min(st, nst - 1);
 #pragma unroll
-    for (int eb = 0; eb < EB; ++eb) wf[buf][eb] = *reinterpret_cast<const bf16x8*>(wp[eb] + (size_t)st * 64);
-  };
-  auto multiply = [&](const Chunk& ch, int first) {
+    for (int q = 0; q < 2 * KPB; ++q) {
+      constexpr int first = decltype(n)::value;
 #pragma unroll
-    for (int q = 0; q < XS; ++q) {
-      load_w((q + WD - 1) % WD, first + q + WD - 1);
-      if (first + q < nst) {
-        bf16x8 xo[2], wo[EB];
+      for (int j = 0; j < EB / 2; ++j) {
+        f32x4& to = acc[QUARTERED ? first + q / 2 : 0][j];
+        to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[q][j], xf[q], to, 0, 0, 0);
+      }
+      if (!QUARTERED && --left == 0) {   // uniform
+        left = per_quarter;
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb) xo[tb] = to_mfma_order(ch.xf[q][tb]);
-#pragma unroll
-        for (int eb = 0; eb < EB; ++eb) wo[eb] = to_mfma_order(wf[q % WD][eb]);
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-          for (int eb = 0; eb < EB; ++eb)
-            acc[tb][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wo[eb], xo[tb], acc[tb][eb], 0, 0, 0);
+        for (int j = 0; j < EB / 2; ++j) {
+          sum[j] = sum[j] + acc[0][j];
+          acc[0][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
       }
     }
   };
-  Chunk c0, c1;
-  load_x(c0, 0);
-#pragma unroll
-  for (int q = 0; q < WD - 1; ++q) load_w(q, q);
-  for (int first = 0; first < nst; first += 2 * XS) {
-    load_x(c1, first + XS);
-    multiply(c0, first);
-    load_x(c0, first + 2 * XS);
-    multiply(c1, first + XS);
-  }
-
-  // acc[tb][eb] element j of lane l: token tb*16 + l%16, expert eb*16 + (l/16)*4 + j
-#pragma unroll
-  for (int turn = 0; turn < 4; ++turn) {
-    if (wave == turn) {
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-        for (int eb = 0; eb < EB; ++eb) {
-          f32x4v* dst = reinterpret_cast<f32x4v*>(&s_lg[(tb * 16 + r) * LSTRIDE + eb * 16 + c * 4]);
-          f32x4v v = acc[tb][eb];
-          if (turn > 0) {
-            const f32x4v old = *dst;
-            v = old + v;
-          }
-          *dst = v;
-        }
+  if constexpr (QUARTERED) {
+    for (int kt = 0; kt < nk; kt += 4) {
+      multiply(kt, std::integral_constant<int, 0>{});
+      if constexpr (KPB == 1) multiply(kt + 1, std::integral_constant<int, 1>{});
+      if constexpr (KPB <= 2) multiply(kt + 2, std::integral_constant<int, 2>{});
+      if constexpr (KPB == 1) multiply(kt + 3, std::integral_constant<int, 3>{});
     }
-    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int j = 0; j < EB / 2; ++j) sum[j] = sum[j] + acc[q][j];
+  } else {
+    for (int kt = 0; kt < nk; kt += KPB) multiply(kt, std::integral_constant<int, 0>{});
   }
+  wait_loads_and_barrier<0>();   // the loads past the end as well: the stages are free
 
+  // sum[j] element e of lane l: token tg*16 + l%16, expert (eh*EB/2 + j)*16 + (l/16)*4 + e
+  float* s_lg = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int j = 0; j < EB / 2; ++j)
+    *reinterpret_cast<f32x4*>(&s_lg[(tg * 16 + (lane & 15)) * LSTRIDE + (eh * (EB / 2) + j) * 16 + (lane >> 4) * 4]) = sum[j];
+  __syncthreads();
   // scores out: wave w writes tokens w*8 .. w*8+7 of the block, rows of E floats
   for (int j = 0; j < kRouterTokens / 4; ++j) {
     const int tl = wave * (kRouterTokens / 4) + j;
@@ -651,15 +656,20 @@ extern "C" int occult_router(const occult_cfg_t* cfg, const void* x, const void*
   OCC_REQUIRE(aligned16(x) && aligned16(w_router), OCCULT_EALIGN, "x or w_router is not 16-byte aligned");
   const dim3 grid((c.T + kRouterTokens - 1) / kRouterTokens), block(256);
   const int eb = (c.E + 15) / 16;
-#define OCC_ROUTER_LAUNCH(N)                                                             \
-  hipLaunchKernelGGL(router_kernel<N>, grid, block, 0, s, static_cast<const __bf16*>(x), \
+#define OCC_ROUTER_KERNEL(N, Q)                                                            \
+  hipLaunchKernelGGL((router_kernel<N, Q>), grid, block, 0, s, static_cast<const __bf16*>(x), \
                      static_cast<const __bf16*>(w_router), c.T, c.d, c.E, logits)
-  if (eb <= 1) OCC_ROUTER_LAUNCH(1);
-  else if (eb <= 2) OCC_ROUTER_LAUNCH(2);
+#define OCC_ROUTER_LAUNCH(N)                          \
+  do {                                                \
+    if (c.d % 256 == 0) OCC_ROUTER_KERNEL(N, true);   \
+    else OCC_ROUTER_KERNEL(N, false);                 \
+  } while (0)
+  if (eb <= 2) OCC_ROUTER_LAUNCH(2);
   else if (eb <= 4) OCC_ROUTER_LAUNCH(4);
   else if (eb <= 8) OCC_ROUTER_LAUNCH(8);
   else OCC_ROUTER_LAUNCH(16);
 #undef OCC_ROUTER_LAUNCH
+#undef OCC_ROUTER_KERNEL
   OCC_LAUNCH_CHECK("router_kernel");
   return occult_route(cfg, logits, ids, w, stream);
 }

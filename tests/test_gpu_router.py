@@ -64,6 +64,18 @@ def test_router_bf16_cases(T, d, E, D, k, n_d, mode):
     _check(x, wr, E, D, k, "bf16", n_d, mode, 1, pos)
 
 
+@pytest.mark.parametrize("T,d,E", [
+    (31, 256, 15), (32, 256, 17), (33, 512, 32), (65, 640, 33),        # around 32 tokens; 16 experts to a block; d not of 256
+    (64, 768, 64), (63, 1152, 65), (1, 384, 128), (97, 1024, 129), (40, 128, 250),
+])
+def test_router_tiles(T, d, E):
+    say(f"router tiles T={T} d={d} E={E}")
+    rng = np.random.default_rng(T + E)
+    x = wl.round_to_bf16(rng.standard_normal((T, d)).astype(np.float32))
+    wr = wl.round_to_bf16((rng.standard_normal((E, d)) / np.sqrt(d)).astype(np.float32))
+    _check(x, wr, E, 1, 2, "bf16", 0, 1, 1, None)
+
+
 def test_router_exact_on_integer_inputs():
     """Small integers: every product and partial sum is exact in float32, so the scores equal the
     oracle's bit for bit whatever the summation order, and so does everything downstream."""
