@@ -1,10 +1,9 @@
 // occult_coactivation: E x E expert co-activation counts (paper Preliminary, the co-activation
 // graph C) and occult_placement_greedy: Algorithm 1 of Sec. 3.2 on the host.
 //
-// Counting: every token contributes k*k increments.  A block keeps a private E x E int32 tile in
-// LDS (64 KiB at E = 128), counts its grid-stride share of tokens there with LDS atomics, and
-// flushes the non-zero entries with global integer atomics.  Integer adds commute, so the
-// result does not depend on scheduling.  E > 128 counts straight into global memory.
+// Counting: every token contributes k*k increments.  Up to 128 experts a block counts its grid-stride share of tokens
+// as a product of bytes and flushes the non-zero entries of its sums with global integer atomics.  Integer adds
+// commute, so the result does not depend on scheduling.  E > 128 counts straight into global memory.
 #include "common.h"
 
 #include <algorithm>
@@ -12,7 +11,9 @@
 
 namespace occult {
 
-constexpr int kCoactThreads = 256;
+constexpr int kCoactThreads = 512;
+constexpr int kCoactMaxBlocks = 64, kCoactSingleTokens = 1024;   // (one block up to 4096 tokens: 8.2 us at 4000 against 6.3)
+constexpr int kCoactGlobalThreads = 256;
 constexpr int kCoactLdsMaxE = 128;
 
 __global__ void fill_i32(int32_t* __restrict__ p, size_t n, int32_t v) {
@@ -20,41 +21,72 @@ __global__ void fill_i32(int32_t* __restrict__ p, size_t n, int32_t v) {
     p[i] = v;
 }
 
-// OVERWRITE: the launch is a single block that owns the whole result: its LDS tile is stored, not added, and C
-// needs no clearing beforehand.
-template <bool OVERWRITE>
+// Counting is a product of bytes: with M[t][e] = how often token t names expert e, C = M^T M, exactly in integers.  A wave
+// takes 64 tokens at a time, adds ones into its own [expert][token] bytes in LDS (k LDS atomics per token; counting pairs
+// there takes k (k + 1) / 2, and those were what the kernel spent its time on) and multiplies the 16-expert blocks on and above
+// the diagonal with v_mfma_i32_16x16x64_i8, both operands from the same fragments.  The waves' sums meet in LDS, the
+// flush mirrors them.
+// (us with the clearing launch, 64 experts, k = 8: 128 tokens 7.4 -> 3.6, 1000 10.5 -> 4.7 (no clearing), 16384 11.2 -> 6.4, 65536
+// 15.8 -> 7.6.  8 waves to a block and at most 64 blocks: with 4 waves and 128 blocks 8.2 and 9.8.)
+// OVERWRITE: the launch is a single block that owns the whole result, which is stored, not added, and needs no clearing.
+template <int NB, bool OVERWRITE>   // blocks of 16 experts, E <= 16 * NB
 __global__ __launch_bounds__(kCoactThreads) void coact_lds_kernel(const int32_t* __restrict__ ids, int T,
                                                                   int k, int E, int32_t* __restrict__ C) {
-  extern __shared__ int s_c[];   // [E*E]
-  for (int i = threadIdx.x; i < E * E; i += kCoactThreads) s_c[i] = 0;
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  constexpr int WAVES = kCoactThreads / 64, ROW = 80;   // 80-byte rows: the 16 rows of a fragment read hit all 64 banks
+  constexpr int EP = 16 * NB;
+  __shared__ __attribute__((aligned(16))) char s_m[WAVES][EP * ROW];
+  __shared__ int s_c[EP * EP];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = threadIdx.x; i < EP * EP; i += kCoactThreads) s_c[i] = 0;
   __syncthreads();
-  // C is symmetric: only the cells on and above the diagonal are counted in LDS (the LDS atomics are what this kernel
-  // spends its time on), the flush mirrors them.  A pair of slots naming the same expert adds 2 to its diagonal cell,
-  // as the two ordered pairs would.
-  for (int t = blockIdx.x * kCoactThreads + threadIdx.x; t < T; t += gridDim.x * kCoactThreads) {
-    const int32_t* row = ids + (size_t)t * k;
-    for (int a = 0; a < k; ++a) {
-      const int ea = row[a];
-      atomicAdd(&s_c[ea * E + ea], 1);
-      for (int b = a + 1; b < k; ++b) {
-        const int eb = row[b];
-        const int lo = min(ea, eb), hi = max(ea, eb);
-        atomicAdd(&s_c[lo * E + hi], lo == hi ? 2 : 1);
-      }
+  char* m = s_m[wave];
+  i32x4 acc[NB * (NB + 1) / 2];
+#pragma unroll
+  for (int i = 0; i < NB * (NB + 1) / 2; ++i) acc[i] = i32x4{0, 0, 0, 0};
+  const int n_chunks = (T + 63) / 64;
+  for (int chunk = blockIdx.x * WAVES + wave; chunk < n_chunks; chunk += gridDim.x * WAVES) {
+#pragma unroll
+    for (int i = 0; i < EP * ROW / 1024; ++i) *reinterpret_cast<i32x4*>(m + (i * 64 + lane) * 16) = i32x4{0, 0, 0, 0};
+    if constexpr (EP * ROW % 1024 != 0) {
+      if (lane < EP * ROW % 1024 / 16) *reinterpret_cast<i32x4*>(m + (EP * ROW / 1024 * 64 + lane) * 16) = i32x4{0, 0, 0, 0};
     }
+    const int t = chunk * 64 + lane;
+    if (t < T) {
+      const int32_t* row = ids + (size_t)t * k;
+      for (int s = 0; s < k; ++s)
+        atomicAdd(reinterpret_cast<int*>(m + row[s] * ROW + (lane & ~3)), 1 << ((lane & 3) * 8));   // (k <= 32: no carry)
+    }
+    i32x4 f[NB];   // lane l: expert l % 16 of its block, tokens (l / 16) * 16 .. +15
+#pragma unroll
+    for (int b = 0; b < NB; ++b) f[b] = *reinterpret_cast<const i32x4*>(m + (b * 16 + (lane & 15)) * ROW + (lane >> 4) * 16);
+    int n = 0;
+#pragma unroll
+    for (int a = 0; a < NB; ++a)
+#pragma unroll
+      for (int b = a; b < NB; ++b, ++n) acc[n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[a], f[b], acc[n], 0, 0, 0);
   }
+  // element i of lane l of block (a, b): experts a*16 + (l/16)*4 + i and b*16 + l%16
+  int n = 0;
+#pragma unroll
+  for (int a = 0; a < NB; ++a)
+#pragma unroll
+    for (int b = a; b < NB; ++b, ++n)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        atomicAdd(&s_c[(a * 16 + (lane >> 4) * 4 + i) * EP + b * 16 + (lane & 15)], acc[n][i]);
   __syncthreads();
   for (int i = threadIdx.x; i < E * E; i += kCoactThreads) {
     const int r = i / E, c = i - r * E;
-    const int v = r <= c ? s_c[i] : s_c[c * E + r];
+    const int v = (r >> 4) <= (c >> 4) ? s_c[r * EP + c] : s_c[c * EP + r];
     if (OVERWRITE) C[i] = v;
     else if (v) atomicAdd(&C[i], v);
   }
 }
 
-__global__ __launch_bounds__(kCoactThreads) void coact_global_kernel(const int32_t* __restrict__ ids, int T,
+__global__ __launch_bounds__(kCoactGlobalThreads) void coact_global_kernel(const int32_t* __restrict__ ids, int T,
                                                                      int k, int E, int32_t* __restrict__ C) {
-  for (int t = blockIdx.x * kCoactThreads + threadIdx.x; t < T; t += gridDim.x * kCoactThreads) {
+  for (int t = blockIdx.x * kCoactGlobalThreads + threadIdx.x; t < T; t += gridDim.x * kCoactGlobalThreads) {
     const int32_t* row = ids + (size_t)t * k;
     for (int a = 0; a < k; ++a) {
       const int ea = row[a];
@@ -77,24 +109,29 @@ extern "C" int occult_coactivation(const occult_cfg_t* cfg, const int32_t* ids, 
   hipStream_t s = static_cast<hipStream_t>(stream);
   const size_t n = (size_t)c.E * c.E;
   int blocks = (c.T + kCoactThreads - 1) / kCoactThreads;
-  if (blocks > 512) blocks = 512;
-  const bool single = !accumulate && blocks == 1 && c.E <= kCoactLdsMaxE;   // decode steps: one launch, no clearing
+  if (blocks > kCoactMaxBlocks) blocks = kCoactMaxBlocks;
+  const bool lds = c.E <= kCoactLdsMaxE;
+  const bool single = !accumulate && c.T <= kCoactSingleTokens && lds;   // one launch, no clearing
   if (!accumulate && !single) {
     hipLaunchKernelGGL(fill_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, C, n, 0);
     OCC_LAUNCH_CHECK("fill_i32");
   }
-  if (c.T == 0) return OCCULT_OK;
-  if (single) {
-    hipLaunchKernelGGL(coact_lds_kernel<true>, dim3(1), dim3(kCoactThreads), n * sizeof(int), s, ids, c.T, c.k, c.E, C);
-    OCC_LAUNCH_CHECK("coact_lds_kernel");
-  } else if (c.E <= kCoactLdsMaxE) {
-    hipLaunchKernelGGL(coact_lds_kernel<false>, dim3(blocks), dim3(kCoactThreads), n * sizeof(int), s, ids, c.T, c.k,
-                       c.E, C);
-    OCC_LAUNCH_CHECK("coact_lds_kernel");
-  } else {
-    hipLaunchKernelGGL(coact_global_kernel, dim3(blocks), dim3(kCoactThreads), 0, s, ids, c.T, c.k, c.E, C);
-    OCC_LAUNCH_CHECK("coact_global_kernel");
-  }
+  if (c.T == 0 && !single) return OCCULT_OK;
+  if (single) blocks = 1;
+#define OCC_COACT(NB)                                                                                                 \
+  do {                                                                                                                \
+    if (single) hipLaunchKernelGGL((coact_lds_kernel<NB, true>), dim3(1), dim3(kCoactThreads), 0, s, ids, c.T, c.k, c.E, C); \
+    else hipLaunchKernelGGL((coact_lds_kernel<NB, false>), dim3(blocks), dim3(kCoactThreads), 0, s, ids, c.T, c.k, c.E, C);   \
+  } while (0)
+  if (!lds) {
+    blocks = (c.T + kCoactGlobalThreads - 1) / kCoactGlobalThreads;
+    hipLaunchKernelGGL(coact_global_kernel, dim3(blocks < 512 ? blocks : 512), dim3(kCoactGlobalThreads), 0, s, ids, c.T, c.k, c.E, C);
+  } else if (c.E <= 16) OCC_COACT(1);
+  else if (c.E <= 32) OCC_COACT(2);
+  else if (c.E <= 64) OCC_COACT(4);
+  else OCC_COACT(8);
+#undef OCC_COACT
+  OCC_LAUNCH_CHECK("coact_kernel");
   return OCCULT_OK;
 }
 

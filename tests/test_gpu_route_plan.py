@@ -228,6 +228,27 @@ def test_coactivation_counts(E, k, T):
     assert np.array_equal(C.cpu().numpy(), 2 * C_ref)
 
 
+@pytest.mark.parametrize("E", [1, 15, 17, 33, 64, 65, 128])
+@pytest.mark.parametrize("T,k", [(1, 1), (63, 32), (65, 3), (1024, 5), (1025, 2), (40000, 4)])
+def test_coactivation_of_any_ids(E, T, k):
+    """Ids as a caller may give them, the same expert named several times by a token: the counts of ordered pairs of slots."""
+    if k > E:
+        return
+    say(f"coactivation of any ids E={E} T={T} k={k}")
+    dev = require_gpu()
+    ids = torch.from_numpy(np.random.default_rng(E + T).integers(0, min(E, 40), (T, k)).astype(np.int32))
+    if T > 1:
+        ids[T // 2] = E - 1   # k times the same
+    M = torch.zeros((T, E), dtype=torch.float64).scatter_add_(1, ids.long(), torch.ones((T, k), dtype=torch.float64))
+    want = (M.T @ M).to(torch.int32)
+    C = torch.full((E, E), 7, dtype=torch.int32, device=dev)
+    cfg = B.make_cfg(T, 64, 64, E, 0, k, 1, "bf16")
+    B.occult_coactivation(cfg, ids.to(dev), C, False)
+    assert torch.equal(C.cpu(), want)
+    B.occult_coactivation(cfg, ids.to(dev), C, True)
+    assert torch.equal(C.cpu(), 2 * want)
+
+
 # ---- expert-similarity-based pruning (prune_mode 3) -------------------------------------------
 
 SIM_CASES = [
