@@ -453,16 +453,19 @@ __global__ __launch_bounds__(256) void router_f32_kernel(const float* __restrict
 }
 
 // Gram matrix of router scores, H^T H in float64, on v_mfma_f64_16x16x4_f64.  A block takes a slice of tokens and a
-// 64 x 64 tile of the matrix, its wave w the tile's rows w*16 .. +15; four tokens per step go straight from the scores
-// into the operands (a lane holds one score of token lane / 16, converted to double), and the tile is added to the
-// result with double atomics, begun at another row in every block.  Tiles below the diagonal are written by the block
-// of their mirror image.  What bounds it is the chain of 64-cycle products of a block and, with more blocks, the
-// atomics on the few thousand cells.  16384 tokens of 64 experts: 160 us with 16 blocks of scalar double arithmetic,
-// 15 us now; 65536 tokens 169 -> 35 us (clearing launch included).
-constexpr int kGramTokens = 64;   // tokens per block, about (the slices are evened out to multiples of 16)
-__global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ logits, int T, int E,
-                                                   int tokens_per_block, double* __restrict__ gram) {
+// 64 x 64 tile of the matrix; wave w takes the tile's rows (w & 3)*16 .. +15 over part w / 4 of the slice.
+// Four tokens per step go straight from the scores into the operands (a lane holds one score of token lane / 16, converted
+// to double), the parts are added in LDS in ascending order and the tile is added to the result with double atomics.  Tiles
+// below the diagonal are written by the block of their mirror image.  What bounds it is the chain of 64-cycle products of a
+// wave and the atomics on the few thousand cells, a set of them per block: hence several parts to a block.
+// (us with the clearing launch, 64 experts: 1000 tokens 10.9 -> 7.6, 16384 21 -> 15, 65536 29 -> 21; 128 experts 37 -> 25 and 89 ->
+// 51 at the latter two.  Before: a wave per 64 tokens and row block, its loads behind a branch each.)
+constexpr int kGramBlocks = 256, kGramMany = 12288;   // see occult_similarity_gram
+template <int PARTS>   // of a slice
+__global__ __launch_bounds__(256 * PARTS) void gram_kernel(const float* __restrict__ logits, int T, int E,
+                                                                int tokens_per_block, double* __restrict__ gram) {
   typedef double f64x4 __attribute__((ext_vector_type(4)));
+  __shared__ double s_part[PARTS][64 * 64];
   // blockIdx.y -> tile (ti, tj), ti <= tj
   int ti = 0, tj = blockIdx.y;
   const int tiles = (E + 63) / 64;
@@ -471,59 +474,65 @@ __global__ __launch_bounds__(256) void gram_kernel(const float* __restrict__ log
     ++ti;
   }
   tj += ti;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3, part = threadIdx.x >> 8;
   const int tk = lane >> 4, c = lane & 15;
   const int ea = ti * 64 + wave * 16 + c;
-  const int t_begin = blockIdx.x * tokens_per_block, t_end = min(T, t_begin + tokens_per_block);
+  const int per_part = tokens_per_block / PARTS;   // host: a multiple of 4 * PARTS
+  const int t_begin = blockIdx.x * tokens_per_block + part * per_part, t_end = min(T, t_begin + per_part);
   f64x4 acc[4] = {};
-  constexpr int UN = 8;   // steps of 4 tokens requested together, one such set ahead of the products
+  constexpr int UN = 4;   // steps of 4 tokens requested together, one such set ahead of the products
   struct Set {
     float a[UN], b[UN][4];
   };
+  // past the slice or the experts the last score of each is read, and zero taken for it: no branch around a load
+  const int ca = min(ea, E - 1);
+  int cb[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) cb[j] = min(tj * 64 + j * 16 + c, E - 1);
   auto load = [&](Set& s, int t0) {
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      const int t = t0 + 4 * u + tk;
-      const float* row = logits + (size_t)t * E;
-      s.a[u] = (t < t_end && ea < E) ? row[ea] : 0.0f;
+      const float* row = logits + (size_t)min(t0 + 4 * u + tk, T - 1) * E;
+      s.a[u] = row[ca];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int eb = tj * 64 + j * 16 + c;
-        s.b[u][j] = (t < t_end && eb < E) ? row[eb] : 0.0f;
-      }
+      for (int j = 0; j < 4; ++j) s.b[u][j] = row[cb[j]];
     }
   };
-  auto multiply = [&](const Set& s) {
+  auto multiply = [&](const Set& s, int t0) {
 #pragma unroll
-    for (int u = 0; u < UN; ++u)
+    for (int u = 0; u < UN; ++u) {
+      const bool live = t0 + 4 * u + tk < t_end;   // (experts past E: their cells are not written)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)s.a[u], (double)s.b[u][j], acc[j], 0, 0, 0);
+        acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(live ? (double)s.a[u] : 0.0, live ? (double)s.b[u][j] : 0.0, acc[j], 0, 0, 0);
+    }
   };
   Set s0, s1;
   load(s0, t_begin);
-  for (int t0 = t_begin; t0 < t_end; t0 += 8 * UN) {   // past the end a set is all zeros
+  for (int t0 = t_begin; t0 < t_end; t0 += 8 * UN) {
     load(s1, t0 + 4 * UN);
-    multiply(s0);
+    multiply(s0, t0);
     load(s0, t0 + 8 * UN);
-    multiply(s1);
+    multiply(s1, t0 + 4 * UN);
   }
   // acc[j] element i of lane l: tile row wave*16 + i*4 + l/16, column j*16 + l%16
 #pragma unroll
-  for (int jj = 0; jj < 4; ++jj) {
-    const int j = (jj + blockIdx.x) & 3;
-    f64x4 v = acc[0];
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int m = 1; m < 4; ++m)
-      if (j == m) v = acc[m];
+    for (int i = 0; i < 4; ++i) s_part[part][(wave * 16 + i * 4 + tk) * 64 + j * 16 + c] = acc[j][i];
+  __syncthreads();
+  for (int n = threadIdx.x; n < 64 * 64; n += 256 * PARTS) {
+    // blocks begin at different cells; off the diagonal a wave takes 8 x 8 cells, so that neither they nor their mirror
+    // images lie in 64 different rows (128 experts, 16384 tokens: 78 us with whole rows, 25 so)
+    int at = (n + blockIdx.x * 256) & (64 * 64 - 1);
+    if (ti != tj) at = (at >> 9) * 512 + (at >> 3 & 7) * 64 + (at >> 6 & 7) * 8 + (at & 7);
+    const int ei = ti * 64 + (at >> 6), ej = tj * 64 + (at & 63);
+    if (ei >= E || ej >= E) continue;
+    double v = s_part[0][at];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int ei = ti * 64 + wave * 16 + i * 4 + tk, ej = tj * 64 + j * 16 + c;
-      if (ei < E && ej < E) {
-        atomicAdd(&gram[(size_t)ei * E + ej], v[i]);
-        if (ti != tj) atomicAdd(&gram[(size_t)ej * E + ei], v[i]);
-      }
-    }
+    for (int q = 1; q < PARTS; ++q) v += s_part[q][at];
+    atomicAdd(&gram[(size_t)ei * E + ej], v);
+    if (ti != tj) atomicAdd(&gram[(size_t)ej * E + ei], v);
   }
 }
 
@@ -551,16 +560,20 @@ extern "C" int occult_similarity_gram(const occult_cfg_t* cfg, const float* logi
   if (c.T == 0) return OCCULT_OK;
   OCC_REQUIRE(logits, OCCULT_ENULLPTR, "logits is NULL");
   const int tiles = (c.E + 63) / 64;
-  // as many slices as give a block 64 tokens, within 512 blocks: beyond that the atomics on the tile's cells cost more than
-  // the shorter chains save (measured, us: T = 16384, E = 64: 28 / 18 / 15 / 15 with 64 / 128 / 256 / 512 slices; E = 200,
-  // ten tiles: 66 / 70 / 93 / 147 with 32 / 64 / 128 / 256)
+  // As many slices as give a wave 32 tokens, within 256 blocks over all tiles (65536 tokens of 64 experts: 29 us with 128, 21
+  // with 256).  Two parts to a block while the blocks are few, four beyond, for a quarter of the atomics per product (64
+  // experts, two / four: 4000 tokens 8.0 / 10.2, 8192 9.5 / 10.8, 16384 17.9 / 14.8)
   const int n_tiles = tiles * (tiles + 1) / 2;
-  int slices = (c.T + kGramTokens - 1) / kGramTokens;
-  const int most = 512 / n_tiles > 32 ? 512 / n_tiles : 32;
+  const bool many = c.T * (long long)n_tiles >= kGramMany;
+  const int parts = many ? 4 : 2, tokens = 32 * parts, step = 4 * parts;
+  int slices = (c.T + tokens - 1) / tokens;
+  const int most = kGramBlocks / n_tiles > 32 ? kGramBlocks / n_tiles : 32;
   if (slices > most) slices = most;
-  const int per = ((c.T + slices - 1) / slices + 15) / 16 * 16;
+  const int per = ((c.T + slices - 1) / slices + step - 1) / step * step;
   slices = (c.T + per - 1) / per;
-  hipLaunchKernelGGL(gram_kernel, dim3(slices, n_tiles), dim3(256), 0, s, logits, c.T, c.E, per, gram);
+  const dim3 grid(slices, n_tiles);
+  if (many) hipLaunchKernelGGL(gram_kernel<4>, grid, dim3(1024), 0, s, logits, c.T, c.E, per, gram);
+  else hipLaunchKernelGGL(gram_kernel<2>, grid, dim3(512), 0, s, logits, c.T, c.E, per, gram);
   OCC_LAUNCH_CHECK("gram_kernel");
   return OCCULT_OK;
 }
