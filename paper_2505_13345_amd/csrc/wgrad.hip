@@ -371,7 +371,11 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs first, const W
 // Groups of a few hundred rows and fewer (small micro-batches): a product is then little more than writing its f32 outputs,
 // and one block per CU does that with nothing beside it: a tile's first loads, its few steps and its stores stand in a row.
 // Here a block takes 128 x 128 outputs (wave tile 64 x 64 = 4 x 4 MFMA tiles) and three blocks share a CU, one storing while the
-// others load and multiply.  More operand bytes and LDS reads per product than the 256 x 256 tiles: @RULE@
+// others load and multiply.  More operand bytes and LDS reads per product than the 256 x 256 tiles: from a few hundred rows
+// those win (launch_wgrad_pair).  Bound by the stores: 1000 tokens of 64 + 2 experts, d = 2048, f = 1408, 694 -> 399 us for
+// the three products = 5.7 TB/s of their 2.28 GB.  How the outputs are stored is half of that: in 64-byte pieces 800 us, marked
+// as not to be kept 583 (the operands stay in L2, but with few rows 420 -> 690: half lines leave the cache), as whole rows
+// through LDS and not to be kept 399 (388 with few rows).
 // The routed experts' groups (`first`) and the shared experts' (`second`, uniform groups over all tokens) are one launch:
 // alone the shared ones are a few dozen blocks.  They come first in the grid, since each of them runs longest.
 // Staging, swizzle, transposing reads and the order of the sums are those of the kernel above; a step's fragments are read
