@@ -42,7 +42,8 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
 // The same for 2-byte elements with 16-byte global accesses on both sides (R % 8 == 0, C % 8 == 0):
 // a thread loads 8 columns of two rows, scatters them into the LDS tile as [column][row], and reads
 // back 8 consecutive rows of one column as one vector.  LDS rows are padded to 72 elements (144
-// bytes), which keeps the vectors 16-byte aligned.
+// bytes), which keeps the vectors 16-byte aligned.  Bound by memory; the copies are larger than any cache and stored as
+// not to be kept (66 experts, d = 2048, f = 1408: 441 -> 410 us for the three matrices, 5.6 TB/s; 64 of f = 1024: 348 -> 306).
 __global__ __launch_bounds__(256) void transpose16_kernel(const unsigned short* __restrict__ in,
                                                           unsigned short* __restrict__ out, int R, int C,
                                                           long long out_mat_stride, int out_ld, int col0) {
@@ -70,7 +71,8 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const unsigned short* 
   for (int h = 0; h < 2; ++h) {
     const int c = c0 + q + 32 * h, r = r0 + v * 8;
     if (r < R && c < C)
-      *reinterpret_cast<u32x4*>(dst + (size_t)c * out_ld + col0 + r) = *reinterpret_cast<const u32x4*>(&tile[q + 32 * h][v * 8]);
+      __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(&tile[q + 32 * h][v * 8]),
+                                  reinterpret_cast<u32x4*>(dst + (size_t)c * out_ld + col0 + r));
   }
 }
 
