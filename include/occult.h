@@ -178,7 +178,7 @@ int occult_plan(const occult_cfg_t* cfg, const int32_t* ids, const float* w,
                 const occult_plan_t* plan, void* ws, size_t ws_bytes, occult_stream_t stream);
 
 /* occult_plan for callers that cannot allocate device memory or bring a workspace (code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc): the same three kernels with their
+ * capture, tight serving loops, harnesses that forbid hipMalloc): the same kernels with their
  * scratch (the per-block counts) in a device array built into the library, OCCULT_PLAN_STATIC_MAX_BYTES
  * on every GPU the library runs on, held until the process ends.  Allocates nothing and calls no
  * allocating routine; the array's device address is looked up on the first call on each device (make
@@ -268,6 +268,31 @@ int occult_expert_ffn_packed(const occult_cfg_t* cfg, const occult_plan_t* plan,
  * epd_y [N_epd][d], sfd_y [>= N_sfd][d], y [T][d]; device ptrs.  Order-fixed, no atomics. */
 int occult_combine(const occult_cfg_t* cfg, const occult_plan_t* plan, const void* epd_y,
                    void* sfd_y, const void* y_shared, void* y, occult_stream_t stream);
+
+/* The whole forward pass in one call: occult_route, occult_plan, occult_dispatch, the expert computation
+ * (occult_expert_ffn_train when epd_gu is given, else occult_expert_ffn_packed with `packed`, which may be
+ * NULL) and occult_combine, in this order on `stream`, with the arguments of those calls and the same
+ * results; the first that fails ends it with its code.  For small batches, where the host's work
+ * between six calls is as long as the GPU's. */
+typedef struct occult_forward_buffers {
+  int32_t* ids;       /* [T][k]          */
+  float*   w;         /* [T][k]          */
+  void*    plan_ws;   /* occult_plan     */
+  void*    sfd_x;     /* occult_dispatch */
+  void*    epd_h;     /* occult_expert_ffn ... */
+  void*    epd_y;
+  void*    h_shared;
+  void*    y_shared;
+  void*    ffn_ws;
+  void*    epd_gu;    /* occult_expert_ffn_train, or NULL */
+  void*    gu_shared;
+  void*    sfd_y;     /* occult_combine  */
+  void*    y;
+  size_t   plan_ws_bytes, ffn_ws_bytes;
+} occult_forward_buffers_t;
+int occult_forward(const occult_cfg_t* cfg, const occult_plan_t* plan, const float* logits, const void* x,
+                   const occult_weights_t* weights, const void* packed,
+                   const occult_forward_buffers_t* buffers, occult_stream_t stream);
 
 /* occult_combine with the paper's own first stage, an atomic merge (paper Sec. 3.1, first-stage merging: thread
  * blocks that write the same SFD rows add with atomic_add into a float32 output tensor that is converted to the

@@ -27,7 +27,7 @@ EXPORTS = [
     "occult_transpose_weights", "occult_expert_ffn_backward", "occult_expert_ffn_backward_weights",
     "occult_pack_weights_bytes", "occult_pack_weights", "occult_expert_ffn_packed", "occult_expert_ffn_train",
     "occult_collaboration_stats", "occult_plan_static", "occult_combine_atomic",
-    "occult_expert_ffn_backward_weights_ws_bytes", "occult_expert_ffn_backward_weights_ws",
+    "occult_expert_ffn_backward_weights_ws_bytes", "occult_expert_ffn_backward_weights_ws", "occult_forward",
 ]
 
 
@@ -53,6 +53,12 @@ class occult_plan_t(Structure):
 
 class occult_weights_t(Structure):
     _fields_ = [("w_gate", c_void_p), ("w_up", c_void_p), ("w_down", c_void_p)]
+
+
+class occult_forward_buffers_t(Structure):
+    _fields_ = [(n, c_void_p) for n in ("ids", "w", "plan_ws", "sfd_x", "epd_h", "epd_y", "h_shared", "y_shared", "ffn_ws",
+                                        "epd_gu", "gu_shared", "sfd_y", "y")] + [
+                ("plan_ws_bytes", c_size_t), ("ffn_ws_bytes", c_size_t)]
 
 
 class occult_stats_t(Structure):
@@ -99,6 +105,8 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.occult_expert_ffn_packed.argtypes = [cfgp, planp, c_void_p, c_void_p, POINTER(occult_weights_t), c_void_p,
                                              c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_size_t, c_void_p]
     lib.occult_combine.argtypes = [cfgp, planp, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p]
+    lib.occult_forward.argtypes = [cfgp, planp, c_void_p, c_void_p, POINTER(occult_weights_t), c_void_p,
+                                   POINTER(occult_forward_buffers_t), c_void_p]
     lib.occult_combine_atomic.argtypes = [cfgp, planp, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_int, c_void_p]
     lib.occult_combine_backward.argtypes = [cfgp, planp, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p,
                                             c_void_p]
@@ -281,6 +289,17 @@ def occult_expert_ffn_packed(cfg, plan, sfd_x, x, w_gate, w_up, w_down, packed, 
 def occult_combine(cfg, plan, epd_y, sfd_y, y_shared, y, stream=None) -> None:
     _check(load_library().occult_combine(ctypes.byref(cfg), ctypes.byref(plan), _ptr(epd_y), _ptr(sfd_y),
                                          _ptr(y_shared), _ptr(y), _stream(stream)))
+
+
+def occult_forward(cfg, plan, logits, x, w_gate, w_up, w_down, packed, ids, w, plan_ws, sfd_x, epd_h, epd_y, h_shared, y_shared,
+                   ffn_ws, epd_gu, gu_shared, sfd_y, y, stream=None) -> None:
+    wts = occult_weights_t(_ptr(w_gate), _ptr(w_up), _ptr(w_down))
+    buf = occult_forward_buffers_t(_ptr(ids), _ptr(w), _ptr(plan_ws), _ptr(sfd_x), _ptr(epd_h), _ptr(epd_y), _ptr(h_shared),
+                                   _ptr(y_shared), _ptr(ffn_ws), _ptr(epd_gu), _ptr(gu_shared), _ptr(sfd_y), _ptr(y),
+                                   plan_ws.numel() * plan_ws.element_size(),
+                                   0 if ffn_ws is None else ffn_ws.numel() * ffn_ws.element_size())
+    _check(load_library().occult_forward(ctypes.byref(cfg), ctypes.byref(plan), _ptr(logits), _ptr(x), ctypes.byref(wts),
+                                         _ptr(packed), ctypes.byref(buf), _stream(stream)))
 
 
 def occult_combine_atomic(cfg, plan, epd_y, sfd_acc, sfd_y, y_shared, y, mode=0, stream=None) -> None:

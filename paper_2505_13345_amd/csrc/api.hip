@@ -146,3 +146,24 @@ extern "C" int occult_plan_stats(const occult_cfg_t* cfg, const occult_plan_t* p
   out_host->c_t = cfg->T > 0 ? (double)h[0] / (double)cfg->T : 0.0;
   return OCCULT_OK;
 }
+
+// The steps below check their own arguments; what only this call can see is checked here.
+extern "C" int occult_forward(const occult_cfg_t* cfg, const occult_plan_t* plan, const float* logits, const void* x,
+                              const occult_weights_t* weights, const void* packed,
+                              const occult_forward_buffers_t* buffers, occult_stream_t stream) {
+  int rc = check_cfg(cfg);
+  if (rc) return rc;
+  OCC_REQUIRE(buffers, OCCULT_ENULLPTR, "buffers is NULL");
+  const occult_forward_buffers_t& b = *buffers;
+  rc = occult_route(cfg, logits, b.ids, b.w, stream);
+  if (rc == OCCULT_OK) rc = occult_plan(cfg, b.ids, b.w, plan, b.plan_ws, b.plan_ws_bytes, stream);
+  if (rc == OCCULT_OK) rc = occult_dispatch(cfg, plan, x, b.sfd_x, stream);
+  if (rc != OCCULT_OK) return rc;
+  if (b.epd_gu != nullptr)
+    rc = occult_expert_ffn_train(cfg, plan, b.sfd_x, x, weights, b.epd_h, b.epd_y, b.h_shared, b.y_shared, b.epd_gu, b.gu_shared,
+                                 b.ffn_ws, b.ffn_ws_bytes, stream);
+  else
+    rc = occult_expert_ffn_packed(cfg, plan, b.sfd_x, x, weights, packed, b.epd_h, b.epd_y, b.h_shared, b.y_shared, b.ffn_ws,
+                                  b.ffn_ws_bytes, stream);
+  return rc ? rc : occult_combine(cfg, plan, b.epd_y, b.sfd_y, b.y_shared, b.y, stream);
+}

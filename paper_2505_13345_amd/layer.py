@@ -115,15 +115,18 @@ class OccultLayer:
 
     def expert_ffn_train(self, x, w_gate, w_up, w_down):
         """expert_ffn() that also keeps the pre-activations [g | u] for expert_ffn_backward(gu_saved=True)."""
-        s = self.shape
-        T, k, f, S = s["T"], s["k"], s["f"], s["S"]
         self._hidden(x, "x")
         self._weights(w_gate, w_up, w_down)
-        epd_gu = self._buf("epd_gu", (T * k, 2 * f), self.tdtype)
-        gu_sh = self._buf("gu_shared", (T, S * 2 * f), self.tdtype) if S > 0 else None
+        epd_gu, gu_sh = self._pre_activations()
         B.occult_expert_ffn_train(self.cfg, self.plan, self.sfd_x, x, w_gate, w_up, w_down, self.epd_h, self.epd_y,
                                   self.h_shared, self.y_shared, epd_gu, gu_sh, self.ffn_ws)
         self.gu_saved = True
+
+    def _pre_activations(self):
+        s = self.shape
+        T, k, f, S = s["T"], s["k"], s["f"], s["S"]
+        return (self._buf("epd_gu", (T * k, 2 * f), self.tdtype),
+                self._buf("gu_shared", (T, S * 2 * f), self.tdtype) if S > 0 else None)
 
     def combine(self, epd_y=None):
         self._hidden(epd_y, "epd_y", self.shape["T"] * self.shape["k"])
@@ -140,14 +143,20 @@ class OccultLayer:
                                 self.y_shared, self.y, mode)
 
     def forward(self, logits, x, w_gate, w_up, w_down, train=False):
-        self.route(logits)
-        self.make_plan()
-        self.dispatch(x)
+        """route(), make_plan(), dispatch(), expert_ffn() or expert_ffn_train(), combine() in one call into the library."""
+        s = self.shape
+        B.expect(logits, "logits", torch.float32, s["T"] * s["E"])
+        self._hidden(x, "x")
+        self._weights(w_gate, w_up, w_down)
+        packed = epd_gu = gu_sh = None
         if train:
-            self.expert_ffn_train(x, w_gate, w_up, w_down)
+            epd_gu, gu_sh = self._pre_activations()
         else:
-            self.expert_ffn(x, w_gate, w_up, w_down)
-        self.combine()
+            packed = getattr(self, "packed", None)
+        B.occult_forward(self.cfg, self.plan, logits, x, w_gate, w_up, w_down, packed, self.ids, self.w, self.ws, self.sfd_x,
+                         self.epd_h, self.epd_y, self.h_shared, self.y_shared, self.ffn_ws, epd_gu, gu_sh, self.sfd_y, self.y)
+        if train:
+            self.gu_saved = True
         return self.y
 
     # ---- backward of the data movement (buffers allocated on first use) -----------------------

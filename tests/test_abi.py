@@ -197,3 +197,11 @@ def test_plan_static_refuses_layers_beyond_its_built_in_scratch(lib):
     assert "4194304" in B.occult_last_error()
     ok = B.make_cfg(T=4096, d=64, f=64, E=64, S=0, k=8, D=8, dtype="bf16")
     assert lib.occult_plan_static(ctypes.byref(ok), None, None, None, None) == -4     # NULL plan, still on the host
+
+
+def test_forward_validates_on_the_host(lib):
+    cfg = B.make_cfg(T=64, d=128, f=256, E=16, S=0, k=4, D=4, dtype="bf16")
+    buf = B.occult_forward_buffers_t()
+    assert lib.occult_forward(None, None, None, None, None, None, ctypes.byref(buf), None) < 0
+    for buffers in (None, ctypes.byref(buf)):
+        assert lib.occult_forward(ctypes.byref(cfg), None, None, None, None, None, buffers, None) == -4

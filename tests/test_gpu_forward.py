@@ -1,0 +1,55 @@
+"""layer.forward() is one call into the library: the same bits in every buffer as the five steps called one by one, for
+each kind of expert computation, and the errors of the steps."""
+import pytest
+import torch
+
+from inputs import workloads as wl
+from paper_2505_13345_amd import binding as B
+from paper_2505_13345_amd.layer import OccultLayer
+from tests.helpers import require_gpu, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,S,dtype,n_d,packed,train", [
+    (1, 2, "bf16", 0, True, False), (40, 0, "bf16", 2, True, False), (300, 2, "bf16", 0, False, False),
+    (300, 2, "bf16", 0, True, True), (33, 0, "bf16", 0, False, True), (50, 1, "f32", 0, False, False),
+    (50, 1, "f32", 0, False, True), (0, 1, "bf16", 0, False, False),
+])
+def test_forward_is_its_steps(T, S, dtype, n_d, packed, train):
+    say(f"forward T={T} S={S} {dtype} n_d={n_d} packed={packed} train={train}")
+    dev = require_gpu()
+    d, f, E, k, D = 192, 128, 16, 4, 4
+    wk = wl.make_workload(wl.LayerShape("fwd", T=max(T, 1), d=d, f=f, E=E, S=S, k=k, D=D, dtype=dtype, components=4), seed=T)
+    x, lg = to_dev(wk.x, dtype, dev)[:T], torch.from_numpy(wk.logits).to(dev)[:T]
+    w = [to_dev(a, dtype, dev) for a in (wk.w_gate, wk.w_up, wk.w_down)]
+    one, steps = (OccultLayer(T, d, f, E, S, k, D, dtype, n_d=n_d) for _ in range(2))
+    for layer in (one, steps):
+        if packed:
+            layer.pack_weights(*w)
+    y = one.forward(lg, x, *w, train=train)
+    steps.route(lg)
+    steps.make_plan()
+    steps.dispatch(x)
+    (steps.expert_ffn_train if train else steps.expert_ffn)(x, *w)
+    steps.combine()
+    torch.cuda.synchronize()
+    assert y is one.y and getattr(one, "gu_saved", False) == train
+    for name in ("plan_mem", "ids", "w", "sfd_x", "sfd_y", "y", "epd_h", "epd_y", "h_shared", "y_shared", "epd_gu", "gu_shared"):
+        a, b = getattr(one, name, None), getattr(steps, name, None)
+        assert (a is None) == (b is None), name
+        assert a is None or torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+def test_forward_refuses_what_its_steps_refuse():
+    say("forward's errors")
+    dev = require_gpu()
+    layer = OccultLayer(8, 64, 64, 8, 0, 2, 2, "bf16")
+    w = [torch.zeros((8, 64, 64), dtype=torch.bfloat16, device=dev) for _ in range(3)]
+    lg, x = torch.zeros((8, 8), device=dev), torch.zeros((8, 64), dtype=torch.bfloat16, device=dev)
+    for bad in ((lg[:4], x, *w), (lg, x.float(), *w), (lg, x, w[0][:7], w[1], w[2]), (lg, x, *w[:2], w[2].transpose(1, 2)),
+                (lg.cpu(), x, *w)):
+        with pytest.raises(ValueError):
+            layer.forward(*bad)
+    with pytest.raises(B.OccultError):   # no buffers for the experts
+        OccultLayer(8, 64, 64, 8, 0, 2, 2, "bf16", with_ffn=False).forward(lg, x, *w)
