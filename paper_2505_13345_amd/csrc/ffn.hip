@@ -1382,8 +1382,10 @@ int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total
 //  - with shared experts one launch does both sets' work, which alone would leave most CUs idle (500 tokens: 118 of
 //    357 us) or add a last round of its own: up to about 800 rows per group (656 rows: 1116 us against 1057; 768: equal),
 //    and down to any number where shares_launch() says so;
-//  - without, from 24 rows (32: 226 us against 220; 20: 215 against 218) up to about 240 (237: 339 against 323 us; 256
-//    and 287: slower, 325: faster, by how the tiles happen to divide over the CUs).
+//  - without, from 24 rows (32: 226 us against 220; 20: 215 against 218) up to 500: half as high, the tiles of a launch divide
+//    more evenly over the CUs (of 37 batches of 240 - 550 rows per group, 512 - 2048 x 384 - 1408, 0.94 of the time of the
+//    256-row tiles on average, gate/up and down projection together; 31 faster, at worst 1.03, at 450 rows and more.  256
+//    rows: 0.87 - 0.97 by how the rows fall; 750: 1.08).
 static bool fits_tile128(const GemmArgs& a) {
   return a.K >= 192 && a.K % 64 == 0 && a.N % 64 == 0 && (long long)a.a_rows_total * a.lda * 2 < (1ll << 32) &&
          weights_below_4gib(a);
@@ -1391,7 +1393,7 @@ static bool fits_tile128(const GemmArgs& a) {
 static bool uses_tile128(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, int total_rows) {
   if (c.dtype != OCCULT_BF16 || a.grp_offset == nullptr || !fits_tile128(a) || (b != nullptr && !fits_tile128(*b)))
     return false;
-  const long long lo = b != nullptr ? 0 : 24, hi = b != nullptr ? 800 : 240;
+  const long long lo = b != nullptr ? 0 : 24, hi = b != nullptr ? 800 : 500;
   return total_rows >= lo * a.ngroups && total_rows < hi * a.ngroups;
 }
 

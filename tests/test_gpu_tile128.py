@@ -187,3 +187,24 @@ def test_shared_down_projection_has_the_bits_of_the_split_product():
         out.append((_bits(layer.h_shared), _bits(layer.y_shared)))
     assert np.array_equal(out[0][0], out[1][0])
     assert np.array_equal(out[0][1], out[1][1]), np.mean(out[0][1] != out[1][1])
+
+
+@pytest.mark.parametrize("train", [False, True])
+def test_many_rows_have_the_bits_of_larger_batches(train):
+    """Without shared experts the 128-row tiles take groups below 500 rows on average and the 256-row tiles the others: the
+    stored activations, products and pre-activations of a token are the same bits on both sides of the line."""
+    d, f, E, k, T = 256, 192, 8, 2, 2000
+    say(f"rows of {T - 1} and {T} tokens E={E} k={k} train={train}")
+    dev = require_gpu()
+    wk = wl.make_workload(wl.LayerShape("many", T=T, d=d, f=f, E=E, S=0, k=k, D=2, dtype="bf16", components=4), seed=T)
+    lg, x = torch.from_numpy(wk.logits).to(dev), to_dev(wk.x, "bf16", dev)
+    w = [to_dev(a, "bf16", dev) for a in (wk.w_gate, wk.w_up, wk.w_down)]
+    part, whole = (OccultLayer(n, d, f, E, 0, k, 2, "bf16") for n in (T - 1, T))
+    part.forward(lg[:T - 1].contiguous(), x[:T - 1].contiguous(), *w, train=train)
+    whole.forward(lg, x, *w, train=train)
+    torch.cuda.synchronize()
+    at, ref = _rows_by_token_and_expert(whole), _rows_by_token_and_expert(part)
+    rows = np.array([(at[key], r) for key, r in ref.items()])
+    for name in ("epd_h", "epd_y") + (("epd_gu",) if train else ()):
+        got, want = _bits(getattr(whole, name))[rows[:, 0]], _bits(getattr(part, name))[rows[:, 1]]
+        assert np.array_equal(got, want), (name, np.mean(got != want))
