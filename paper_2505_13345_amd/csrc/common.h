@@ -75,6 +75,11 @@ __device__ __forceinline__ void load_to_lds_16(const char* base, unsigned off, u
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
                : "memory", "m0");
 }
+// the same for data that is read once (not to be kept in L2)
+__device__ __forceinline__ void load_to_lds_16_streaming(const char* base, unsigned off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base)
+               : "memory", "m0");
+}
 // 64 lanes x 4 bytes to LDS [lds, lds + 256)
 __device__ __forceinline__ void load_to_lds_4(const char* src, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(src) : "memory", "m0");

@@ -49,7 +49,8 @@ struct Tile {
 // that the weight-streaming or small-tile kernel gives the same rows.  The finished parts' sums have registers of
 // their own (one wave per SIMD: there is room) and cost one addition per accumulator and part (500 tokens of 64 + 2 experts,
 // shared down projection in parts: 312 -> 318 us; 300 of 60 + 4, gate/up in quarters as well: 305 -> 325 us).
-template <bool SWIGLU, bool SAVE, bool PARTS>
+// ONCE: the weights are requested as not to be kept (launch_tile128).
+template <bool SWIGLU, bool SAVE, bool PARTS, bool ONCE>
 __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first, const GemmArgs second) {
   static_assert(SWIGLU || !SAVE, "pre-activations exist only with the fused activation");
   static_assert(!SAVE || !PARTS, "stored pre-activations are one sum over K");
@@ -183,8 +184,11 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
   constexpr int LOADS = 12;
   // load i (0..11) of the K tile being requested, into the stage at byte st; the last one moves on to the next K tile
   auto issue = [&](unsigned st, int i) {
-    if (i < 8) load_to_lds_16((SWIGLU && (i & 2) ? ld.w_odd : ld.w_even) + ld.kb, ld.b_off[i], lds_b + st + i * 1024);
-    else load_to_lds_16(ld.a + ld.ka, ld.a_off[i - 8], lds_a + st + (i - 8) * 1024);
+    if (i < 8) {
+      const char* w = (SWIGLU && (i & 2) ? ld.w_odd : ld.w_even) + ld.kb;
+      if constexpr (ONCE) load_to_lds_16_streaming(w, ld.b_off[i], lds_b + st + i * 1024);
+      else load_to_lds_16(w, ld.b_off[i], lds_b + st + i * 1024);
+    } else load_to_lds_16(ld.a + ld.ka, ld.a_off[i - 8], lds_a + st + (i - 8) * 1024);
     if (i == LOADS - 1) {
       ld.ka += BK * 2;
       ld.kb += BK * 2;
@@ -376,6 +380,12 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
 }
 }  // namespace t128
 
+// ONCE: the weights are read past the caches' keeping where almost every expert has one row tile, so that nobody reads them
+// again, and where they are larger than the memory-side cache (256 MiB), which otherwise has some of them from the call before
+// (us without / with: 64 experts, d = 2048, f = 1408, gate/up + down, 24 rows per expert 159 + 97 / 150 + 92, 47 rows
+// 169 + 106 / 163 + 96, 71 rows 171 + 111 / 171 + 111, 125 rows of f = 1024 134 / 144; 38 rows of f = 1024, 537 MB of gate/up
+// 100 / 92, 268 MB of down 47 / 52; d = 1152, f = 704, 207 MB of gate/up 44 / 55).
+constexpr long long kOnceRows = 72, kOnceBytes = 320ll << 20;
 int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, hipStream_t s) {
   const int bn_out = swiglu ? t128::BN / 2 : t128::BN;
   const long long n_tiles = (a.N + bn_out - 1) / bn_out;
@@ -397,11 +407,18 @@ int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_
   OCC_REQUIRE(!(save && parts) && (!parts || (a.ksplit >= 1 && (b == nullptr || second.ksplit >= 1))), OCCULT_EINVAL,
               "grouped GEMM: parts of K outside the 128-row tiles' range");
   const dim3 grid((unsigned)blocks), block(256);
-  if (save) hipLaunchKernelGGL((t128::grouped_gemm_bf16<true, true, false>), grid, block, 0, s, a, second);
-  else if (swiglu && parts) hipLaunchKernelGGL((t128::grouped_gemm_bf16<true, false, true>), grid, block, 0, s, a, second);
-  else if (swiglu) hipLaunchKernelGGL((t128::grouped_gemm_bf16<true, false, false>), grid, block, 0, s, a, second);
-  else if (parts) hipLaunchKernelGGL((t128::grouped_gemm_bf16<false, false, true>), grid, block, 0, s, a, second);
-  else hipLaunchKernelGGL((t128::grouped_gemm_bf16<false, false, false>), grid, block, 0, s, a, second);
+  const bool once = total_rows < kOnceRows * a.ngroups && (long long)a.ngroups * a.N * a.K * (swiglu ? 4 : 2) > kOnceBytes;
+#define OCC_T128(SW, SAVE, PARTS)                                                                                        \
+  do {                                                                                                                   \
+    if (once) hipLaunchKernelGGL((t128::grouped_gemm_bf16<SW, SAVE, PARTS, true>), grid, block, 0, s, a, second);        \
+    else hipLaunchKernelGGL((t128::grouped_gemm_bf16<SW, SAVE, PARTS, false>), grid, block, 0, s, a, second);            \
+  } while (0)
+  if (save) OCC_T128(true, true, false);
+  else if (swiglu && parts) OCC_T128(true, false, true);
+  else if (swiglu) OCC_T128(true, false, false);
+  else if (parts) OCC_T128(false, false, true);
+  else OCC_T128(false, false, false);
+#undef OCC_T128
   OCC_LAUNCH_CHECK("grouped_gemm");
   return OCCULT_OK;
 }

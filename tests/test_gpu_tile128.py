@@ -208,3 +208,25 @@ def test_many_rows_have_the_bits_of_larger_batches(train):
     for name in ("epd_h", "epd_y") + (("epd_gu",) if train else ()):
         got, want = _bits(getattr(whole, name))[rows[:, 0]], _bits(getattr(part, name))[rows[:, 1]]
         assert np.array_equal(got, want), (name, np.mean(got != want))
+
+
+def test_weights_read_once_give_the_same_bits():
+    """Below 72 rows per expert, and with weights larger than the memory-side cache, the weights are requested as not to be
+    kept: the rows of the first 500 tokens are those that the same tokens get in a batch of 800."""
+    d, f, E, k, T, part = 2048, 1408, 64, 6, 800, 500
+    say(f"weights read once: {part} and {T} tokens E={E} d={d} f={f}")
+    dev = require_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(1)
+    rand = lambda *shape: torch.randn(shape, device=dev, generator=gen)
+    lg, x = rand(T, E), rand(T, d).bfloat16()
+    w = [(rand(E, *s) / s[1] ** 0.5).bfloat16() for s in ((f, d), (f, d), (d, f))]
+    small, whole = (OccultLayer(n, d, f, E, 0, k, 4, "bf16") for n in (part, T))
+    small.forward(lg[:part].contiguous(), x[:part].contiguous(), *w)
+    whole.forward(lg, x, *w)
+    torch.cuda.synchronize()
+    at, ref = _rows_by_token_and_expert(whole), _rows_by_token_and_expert(small)
+    rows = np.array([(at[key], r) for key, r in ref.items()])
+    for name in ("epd_h", "epd_y"):
+        got, want = _bits(getattr(whole, name))[rows[:, 0]], _bits(getattr(small, name))[rows[:, 1]]
+        assert np.array_equal(got, want), (name, np.mean(got != want))
