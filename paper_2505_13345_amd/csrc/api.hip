@@ -156,8 +156,8 @@ extern "C" int occult_forward(const occult_cfg_t* cfg, const occult_plan_t* plan
   OCC_REQUIRE(buffers, OCCULT_ENULLPTR, "buffers is NULL");
   const occult_forward_buffers_t& b = *buffers;
   rc = occult_route(cfg, logits, b.ids, b.w, stream);
-  if (rc == OCCULT_OK) rc = occult_plan(cfg, b.ids, b.w, plan, b.plan_ws, b.plan_ws_bytes, stream);
-  if (rc == OCCULT_OK) rc = occult_dispatch(cfg, plan, x, b.sfd_x, stream);
+  if (rc == OCCULT_OK)
+    rc = plan_and_dispatch(cfg, b.ids, b.w, plan, b.plan_ws, b.plan_ws_bytes, x, b.sfd_x, static_cast<hipStream_t>(stream));
   if (rc != OCCULT_OK) return rc;
   if (b.epd_gu != nullptr)
     rc = occult_expert_ffn_train(cfg, plan, b.sfd_x, x, weights, b.epd_h, b.epd_y, b.h_shared, b.y_shared, b.epd_gu, b.gu_shared,

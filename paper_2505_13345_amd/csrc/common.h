@@ -49,6 +49,10 @@ inline int merge_width(const occult_cfg_t& c) { return min_i(c.k, c.E / c.D); }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 size_t plan_workspace_bytes(const occult_cfg_t& c);
+int check_dispatch_args(const occult_cfg_t& c, const occult_plan_t* plan, const void* x, const void* sfd_x);
+// occult_plan and occult_dispatch, in one launch where the planner is one
+int plan_and_dispatch(const occult_cfg_t* cfg, const int32_t* ids, const float* w, const occult_plan_t* plan, void* ws,
+                      size_t ws_bytes, const void* x, void* sfd_x, hipStream_t s);
 
 // native 16-byte vectors (usable with the nontemporal builtins)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

@@ -75,6 +75,15 @@ __global__ __launch_bounds__(256) void dispatch_meta_kernel(const int32_t* __res
   sfd_w[(size_t)r * k + s] = w[t * k + s];
 }
 
+int check_dispatch_args(const occult_cfg_t& c, const occult_plan_t* plan, const void* x, const void* sfd_x) {
+  OCC_REQUIRE(plan && plan->tok_sfd_row, OCCULT_ENULLPTR, "plan or plan->tok_sfd_row is NULL");
+  OCC_REQUIRE(x && sfd_x, OCCULT_ENULLPTR, "x or sfd_x is NULL");
+  const size_t row_bytes = (size_t)c.d * elem_size(c);
+  OCC_REQUIRE(row_bytes % 16 == 0, OCCULT_EALIGN, "row of %zu bytes is not a multiple of 16", row_bytes);
+  OCC_REQUIRE(aligned16(x) && aligned16(sfd_x), OCCULT_EALIGN, "x or sfd_x is not 16-byte aligned");
+  return OCCULT_OK;
+}
+
 }  // namespace occult
 
 using namespace occult;
@@ -101,11 +110,9 @@ extern "C" int occult_dispatch(const occult_cfg_t* cfg, const occult_plan_t* pla
   if (rc) return rc;
   const occult_cfg_t c = *cfg;
   if (c.T == 0) return OCCULT_OK;
-  OCC_REQUIRE(plan && plan->tok_sfd_row, OCCULT_ENULLPTR, "plan or plan->tok_sfd_row is NULL");
-  OCC_REQUIRE(x && sfd_x, OCCULT_ENULLPTR, "x or sfd_x is NULL");
+  rc = check_dispatch_args(c, plan, x, sfd_x);
+  if (rc) return rc;
   const size_t row_bytes = (size_t)c.d * elem_size(c);
-  OCC_REQUIRE(row_bytes % 16 == 0, OCCULT_EALIGN, "row of %zu bytes is not a multiple of 16", row_bytes);
-  OCC_REQUIRE(aligned16(x) && aligned16(sfd_x), OCCULT_EALIGN, "x or sfd_x is not 16-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int row_vecs = (int)(row_bytes / 16);
   const int vpl = (row_vecs + 63) / 64;

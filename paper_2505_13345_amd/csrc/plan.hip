@@ -251,11 +251,20 @@ __device__ __forceinline__ void scan_columns(const int* s_total, int* s_start, c
   }
 }
 
-// FT: tokens of a workgroup
-template <int KMAX, Bases FROM, int FT>
+// The rows that plan_fill copies on the side: occult_dispatch's work for batches whose planner is one launch.
+struct Rows {
+  const u32x4* x;
+  u32x4* sfd_x;
+  int vecs;   // 16-byte vectors of a row, <= 64 * VPL
+};
+
+// FT: tokens of a workgroup.  VPL > 0: a wave has a token, whose row it requests at the start and copies to the SFD rows once
+// it knows them (plan and dispatch in two launches, both chains of latencies: see launch_plan_dispatch).
+template <int KMAX, Bases FROM, int FT, int VPL>
 __global__ __launch_bounds__(kTPB) void plan_fill(const int32_t* __restrict__ ids, const float* __restrict__ w, int T, int k,
                                                   int E, int D, int G, int M1, int nblk, const int32_t* __restrict__ expert_pos,
-                                                  const int32_t* __restrict__ blk, const occult_plan_t p) {
+                                                  const int32_t* __restrict__ blk, const occult_plan_t p, const Rows rows) {
+  static_assert(VPL == 0 || FT == kTPB / 64, "a token per wave");
   constexpr int PER_BLOCK = kTPB / FT;   // workgroups that share a block of 256 tokens
   __shared__ int s_pos[OCCULT_MAX_E];
   __shared__ TokenSet s_set[kMaxCols];
@@ -266,6 +275,16 @@ __global__ __launch_bounds__(kTPB) void plan_fill(const int32_t* __restrict__ id
   const int tl = threadIdx.x, C = D + E;
   const int block = blockIdx.x / PER_BLOCK, first = (blockIdx.x % PER_BLOCK) * FT;   // first: my first bit
   const int t0 = block * kTPB;
+  const int lane = tl & 63, wave = tl >> 6;
+  u32x4 v[VPL > 0 ? VPL : 1];   // VPL: the row of token t0 + first + wave
+  if constexpr (VPL > 0) {
+    if (t0 + first + wave < T) {
+      const u32x4* src = rows.x + (size_t)(t0 + first + wave) * rows.vecs;
+#pragma unroll
+      for (int i = 0; i < VPL; ++i)
+        if (lane + 64 * i < rows.vecs) v[i] = __builtin_nontemporal_load(src + lane + 64 * i);
+    }
+  }
   for (int e = tl; e < E; e += kTPB) s_pos[e] = expert_pos ? expert_pos[e] : e;
   for (int i = tl; i < C * 4; i += kTPB) (&s_set[0][0])[i] = 0ull;
   for (int c = tl; c < C; c += kTPB) {
@@ -323,13 +342,17 @@ __global__ __launch_bounds__(kTPB) void plan_fill(const int32_t* __restrict__ id
 
   // (token, device): the token's row of destinations, the row's token, the unused end of the row's merge list
   const int mine = min(FT, T - t0 - first);   // may be <= 0
-  for (int i = tl; i < mine * D; i += kTPB) {
-    const int m = i / D, j = i - m * D;
+  const int entries = VPL > 0 ? mine * 64 : mine * D;   // VPL: lane j of a wave for device j of its token (D <= 64)
+  int my_row = -1;                                      // VPL: of this lane's device
+  for (int i = tl; i < entries; i += kTPB) {
+    const int m = VPL > 0 ? wave : i / D, j = VPL > 0 ? lane : i - m * D;
+    if (VPL > 0 && j >= D) continue;
     int filled = 0;
 #pragma unroll
     for (int s = 0; s < KMAX; ++s) filled += s_slot[m][s] >> 16 == j ? 1 : 0;   // (unused slots: -1 >> 16 = -1)
     const int r = filled > 0 ? s_base[j] + bits_below(s_set[j], first + m) : -1;
-    p.tok_sfd_row[(size_t)(t0 + first) * D + i] = r;
+    p.tok_sfd_row[(size_t)(t0 + first + m) * D + j] = r;
+    my_row = r;
     if (filled > 0) {
       p.sfd_token[r] = t0 + first + m;
       for (int e = filled; e < M1; ++e) p.sfd_epd_rows[(size_t)r * M1 + e] = -1;
@@ -352,9 +375,30 @@ __global__ __launch_bounds__(kTPB) void plan_fill(const int32_t* __restrict__ id
     p.epd_gate[q] = w[(size_t)(t0 + first) * k + i];
     p.sfd_epd_rows[(size_t)r * M1 + before] = q;
   }
+  if constexpr (VPL > 0) {
+    if (wave >= mine) return;
+    for (int j = 0; j < D; ++j) {
+      const int r = __builtin_amdgcn_readlane(my_row, j);
+      if (r < 0) continue;
+      u32x4* dst = rows.sfd_x + (size_t)r * rows.vecs;
+#pragma unroll
+      for (int i = 0; i < VPL; ++i)
+        if (lane + 64 * i < rows.vecs) __builtin_nontemporal_store(v[i], dst + lane + 64 * i);
+    }
+  }
 }
 
 size_t plan_workspace_bytes(const occult_cfg_t& c);
+
+#define OCC_PLAN_KMAX(LAUNCH)       \
+  do {                              \
+    if (c.k <= 8) LAUNCH(8);        \
+    else if (c.k <= 16) LAUNCH(16); \
+    else LAUNCH(32);                \
+  } while (0)
+#define OCC_PLAN_FILL(KM, FROM, FT, VPL)                                                                                 \
+  hipLaunchKernelGGL((plan_fill<KM, FROM, FT, VPL>), dim3((unsigned)(c.T > 0 ? ((long long)c.T + FT - 1) / FT : 1)),     \
+                     dim3(kTPB), 0, s, ids, w, c.T, c.k, c.E, c.D, G, merge_width(c), nblk, c.expert_pos, blk, p, rows)
 
 // The launches of the planner on a block-count buffer `blk` of >= nblk * (D + E) ints.  plan_count writes every entry of the
 // first nblk rows before they are read: the buffer need not be cleared.
@@ -362,13 +406,8 @@ static int launch_plan(const occult_cfg_t& c, const int32_t* ids, const float* w
                        int32_t* blk, hipStream_t s) {
   const int G = c.E / c.D;
   const int nblk = (c.T + kTPB - 1) / kTPB;
+  const Rows rows{};
   const Bases from = c.T <= kSingleMaxTokens ? Bases::kIds : nblk <= kCountsMaxBlocks ? Bases::kCounts : Bases::kScanned;
-#define OCC_PLAN_KMAX(LAUNCH) \
-  do {                        \
-    if (c.k <= 8) LAUNCH(8);  \
-    else if (c.k <= 16) LAUNCH(16); \
-    else LAUNCH(32);          \
-  } while (0)
   if (from != Bases::kIds) {
 #define OCC_PLAN_COUNT(KM)                                                                               \
   hipLaunchKernelGGL(plan_count<KM>, dim3(nblk), dim3(kTPB), 0, s, ids, c.T, c.k, c.E, c.D, G, c.expert_pos, \
@@ -383,13 +422,10 @@ static int launch_plan(const occult_cfg_t& c, const int32_t* ids, const float* w
                        p.counters);
     OCC_LAUNCH_CHECK("plan_scan");
   }
-#define OCC_PLAN_FILL(KM, FROM, FT)                                                                                      \
-  hipLaunchKernelGGL((plan_fill<KM, FROM, FT>), dim3((unsigned)(c.T > 0 ? ((long long)c.T + FT - 1) / FT : 1)), dim3(kTPB), 0, \
-                     s, ids, w, c.T, c.k, c.E, c.D, G, merge_width(c), nblk, c.expert_pos, blk, p)
-#define OCC_PLAN_FILL_IDS(KM) OCC_PLAN_FILL(KM, Bases::kIds, 32)   // T = 0: one workgroup writes zero counts and offsets
-#define OCC_PLAN_FILL_COUNTS(KM) OCC_PLAN_FILL(KM, Bases::kCounts, 32)
-#define OCC_PLAN_FILL_MANY(KM) OCC_PLAN_FILL(KM, Bases::kCounts, kTPB)
-#define OCC_PLAN_FILL_SCANNED(KM) OCC_PLAN_FILL(KM, Bases::kScanned, kTPB)
+#define OCC_PLAN_FILL_IDS(KM) OCC_PLAN_FILL(KM, Bases::kIds, 32, 0)   // T = 0: one workgroup writes zero counts and offsets
+#define OCC_PLAN_FILL_COUNTS(KM) OCC_PLAN_FILL(KM, Bases::kCounts, 32, 0)
+#define OCC_PLAN_FILL_MANY(KM) OCC_PLAN_FILL(KM, Bases::kCounts, kTPB, 0)
+#define OCC_PLAN_FILL_SCANNED(KM) OCC_PLAN_FILL(KM, Bases::kScanned, kTPB, 0)
   if (from == Bases::kIds) OCC_PLAN_KMAX(OCC_PLAN_FILL_IDS);
   else if (from == Bases::kScanned) OCC_PLAN_KMAX(OCC_PLAN_FILL_SCANNED);
   else if (nblk <= kSmallMaxBlocks) OCC_PLAN_KMAX(OCC_PLAN_FILL_COUNTS);
@@ -398,11 +434,36 @@ static int launch_plan(const occult_cfg_t& c, const int32_t* ids, const float* w
 #undef OCC_PLAN_FILL_COUNTS
 #undef OCC_PLAN_FILL_MANY
 #undef OCC_PLAN_FILL_SCANNED
-#undef OCC_PLAN_FILL
-#undef OCC_PLAN_KMAX
   OCC_LAUNCH_CHECK("plan_fill");
   return OCCULT_OK;
 }
+
+// Planner and row copies of at most kSingleMaxTokens tokens in one launch (us per forward pass, separate / together: 1 token
+// of 60 experts 44.8 / 44.3, 8 of 64 119.8 / 118.3, 128 234.2 / 233.1, 256 246.9 / 244.1, 512 309.7 / 307.3; 256 tokens of the small
+// f32 layer 29.9 / 28.4).  Rows of more than 8 KiB do not fit a wave's registers and are copied by the other kernel.
+static int launch_plan_dispatch(const occult_cfg_t& c, const int32_t* ids, const float* w, const occult_plan_t& p,
+                                const Rows& rows, hipStream_t s) {
+  const int G = c.E / c.D;
+  const int nblk = (c.T + kTPB - 1) / kTPB;
+  const int32_t* blk = nullptr;   // (not read with kIds)
+  const int vpl = (rows.vecs + 63) / 64;
+#define OCC_PLAN_ROWS_1(KM) OCC_PLAN_FILL(KM, Bases::kIds, 4, 1)
+#define OCC_PLAN_ROWS_2(KM) OCC_PLAN_FILL(KM, Bases::kIds, 4, 2)
+#define OCC_PLAN_ROWS_4(KM) OCC_PLAN_FILL(KM, Bases::kIds, 4, 4)
+#define OCC_PLAN_ROWS_8(KM) OCC_PLAN_FILL(KM, Bases::kIds, 4, 8)
+  if (vpl <= 1) OCC_PLAN_KMAX(OCC_PLAN_ROWS_1);
+  else if (vpl <= 2) OCC_PLAN_KMAX(OCC_PLAN_ROWS_2);
+  else if (vpl <= 4) OCC_PLAN_KMAX(OCC_PLAN_ROWS_4);
+  else OCC_PLAN_KMAX(OCC_PLAN_ROWS_8);
+#undef OCC_PLAN_ROWS_1
+#undef OCC_PLAN_ROWS_2
+#undef OCC_PLAN_ROWS_4
+#undef OCC_PLAN_ROWS_8
+  OCC_LAUNCH_CHECK("plan_fill");
+  return OCCULT_OK;
+}
+#undef OCC_PLAN_FILL
+#undef OCC_PLAN_KMAX
 
 static int check_plan_args(const occult_cfg_t& c, const int32_t* ids, const float* w, const occult_plan_t* plan) {
   OCC_REQUIRE(plan, OCCULT_ENULLPTR, "plan is NULL");
@@ -446,8 +507,8 @@ static int static_scratch(int32_t** out) {
 
 using namespace occult;
 
-extern "C" int occult_plan(const occult_cfg_t* cfg, const int32_t* ids, const float* w,
-                           const occult_plan_t* plan, void* ws, size_t ws_bytes, occult_stream_t stream) {
+static int check_plan_ws_args(const occult_cfg_t* cfg, const int32_t* ids, const float* w, const occult_plan_t* plan, void* ws,
+                              size_t ws_bytes) {
   int rc = check_cfg(cfg);
   if (rc) return rc;
   const occult_cfg_t c = *cfg;
@@ -456,6 +517,31 @@ extern "C" int occult_plan(const occult_cfg_t* cfg, const int32_t* ids, const fl
   OCC_REQUIRE(ws, OCCULT_ENULLPTR, "workspace is NULL");
   OCC_REQUIRE(ws_bytes >= plan_workspace_bytes(c), OCCULT_EWORKSPACE, "workspace of %zu bytes < required %zu",
               ws_bytes, plan_workspace_bytes(c));
+  return OCCULT_OK;
+}
+
+namespace occult {
+int plan_and_dispatch(const occult_cfg_t* cfg, const int32_t* ids, const float* w, const occult_plan_t* plan, void* ws,
+                      size_t ws_bytes, const void* x, void* sfd_x, hipStream_t s) {
+  int rc = check_plan_ws_args(cfg, ids, w, plan, ws, ws_bytes);
+  if (rc) return rc;
+  const occult_cfg_t c = *cfg;
+  const size_t vecs = (size_t)c.d * elem_size(c) / 16;
+  if (c.T == 0 || c.T > kSingleMaxTokens || vecs > 64 * 8) {
+    rc = launch_plan(c, ids, w, *plan, static_cast<int32_t*>(ws), s);
+    return rc ? rc : occult_dispatch(cfg, plan, x, sfd_x, s);
+  }
+  rc = check_dispatch_args(c, plan, x, sfd_x);
+  if (rc) return rc;
+  return launch_plan_dispatch(c, ids, w, *plan, Rows{static_cast<const u32x4*>(x), static_cast<u32x4*>(sfd_x), (int)vecs}, s);
+}
+}  // namespace occult
+
+extern "C" int occult_plan(const occult_cfg_t* cfg, const int32_t* ids, const float* w,
+                           const occult_plan_t* plan, void* ws, size_t ws_bytes, occult_stream_t stream) {
+  const int rc = check_plan_ws_args(cfg, ids, w, plan, ws, ws_bytes);
+  if (rc) return rc;
+  const occult_cfg_t c = *cfg;
   return launch_plan(c, ids, w, *plan, static_cast<int32_t*>(ws), static_cast<hipStream_t>(stream));
 }
 

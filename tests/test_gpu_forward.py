@@ -53,3 +53,30 @@ def test_forward_refuses_what_its_steps_refuse():
             layer.forward(*bad)
     with pytest.raises(B.OccultError):   # no buffers for the experts
         OccultLayer(8, 64, 64, 8, 0, 2, 2, "bf16", with_ffn=False).forward(lg, x, *w)
+
+
+@pytest.mark.parametrize("T,d,E,k,D,dtype", [
+    (3, 64, 8, 2, 2, "f32"), (4, 512, 60, 4, 4, "bf16"), (5, 576, 64, 8, 64, "bf16"), (255, 2048, 64, 6, 16, "bf16"),
+    (256, 2112, 16, 12, 1, "bf16"), (257, 4096, 20, 20, 5, "bf16"), (512, 1024, 256, 32, 64, "bf16"), (513, 64, 16, 4, 4, "bf16"),
+    (7, 4160, 8, 2, 4, "bf16"),
+])
+def test_forward_of_small_batches(T, d, E, k, D, dtype):
+    """Plan and row copies in one launch: tokens around a workgroup's four, a block of 256 and the last size, rows of one
+    vector and fewer up to eight per lane and beyond, all devices, up to 32 slots; tables and rows as the separate calls'."""
+    say(f"forward T={T} d={d} E={E} k={k} D={D} {dtype}")
+    dev = require_gpu()
+    gen = torch.Generator().manual_seed(T)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.randn((T, d), generator=gen).to(dt).to(dev)
+    lg = torch.randn((T, E), generator=gen).to(dev)
+    w = [torch.randn(s, generator=gen).mul_(0.05).to(dt).to(dev) for s in ((E, 64, d), (E, 64, d), (E, d, 64))]
+    one, steps = (OccultLayer(T, d, 64, E, 0, k, D, dtype) for _ in range(2))
+    one.forward(lg, x, *w)
+    steps.route(lg)
+    steps.make_plan()
+    steps.dispatch(x)
+    steps.expert_ffn(x, *w)
+    steps.combine()
+    torch.cuda.synchronize()
+    for name in ("plan_mem", "ids", "w", "sfd_x", "y"):
+        assert torch.equal(getattr(one, name).view(torch.uint8), getattr(steps, name).view(torch.uint8)), name
