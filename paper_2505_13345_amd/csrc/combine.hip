@@ -202,6 +202,103 @@ __global__ __launch_bounds__(kCombWaves * 64) void combine_kernel(
   }
 }
 
+// The same for batches that leave most wavefronts of the chip idle: a token's columns are dealt out to the `split` (1, 2 or 4)
+// waves that its row has work for, and a wave requests DEPTH rows together.  What bounds such a batch is a token's chain of
+// memory round trips, list -> row index -> rows, two rows at a time.  The sums of a column, their order and their roundings
+// are those of combine_kernel.  (Needs lists_fit and a row within 64 * VPL * split vectors.)
+template <bool BF16, int VPL>
+__global__ __launch_bounds__(kCombWaves * 64) void combine_split_kernel(
+    const void* __restrict__ epd_y, void* __restrict__ sfd_y, const void* __restrict__ y_shared, void* __restrict__ y,
+    const int32_t* __restrict__ tok_sfd_row, const int32_t* __restrict__ sfd_epd_rows, const float* __restrict__ epd_gate,
+    int T, int D, int M1, int row_vecs, int split) {
+  using R = Row<BF16>;
+  typedef typename R::Raw Raw;
+  constexpr int NE = R::kElems, DEPTH = 8 / VPL;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int t = blockIdx.x * (kCombWaves / split) + wave / split;
+  if (t >= T) return;   // whole wave; no barrier follows
+  const int c0 = (wave & (split - 1)) * 64 * VPL + lane;
+  if (c0 - lane >= row_vecs) return;
+
+  Raw sh[VPL];
+#pragma unroll
+  for (int v = 0; v < VPL; ++v)
+    if (y_shared && c0 + 64 * v < row_vecs) sh[v] = R::load_raw(y_shared, (size_t)t, row_vecs, c0 + 64 * v);
+  // the token's lists, as in combine_kernel
+  const int rl = lane < D ? tok_sfd_row[(size_t)t * D + lane] : -1;
+  const unsigned long long present = __ballot(rl >= 0);
+  const int n_dev = __popcll(present);
+  const int ord = __popcll(present & ((1ull << lane) - 1ull));
+  int my_row = __builtin_amdgcn_ds_permute((rl >= 0 ? ord : 63) * 4, rl);
+  if (lane >= n_dev) my_row = -1;
+  const int my_o = lane / M1, m = lane - my_o * M1;
+  const int r_o = __shfl(my_row, my_o < 64 ? my_o : 0, 64);
+  const int my_q = my_o < n_dev ? sfd_epd_rows[(size_t)r_o * M1 + m] : -1;
+  const float my_g = my_q >= 0 && epd_gate ? epd_gate[my_q] : 1.0f;
+
+  unsigned long long todo = __ballot(my_q >= 0);
+  float acc[VPL][NE], part[VPL][NE];
+#pragma unroll
+  for (int v = 0; v < VPL; ++v)
+#pragma unroll
+    for (int e = 0; e < NE; ++e) acc[v][e] = part[v][e] = 0.0f;
+  while (todo != 0) {   // wave-uniform
+    Raw x[DEPTH][VPL];
+    unsigned long long ahead = todo;
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) {
+      if (ahead == 0) break;
+      const int q = __builtin_amdgcn_readlane(my_q, __ffsll((long long)ahead) - 1);
+      ahead &= ahead - 1;
+#pragma unroll
+      for (int v = 0; v < VPL; ++v)
+        if (c0 + 64 * v < row_vecs) x[i][v] = R::load_raw(epd_y, (size_t)q, row_vecs, c0 + 64 * v);
+    }
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) {
+      if (todo == 0) break;
+      const int at = __ffsll((long long)todo) - 1;
+      todo &= todo - 1;
+      const float g = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_g), at));
+      const int j = __builtin_amdgcn_readlane(my_o, at);
+      const bool last_of_device = todo == 0 || __builtin_amdgcn_readlane(my_o, todo != 0 ? __ffsll((long long)todo) - 1 : 0) != j;
+      const int r = __builtin_amdgcn_readlane(my_row, j);
+#pragma unroll
+      for (int v = 0; v < VPL; ++v) {
+        if (c0 + 64 * v >= row_vecs) continue;
+        float xe[NE];
+        R::unpack(x[i][v], xe);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) part[v][e] = fmaf(g, xe[e], part[v][e]);
+        if (last_of_device) {
+          R::store_round(sfd_y, (size_t)r, row_vecs, c0 + 64 * v, part[v]);
+#pragma unroll
+          for (int e = 0; e < NE; ++e) {
+            acc[v][e] += part[v][e];
+            part[v][e] = 0.0f;
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < VPL; ++v) {
+    if (c0 + 64 * v >= row_vecs) continue;
+    if (y_shared) {
+      float se[NE];
+      R::unpack(sh[v], se);
+#pragma unroll
+      for (int e = 0; e < NE; ++e) acc[v][e] += se[e];
+    }
+    R::store_round(y, (size_t)t, row_vecs, c0 + 64 * v, acc[v]);
+  }
+}
+
+// Where combine_split_kernel is the faster one (us per call back to back, 7.8 of them the host's; whole rows / split, d = 2048 in
+// bf16: k = 8, 17 tokens 9.3 / 7.8, 128 10.9 / 7.8, 500 12.3 / 7.9, 1000 14.7 / 13.0, 1500 18.7 / 18.7, 2048 22.8 / 25.0; k = 4, 256
+// tokens 9.4 / 8.0, 1000 11.8 / 9.2, 1500 13.8 / 12.0, 2048 15.8 / 15.6, 3000 even): beyond, there are waves enough and
+// the lists of a token would be read by four.  Decoding: 1 token 55.1 -> 52.2 us for the layer, 17 153.4 -> 148.9, 128 234.6 -> 231.4.
+constexpr int kSplitRows = 8192;
 // launches the two-stage sum; gates == NULL means unit weights
 static int launch_combine(const occult_cfg_t& c, const occult_plan_t* plan, const float* gates, const void* epd,
                           void* sfd, const void* shared, void* out, occult_stream_t stream) {
@@ -215,6 +312,23 @@ static int launch_combine(const occult_cfg_t& c, const occult_plan_t* plan, cons
   const dim3 grid((c.T + kCombWaves - 1) / kCombWaves), block(kCombWaves * 64);
   const int M1 = merge_width(c);
   const int lists_fit = min_i(c.k, c.D) * M1 <= 64 ? 1 : 0;
+  if (lists_fit && vpl <= 8 && (long long)c.T * c.k <= kSplitRows) {
+    const int split = vpl >= 3 ? 4 : vpl;
+    const dim3 sgrid(((long long)c.T * split + kCombWaves - 1) / kCombWaves);
+#define OCC_COMB_SPLIT(B, N)                                                                              \
+  hipLaunchKernelGGL((combine_split_kernel<B, N>), sgrid, block, 0, s, epd, sfd, shared, out, plan->tok_sfd_row, \
+                     plan->sfd_epd_rows, gates, c.T, c.D, M1, row_vecs, split)
+    if (c.dtype == OCCULT_BF16) {
+      if (vpl <= 4) OCC_COMB_SPLIT(true, 1);
+      else OCC_COMB_SPLIT(true, 2);
+    } else {
+      if (vpl <= 4) OCC_COMB_SPLIT(false, 1);
+      else OCC_COMB_SPLIT(false, 2);
+    }
+#undef OCC_COMB_SPLIT
+    OCC_LAUNCH_CHECK("combine_split_kernel");
+    return OCCULT_OK;
+  }
   const bool ahead = lists_fit && vpl <= 8;
 #define OCC_COMB(B, N)                                                                                     \
   do {                                                                                                     \

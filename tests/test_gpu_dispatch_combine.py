@@ -183,3 +183,37 @@ def test_dispatch_meta_bit_exact(E, D, k, T, placement):
     assert np.array_equal(sfd_ids[:n].cpu().numpy(), trace.ids_sfd)
     assert np.array_equal(sfd_w[:n].cpu().numpy(), trace.w_sfd)
     assert bool((sfd_ids[n:] == -7).all()) and bool((sfd_w[n:] == -7.0).all())   # nothing past N_sfd
+
+
+@pytest.mark.parametrize("E,D,k,T,d,dtype", [
+    (64, 8, 8, 1, 2048, "bf16"), (8, 4, 4, 300, 1536, "bf16"), (16, 2, 8, 1024, 64, "bf16"), (8, 1, 8, 50, 1024, "bf16"),
+    (64, 64, 8, 17, 4096, "bf16"), (16, 4, 4, 33, 1032, "f32"), (20, 5, 20, 40, 2048, "bf16"), (20, 5, 20, 40, 3072, "bf16"),
+])
+def test_small_batches_combine_as_large_ones(E, D, k, T, d, dtype):
+    """A token's columns dealt out to one, two or four waves, more rows than are requested together, the largest batch of that
+    path: the same bits as in a batch that holds these tokens several times and takes whole rows."""
+    say(f"combine small/large E={E} D={D} k={k} T={T} d={d} {dtype}")
+    dev = require_gpu()
+    copies = 8192 // (T * k) + 1
+    gen = torch.Generator(device=dev).manual_seed(T)
+    ids = torch.argsort(torch.rand((T, E), generator=gen, device=dev), 1)[:, :k].int().contiguous()
+    w = torch.rand((T, k), generator=gen, device=dev)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    values = torch.randn((T, E, d), generator=gen, device=dev).to(dt)
+    values[0, :, 3] = float("inf")
+    values[T - 1, :, d - 1] = float("nan")
+    shared = torch.randn((T, d), generator=gen, device=dev).to(dt)
+    out = []
+    for n in (1, copies):
+        layer = OccultLayer(T * n, d, 64, E, 1, k, D, dtype, with_ffn=False)
+        layer.make_plan(ids.repeat(n, 1), w.repeat(n, 1))
+        layer.y_shared = shared.repeat(n, 1)
+        tabs = layer.tables()
+        position = torch.repeat_interleave(torch.arange(E, device=dev), tabs["exp_count"].long())
+        epd = values[tabs["sfd_token"].long()[tabs["epd_sfd_row"].long()] % T, position]
+        layer.combine(epd)
+        rows = tabs["tok_sfd_row"][:T].long()
+        back = layer.dispatch_backward(epd, layer.y_shared)[1]
+        out.append((layer.y[:T].clone(), torch.where(rows[..., None] >= 0, layer.sfd_y[rows.clamp(min=0)], 0), back[:T].clone()))
+    for a, b in zip(*out):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
