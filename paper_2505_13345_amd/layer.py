@@ -40,6 +40,9 @@ class OccultLayer:
         self.sfd_y = torch.zeros((n_sfd_max, d), dtype=self.tdtype, device=dev)
         self.y = torch.zeros((T, d), dtype=self.tdtype, device=dev)
         self.epd_h = self.epd_y = self.h_shared = self.y_shared = self.ffn_ws = None
+        # epd_gu and gu_shared hold the pre-activations of the present plan, rows and inputs: set by expert_ffn_train(),
+        # cleared by every step that brings another plan, other rows or other outputs, and by the backward that overwrites them
+        self.gu_saved = False
         if with_ffn:
             ws_bytes = B.occult_expert_ffn_ws_bytes(self.cfg)
             if ws_bytes:
@@ -81,11 +84,13 @@ class OccultLayer:
 
     def make_plan(self, ids=None, w=None):
         self._routing(ids, w)
+        self.gu_saved = False
         B.occult_plan(self.cfg, self.ids if ids is None else ids, self.w if w is None else w,
                       self.plan, self.ws)
 
     def dispatch(self, x):
         self._hidden(x, "x")
+        self.gu_saved = False
         B.occult_dispatch(self.cfg, self.plan, x, self.sfd_x)
 
     def pack_weights(self, w_gate, w_up, w_down):
@@ -102,6 +107,7 @@ class OccultLayer:
     def expert_ffn(self, x, w_gate, w_up, w_down, use_ws=True):
         self._hidden(x, "x")
         self._weights(w_gate, w_up, w_down)
+        self.gu_saved = False
         if getattr(self, "packed", None) is not None:
             B.occult_expert_ffn_packed(self.cfg, self.plan, self.sfd_x, x, w_gate, w_up, w_down, self.packed, self.epd_h,
                                        self.epd_y, self.h_shared, self.y_shared, self.ffn_ws if use_ws else None)
@@ -118,6 +124,7 @@ class OccultLayer:
         self._hidden(x, "x")
         self._weights(w_gate, w_up, w_down)
         epd_gu, gu_sh = self._pre_activations()
+        self.gu_saved = False   # (until the call has succeeded)
         B.occult_expert_ffn_train(self.cfg, self.plan, self.sfd_x, x, w_gate, w_up, w_down, self.epd_h, self.epd_y,
                                   self.h_shared, self.y_shared, epd_gu, gu_sh, self.ffn_ws)
         self.gu_saved = True
@@ -153,10 +160,10 @@ class OccultLayer:
             epd_gu, gu_sh = self._pre_activations()
         else:
             packed = getattr(self, "packed", None)
+        self.gu_saved = False
         B.occult_forward(self.cfg, self.plan, logits, x, w_gate, w_up, w_down, packed, self.ids, self.w, self.ws, self.sfd_x,
                          self.epd_h, self.epd_y, self.h_shared, self.y_shared, self.ffn_ws, epd_gu, gu_sh, self.sfd_y, self.y)
-        if train:
-            self.gu_saved = True
+        self.gu_saved = bool(train)
         return self.y
 
     # ---- backward of the data movement (buffers allocated on first use) -----------------------
@@ -215,8 +222,8 @@ class OccultLayer:
         self._hidden(dy, "dy")
         self._hidden(epd_dy, "epd_dy", T * k)
         self._weights(w_gate, w_up, None)
-        if gu_saved is None:   # pre-activations kept by expert_ffn_train() since the last backward
-            gu_saved = getattr(self, "gu_saved", False)
+        if gu_saved is None:   # pre-activations kept by expert_ffn_train() for this very batch
+            gu_saved = self.gu_saved
         B.occult_expert_ffn_backward(self.cfg, self.plan, self.sfd_x, x, w_gate, w_up, self.w_down_t, self.w_gu_t,
                                      epd_dy, dy, epd_gu, epd_dh, epd_dx, gu_sh, dh_sh, dx_sh, gu_saved)
         self.gu_saved = False      # overwritten with [dg | du]

@@ -80,3 +80,38 @@ def test_forward_of_small_batches(T, d, E, k, D, dtype):
     torch.cuda.synchronize()
     for name in ("plan_mem", "ids", "w", "sfd_x", "y"):
         assert torch.equal(getattr(one, name).view(torch.uint8), getattr(steps, name).view(torch.uint8)), name
+
+
+@pytest.mark.parametrize("S,one_call", [(0, True), (1, True), (0, False), (1, False)])
+def test_kept_pre_activations_are_of_the_present_batch(S, one_call):
+    """A training pass on one batch, a plain one on another, the backward on the latter: what a layer gives that has only
+    seen the second batch (its pre-activations are recomputed), not the first batch's pre-activations in the second's rows."""
+    say(f"pre-activations S={S} one_call={one_call}")
+    dev = require_gpu()
+    T, d, f, E, k, D = 96, 128, 64, 8, 2, 4
+    gen = torch.Generator().manual_seed(S)
+    bf = lambda *shape: torch.randn(shape, generator=gen).to(torch.bfloat16).to(dev)
+    w = [bf(E + S, f, d) * 0.1, bf(E + S, f, d) * 0.1, bf(E + S, d, f) * 0.1]
+    xa, xb, dy = bf(T, d), bf(T, d), bf(T, d)
+    la, lb = (torch.randn((T, E), generator=gen).to(dev) for _ in range(2))
+    both, fresh = (OccultLayer(T, d, f, E, S, k, D, "bf16") for _ in range(2))
+
+    def plain(layer):
+        if one_call:
+            return layer.forward(lb, xb, *w)
+        layer.route(lb)
+        layer.make_plan()
+        layer.dispatch(xb)
+        layer.expert_ffn(xb, *w)
+        layer.combine()
+
+    both.forward(la, xa, *w, train=True)
+    assert both.gu_saved
+    got = []
+    for layer in (both, fresh):
+        plain(layer)
+        layer.transpose_weights(*w)
+        got.append(layer.backward_input(xb, w[0], w[1], dy) + layer.expert_ffn_backward_weights(xb, dy))
+    torch.cuda.synchronize()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
