@@ -150,7 +150,15 @@ class OccultLayer:
                                 self.y_shared, self.y, mode)
 
     def forward(self, logits, x, w_gate, w_up, w_down, train=False):
-        """route(), make_plan(), dispatch(), expert_ffn() or expert_ffn_train(), combine() in one call into the library."""
+        """route(), make_plan(), dispatch(), expert_ffn() or expert_ffn_train(), combine(): in one call into the library, or
+        one by one where a subclass or this object has its own version of one of them."""
+        if self._has_own_steps():
+            self.route(logits)
+            self.make_plan()
+            self.dispatch(x)
+            (self.expert_ffn_train if train else self.expert_ffn)(x, w_gate, w_up, w_down)
+            self.combine()
+            return self.y
         s = self.shape
         B.expect(logits, "logits", torch.float32, s["T"] * s["E"])
         self._hidden(x, "x")
@@ -165,6 +173,10 @@ class OccultLayer:
                          self.epd_h, self.epd_y, self.h_shared, self.y_shared, self.ffn_ws, epd_gu, gu_sh, self.sfd_y, self.y)
         self.gu_saved = bool(train)
         return self.y
+
+    def _has_own_steps(self):
+        cls = type(self)
+        return any(getattr(cls, n) is not f for n, f in _STEPS.items()) or not _STEPS.keys().isdisjoint(self.__dict__)
 
     # ---- backward of the data movement (buffers allocated on first use) -----------------------
     def _buf(self, name, shape, dtype):
@@ -291,3 +303,7 @@ class OccultLayer:
             "sfd_epd_rows": self._view("sfd_epd_rows", self.n_sfd_max * m1, i32).view(self.n_sfd_max, m1),
             "counters": self._view("counters", 8, torch.int64),
         }
+
+
+# what forward() stands for
+_STEPS = {n: getattr(OccultLayer, n) for n in ("route", "make_plan", "dispatch", "expert_ffn", "expert_ffn_train", "combine")}

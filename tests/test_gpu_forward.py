@@ -115,3 +115,30 @@ def test_kept_pre_activations_are_of_the_present_batch(S, one_call):
     torch.cuda.synchronize()
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("step", ["route", "make_plan", "dispatch", "expert_ffn", "expert_ffn_train", "combine"])
+@pytest.mark.parametrize("where", ["subclass", "object", "class"])
+def test_forward_goes_through_replaced_steps(step, where, monkeypatch):
+    say(f"forward with its own {step} in the {where}")
+    dev = require_gpu()
+    T, d, f, E, k, D, train = 20, 64, 64, 8, 2, 4, step == "expert_ffn_train"
+    gen = torch.Generator().manual_seed(1)
+    bf = lambda *shape: torch.randn(shape, generator=gen).to(torch.bfloat16).to(dev)
+    x, lg, w = bf(T, d), torch.randn((T, E), generator=gen).to(dev), (bf(E, f, d), bf(E, f, d), bf(E, d, f))
+    want = OccultLayer(T, d, f, E, 0, k, D, "bf16").forward(lg, x, *w, train=train)
+    own, calls = getattr(OccultLayer, step), []
+
+    def replaced(self, *args):
+        calls.append(step)
+        return own(self, *args)
+
+    layer = (type("Own", (OccultLayer,), {step: replaced}) if where == "subclass" else OccultLayer)(T, d, f, E, 0, k, D, "bf16")
+    if where == "object":
+        setattr(layer, step, replaced.__get__(layer))
+    if where == "class":
+        monkeypatch.setattr(OccultLayer, step, replaced)
+    y = layer.forward(lg, x, *w, train=train)
+    torch.cuda.synchronize()
+    assert calls == [step] and layer.gu_saved == train
+    assert torch.equal(y, want)
