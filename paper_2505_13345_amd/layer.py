@@ -7,6 +7,8 @@ synchronises or computes.  Table views onto the plan block are for tests and rep
 """
 from __future__ import annotations
 
+import operator
+
 import torch
 
 from . import binding as B
@@ -175,8 +177,7 @@ class OccultLayer:
         return self.y
 
     def _has_own_steps(self):
-        cls = type(self)
-        return any(getattr(cls, n) is not f for n, f in _STEPS.items()) or not _STEPS.keys().isdisjoint(self.__dict__)
+        return _steps_of(type(self)) != _STEPS or not self.__dict__.keys().isdisjoint(_STEP_NAMES)
 
     # ---- backward of the data movement (buffers allocated on first use) -----------------------
     def _buf(self, name, shape, dtype):
@@ -305,5 +306,7 @@ class OccultLayer:
         }
 
 
-# what forward() stands for
-_STEPS = {n: getattr(OccultLayer, n) for n in ("route", "make_plan", "dispatch", "expert_ffn", "expert_ffn_train", "combine")}
+# the steps that forward() stands for (one attribute lookup for all of them: this runs on every pass)
+_STEP_NAMES = ("route", "make_plan", "dispatch", "expert_ffn", "expert_ffn_train", "combine")
+_steps_of = operator.attrgetter(*_STEP_NAMES)
+_STEPS = _steps_of(OccultLayer)
