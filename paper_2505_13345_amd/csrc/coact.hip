@@ -51,12 +51,14 @@ __global__ __launch_bounds__(kCoactThreads) void coact_lds_kernel(const int32_t*
     if constexpr (EP * ROW % 1024 != 0) {
       if (lane < EP * ROW % 1024 / 16) *reinterpret_cast<i32x4*>(m + (EP * ROW / 1024 * 64 + lane) * 16) = i32x4{0, 0, 0, 0};
     }
+    wave_lds_order();   // cleared by all lanes
     const int t = chunk * 64 + lane;
     if (t < T) {
       const int32_t* row = ids + (size_t)t * k;
       for (int s = 0; s < k; ++s)
         atomicAdd(reinterpret_cast<int*>(m + row[s] * ROW + (lane & ~3)), 1 << ((lane & 3) * 8));   // (k <= 32: no carry)
     }
+    wave_lds_order();   // counted by all lanes
     i32x4 f[NB];   // lane l: expert l % 16 of its block, tokens (l / 16) * 16 .. +15
 #pragma unroll
     for (int b = 0; b < NB; ++b) f[b] = *reinterpret_cast<const i32x4*>(m + (b * 16 + (lane & 15)) * ROW + (lane >> 4) * 16);
@@ -65,6 +67,7 @@ __global__ __launch_bounds__(kCoactThreads) void coact_lds_kernel(const int32_t*
     for (int a = 0; a < NB; ++a)
 #pragma unroll
       for (int b = a; b < NB; ++b, ++n) acc[n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[a], f[b], acc[n], 0, 0, 0);
+    wave_lds_order();   // read by all lanes, before the next 64 tokens clear it
   }
   // element i of lane l of block (a, b): experts a*16 + (l/16)*4 + i and b*16 + l%16
   int n = 0;

@@ -95,6 +95,15 @@ __device__ __forceinline__ void wait_loads_and_barrier() {
 }
 #pragma clang diagnostic pop
 
+// Holds a wave's LDS accesses before it against those behind it, where lanes read what other lanes of the wave have written (or
+// write again what they have read).  The LDS serves a wave's accesses in their order, so there is nothing to wait for
+// and no instruction comes of it; without it only the compiler's not knowing the lanes' addresses keeps the order.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // silu(g) * u with the hardware exp2 and reciprocal (about 1 ulp each: far inside bf16 rounding);
 // the IEEE division would cost more VALU time per 256-row tile than the epilogue's stores
 __device__ __forceinline__ float swiglu_rcp(float g, float u) {

@@ -345,6 +345,7 @@ __global__ __launch_bounds__(256) void wgrad_bf16(const WgradArgs first, const W
 #pragma unroll
     for (int ni = 0; ni < 8; ++ni)
       *reinterpret_cast<f32x4*>(buf + w_row * 512 + ((ni * 4 + w_q) ^ w_row) * 16) = acc[mi][ni];
+    wave_lds_order();   // (and the other half's reads before its next writes)
     f32x4 v[8];
     unsigned off[8];
 #pragma unroll
@@ -525,6 +526,7 @@ __global__ __launch_bounds__(256, 3) void wgrad_bf16(const WgradArgs first, cons
 #pragma unroll
     for (int ni = 0; ni < 4; ++ni)
       *reinterpret_cast<f32x4*>(buf + w_row * 256 + ((ni * 4 + w_q) ^ w_row) * 16) = acc[mi][ni];
+    wave_lds_order();   // (and the other half's reads before its next writes)
     f32x4 v[4];
     unsigned off[4];
 #pragma unroll

@@ -38,6 +38,30 @@ def test_accumulators_are_read_behind_the_wait_states(source, tag, tmp_path):
             assert not early, (name, early[:3])
 
 
+@pytest.mark.parametrize("source,tag,changes", [
+    ("coact.hip", "coact_lds", ["write add", "add read", "read write"]),   # one buffer: cleared, counted, read, cleared
+    ("wgrad.hip", "wgd", ["write read"]),   # two halves in turn: written, read
+    ("wgrad.hip", "wgs", ["write read"])])
+def test_lds_accesses_of_a_wave_are_held_in_order(source, tag, changes, tmp_path):
+    """Where lanes read LDS that other lanes of their wave wrote, a barrier of the block or of the wave (which emits no
+    instruction, only its mark) stands between."""
+    kernels = _kernels(source, str(tmp_path), tag)
+    assert kernels
+    for name, lines in kernels.items():
+        last, held, seen = None, True, set()
+        for l in lines:
+            if l.startswith(("; wave barrier", "s_barrier")):
+                held = True
+            access = re.match(r"ds_(write|add|read)", l)
+            if access:
+                change = f"{last} {access.group(1)}"
+                if change in changes:
+                    assert held, (name, l)
+                    seen.add(change)
+                last, held = access.group(1), False
+        assert seen == set(changes), (name, seen)
+
+
 @pytest.mark.parametrize("tag", ["t256", "t128", "wgd"])
 def test_build_refuses_kernels_that_spill(tag, tmp_path, monkeypatch):
     """A kernel of that name whose registers do not suffice does not build."""
