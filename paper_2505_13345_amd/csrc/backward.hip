@@ -34,7 +34,8 @@ __device__ __forceinline__ float wave_max_all(float v) {
   return v;
 }
 
-template <bool BF16, int VPL>
+// DW: gate gradients are asked for (dw not NULL).  AHEAD: a slot's row is requested before the slot before it is reduced.
+template <bool BF16, int VPL, bool DW, bool AHEAD>
 __global__ __launch_bounds__(kBwdWaves * 64) void combine_bwd_kernel(
     const void* __restrict__ dy, const void* __restrict__ epd_y, void* __restrict__ epd_dy, float* __restrict__ dw,
     const int32_t* __restrict__ ids, const int32_t* __restrict__ expert_pos,
@@ -77,25 +78,25 @@ __global__ __launch_bounds__(kBwdWaves * 64) void combine_bwd_kernel(
           for (int e = 0; e < NE; ++e) g_row[i][e] = 0.0f;
         }
       }
-      // The next slot's row is requested before the current one is reduced: a reduction is a chain of cross-lane steps, and
-      // with one row in flight its latency stood between them (us for the call with gate gradients, d = 2048: 1000 tokens, k = 6,
-      // 28.9 -> 19.2, k = 8 36.2 -> 22.5; 4096 77.4 -> 74.9; 16384 311 -> 302; d = 4096, k = 4: 1000 37 -> 24, 4096 81 -> 85,
-      // 16384 352 -> 325).
+      // A reduction is a chain of cross-lane steps, and with one row in flight its latency stands between the rows (AHEAD where it
+      // pays: see row_ahead).
       typename R::Raw cur[VPL], nxt[VPL];
       auto request = [&](int s, typename R::Raw (&into)[VPL]) {
         const int q = __builtin_amdgcn_readlane(my_q, s);
-        if (!dw || q < 0) return;   // wave-uniform
+        if (q < 0) return;   // wave-uniform
 #pragma unroll
         for (int i = 0; i < VPL; ++i) {
           const int c = cbase + lane + 64 * i;
           if (c < row_vecs) into[i] = R::load_raw(epd_y, (size_t)q, row_vecs, c);
         }
       };
-      request(0, nxt);
+      if constexpr (AHEAD) request(0, nxt);
       for (int s = 0; s < k; ++s) {
+        if constexpr (AHEAD) {
 #pragma unroll
-        for (int i = 0; i < VPL; ++i) cur[i] = nxt[i];
-        if (s + 1 < k) request(s + 1, nxt);
+          for (int i = 0; i < VPL; ++i) cur[i] = nxt[i];
+          if (s + 1 < k) request(s + 1, nxt);
+        }
         const int q = __builtin_amdgcn_readlane(my_q, s);
         if (q < 0) continue;   // a plan that does not belong to these ids: nothing to address
         const float g = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_g), s));
@@ -104,9 +105,10 @@ __global__ __launch_bounds__(kBwdWaves * 64) void combine_bwd_kernel(
         for (int i = 0; i < VPL; ++i) {
           const int c = cbase + lane + 64 * i;
           if (c < row_vecs) {
-            if (dw) {
+            if constexpr (DW) {
               float v[NE];
-              R::unpack(cur[i], v);
+              if constexpr (AHEAD) R::unpack(cur[i], v);
+              else R::load(epd_y, (size_t)q, row_vecs, c, v);
 #pragma unroll
               for (int e = 0; e < NE; ++e) dot = fmaf(g_row[i][e], v[e], dot);
             }
@@ -118,15 +120,22 @@ __global__ __launch_bounds__(kBwdWaves * 64) void combine_bwd_kernel(
             }
           }
         }
-        if (dw) {
+        if constexpr (DW) {
           dot = wave_sum_all(dot);
           if (lane == s) my_dw += dot;
         }
       }
     }
-    if (dw && lane < k) dw[(size_t)t * k + lane] = my_dw;
+    if (DW && lane < k) dw[(size_t)t * k + lane] = my_dw;
   }
 }
+
+// A second row in flight (us for the call with gate gradients, one row / two, d = 2048 in bf16: 1000 tokens, k = 8, 31.8 / 17.2; 2048
+// 39.0 / 29.0; 4096 59.9 / 56.2; 16384 232 / 225; rows of 8 KiB, k = 4: 1000 32.1 / 17.6, 3000 47.2 / 43.8, 3400 52.2 / 54.4, 4096 59.9 /
+// 64.3, 4600 86 / 72, 16384 242 / 231).  In rows of more than 4 KiB its registers (97 -> 166) leave three waves to a SIMD, 3072
+// tokens to a round over the 1024 SIMDs, where one row in flight goes on to 4096.  Without gate gradients there is no row to
+// request and none of those registers (4096 tokens of 8 KiB, k = 4: 41.0 -> 33.0).
+static bool row_ahead(int T, int vpl) { return vpl <= 4 || T <= 3072 || T > 4096; }
 
 // Gradient of the gate values with respect to the router scores (paper Eq. 1: Softmax over all E
 // experts, the values at the k selected ones, divided by their sum when renorm).  One wavefront
@@ -226,8 +235,14 @@ extern "C" int occult_combine_backward(const occult_cfg_t* cfg, const occult_pla
   const int vpl = (row_vecs + 63) / 64;   // beyond 8 the kernel walks the row in chunks of 8 KiB
   hipStream_t s = static_cast<hipStream_t>(stream);
   const dim3 grid((c.T + kBwdWaves - 1) / kBwdWaves), block(kBwdWaves * 64);
-#define OCC_CBWD(B, N)                                                                                       \
-  hipLaunchKernelGGL((combine_bwd_kernel<B, N>), grid, block, 0, s, dy, epd_y, epd_dy, dw, ids, c.expert_pos, \
+#define OCC_CBWD(B, N)                                              \
+  do {                                                              \
+    if (!dw) OCC_CBWD_DW(B, N, false, false);                       \
+    else if (row_ahead(c.T, vpl)) OCC_CBWD_DW(B, N, true, true);    \
+    else if constexpr (N == 8) OCC_CBWD_DW(B, N, true, false);      \
+  } while (0)
+#define OCC_CBWD_DW(B, N, DW, AHEAD)                                                                         \
+  hipLaunchKernelGGL((combine_bwd_kernel<B, N, DW, AHEAD>), grid, block, 0, s, dy, epd_y, epd_dy, dw, ids, c.expert_pos, \
                      plan->tok_sfd_row, plan->sfd_epd_rows, plan->exp_offset, plan->epd_gate, c.T, c.k, c.D,  \
                      c.E / c.D, merge_width(c), row_vecs)
   if (c.dtype == OCCULT_BF16) {
@@ -241,6 +256,7 @@ extern "C" int occult_combine_backward(const occult_cfg_t* cfg, const occult_pla
     else if (vpl <= 4) OCC_CBWD(false, 4);
     else OCC_CBWD(false, 8);
   }
+#undef OCC_CBWD_DW
 #undef OCC_CBWD
   OCC_LAUNCH_CHECK("combine_bwd_kernel");
   return OCCULT_OK;

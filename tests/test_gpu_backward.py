@@ -236,3 +236,32 @@ def test_backward_empty_batch_and_argument_checks():
         B.occult_dispatch_backward(layer.cfg, layer.plan, None, dy, None, dy)
     assert e.value.code == -4
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 2560), ("bf16", 2048), ("f32", 1088)])
+@pytest.mark.parametrize("T", [3072, 3073, 4096, 4097])
+def test_combine_backward_with_and_without_gate_gradients(T, d, dtype):
+    """Batches on both sides of the lines where long rows are requested one or two at a time; without gate gradients the
+    same scaled rows.  Small integers and gates of powers of two: every product and sum is exact."""
+    say(f"combine backward T={T} d={d} {dtype}")
+    dev = require_gpu()
+    E, D, k = 8, 4, 3
+    gen = torch.Generator().manual_seed(T + d)
+    ids = torch.rand((T, E), generator=gen).argsort(1)[:, :k].to(torch.int32).to(dev)
+    w = torch.tensor([.5, .25, .25]).repeat(T, 1).to(dev)
+    ints = lambda *shape: torch.randint(-3, 4, shape, generator=gen).float().to(dev)
+    dy, v = ints(T, d), ints(T, d)
+    layer = OccultLayer(T, d, 64, E, 0, k, D, dtype, with_ffn=False)
+    layer.make_plan(ids, w)
+    t = layer.tables()
+    token = t["sfd_token"][t["epd_sfd_row"].long()].long()                # of each EPD row
+    expert = torch.repeat_interleave(t["pos_expert"].long(), t["exp_count"].long())
+    epd_y = v[token] * (1 + expert[:, None])                              # |.| <= 24: exact in bf16
+    epd_y, dy_t = epd_y.to(layer.tdtype), dy.to(layer.tdtype)
+    _, epd_dy, dw = layer.combine_backward(dy_t, ids, epd_y, want_sfd=False)
+    assert torch.equal(dw, (dy * v).sum(1)[:, None] * (1 + ids))
+    want = t["epd_gate"][:, None] * dy[token]
+    assert torch.equal(epd_dy.float(), want)
+    epd_dy.fill_(7)
+    _, epd_dy, none = layer.combine_backward(dy_t, ids, epd_y, want_sfd=False, want_dw=False)
+    assert none is None and torch.equal(epd_dy.float(), want)
