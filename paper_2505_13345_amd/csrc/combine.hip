@@ -294,11 +294,20 @@ __global__ __launch_bounds__(kCombWaves * 64) void combine_split_kernel(
   }
 }
 
-// Where combine_split_kernel is the faster one (us per call back to back, 7.8 of them the host's; whole rows / split, d = 2048 in
-// bf16: k = 8, 17 tokens 9.3 / 7.8, 128 10.9 / 7.8, 500 12.3 / 7.9, 1000 14.7 / 13.0, 1500 18.7 / 18.7, 2048 22.8 / 25.0; k = 4, 256
-// tokens 9.4 / 8.0, 1000 11.8 / 9.2, 1500 13.8 / 12.0, 2048 15.8 / 15.6, 3000 even): beyond, there are waves enough and
-// the lists of a token would be read by four.  Decoding: 1 token 55.1 -> 52.2 us for the layer, 17 153.4 -> 148.9, 128 234.6 -> 231.4.
-constexpr int kSplitRows = 8192;
+// Where combine_split_kernel is the faster one, whatever the slots of a token (us per call back to back, 7.8 of them the host's; whole
+// rows / split, k = 8 in bf16): as long as its waves have about a round on the 1024 SIMDs each.
+//  - rows of at most 2 KiB, a wave per KiB: 4096 waves (1 KiB: 3000 tokens 11.0 / 8.1, 4096 12.3 / 12.2, 5120 14.6 / 15.6; 2 KiB: 1500 11.4
+//    / 8.0, 2048 12.6 / 12.2, 2560 14.5 / 15.5);
+//  - longer rows, four waves: 1280 tokens (4 KiB: 128 10.9 / 7.8, 500 12.3 / 7.9, 1024 14.3 / 11.9, 1280 16.2 / 15.4, 1500 17.6 / 18.0, 2048
+//    21.0 / 24.0; with two slots 2048 tokens 7.5 / 10.0);
+//  - with all four waves full, beyond 6 KiB, the fullest CU decides: four blocks of a token each (769 to 1024 tokens) take what the one
+//    block of four whole rows takes, five less than two of those (8 KiB: 768 19.8 / 17.6, 850 20.5 / 20.6 and in f32 18.6 / 20.4,
+//    1024 22.3 / 22.8, 1100 29.3 / 25.9, 1280 32.0 / 28.4, 1500 34.9 / 34.0, with two slots 10.6 / 12.5).
+// Decoding: 1 token 55.1 -> 52.2 us for the layer, 17 153.4 -> 148.9, 128 234.6 -> 231.4.
+static bool splits_rows(int T, int vpl) {
+  if (vpl <= 2) return (long long)T * vpl <= 4096;
+  return vpl <= 8 && T <= 1280 && (vpl <= 6 || T <= 768 || T > 1024);
+}
 // launches the two-stage sum; gates == NULL means unit weights
 static int launch_combine(const occult_cfg_t& c, const occult_plan_t* plan, const float* gates, const void* epd,
                           void* sfd, const void* shared, void* out, occult_stream_t stream) {
@@ -312,7 +321,7 @@ static int launch_combine(const occult_cfg_t& c, const occult_plan_t* plan, cons
   const dim3 grid((c.T + kCombWaves - 1) / kCombWaves), block(kCombWaves * 64);
   const int M1 = merge_width(c);
   const int lists_fit = min_i(c.k, c.D) * M1 <= 64 ? 1 : 0;
-  if (lists_fit && vpl <= 8 && (long long)c.T * c.k <= kSplitRows) {
+  if (lists_fit && splits_rows(c.T, vpl)) {
     const int split = vpl >= 3 ? 4 : vpl;
     const dim3 sgrid(((long long)c.T * split + kCombWaves - 1) / kCombWaves);
 #define OCC_COMB_SPLIT(B, N)                                                                              \

@@ -188,13 +188,16 @@ def test_dispatch_meta_bit_exact(E, D, k, T, placement):
 @pytest.mark.parametrize("E,D,k,T,d,dtype", [
     (64, 8, 8, 1, 2048, "bf16"), (8, 4, 4, 300, 1536, "bf16"), (16, 2, 8, 1024, 64, "bf16"), (8, 1, 8, 50, 1024, "bf16"),
     (64, 64, 8, 17, 4096, "bf16"), (16, 4, 4, 33, 1032, "f32"), (20, 5, 20, 40, 2048, "bf16"), (20, 5, 20, 40, 3072, "bf16"),
+    # the last batch on each side of every line
+    (16, 4, 2, 4096, 512, "bf16"), (16, 4, 2, 2048, 512, "f32"), (8, 4, 3, 1280, 2048, "bf16"), (8, 4, 2, 768, 4096, "bf16"),
+    (8, 4, 2, 1025, 3584, "bf16"), (8, 4, 2, 1280, 2048, "f32"),
 ])
 def test_small_batches_combine_as_large_ones(E, D, k, T, d, dtype):
     """A token's columns dealt out to one, two or four waves, more rows than are requested together, the largest batch of that
     path: the same bits as in a batch that holds these tokens several times and takes whole rows."""
     say(f"combine small/large E={E} D={D} k={k} T={T} d={d} {dtype}")
     dev = require_gpu()
-    copies = 8192 // (T * k) + 1
+    copies = 4096 // T + 1   # more than 4096 tokens always take whole rows
     gen = torch.Generator(device=dev).manual_seed(T)
     ids = torch.argsort(torch.rand((T, E), generator=gen, device=dev), 1)[:, :k].int().contiguous()
     w = torch.rand((T, k), generator=gen, device=dev)
