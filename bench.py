@@ -292,7 +292,7 @@ def main():
         "route": {"bound": "hbm", "achieved": gbs(bytes_route, calls["route"]), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                   "note": "launch- and latency-bound at this size"},
         "plan": {"bound": "hbm", "achieved": gbs(bytes_plan, calls["plan"]), "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                 "note": "three dependent launches; latency-bound"},
+                 "note": "one to three dependent launches by the batch; latency-bound"},
         "router_projection_and_route": {"bound": "hbm", "achieved": gbs(bytes_router, calls["router_projection_and_route"]),
                                         "peak": PEAK_HBM_GBS, "unit": "GB/s"},
         "ffn_gemm1_swiglu": {"bound": "mfma", "achieved": tf(flops1, calls["ffn_gemm1_swiglu"]),

@@ -1,5 +1,5 @@
-// Host-side pieces of the C ABI that launch nothing: version, error text, argument checks,
-// plan memory layout, plan statistics.
+// Host-side pieces of the C ABI, without kernels of their own: version, error text, argument checks, plan memory layout,
+// plan statistics, and the whole forward pass as one call.
 #include "common.h"
 
 #include <string.h>

@@ -1383,9 +1383,10 @@ int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total
 //    357 us) or add a last round of its own: up to about 800 rows per group (656 rows: 1116 us against 1057; 768: equal),
 //    and down to any number where shares_launch() says so;
 //  - without, from 24 rows (32: 226 us against 220; 20: 215 against 218) up to 500: half as high, the tiles of a launch divide
-//    more evenly over the CUs (of 37 batches of 240 - 550 rows per group, 512 - 2048 x 384 - 1408, 0.94 of the time of the
-//    256-row tiles on average, gate/up and down projection together; 31 faster, at worst 1.03, at 450 rows and more.  256
-//    rows: 0.87 - 0.97 by how the rows fall; 750: 1.08).
+//    more evenly over the CUs.  Time over that of the 256-row tiles, 242 - 490 rows per group of 32 - 128 experts, K = 384 - 2816, N = 384 -
+//    2048: 336 gate/up products 0.84 on average (with and without stored pre-activations), 27 of them more than 1.03, at worst
+//    1.16; 700 down projections, whose shapes are the backward's two products as well, 0.91, 108 more than 1.03, at worst 1.14, by
+//    how the tiles happen to fill their last round.  The better of the two at every size would be 0.83 and 0.90.  750 rows: 1.08.
 static bool fits_tile128(const GemmArgs& a) {
   return a.K >= 192 && a.K % 64 == 0 && a.N % 64 == 0 && (long long)a.a_rows_total * a.lda * 2 < (1ll << 32) &&
          weights_below_4gib(a);

@@ -42,8 +42,11 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
 // The same for 2-byte elements with 16-byte global accesses on both sides (R % 8 == 0, C % 8 == 0):
 // a thread loads 8 columns of two rows, scatters them into the LDS tile as [column][row], and reads
 // back 8 consecutive rows of one column as one vector.  LDS rows are padded to 72 elements (144
-// bytes), which keeps the vectors 16-byte aligned.  Bound by memory; the copies are larger than any cache and stored as
-// not to be kept (66 experts, d = 2048, f = 1408: 441 -> 410 us for the three matrices, 5.6 TB/s; 64 of f = 1024: 348 -> 306).
+// bytes), which keeps the vectors 16-byte aligned.  Bound by memory; the copies are stored as not to be kept
+// (66 experts, d = 2048, f = 1408, 1.1 GB: 441 -> 410 us for the three matrices, 5.6 TB/s; 64 of f = 1024: 348 -> 306).  Copies that the
+// memory-side cache (256 MiB) would hold gain as well, and the products that read them next lose about as much: 64 experts of 512 x
+// 384, 75 MB, 28.9 -> 26.3, with the backward behind them 68.1 -> 67.4 (1000 tokens) and 139.8 -> 138.5 (6000); 768 x 512, 151 MB, 61.6 ->
+// 49.1, 120.6 -> 122.5 and 225.8 -> 221.6; 896 x 640, 220 MB, 88.3 -> 68.9, 182.9 -> 173.2 and 299.8 -> 293.8.
 __global__ __launch_bounds__(256) void transpose16_kernel(const unsigned short* __restrict__ in,
                                                           unsigned short* __restrict__ out, int R, int C,
                                                           long long out_mat_stride, int out_ld, int col0) {

@@ -384,7 +384,12 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
 // again, and where they are larger than the memory-side cache (256 MiB), which otherwise has some of them from the call before
 // (us without / with: 64 experts, d = 2048, f = 1408, gate/up + down, 24 rows per expert 159 + 97 / 150 + 92, 47 rows
 // 169 + 106 / 163 + 96, 71 rows 171 + 111 / 171 + 111, 125 rows of f = 1024 134 / 144; 38 rows of f = 1024, 537 MB of gate/up
-// 100 / 92, 268 MB of down 47 / 52; d = 1152, f = 704, 207 MB of gate/up 44 / 55).
+// 100 / 92, 268 MB of down 47 / 52; d = 1152, f = 704, 207 MB of gate/up 44 / 55).  The line is put above the cache's size because it holds
+// other tensors too; between 268 and 377 MB of weights nothing was measured that would move it.  These are calls of one layer
+// back to back: below the line, layers in turn gain by it what one layer loses (forward, kept / not kept: 64 experts of 768 x 512,
+// 47 rows, one layer 68.5 / 73.7, six in turn 463 / 441; 1152 x 704, 26 rows, 98.6 / 97.8 and 622 / 591).  The shared experts' weights,
+// which several row tiles read, go the same way: with 2 and 4 of them a forward takes 0.78 - 0.98 up to 47 rows and 0.87 - 1.04 at 60
+// and 70.
 constexpr long long kOnceRows = 72, kOnceBytes = 320ll << 20;
 int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, hipStream_t s) {
   const int bn_out = swiglu ? t128::BN / 2 : t128::BN;

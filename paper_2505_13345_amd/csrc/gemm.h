@@ -41,7 +41,7 @@ struct GemmArgs {
 };
 
 // Launches C[rows][N] = A[rows][K] x B[group][N][K]^T group by group (cfg.dtype: bf16 on MFMA with f32
-// accumulation, or plain f32); with `swiglu` the output is silu(A B^T) * (A B2^T).  `total_rows` = logical
+// accumulation, or f32 matrix instructions); with `swiglu` the output is silu(A B^T) * (A B2^T).  `total_rows` = logical
 // rows over all groups.  Picks the tile shape from the rows per group.  Returns an OCCULT_* code.
 int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total_rows, hipStream_t s);
 

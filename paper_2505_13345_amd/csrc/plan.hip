@@ -194,6 +194,9 @@ enum class Bases {
 //    it grows with the square of the blocks, so the scan keeps what is beyond;
 //  - 32 tokens per workgroup against 256, which build a block's sets once instead of eight times: 16384 tokens 17 / 22,
 //    32768 21.5 / 23, 65536 33 / 30, 131072 57 / 47.
+//  - the same lines for any number of columns, with 320 of them (E = 256, D = 64) as with 72: a scan launch has as many more to
+//    walk (three launches with a token per thread in the last / these: 65536 tokens 120 / 69, 262144 404 / 201, 300000 419 / 281; E = 256,
+//    D = 8: 72 / 44, 231 / 146, 263 / 241).
 // (Three launches with a token per thread in the last: 256 tokens 12 (in one launch of one workgroup), 500 19.6, 16384 23,
 // 65536 37, 262144 114.)
 constexpr int kSingleMaxTokens = 512;

@@ -14,7 +14,8 @@
 // block per CU).  Outputs are f32 (gradient accumulation across calls is exact to f32), stored
 // as whole rows of a wave tile, 16 rows at a time through LDS, and marked as not to be kept in L2 (the operands are what is
 // read again: 64 + 2 experts, 562 rows each, 1460 us for the three products with 64-byte pieces straight from the
-// accumulators, 1359 with whole rows, 1290 not kept).  With 8 groups or more a
+// accumulators, 1359 with whole rows, 1290 not kept; gradients that a cache would hold, read once right behind, are even: 64 + 2
+// experts of 768 x 512, 1000 tokens, 204 / 205, 12000 506 / 505).  With 8 groups or more a
 // group's tiles are launched on one XCD (workgroup id % 8), so its rows are fetched into one L2.
 #include "common.h"
 
@@ -600,6 +601,10 @@ __global__ __launch_bounds__(256) void wgrad_f32(const WgradArgs a) {
 // Row slices for a product with fewer than 8 uniform groups of many rows (shared experts of a large batch): its
 // groups x tiles workgroups alone leave most of the chip idle.  Returns the number of slices (1 = no split) that
 // minimises rounds of workgroups x rows per slice, at most 8, each of at least 2048 rows; *rslice = rows per slice.
+// That is the price of the product in a launch of its own.  Beside the routed experts', where it runs, a split is still
+// worth its partial sums and its second launch in narrow layers (us for the three products, split / not: 64 + 2 experts of 512 x 384,
+// 4096 tokens 158 / 262, 16384 476 / 1005; 1024 x 704, 8192 474 / 588), and costs 6 % in wide ones (2048 x 1408, 4096 1133 / 1065, 16384 3218 /
+// 2979) and up to a third with few experts (8 + 1, 8192 794 / 584).
 static int choose_row_split(const occult_cfg_t& c, int ngroups, int M, int N, int R, int* rslice) {
   *rslice = R;
   if (c.dtype != OCCULT_BF16 || ngroups <= 0 || ngroups >= 8 || N % 4 != 0) return 1;
@@ -631,7 +636,7 @@ static int choose_row_split(const occult_cfg_t& c, int ngroups, int M, int N, in
 
 // The routed experts' product and, unless b is NULL, the shared experts' (same M and N), which come first in the grid: their
 // workgroups run longest.
-// 128 x 128 tiles for fewer than 240 rows per group, shared ones included, where the products are mostly stores (us for the
+// 128 x 128 tiles for fewer than 240 rows per group, shared ones included and their rows not split, where the products are mostly stores (us for the
 // three, d = 2048, 128 / 256 tiles: 64 + 2 experts of f = 1408, 91 rows 388 / 441, 182 473 / 530, 242 624 / 595, 303 841 / 724;
 // 64 of f = 1024, 125 rows 274 / 357, 250 387 / 419, 312 495 / 464; 60 + 4, 250 538 / 588, 375 873 / 767), and where the
 // larger tiles would leave half of the CUs without one (4 + 1 experts, d = 256, f = 192, 420 rows: 38 / 66).
