@@ -49,7 +49,7 @@ struct Tile {
 // that the weight-streaming or small-tile kernel gives the same rows.  The finished parts' sums have registers of
 // their own (one wave per SIMD: there is room) and cost one addition per accumulator and part (500 tokens of 64 + 2 experts,
 // shared down projection in parts: 312 -> 318 us; 300 of 60 + 4, gate/up in quarters as well: 305 -> 325 us).
-// ONCE: the weights are requested as not to be kept (launch_tile128).
+// ONCE: the weights are requested, and the output stored, as not to be kept (launch_tile128).
 template <bool SWIGLU, bool SAVE, bool PARTS, bool ONCE>
 __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first, const GemmArgs second) {
   static_assert(SWIGLU || !SAVE, "pre-activations exist only with the fused activation");
@@ -320,7 +320,10 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
 
     // epilogue.  sum(ni, mi) element e of lane l: token row mi*16 + l%16, weight row ni*16 + (l/16)*4 + e of the wave
     // tile.  bf16 results pass through the wave's 2 KiB of LDS, 16 rows x 64 columns at a time (16-byte slots swizzled by
-    // the row), and leave as row segments of 128 bytes.
+    // the row), and leave as row segments of 128 bytes; with ONCE marked as not to be kept: what lies dirty in the XCDs' L2s at the
+    // end of a launch is written back before the next one may start (forward of 500 tokens of 64 + 2 experts 282 -> 271 us,
+    // the products of a training step of 1000 tokens 712 -> 697; 2048 and 3500 tokens of 64 experts, whose next launch
+    // finds some of it, 326.6 -> 329.4 and 467.6 -> 476.1: not there).
     {
       char* stg = s_out[wave];
       constexpr int W_COLS = SWIGLU ? 64 : 128;      // output columns of a wave tile
@@ -367,7 +370,10 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
           for (int it = 0; it < 2; ++it) {
             const int row = it * 8 + srow;
             const u32x4 v = *reinterpret_cast<const u32x4*>(stg + row * 128 + (((lane & 7) ^ ((row >> 1) & 7)) * 16));
-            if (mi * 16 + row < rows_left && col < first.N) *reinterpret_cast<u32x4*>(dst + row * pitch) = v;
+            if (mi * 16 + row < rows_left && col < first.N) {
+              if constexpr (ONCE) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst + row * pitch));
+              else *reinterpret_cast<u32x4*>(dst + row * pitch) = v;
+            }
           }
           __builtin_amdgcn_sched_barrier(0);
         }
