@@ -232,6 +232,7 @@ extern "C" int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_
   {   // dh = epd_dy W_down: contraction over d against the transposed down projection [f][d]
     GemmArgs a = base, b = sh;
     a.A = epd_dy; a.a_rows_total = n_epd;
+    a.rows_again = 1;   // by the weight gradients, as all that the next product reads and the forward kept
     b.A = dy;
     a.lda = b.lda = a.ldb = b.ldb = a.kseg = b.kseg = a.K = b.K = c.d;
     a.B = b.B = w_down_t; a.b_group_stride = b.b_group_stride = mat;
@@ -250,6 +251,7 @@ extern "C" int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_
   {   // epd_dx = [dg | du] [W_gate^T | W_up^T]^T: one product over K = 2f; the shared experts' K walks their S matrices
     GemmArgs a = base, b = sh;
     a.A = epd_gu; a.lda = 2 * c.f; a.a_rows_total = n_epd;
+    a.rows_again = 1;
     b.A = gu_shared; b.lda = c.S * 2 * c.f;
     b.ngroups = 1;
     a.B = b.B = w_gu_t; a.b_group_stride = b.b_group_stride = 2 * mat;

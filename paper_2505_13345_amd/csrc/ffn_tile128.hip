@@ -389,14 +389,20 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
 // ONCE: the weights are read past the caches' keeping where almost every expert has one row tile, so that nobody reads them
 // again, and where they are larger than the memory-side cache (256 MiB), which otherwise has some of them from the call before
 // (us without / with: 64 experts, d = 2048, f = 1408, gate/up + down, 24 rows per expert 159 + 97 / 150 + 92, 47 rows
-// 169 + 106 / 163 + 96, 71 rows 171 + 111 / 171 + 111, 125 rows of f = 1024 134 / 144; 38 rows of f = 1024, 537 MB of gate/up
-// 100 / 92, 268 MB of down 47 / 52; d = 1152, f = 704, 207 MB of gate/up 44 / 55).  The line is put above the cache's size because it holds
-// other tensors too; between 268 and 377 MB of weights nothing was measured that would move it.  These are calls of one layer
-// back to back: below the line, layers in turn gain by it what one layer loses (forward, kept / not kept: 64 experts of 768 x 512,
-// 47 rows, one layer 68.5 / 73.7, six in turn 463 / 441; 1152 x 704, 26 rows, 98.6 / 97.8 and 622 / 591).  The shared experts' weights,
-// which several row tiles read, go the same way: with 2 and 4 of them a forward takes 0.78 - 0.98 up to 47 rows and 0.87 - 1.04 at 60
-// and 70.
-constexpr long long kOnceRows = 72, kOnceBytes = 320ll << 20;
+// 169 + 106 / 163 + 96; 38 rows of f = 1024, 537 MB of gate/up 100 / 92, 268 MB of down 47 / 52; d = 1152, f = 704, 207 MB of gate/up
+// 44 / 55).  The line is put above the cache's size because it holds other tensors too; between 268 and 377 MB of weights
+// nothing was measured that would move it.  By rows, forward passes of three layers in turn / of one again and again, without -> with: f = 1408,
+// 64 + 2 experts, 75 rows 306 -> 303 / 303 -> 302, 94 rows 324 -> 320 / 312 -> 311, 112 rows 345 -> 366 / 334 -> 372; 60 + 4, 73 rows
+// 369 -> 366 / 369 -> 349, 100 rows 406 -> 399 / 400 -> 392; f = 1024, 64 experts, 75 rows 259 -> 233 / 261 -> 214, 100 rows 232 -> 243 /
+// 227 -> 250.  Below the line of bytes layers in turn gain by it what one layer loses (64 experts of 768 x 512, 47 rows, one layer
+// 68.5 / 73.7, six in turn 463 / 441).  The shared experts' weights, which several row tiles read, go the same way: with 2 and
+// 4 of them a forward takes 0.78 - 0.98 up to 47 rows and 0.87 - 1.04 at 60 and 70.
+// The backward's products keep their weights out of the memory-side cache in larger batches too, up to the line of the small weight-gradient
+// tiles: these read the rows of all products next, and wait for memory at every group if the weights have taken their place
+// (1000 tokens of 64 + 2 experts, the three weight gradients 550 -> 400 us; training steps without -> with, d = 2048: f = 1408, 94 rows
+// 1685 -> 1580, with the forward's line 1526, 131 rows 1926 -> 1763, 188 rows 2105 -> 2105; f = 1024, 125 rows 1256 -> 1188, 188 rows
+// 1472 -> 1418; from 312 rows on 1 - 2 % slower: the rows of a step are then more than that cache holds).
+constexpr long long kOnceRows = 96, kOnceRowsAgain = 240, kOnceBytes = 320ll << 20;
 int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, hipStream_t s) {
   const int bn_out = swiglu ? t128::BN / 2 : t128::BN;
   const long long n_tiles = (a.N + bn_out - 1) / bn_out;
@@ -418,7 +424,8 @@ int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_
   OCC_REQUIRE(!(save && parts) && (!parts || (a.ksplit >= 1 && (b == nullptr || second.ksplit >= 1))), OCCULT_EINVAL,
               "grouped GEMM: parts of K outside the 128-row tiles' range");
   const dim3 grid((unsigned)blocks), block(256);
-  const bool once = total_rows < kOnceRows * a.ngroups && (long long)a.ngroups * a.N * a.K * (swiglu ? 4 : 2) > kOnceBytes;
+  const bool once = total_rows < (a.rows_again ? kOnceRowsAgain : kOnceRows) * a.ngroups &&
+                    (long long)a.ngroups * a.N * a.K * (swiglu ? 4 : 2) > kOnceBytes;
 #define OCC_T128(SW, SAVE, PARTS)                                                                                        \
   do {                                                                                                                   \
     if (once) hipLaunchKernelGGL((t128::grouped_gemm_bf16<SW, SAVE, PARTS, true>), grid, block, 0, s, a, second);        \
