@@ -1,6 +1,7 @@
 // Host-side pieces of the C ABI, without kernels of their own: version, error text, argument checks, plan memory layout,
 // plan statistics, and the whole forward pass as one call.
 #include "common.h"
+#include "gemm.h"
 
 #include <string.h>
 
@@ -155,6 +156,24 @@ extern "C" int occult_forward(const occult_cfg_t* cfg, const occult_plan_t* plan
   if (rc) return rc;
   OCC_REQUIRE(buffers, OCCULT_ENULLPTR, "buffers is NULL");
   const occult_forward_buffers_t& b = *buffers;
+  if (b.epd_gu == nullptr && forward_uses_front(*cfg)) {   // all steps' arguments first: the launch has work of four of them
+    occult_cfg_t c = *cfg;
+    const void* pk = packed;
+    rc = check_route_args(c, logits, b.ids, b.w);
+    if (rc == OCCULT_OK) rc = check_plan_dispatch_args(cfg, b.ids, b.w, plan, b.plan_ws, b.plan_ws_bytes, x, b.sfd_x);
+    if (rc != OCCULT_OK) return rc;
+    OCC_REQUIRE(aligned16(pk) && aligned16(b.ffn_ws), OCCULT_EALIGN, "packed or ws is not 16-byte aligned");
+    rc = check_ffn_args(c, plan, b.sfd_x, x, weights, b.epd_h, b.epd_y, b.h_shared, b.y_shared);
+    if (rc != OCCULT_OK) return rc;
+    GemmArgs first, second;
+    front_products(c, x, weights, pk, b.epd_h, b.h_shared, &first, &second);
+    rc = launch_front(c, logits, b.ids, b.w, *plan, x, b.sfd_x, first, c.S > 0 ? &second : nullptr, static_cast<hipStream_t>(stream));
+    c.ffn_phase = 2;   // what is left: the down projection
+    if (rc == OCCULT_OK)
+      rc = occult_expert_ffn_packed(&c, plan, b.sfd_x, x, weights, pk, b.epd_h, b.epd_y, b.h_shared, b.y_shared, b.ffn_ws,
+                                    b.ffn_ws_bytes, stream);
+    return rc ? rc : occult_combine(cfg, plan, b.epd_y, b.sfd_y, b.y_shared, b.y, stream);
+  }
   rc = occult_route(cfg, logits, b.ids, b.w, stream);
   if (rc == OCCULT_OK)
     rc = plan_and_dispatch(cfg, b.ids, b.w, plan, b.plan_ws, b.plan_ws_bytes, x, b.sfd_x, static_cast<hipStream_t>(stream));

@@ -50,6 +50,9 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 size_t plan_workspace_bytes(const occult_cfg_t& c);
 int check_dispatch_args(const occult_cfg_t& c, const occult_plan_t* plan, const void* x, const void* sfd_x);
+int check_route_args(const occult_cfg_t& c, const float* logits, const int32_t* ids, const float* w);
+int check_plan_dispatch_args(const occult_cfg_t* cfg, const int32_t* ids, const float* w, const occult_plan_t* plan, void* ws,
+                             size_t ws_bytes, const void* x, const void* sfd_x);
 // occult_plan and occult_dispatch, in one launch where the planner is one
 int plan_and_dispatch(const occult_cfg_t* cfg, const int32_t* ids, const float* w, const occult_plan_t* plan, void* ws,
                       size_t ws_bytes, const void* x, void* sfd_x, hipStream_t s);

@@ -15,19 +15,13 @@
 // f32 path: f32 matrix instructions, for small parity-sized layers.
 #include "common.h"
 #include "gemm.h"
+#include "stream_gemm.h"
 
 #include <type_traits>
 
 namespace occult {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-struct TileInfo {
-  int group, m0, rows, row_base;
-};
-// first output column of a group
-__device__ __forceinline__ int group_col0(const GemmArgs& a, int group) { return a.c_col0 + group * a.c_group_cols; }
 
 // Workgroup id -> (m-tile, n-tile).  Workgroups are handed to the 8 XCDs round-robin and each XCD
 // has its own L2, so the tiles an XCD runs at the same time should share operands: XCD x gets
@@ -55,54 +49,6 @@ static long long mapped_grid(long long m_tiles, int n_tiles) {
   long long chunks = (m_tiles + mc - 1) / mc;
   chunks = (chunks + 7) / 8 * 8;
   return chunks * mc * n_tiles;
-}
-
-// Which group and row block does m-tile `mt` fall in?  Group g owns ceil(rows_g / BM) tiles.
-// Executed by every thread of the first wave; result through LDS.  group = -1: past the end.
-template <int BM>
-__device__ __forceinline__ TileInfo find_tile(const GemmArgs& a, int mt, TileInfo* s_info) {
-  const int lane = threadIdx.x & 63;
-  if (threadIdx.x < 64) {
-    TileInfo ti;
-    ti.group = -1;
-    ti.m0 = ti.rows = ti.row_base = 0;
-    if (a.grp_offset == nullptr) {
-      const int per_group = (a.M + BM - 1) / BM;
-      if (mt < per_group * a.ngroups) {
-        ti.group = mt / per_group;
-        ti.m0 = (mt % per_group) * BM;
-        ti.rows = a.M;
-      }
-      if (lane == 0) *s_info = ti;
-    } else {
-      if (lane == 0) *s_info = ti;
-      int tiles_before = 0;
-      for (int c0 = 0; c0 < a.ngroups; c0 += 64) {
-        const int g = c0 + lane;
-        const int lo = (g < a.ngroups) ? a.grp_offset[g] : 0;
-        const int hi = (g < a.ngroups) ? a.grp_offset[g + 1] : 0;
-        const int nt = (hi - lo + BM - 1) / BM;
-        int incl = nt;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int v = __shfl_up(incl, o, 64);
-          if (lane >= o) incl += v;
-        }
-        const int excl = tiles_before + incl - nt;
-        if (mt >= excl && mt < excl + nt) {   // at most one lane over all chunks
-          ti.group = g;
-          ti.m0 = (mt - excl) * BM;
-          ti.rows = hi - lo;
-          ti.row_base = lo;
-          *s_info = ti;
-        }
-        tiles_before += __shfl(incl, 63, 64);
-        if (tiles_before > mt) break;   // wave-uniform
-      }
-    }
-  }
-  __syncthreads();
-  return *s_info;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -274,255 +220,6 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs a) {
 }
 }  // namespace small
 
-// ------------------------------------------------------------------------------------------
-// bf16 MFMA kernel for groups of a few rows (decode-shaped layers), where the work is streaming
-// every active expert's weights from HBM once.  No LDS tiles, no barriers in the K loop: each wave
-// owns 32 output columns x up to 16*MT tokens over the whole K (or a quarter of it: KSPLIT below)
-// and loads both operands straight into MFMA fragment registers.  v_mfma_f32_16x16x32_bf16 takes 8 consecutive K elements per lane
-// and 4 lanes per row, so one load instruction reads 16 rows x one whole 64-byte sector.  Weights
-// are the row operand: a lane ends up with 4 consecutive output columns of one token (8-byte
-// stores).  The operands of the next K step (4 or 8 KiB of weights per wave) are in flight while
-// the current ones are multiplied; token blocks past the group's rows are skipped.
-//
-// One launch can carry two problems of the same shape class (N, SWIGLU, weight order): workgroups
-// [0, a_blocks) work on `first`, the rest on `second`.  A small batch's shared experts ride with its
-// routed experts this way: alone their few workgroups would stream weights at a fraction of the memory
-// system's rate, and run after the routed experts they would add their whole duration to the call.
-// The second problem has uniform groups and always splits K over the four waves of a workgroup (below);
-// its K may walk several weight matrices (the shared experts' down projection: K = S * f), so that
-// the sum over the shared experts happens in the accumulators and in the in-LDS addition, in K order.
-namespace skinny {
-constexpr int BN_OUT = 32;
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-
-// KSPLIT (for the first problem; the second always does): the four waves of a workgroup take the four quarters of K
-// of ONE column block and add their sums through LDS (quarters in ascending order, so the result is reproducible)
-// instead of taking four column blocks over the whole K.  A wave's stream is then a quarter as long and there are four times as many workgroups, which the
-// hardware hands to whichever CU has room: with whole-K waves a layer's 2000-4000 waves fill the chip's 1024 SIMDs
-// two to four deep, all finish together, and a last partly filled layer of waves costs a whole stream's time.
-template <bool SWIGLU, int MT, bool PACKED, bool KSPLIT>   // MT token blocks of 16 per m-tile; PACKED: weights from a.Bp
-__global__ __launch_bounds__(256) void grouped_gemm_bf16(const GemmArgs first, const GemmArgs second, const int a_blocks) {
-  constexpr int BM = 16 * MT;
-  constexpr int KS = MT <= 2 ? 2 : 1;   // 32-wide K steps per pipeline stage
-  constexpr int NW = SWIGLU ? 2 : 1;
-  static_assert(!PACKED || KS == 2, "the packed order is written for two K steps per stage");
-  __shared__ TileInfo s_info;
-  const bool is_second = (int)blockIdx.x >= a_blocks;   // uniform over the workgroup
-  const GemmArgs& a = is_second ? second : first;
-  const bool ksplit = KSPLIT || is_second;   // uniform: the second problem's workgroups always split K
-  const int cbw = ksplit ? 1 : 4;            // column blocks per workgroup
-  const int n_cb = a.N / BN_OUT;   // column blocks (host: N % 32 == 0)
-  const int wgs_per_mt = (n_cb + cbw - 1) / cbw;
-  int mt, cbq;   // m-tile and group of cbw column blocks
-  if (!is_second) {
-    mt = (int)blockIdx.x / wgs_per_mt;
-    cbq = (int)blockIdx.x % wgs_per_mt;
-  } else {
-    // Uniform groups of P m-tiles each: the P workgroups that stream the same weights (one per m-tile) get ids
-    // 8 apart, so they run on the same XCD (workgroups go to the 8 XCDs round-robin) at about the same time and
-    // all but the first of them find the weights in that XCD's L2.  unit = (group, column block).
-    // (Measured against the four waves of one workgroup taking the m-tiles of one column block, which shares
-    // the weights inside a CU: that was slower from 64 tokens on.)
-    const int b = (int)blockIdx.x - a_blocks;
-    const int P = (a.M + BM - 1) / BM;
-    const int unit = b / (8 * P) * 8 + (b & 7), m = (b >> 3) % P;
-    if (unit >= a.ngroups * wgs_per_mt) return;   // uniform: the grid is padded to whole sets of 8 units
-    mt = unit / wgs_per_mt * P + m;
-    cbq = unit % wgs_per_mt;
-  }
-  TileInfo ti = find_tile<BM>(a, mt, &s_info);
-  if (ti.group < 0) return;
-  // what came through LDS is the same in every lane: kept in scalar registers, so that the addresses built from it
-  // are a scalar base plus a per-lane 32-bit offset
-  ti.group = __builtin_amdgcn_readfirstlane(ti.group);
-  ti.m0 = __builtin_amdgcn_readfirstlane(ti.m0);
-  ti.rows = __builtin_amdgcn_readfirstlane(ti.rows);
-  ti.row_base = __builtin_amdgcn_readfirstlane(ti.row_base);
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int cb = ksplit ? cbq : cbq * 4 + wave;
-  if (cb >= n_cb) return;   // whole-K workgroups meet no barrier after this; K-splitting ones never take it
-  const int n0 = cb * BN_OUT;
-  const int r = lane & 15, c = lane >> 4;
-  const long long widx = __builtin_amdgcn_readfirstlane(a.grp_widx ? a.grp_widx[ti.group] : (a.w_base + ti.group));
-  const int nblk = min(MT, (ti.rows - ti.m0 + 15) / 16);   // token blocks with any valid row
-  const bool reread = is_second && a.M > BM;   // uniform
-
-  // this lane's weight rows (column blocks 0 and 1 of the unit) and token rows, at its 16-byte K group
-  const char* w[NW][2];
-#pragma unroll
-  for (int m = 0; m < NW; ++m)
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-      w[m][nb] = static_cast<const char*>(m == 0 ? a.B : a.B2) +   // loaded like the token rows: lane l on row l / 4
-                 ((widx * a.b_group_stride + (long long)(n0 + nb * 16 + (lane >> 2)) * a.ldb) * 2 + (lane & 3) * 16);
-  // packed order: this wave's unit is one contiguous stream of stages, a load instruction reads 1 KiB of it
-  const long long unit_bytes = (long long)(BN_OUT * NW * 2) * a.kseg;   // one unit's stream inside one weight matrix
-  const char* wp = PACKED ? static_cast<const char*>(a.Bp) + widx * a.bp_group_stride + cb * unit_bytes
-                          : nullptr;   // scalar; a lane reads at lane * 16 from it
-  const unsigned lane16 = lane * 16;
-  // token rows: a scalar base plus a 32-bit byte offset per lane (host: A < 4 GiB).  The MFMA wants lane l to hold row
-  // l % 16, K group l / 16, which would make neighbouring lanes read rows that lie a whole row pitch apart (16 cache
-  // lines looked up per 16 lanes).  The rows are loaded instead with lane l on row l / 4, K group l % 4 (four
-  // neighbouring lanes = one 64-byte sector, 4 lines per 16 lanes) and put into the MFMA's order by a lane permutation
-  // just before use (ds_bpermute: the LDS crossbar, no LDS memory).
-  const char* xbase = static_cast<const char*>(a.A);
-  unsigned xo[MT];
-#pragma unroll
-  for (int tb = 0; tb < MT; ++tb) {
-    int lr = ti.m0 + tb * 16 + (lane >> 2);
-    if (lr >= ti.rows) lr = ti.rows - 1;   // tokens past the group's end repeat its last row; dropped at the end
-    const int logical = ti.row_base + lr;
-    const unsigned src = a.a_rows ? a.a_rows[logical] : logical;
-    xo[tb] = (src * (unsigned)a.lda) * 2u + (lane & 3) * 16;
-  }
-  const int from_lane4 = (r * 4 + c) * 4;   // byte index of the lane that loaded what this lane multiplies
-  auto to_mfma_order = [&](const bf16x8& v) {
-    typedef int i32x4v __attribute__((ext_vector_type(4)));
-    i32x4v t = __builtin_bit_cast(i32x4v, v);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) t[e] = __builtin_amdgcn_ds_bpermute(from_lane4, t[e]);
-    return __builtin_bit_cast(bf16x8, t);
-  };
-
-  f32x4v acc[NW][2][MT];
-#pragma unroll
-  for (int m = 0; m < NW; ++m)
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int tb = 0; tb < MT; ++tb) acc[m][nb][tb] = f32x4v{0.0f, 0.0f, 0.0f, 0.0f};
-
-  const int nst = a.K / (32 * KS);   // pipeline stages along K (host: K % 64 == 0)
-  // byte offset of the current stage inside a weight row; K > kseg walks consecutive weight matrices
-  long long w_off = 0, p_off = 0;   // caller's layout / packed order
-  int w_kin = 0;
-  auto w_advance = [&]() {
-    w_off += 64 * KS;
-    p_off += KS * NW * 2048;
-    w_kin += 32 * KS;
-    if (w_kin >= a.kseg) {   // host: kseg % 64 == 0, so a stage never straddles two matrices
-      w_kin = 0;
-      w_off += (a.b_group_stride - a.kseg) * 2;
-      p_off += a.bp_group_stride - unit_bytes;
-    }
-  };
-  struct Stage {
-    bf16x8 wf[KS][NW][2], xf[KS][MT];
-  };
-  auto load_stage = [&](Stage& st, long long woff, long long poff, int i) {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-      for (int m = 0; m < NW; ++m)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-          {
-            // measured: the streaming hint helps the single-matrix product and hurts the gate/up pair
-            const bf16x8* src = PACKED ? reinterpret_cast<const bf16x8*>(wp + (poff + ((ks * NW + m) * 2 + nb) * 1024) +
-                                                                           (size_t)lane16)
-                                       : reinterpret_cast<const bf16x8*>(w[m][nb] + woff + ks * 64);
-            // (a problem whose groups span several m-tiles reads its weights once per m-tile: those stay cacheable)
-            st.wf[ks][m][nb] = (SWIGLU || reread) ? *src : __builtin_nontemporal_load(src);
-          }
-#pragma unroll
-      for (int tb = 0; tb < MT; ++tb)
-        if (tb < nblk) st.xf[ks][tb] = *reinterpret_cast<const bf16x8*>(xbase + ((long long)i * KS + ks) * 64 + (size_t)xo[tb]);
-    }
-  };
-  auto multiply = [&](const Stage& st) {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      bf16x8 wfo[NW][2];   // the packed order is the MFMA's already
-#pragma unroll
-      for (int m = 0; m < NW; ++m)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) wfo[m][nb] = PACKED ? st.wf[ks][m][nb] : to_mfma_order(st.wf[ks][m][nb]);
-#pragma unroll
-      for (int tb = 0; tb < MT; ++tb)
-        if (tb < nblk) {
-          const bf16x8 xf = to_mfma_order(st.xf[ks][tb]);
-#pragma unroll
-          for (int m = 0; m < NW; ++m)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-              acc[m][nb][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wfo[m][nb], xf, acc[m][nb][tb], 0, 0, 0);
-        }
-    }
-  };
-
-  // this wave's stages of K
-  const int i_begin = ksplit ? wave * nst / 4 : 0, i_end = ksplit ? (wave + 1) * nst / 4 : nst;
-  if (i_begin > 0) {
-    const int kin = i_begin * 32 * KS, mat = kin / a.kseg;
-    w_kin = kin - mat * a.kseg;
-    w_off = ((long long)mat * a.b_group_stride + w_kin) * 2;
-    p_off = mat * a.bp_group_stride + (long long)(w_kin / 32) * (NW * 2048);
-  }
-  if (i_begin < i_end) {   // wave-uniform
-    Stage s0, s1;
-    load_stage(s0, w_off, p_off, i_begin);
-    for (int i = i_begin; i < i_end; i += 2) {
-      // past the end the last stage is fetched again and not used
-      const bool more1 = i + 1 < i_end;
-      if (more1) w_advance();
-      load_stage(s1, w_off, p_off, more1 ? i + 1 : i);
-      multiply(s0);
-      const bool more2 = i + 2 < i_end;
-      if (more2) w_advance();
-      load_stage(s0, w_off, p_off, more2 ? i + 2 : (more1 ? i + 1 : i));
-      if (more1) multiply(s1);
-    }
-  }
-  if (ksplit) {   // uniform over the workgroup
-    // waves 1..3 hand their sums to wave 0, which adds them in that order and writes the tile
-    __shared__ float s_red[3][NW * 2 * MT * 4][64];
-    if (wave > 0) {
-#pragma unroll
-      for (int m = 0; m < NW; ++m)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int tb = 0; tb < MT; ++tb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s_red[wave - 1][((m * 2 + nb) * MT + tb) * 4 + e][lane] = acc[m][nb][tb][e];
-    }
-    __syncthreads();
-    if (wave > 0) return;
-#pragma unroll
-    for (int wv = 0; wv < 3; ++wv)
-#pragma unroll
-      for (int m = 0; m < NW; ++m)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int tb = 0; tb < MT; ++tb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[m][nb][tb][e] += s_red[wv][((m * 2 + nb) * MT + tb) * 4 + e][lane];
-  }
-
-  // acc element e of lane l: token l%16 of its block, output column nb*16 + (l/16)*4 + e of the unit
-#pragma unroll
-  for (int tb = 0; tb < MT; ++tb) {
-    const int token = ti.m0 + tb * 16 + r;
-    if (token < ti.rows) {
-      __bf16* crow = static_cast<__bf16*>(a.C) + (long long)(ti.row_base + token) * a.ldc + group_col0(a, ti.group) + n0 + c * 4;
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float g = acc[0][nb][tb][e];
-          v[e] = SWIGLU ? g / (1.0f + __expf(-g)) * acc[NW - 1][nb][tb][e] : g;
-        }
-        uint2 pk;
-        pk.x = pack_bf16(v[0], v[1]);
-        pk.y = pack_bf16(v[2], v[3]);
-        *reinterpret_cast<uint2*>(crow + nb * 16) = pk;
-      }
-    }
-  }
-}
-}  // namespace skinny
 
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA kernel, main variant (prefill-shaped layers).  Block = 256 threads = 4 waves (2 x 2),
@@ -1257,7 +954,7 @@ static int launch_skinny(const GemmArgs& a, const GemmArgs* b, bool swiglu, int 
     OCC_REQUIRE(b->N == a.N && b->grp_offset == nullptr && (b->Bp != nullptr) == (a.Bp != nullptr) && a.kseg == a.K &&
                     b->K % b->kseg == 0,
                 OCCULT_EINVAL, "the two problems of one weight-streaming launch differ in shape class");
-    blocks += (b->ngroups * n_cb + 7) / 8 * 8 * (long long)((b->M + 31) / 32);   // whole sets of 8 units
+    blocks += skinny::second_blocks(*b);
   }
   OCC_REQUIRE(blocks < (1ll << 31), OCCULT_EINVAL, "grouped GEMM grid too large");
   const dim3 grid((unsigned)blocks), block(256);
@@ -1265,10 +962,10 @@ static int launch_skinny(const GemmArgs& a, const GemmArgs* b, bool swiglu, int 
   const bool packed = a.Bp != nullptr && (a.kseg == a.K || a.K % a.kseg == 0);
   const GemmArgs& b2 = b ? *b : a;
   const int ab = (int)a_blocks;
-  if (swiglu && packed) hipLaunchKernelGGL((skinny::grouped_gemm_bf16<true, 2, true, true>), grid, block, 0, s, a, b2, ab);
-  else if (swiglu) hipLaunchKernelGGL((skinny::grouped_gemm_bf16<true, 2, false, true>), grid, block, 0, s, a, b2, ab);
-  else if (packed) hipLaunchKernelGGL((skinny::grouped_gemm_bf16<false, 2, true, false>), grid, block, 0, s, a, b2, ab);
-  else hipLaunchKernelGGL((skinny::grouped_gemm_bf16<false, 2, false, false>), grid, block, 0, s, a, b2, ab);
+  if (swiglu && packed) hipLaunchKernelGGL((skinny::grouped_gemm_bf16<true, 2, true, true>), grid, block, 0, s, a, b2, ab, skinny::NoFront{});
+  else if (swiglu) hipLaunchKernelGGL((skinny::grouped_gemm_bf16<true, 2, false, true>), grid, block, 0, s, a, b2, ab, skinny::NoFront{});
+  else if (packed) hipLaunchKernelGGL((skinny::grouped_gemm_bf16<false, 2, true, false>), grid, block, 0, s, a, b2, ab, skinny::NoFront{});
+  else hipLaunchKernelGGL((skinny::grouped_gemm_bf16<false, 2, false, false>), grid, block, 0, s, a, b2, ab, skinny::NoFront{});
   OCC_LAUNCH_CHECK("grouped_gemm");
   return OCCULT_OK;
 }
@@ -1511,14 +1208,9 @@ extern "C" int occult_expert_ffn_ws_bytes(const occult_cfg_t* cfg, size_t* ws_by
   return OCCULT_OK;
 }
 
-static int expert_ffn_impl(const occult_cfg_t* cfg, const occult_plan_t* plan, const void* sfd_x,
-                           const void* x, const occult_weights_t* weights, const void* packed, void* epd_h,
-                           void* epd_y, void* h_shared, void* y_shared, void* ws, size_t ws_bytes,
-                           occult_stream_t stream, void* epd_gu = nullptr, void* gu_shared = nullptr) {
-  int rc = check_cfg(cfg);
-  if (rc) return rc;
-  const occult_cfg_t c = *cfg;
-  if (c.T == 0) return OCCULT_OK;
+namespace occult {
+int check_ffn_args(const occult_cfg_t& c, const occult_plan_t* plan, const void* sfd_x, const void* x,
+                   const occult_weights_t* weights, const void* epd_h, const void* epd_y, const void* h_shared, const void* y_shared) {
   OCC_REQUIRE(plan && plan->exp_offset && plan->pos_expert && plan->epd_sfd_row, OCCULT_ENULLPTR,
               "plan or one of its tables is NULL");
   OCC_REQUIRE(weights && weights->w_gate && weights->w_up && weights->w_down, OCCULT_ENULLPTR,
@@ -1536,27 +1228,62 @@ static int expert_ffn_impl(const occult_cfg_t* cfg, const occult_plan_t* plan, c
                   aligned16(h_shared) && aligned16(y_shared) && aligned16(weights->w_gate) &&
                   aligned16(weights->w_up) && aligned16(weights->w_down),
               OCCULT_EALIGN, "a buffer is not 16-byte aligned");
+  return OCCULT_OK;
+}
+
+bool forward_uses_front(const occult_cfg_t& c) {
+  return c.dtype == OCCULT_BF16 && c.ffn_phase == 0 && fits_front(c) && (long long)c.T * c.k < 24ll * c.E &&
+         c.f % skinny::BN_OUT == 0 && (c.S == 0 || pairs_shared_with_routed(c));
+}
+
+// the two problems of the gate/up product: h = silu(x W_gate^T) * (x W_up^T); the shared experts as S groups over the rows of x
+static void gate_up_products(const occult_cfg_t& c, const void* x, const occult_weights_t* weights, const void* packed, void* epd_h,
+                             void* h_shared, GemmArgs* first, GemmArgs* second) {
+  GemmArgs g1{}, a1{};
+  a1.A = x; g1.lda = a1.lda = c.d;
+  g1.B = a1.B = weights->w_gate; g1.B2 = a1.B2 = weights->w_up;
+  g1.b_group_stride = a1.b_group_stride = (long long)c.f * c.d;
+  g1.ldb = a1.ldb = g1.kseg = a1.kseg = g1.K = a1.K = c.d;
+  g1.Bp = packed; g1.bp_group_stride = a1.bp_group_stride = 4ll * c.f * c.d;
+  g1.N = a1.N = c.f;
+  g1.C = epd_h; g1.ldc = c.f;
+  a1.C = h_shared; a1.ldc = c.S * c.f; a1.c_group_cols = c.f;
+  g1.ngroups = c.E;
+  a1.w_base = c.E; a1.ngroups = c.S; a1.M = c.T; a1.a_rows_total = c.T;
+  *first = g1;
+  *second = a1;
+}
+
+void front_products(const occult_cfg_t& c, const void* x, const occult_weights_t* weights, const void* packed, void* epd_h,
+                    void* h_shared, GemmArgs* first, GemmArgs* second) {
+  gate_up_products(c, x, weights, packed, epd_h, h_shared, first, second);
+  first->A = x;
+  second->Bp = packed;
+}
+}  // namespace occult
+
+static int expert_ffn_impl(const occult_cfg_t* cfg, const occult_plan_t* plan, const void* sfd_x,
+                           const void* x, const occult_weights_t* weights, const void* packed, void* epd_h,
+                           void* epd_y, void* h_shared, void* y_shared, void* ws, size_t ws_bytes,
+                           occult_stream_t stream, void* epd_gu = nullptr, void* gu_shared = nullptr) {
+  int rc = check_cfg(cfg);
+  if (rc) return rc;
+  const occult_cfg_t c = *cfg;
+  if (c.T == 0) return OCCULT_OK;
+  rc = check_ffn_args(c, plan, sfd_x, x, weights, epd_h, epd_y, h_shared, y_shared);
+  if (rc) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int n_epd = c.T * c.k;
 
   const bool do1 = c.ffn_phase != 2, do2 = c.ffn_phase != 1;
 
   if (do1) {   // h = silu(x W_gate^T) * (x W_up^T); the S shared experts as S groups over the same T rows
-    GemmArgs g1{}, a1{};
-    g1.A = sfd_x; g1.lda = c.d; g1.a_rows = plan->epd_sfd_row;
-    a1.A = x; a1.lda = c.d;
-    g1.B = a1.B = weights->w_gate; g1.B2 = a1.B2 = weights->w_up;
-    g1.b_group_stride = a1.b_group_stride = (long long)c.f * c.d;
-    g1.ldb = a1.ldb = g1.kseg = a1.kseg = g1.K = a1.K = c.d;
-    g1.Bp = packed; g1.bp_group_stride = a1.bp_group_stride = 4ll * c.f * c.d;
-    g1.N = a1.N = c.f;
-    g1.C = epd_h; g1.ldc = c.f;
+    GemmArgs g1, a1;
+    gate_up_products(c, x, weights, packed, epd_h, h_shared, &g1, &a1);
+    g1.A = sfd_x; g1.a_rows = plan->epd_sfd_row; g1.a_rows_total = sfd_rows_max(c);
     g1.C2 = epd_gu;      // rows of 2f: [gate | up]
-    a1.C = h_shared; a1.ldc = c.S * c.f; a1.c_group_cols = c.f;
     a1.C2 = gu_shared;   // rows of S * 2f: per shared expert [gate | up]
-    g1.grp_offset = plan->exp_offset; g1.grp_widx = plan->pos_expert; g1.ngroups = c.E;
-    g1.a_rows_total = sfd_rows_max(c);
-    a1.w_base = c.E; a1.ngroups = c.S; a1.M = c.T; a1.a_rows_total = c.T;
+    g1.grp_offset = plan->exp_offset; g1.grp_widx = plan->pos_expert;
     if (pairs_shared_with_routed(c)) {
       a1.Bp = packed;
       rc = launch_skinny(g1, &a1, true, n_epd, s);

@@ -51,6 +51,18 @@ int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total
 int launch_gemm_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, int rows_b,
                      hipStream_t s);
 
+// A forward pass of a few tokens up to the gate/up product of its experts in one launch (plan.hip): routing, plan, row copies, and the
+// products `first` (routed experts; its rows are those of x, found by the launch's own routing) and `second` (shared ones, or NULL)
+bool fits_front(const occult_cfg_t& c);
+int launch_front(const occult_cfg_t& c, const float* logits, int32_t* ids, float* w, const occult_plan_t& p, const void* x, void* sfd_x,
+                 const GemmArgs& first, const GemmArgs* second, hipStream_t s);
+// whether the expert products of a forward pass without kept pre-activations take that launch, and its two problems
+bool forward_uses_front(const occult_cfg_t& c);
+void front_products(const occult_cfg_t& c, const void* x, const occult_weights_t* weights, const void* packed, void* epd_h,
+                    void* h_shared, GemmArgs* first, GemmArgs* second);
+int check_ffn_args(const occult_cfg_t& c, const occult_plan_t* plan, const void* sfd_x, const void* x,
+                   const occult_weights_t* weights, const void* epd_h, const void* epd_y, const void* h_shared, const void* y_shared);
+
 // compute units of the current device
 int device_cu_count(int* out);
 

@@ -19,6 +19,8 @@
 // blocks itself (no scan launch) up to kCountsMaxBlocks blocks, and counts all tokens itself (one launch) up
 // to kSingleMaxTokens tokens.
 #include "common.h"
+#include "route_tokens.h"
+#include "stream_gemm.h"
 
 #include <mutex>
 
@@ -264,9 +266,9 @@ struct Rows {
 // FT: tokens of a workgroup.  VPL > 0: a wave has a token, whose row it requests at the start and copies to the SFD rows once
 // it knows them (plan and dispatch in two launches, both chains of latencies: see launch_plan_dispatch).
 template <int KMAX, Bases FROM, int FT, int VPL>
-__global__ __launch_bounds__(kTPB) void plan_fill(const int32_t* __restrict__ ids, const float* __restrict__ w, int T, int k,
-                                                  int E, int D, int G, int M1, int nblk, const int32_t* __restrict__ expert_pos,
-                                                  const int32_t* __restrict__ blk, const occult_plan_t p, const Rows rows) {
+__device__ __forceinline__ void fill_block(int wg, const int32_t* __restrict__ ids, const float* __restrict__ w, int T, int k, int E,
+                                           int D, int G, int M1, int nblk, const int32_t* __restrict__ expert_pos,
+                                           const int32_t* __restrict__ blk, const occult_plan_t& p, const Rows& rows) {
   static_assert(VPL == 0 || FT == kTPB / 64, "a token per wave");
   constexpr int PER_BLOCK = kTPB / FT;   // workgroups that share a block of 256 tokens
   __shared__ int s_pos[OCCULT_MAX_E];
@@ -276,7 +278,7 @@ __global__ __launch_bounds__(kTPB) void plan_fill(const int32_t* __restrict__ id
   __shared__ int s_base[kMaxCols];     // rank of my block's first token
   __shared__ int s_slot[FT][KMAX];   // my tokens' slots: device << 16 | position, or -1
   const int tl = threadIdx.x, C = D + E;
-  const int block = blockIdx.x / PER_BLOCK, first = (blockIdx.x % PER_BLOCK) * FT;   // first: my first bit
+  const int block = wg / PER_BLOCK, first = (wg % PER_BLOCK) * FT;   // first: my first bit
   const int t0 = block * kTPB;
   const int lane = tl & 63, wave = tl >> 6;
   u32x4 v[VPL > 0 ? VPL : 1];   // VPL: the row of token t0 + first + wave
@@ -337,7 +339,7 @@ __global__ __launch_bounds__(kTPB) void plan_fill(const int32_t* __restrict__ id
   }
   if constexpr (FROM != Bases::kScanned) {
     __syncthreads();
-    scan_columns(s_total, s_base, s_pos, blockIdx.x == 0, T, k, E, D, p);
+    scan_columns(s_total, s_base, s_pos, wg == 0, T, k, E, D, p);
     __syncthreads();
     for (int c = tl; c < C; c += kTPB) s_base[c] += s_before[c];
   }
@@ -390,6 +392,118 @@ __global__ __launch_bounds__(kTPB) void plan_fill(const int32_t* __restrict__ id
     }
   }
 }
+
+template <int KMAX, Bases FROM, int FT, int VPL>
+__global__ __launch_bounds__(kTPB) void plan_fill(const int32_t* __restrict__ ids, const float* __restrict__ w, int T, int k,
+                                                  int E, int D, int G, int M1, int nblk, const int32_t* __restrict__ expert_pos,
+                                                  const int32_t* __restrict__ blk, const occult_plan_t p, const Rows rows) {
+  fill_block<KMAX, FROM, FT, VPL>((int)blockIdx.x, ids, w, T, k, E, D, G, M1, nblk, expert_pos, blk, p, rows);
+}
+
+// A forward pass of at most kFrontTokens tokens up to the gate/up product in ONE launch: workgroups [0, plan_blocks) plan and copy
+// rows as plan_fill does, the next a_blocks stream the routed experts' weights, the others the shared experts'.  Each of the first
+// two kinds routes all tokens for itself, four at a time: a chain of about 2 us, in place of a launch of that length, one of 6 us and the
+// gaps behind both.  The products read the rows of x that the plan's tables name as copies; same bits.
+// Which batches (us per pass, separate / this, three layers in turn; d = 2048 unless given):
+//  - up to 4 tokens, one round of routing: all.  1 token: 60 + 4 experts of f = 1408, k = 4 53.0 / 44.0, 64 of 1024, k = 8 47.0 / 37.4, 256 of
+//    512, d = 512 33.3 / 24.6; 4 tokens 75.2 / 65.0, 81.6 / 72.8, 36.9 / 27.2; pruned 92.7 / 84.0.
+//  - more where the workgroups that route are few for what each of them streams (128 bytes per element of K), since every round of them
+//    over the CUs routes again: 8 tokens of 60 + 4 113 / 107, 64 + 2 135 / 125, 64 of 1024 116 / 110, d = 1024 and f = 704 53 / 45; 12 tokens
+//    139 / 131, d = 4096 330 / 320, 64 of 1024 139 / 138.  Past the line: d = 1024, f = 1408, k = 8, 8 tokens 94 / 96, d = 512 66 / 72; 16 tokens
+//    of 64 of 1024 147 / 149.  Not with a second round of selection or more than 64 experts to look at: 8 tokens pruned 130 / 134 and, by
+//    similarity, 134 / 148, 256 experts of f = 1024, d = 1024 93 / 100.
+constexpr int kFrontTokens = 12, kFrontSlots = 8;
+
+template <int EPL, bool PRUNE, int VPL>
+struct Few {
+  static constexpr bool kOn = true;
+  const float* logits;
+  int T, E, k, D, G, M1;
+  const int32_t* expert_pos;
+  int n_d, prune_mode, renorm;
+  const int32_t* sim_table;
+  int32_t* ids;
+  float* w;
+  occult_plan_t p;
+  Rows rows;
+  int plan_blocks;
+
+  struct Shared {
+    int ids[kFrontTokens * kFrontSlots];
+    float w[kFrontTokens * kFrontSlots];
+    unsigned tokens[OCCULT_MAX_E];   // of each position, as bits
+    int expert[OCCULT_MAX_E];        // at each position
+  };
+  __device__ static Shared& shared() {
+    __shared__ Shared s;
+    return s;
+  }
+
+  // true: the workgroup was one of the plan's
+  __device__ __forceinline__ bool begin(int bid, int a_blocks) const {
+    if (bid >= plan_blocks + a_blocks) return false;   // the shared experts' need no routing
+    Shared& s = shared();
+    const int tid = threadIdx.x;
+    const bool plans = bid < plan_blocks;
+    if (!plans)
+      for (int e = tid; e < E; e += kTPB) {
+        s.tokens[e] = 0;
+        s.expert[expert_pos ? expert_pos[e] : e] = e;
+      }
+    for (int b = 0; b * 4 < T; ++b)
+      route_tokens<64, EPL, PRUNE>(b, logits, T, E, k, D, G, expert_pos, n_d, prune_mode, renorm, sim_table, s.ids, s.w);
+    __syncthreads();
+    if (plans) {
+      if (bid == 0 && tid < T * k) {
+        ids[tid] = s.ids[tid];
+        w[tid] = s.w[tid];
+      }
+      fill_block<kFrontSlots, Bases::kIds, 4, VPL>(bid, s.ids, s.w, T, k, E, D, G, M1, 1, expert_pos, nullptr, p, rows);
+      return true;
+    }
+    if (tid < T * k) {
+      const int e = s.ids[tid];
+      atomicOr(&s.tokens[expert_pos ? expert_pos[e] : e], 1u << (tid / k));
+    }
+    __syncthreads();
+    return false;
+  }
+
+  // the mt-th position that has rows (they are one tile); every wave for itself, wave-uniform.  group = -1: there are fewer
+  __device__ __forceinline__ TileInfo tile(int mt) const {
+    static_assert(kFrontTokens <= 32, "a position's tokens are the bits of a word, its rows one tile of the kernel");
+    const unsigned* tokens = shared().tokens;
+    const int lane = threadIdx.x & 63;
+    TileInfo ti{-1, 0, 0, 0};
+    for (int c0 = 0; c0 < E; c0 += 64) {
+      const int n = c0 + lane < E ? __popc(tokens[c0 + lane]) : 0;
+      unsigned long long active = __ballot(n > 0);
+      const int here = __popcll(active);
+      int at = 64;   // the position's lane, if it is among these
+      if (mt < here) {
+        for (int i = 0; i < mt; ++i) active &= active - 1;
+        at = __ffsll((long long)active) - 1;
+      }
+      int before = lane < at ? n : 0;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) before += __shfl_xor(before, o, 64);
+      ti.row_base += before;
+      if (at < 64) {
+        ti.group = c0 + at;
+        ti.rows = __shfl(n, at, 64);
+        break;
+      }
+      mt -= here;
+    }
+    return ti;
+  }
+  __device__ __forceinline__ int matrix(int group) const { return shared().expert[group]; }
+  __device__ __forceinline__ unsigned row(int group, int lr) const {   // the token of its row lr
+    unsigned m = shared().tokens[group];
+    for (int i = 0; i < lr; ++i) m &= m - 1;
+    return __ffs((int)m) - 1;
+  }
+};
 
 size_t plan_workspace_bytes(const occult_cfg_t& c);
 
@@ -524,6 +638,59 @@ static int check_plan_ws_args(const occult_cfg_t* cfg, const int32_t* ids, const
 }
 
 namespace occult {
+// routed workgroups of the launch: a tile per position with rows
+static long long front_blocks(const occult_cfg_t& c) { return (long long)min_i(c.T * c.k, c.E) * (c.f / skinny::BN_OUT); }
+
+bool fits_front(const occult_cfg_t& c) {
+  if (c.T < 1 || c.T > kFrontTokens || c.k > kFrontSlots || (size_t)c.d * elem_size(c) / 16 > 64 * 8) return false;
+  return c.T <= 4 || (c.n_d == 0 && c.E <= 64 && 10 * front_blocks(c) <= 11ll * c.d);
+}
+
+int check_plan_dispatch_args(const occult_cfg_t* cfg, const int32_t* ids, const float* w, const occult_plan_t* plan, void* ws,
+                             size_t ws_bytes, const void* x, const void* sfd_x) {
+  const int rc = check_plan_ws_args(cfg, ids, w, plan, ws, ws_bytes);
+  return rc ? rc : check_dispatch_args(*cfg, plan, x, sfd_x);
+}
+
+int launch_front(const occult_cfg_t& c, const float* logits, int32_t* ids, float* w, const occult_plan_t& p, const void* x, void* sfd_x,
+                 const GemmArgs& first, const GemmArgs* second, hipStream_t s) {
+  const int vecs = c.d * elem_size(c) / 16, plan_blocks = (c.T + 3) / 4;
+  const int a_blocks = (int)front_blocks(c);
+  const Rows rows{static_cast<const u32x4*>(x), static_cast<u32x4*>(sfd_x), vecs};
+  const long long blocks = plan_blocks + a_blocks + (second ? skinny::second_blocks(*second) : 0);
+  OCC_REQUIRE(blocks < (1ll << 31), OCCULT_EINVAL, "grouped GEMM grid too large");
+  const dim3 grid((unsigned)blocks), block(kTPB);
+  const bool prune = c.n_d > 0, packed = first.Bp != nullptr, wide = vecs > 64 * 4, many = c.E > 64;
+#define OCC_FRONT(N, P, V, K)                                                                                                \
+  hipLaunchKernelGGL((skinny::grouped_gemm_bf16<true, 2, K, true, Few<N, P, V>>), grid, block, 0, s, first,                  \
+                     second ? *second : first, a_blocks,                                                                     \
+                     (Few<N, P, V>{logits, c.T, c.E, c.k, c.D, c.E / c.D, merge_width(c), c.expert_pos, c.n_d, c.prune_mode, \
+                                   c.renorm, c.sim_table, ids, w, p, rows, plan_blocks}))
+#define OCC_FRONT_K(N, P, V)              \
+  do {                                    \
+    if (packed) OCC_FRONT(N, P, V, true); \
+    else OCC_FRONT(N, P, V, false);       \
+  } while (0)
+#define OCC_FRONT_V(N, P)           \
+  do {                              \
+    if (wide) OCC_FRONT_K(N, P, 8); \
+    else OCC_FRONT_K(N, P, 4);      \
+  } while (0)
+#define OCC_FRONT_P(N)                \
+  do {                                \
+    if (prune) OCC_FRONT_V(N, true);  \
+    else OCC_FRONT_V(N, false);       \
+  } while (0)
+  if (many) OCC_FRONT_P(4);
+  else OCC_FRONT_P(1);
+#undef OCC_FRONT_P
+#undef OCC_FRONT_V
+#undef OCC_FRONT_K
+#undef OCC_FRONT
+  OCC_LAUNCH_CHECK("grouped_gemm");
+  return OCCULT_OK;
+}
+
 int plan_and_dispatch(const occult_cfg_t* cfg, const int32_t* ids, const float* w, const occult_plan_t* plan, void* ws,
                       size_t ws_bytes, const void* x, void* sfd_x, hipStream_t s) {
   int rc = check_plan_ws_args(cfg, ids, w, plan, ws, ws_bytes);

@@ -82,6 +82,47 @@ def test_forward_of_small_batches(T, d, E, k, D, dtype):
         assert torch.equal(getattr(one, name).view(torch.uint8), getattr(steps, name).view(torch.uint8)), name
 
 
+@pytest.mark.parametrize("T,d,f,E,S,k,D,n_d,mode,packed", [
+    (1, 256, 64, 60, 4, 4, 4, 0, 1, True), (1, 64, 64, 2, 0, 1, 1, 0, 1, False), (2, 576, 128, 8, 1, 8, 2, 0, 1, False),
+    (3, 4096, 64, 130, 0, 8, 10, 2, 1, False), (4, 192, 64, 256, 1, 8, 8, 2, 3, True), (4, 128, 64, 64, 0, 6, 16, 3, 2, False),
+    (4, 2112, 192, 64, 2, 7, 64, 0, 1, True), (5, 704, 64, 64, 0, 8, 64, 0, 1, False), (8, 320, 192, 16, 2, 2, 4, 0, 1, True),
+    (12, 1408, 384, 64, 1, 8, 8, 0, 1, False), (12, 128, 64, 61, 0, 3, 1, 0, 1, True),
+    # routed and planned in launches of their own
+    (13, 320, 64, 16, 2, 2, 4, 0, 1, True), (5, 128, 128, 65, 0, 3, 5, 0, 1, False), (5, 128, 128, 16, 0, 3, 4, 2, 1, False),
+    (12, 256, 384, 64, 0, 8, 8, 0, 1, False), (4, 64, 64, 16, 0, 9, 4, 0, 1, False), (1, 4160, 64, 16, 1, 2, 4, 0, 1, True),
+])
+def test_forward_of_a_few_tokens(T, d, f, E, S, k, D, n_d, mode, packed):
+    """Routing, plan, row copies and the gate/up product in one launch, and the sizes around it: every workgroup's own routing and row
+    tiles (one or three rounds of tokens, pruned each way, ties, scores that are no numbers, experts placed anywhere, more than
+    64 of them) give the bits of the separate steps in every buffer."""
+    say(f"forward T={T} d={d} f={f} E={E} S={S} k={k} D={D} n_d={n_d} mode={mode} packed={packed}")
+    dev = require_gpu()
+    gen = torch.Generator().manual_seed(T * E + d)
+    bf = lambda *shape: torch.randn(shape, generator=gen).mul_(0.1).to(torch.bfloat16).to(dev)
+    x, w = bf(T, d), (bf(E + S, f, d), bf(E + S, f, d), bf(E + S, d, f))
+    lg = torch.randn((T, E), generator=gen).mul_(2).round().mul_(0.5)   # many ties
+    lg[0, 0], lg[T - 1, E - 1], lg[T // 2, E // 2] = float("nan"), float("inf"), float("-inf")
+    lg = lg.to(dev)
+    pos = torch.randperm(E, generator=gen).to(torch.int32)
+    table = None
+    if mode == 3:
+        table = torch.stack([p[p != e] for e, p in ((e, torch.randperm(E, generator=gen)) for e in range(E))]).to(torch.int32)
+    one, steps = (OccultLayer(T, d, f, E, S, k, D, "bf16", n_d, mode, 1, pos, sim_table=table) for _ in range(2))
+    for layer in (one, steps):
+        if packed:
+            layer.pack_weights(*w)
+    one.forward(lg, x, *w)
+    steps.route(lg)
+    steps.make_plan()
+    steps.dispatch(x)
+    steps.expert_ffn(x, *w)
+    steps.combine()
+    torch.cuda.synchronize()
+    for name in ("plan_mem", "ids", "w", "sfd_x", "sfd_y", "y", "epd_h", "epd_y", "h_shared", "y_shared"):
+        a, b = getattr(one, name), getattr(steps, name)
+        assert a is None or torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
 @pytest.mark.parametrize("S,one_call", [(0, True), (1, True), (0, False), (1, False)])
 def test_kept_pre_activations_are_of_the_present_batch(S, one_call):
     """A training pass on one batch, a plain one on another, the backward on the latter: what a layer gives that has only
