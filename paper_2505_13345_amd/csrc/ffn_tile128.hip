@@ -25,6 +25,13 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // XCD (workgroups go to the XCDs round-robin).  The row tiles of one expert and weight block so run next to each
 // other on one XCD and the weights leave HBM once; and no XCD gets a whole tile more than an eighth of both problems'.
 //
+// What is left of an XCD's run beyond whole rounds of its blocks is cut in two by columns where every half then still finds
+// a block of its own (`halved`): a lone round costs the time of a whole tile whoever takes part in it, a half tile little more than
+// half of that.  Its K loop multiplies half of the weight rows, and the ring's stages hold so many fewer.
+// (gate/up product of 500 tokens of 64 + 2 experts, d = 2048, f = 1408, 24 tiles beyond three rounds: 161 us, 140 without these tiles, 150
+// in halves, pass 273 -> 265; K = 1408 of a training step's 1000 tokens 107 -> 98.  More than half a round is left whole: the halves
+// would need a second one.)
+//
 // One launch carries two problems of the same N: `second` (uniform groups: the shared experts) has its tiles at the
 // front of every XCD's run because its K can be longer (the shared down projection walks S matrices).
 namespace t128 {
@@ -41,7 +48,7 @@ __device__ __forceinline__ float swiglu_div(float g, float u) { return g / (1.0f
 
 // one output tile; every field is wave-uniform
 struct Tile {
-  int valid, is_second, group, m0, n0, rows, row_base, widx;
+  int valid, is_second, group, m0, n0, rows, row_base, widx, half;   // half: BN_OUT / 2 columns from n0
 };
 
 // SAVE (with SWIGLU): the gate and up pre-activations are stored too (C2).
@@ -92,8 +99,16 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
   const int cnt1 = __builtin_amdgcn_readfirstlane((total1 >> 3) + (xcd >= 8 - over1));
   const int lo1 = __builtin_amdgcn_readfirstlane(xcd * (total1 >> 3) + max(0, xcd - (8 - over1)));
   const int cnt2 = (total2 >> 3) + (xcd < over2), lo2 = xcd * (total2 >> 3) + min(xcd, over2);
+  const int whole = (cnt1 + cnt2) / stride * stride, left = cnt1 + cnt2 - whole;   // slots of whole rounds, and beyond
+  const bool halved = whole > 0 && 2 * left <= stride;   // so a block takes at most one half, as its last tile and not its first
   auto tile_at = [&](int slot) {
     Tile t{};
+    int second_half = 0;
+    if (halved && slot >= whole) {
+      t.half = 1;
+      second_half = (slot - whole) & 1;
+      slot = whole + ((slot - whole) >> 1);
+    }
     if (slot < cnt2) {
       const int n = lo2 + slot, per_group = mt2 * n_tiles, within = n % per_group;
       t.valid = t.is_second = 1;
@@ -118,9 +133,10 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
       t.m0 = within % mt * BM; t.n0 = within / mt * BN_OUT;
       t.widx = first.grp_widx ? first.grp_widx[t.group] : first.w_base + t.group;
     }
+    t.half = __builtin_amdgcn_readfirstlane(t.half);
     t.group = __builtin_amdgcn_readfirstlane(t.group);
     t.m0 = __builtin_amdgcn_readfirstlane(t.m0);
-    t.n0 = __builtin_amdgcn_readfirstlane(t.n0);
+    t.n0 = __builtin_amdgcn_readfirstlane(t.n0 + second_half * (BN_OUT / 2));
     t.rows = __builtin_amdgcn_readfirstlane(t.rows);
     t.row_base = __builtin_amdgcn_readfirstlane(t.row_base);
     t.widx = __builtin_amdgcn_readfirstlane(t.widx);
@@ -140,6 +156,7 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
     long long kb;                     // byte offset of the K tile inside a token row (kt) and a weight row
     int kin, kseg;                    // K > kseg walks consecutive weight matrices
     long long ka, seg_step;
+    unsigned lds_b[2];                // where weight-row loads 0..3 and 4..7 go in a stage
   } ld;
   // tile row of this lane for index slot `lane` (0..31) of s_idx, clamped to the group
   auto idx_row = [&](const Tile& t, int r) { return t.row_base + min(t.m0 + r, t.rows - 1); };
@@ -149,6 +166,9 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
       load_to_lds_4(reinterpret_cast<const char*>(a_rows + idx_row(t, wave * 32 + (lane & 31))),
                     __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) int*)&s_idx[wave][0]));
   };
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+  const unsigned lds_a = __builtin_amdgcn_readfirstlane(lds0 + wave * 4096);
+  const unsigned lds_b = __builtin_amdgcn_readfirstlane(lds0 + A_BYTES);
   auto start_loading = [&](const Tile& t) {   // the rows requested for t have landed
     const bool gather = OCC_PICK(t, a_rows) != nullptr;
     const unsigned lda = OCC_PICK(t, lda), ldb = OCC_PICK(t, ldb);
@@ -164,7 +184,8 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const unsigned chunk = (lane & 7) ^ ((i * 4 + (lane >> 4)) & 7);
-      const int blk = wave * 4 + (i >> 1);
+      // (a half tile's weight rows are loads 0..3 of the four waves; what the tile before requests of it beyond them are these again)
+      const int blk = t.half ? wave * 2 + ((i & 3) >> 1) : wave * 4 + (i >> 1);
       int ncol = t.n0 + (SWIGLU ? (blk >> 1) * 16 : blk * 16) + (i & 1) * 8 + lrow;
       if (ncol >= first.N) ncol = first.N - 1;
       ld.b_off[i] = ((unsigned)ncol * ldb + chunk * 8) * 2;   // host: a weight matrix is below 4 GiB
@@ -173,21 +194,21 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
     ld.a = static_cast<const char*>(OCC_PICK(t, A));
     ld.w_even = static_cast<const char*>(OCC_PICK(t, B)) + t.widx * stride_b * 2;
     ld.w_odd = SWIGLU ? static_cast<const char*>(OCC_PICK(t, B2)) + t.widx * stride_b * 2 : ld.w_even;
+    ld.lds_b[0] = lds_b + (t.half ? wave * 4096 : wave * 8192);
+    ld.lds_b[1] = ld.lds_b[0] + (t.half ? 16384 : 4096);   // a half tile: beyond its weight rows
     ld.ka = ld.kb = 0;
     ld.kin = 0;
     ld.kseg = OCC_PICK(t, kseg);
     ld.seg_step = (stride_b - ld.kseg) * 2;
   };
-  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
-  const unsigned lds_a = __builtin_amdgcn_readfirstlane(lds0 + wave * 4096);
-  const unsigned lds_b = __builtin_amdgcn_readfirstlane(lds0 + A_BYTES + wave * 8192);
   constexpr int LOADS = 12;
   // load i (0..11) of the K tile being requested, into the stage at byte st; the last one moves on to the next K tile
   auto issue = [&](unsigned st, int i) {
     if (i < 8) {
       const char* w = (SWIGLU && (i & 2) ? ld.w_odd : ld.w_even) + ld.kb;
-      if constexpr (ONCE) load_to_lds_16_streaming(w, ld.b_off[i], lds_b + st + i * 1024);
-      else load_to_lds_16(w, ld.b_off[i], lds_b + st + i * 1024);
+      const unsigned to = ld.lds_b[i >> 2] + st + (i & 3) * 1024;
+      if constexpr (ONCE) load_to_lds_16_streaming(w, ld.b_off[i], to);
+      else load_to_lds_16(w, ld.b_off[i], to);
     } else load_to_lds_16(ld.a + ld.ka, ld.a_off[i - 8], lds_a + st + (i - 8) * 1024);
     if (i == LOADS - 1) {
       ld.ka += BK * 2;
@@ -262,8 +283,97 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
       }
     }
   };
+  // The same of a half tile: 4 groups.  Fragments of the weight rows in two sets, fb[4 * kk ..], so that all of the next step's
+  // can be read meanwhile.  Step 0 requests the token rows of the K tile two ahead, step 1, behind the wait, the weight rows of
+  // the one three ahead.
+  const char* half_b = smem + A_BYTES + wn * 8192;
+  auto read_half_b = [&](int kk, unsigned st, int i) {
+    fb[4 * kk + i] = *reinterpret_cast<const bf16x8*>(half_b + st + foff[kk] + i * 2048);
+  };
+  auto half_step = [&](auto kk_, unsigned st_next, unsigned st_load) {
+    constexpr int kk = decltype(kk_)::value, LEAD = kk == 1 ? 4 : 0;   // products before the wait
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      if (kk == 1 && g == 1) wait_loads_and_barrier<8>();
+#pragma unroll
+      for (int mi = 0; mi < 4; ++mi) {
+        acc[g][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[4 * kk + g], fa[kk][mi], acc[g][mi], 0, 0, 0);
+        const int at = 4 * g + mi - LEAD;
+        if (at >= 0 && at < 12) {
+          const int n = at - at / 3 - 1;   // two fragments behind every load
+          if (at % 3 == 0) issue(st_load, (kk == 1 ? 0 : 8) + at / 3);
+          else if (n < 4) read_a(kk ^ 1, st_next, n);
+          else read_half_b(kk ^ 1, st_next, n - 4);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
   const std::integral_constant<int, 0> k0{};
   const std::integral_constant<int, 1> k1{};
+
+  // epilogue.  sum(ni, mi) element e of lane l: token row mi*16 + l%16, weight row ni*16 + (l/16)*4 + e of the wave
+  // tile.  bf16 results pass through the wave's 2 KiB of LDS, 16 rows x 64 columns at a time (16-byte slots swizzled by
+  // the row), and leave as row segments of 128 bytes; with ONCE marked as not to be kept: what lies dirty in the XCDs' L2s at the
+  // end of a launch is written back before the next one may start (forward of 500 tokens of 64 + 2 experts 282 -> 271 us,
+  // the products of a training step of 1000 tokens 712 -> 697; 2048 and 3500 tokens of 64 experts, whose next launch
+  // finds some of it, 326.6 -> 329.4 and 467.6 -> 476.1: not there).
+  auto store = [&](auto half_) {
+    constexpr bool HALF = decltype(half_)::value;
+    char* stg = s_out[wave];
+    constexpr int W_COLS = (SWIGLU ? 64 : 128) / (HALF ? 2 : 1);      // output columns of a wave tile
+    const int rows_left = cur.rows - cur.m0 - wm * 64;
+    const int col_w = cur.n0 + wn * W_COLS;
+    const int ccol = OCC_PICK(cur, c_col0) + cur.group * OCC_PICK(cur, c_group_cols);
+    const int ldc = OCC_PICK(cur, ldc);
+    const int scol = (lane & 7) * 8, srow = lane >> 3;
+    constexpr int CH_COLS = W_COLS < 64 ? W_COLS : 64;
+    constexpr int CHUNKS = SAVE ? 3 : W_COLS / CH_COLS;   // per 16-row block; SAVE: outputs, gate, up
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+      for (int ch = 0; ch < CHUNKS; ++ch) {
+#pragma unroll
+        for (int nn = 0; nn < CH_COLS / 16; ++nn) {   // 16 output columns
+          float v[4];
+          if (SWIGLU && ch == 0) {
+            const f32x4 g = sum(2 * nn, mi), u = sum(2 * nn + 1, mi);
+            if (OCC_PICK(cur, silu_rcp)) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = swiglu_rcp(g[e], u[e]);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = swiglu_div(g[e], u[e]);
+            }
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = SWIGLU ? sum(2 * nn + ch - 1, mi)[e] : sum(4 * ch + nn, mi)[e];
+          }
+          uint2 pk;
+          pk.x = pack_bf16(v[0], v[1]);
+          pk.y = pack_bf16(v[2], v[3]);
+          const int row = lane & 15;
+          *reinterpret_cast<uint2*>(stg + row * 128 + (((nn * 2 + (lane >> 5)) ^ ((row >> 1) & 7)) * 16) +
+                                    ((lane >> 4) & 1) * 8) = pk;
+        }
+        const bool pre = SAVE && ch > 0;
+        const int col = col_w + (SWIGLU ? 0 : ch * 64) + scol;
+        __bf16* C = static_cast<__bf16*>(pre ? OCC_PICK(cur, C2) : OCC_PICK(cur, C));
+        const long long pitch = pre ? 2ll * ldc : ldc;
+        const int c0 = pre ? 2 * ccol + (ch - 1) * first.N : ccol;
+        __bf16* dst = C + (cur.row_base + cur.m0 + wm * 64 + mi * 16) * pitch + c0 + col;
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+          const int row = it * 8 + srow;
+          const u32x4 v = *reinterpret_cast<const u32x4*>(stg + row * 128 + (((lane & 7) ^ ((row >> 1) & 7)) * 16));
+          if (mi * 16 + row < rows_left && col < first.N && (CH_COLS == 64 || scol < CH_COLS)) {
+            if constexpr (ONCE) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst + row * pitch));
+            else *reinterpret_cast<u32x4*>(dst + row * pitch) = v;
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  };
 
   // first tile: rows, K tiles 0 and 1, half of K tile 2
   request_rows(cur);
@@ -318,68 +428,38 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
       step(k1, s2, st, s2);
     }
 
-    // epilogue.  sum(ni, mi) element e of lane l: token row mi*16 + l%16, weight row ni*16 + (l/16)*4 + e of the wave
-    // tile.  bf16 results pass through the wave's 2 KiB of LDS, 16 rows x 64 columns at a time (16-byte slots swizzled by
-    // the row), and leave as row segments of 128 bytes; with ONCE marked as not to be kept: what lies dirty in the XCDs' L2s at the
-    // end of a launch is written back before the next one may start (forward of 500 tokens of 64 + 2 experts 282 -> 271 us,
-    // the products of a training step of 1000 tokens 712 -> 697; 2048 and 3500 tokens of 64 experts, whose next launch
-    // finds some of it, 326.6 -> 329.4 and 467.6 -> 476.1: not there).
-    {
-      char* stg = s_out[wave];
-      constexpr int W_COLS = SWIGLU ? 64 : 128;      // output columns of a wave tile
-      const int rows_left = cur.rows - cur.m0 - wm * 64;
-      const int col_w = cur.n0 + wn * W_COLS;
-      const int ccol = OCC_PICK(cur, c_col0) + cur.group * OCC_PICK(cur, c_group_cols);
-      const int ldc = OCC_PICK(cur, ldc);
-      const int scol = (lane & 7) * 8, srow = lane >> 3;
-      constexpr int CHUNKS = SAVE ? 3 : W_COLS / 64;   // per 16-row block; SAVE: outputs, gate, up
-#pragma unroll
-      for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-        for (int ch = 0; ch < CHUNKS; ++ch) {
-#pragma unroll
-          for (int nn = 0; nn < 4; ++nn) {   // 16 output columns
-            float v[4];
-            if (SWIGLU && ch == 0) {
-              const f32x4 g = sum(2 * nn, mi), u = sum(2 * nn + 1, mi);
-              if (OCC_PICK(cur, silu_rcp)) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = swiglu_rcp(g[e], u[e]);
-              } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = swiglu_div(g[e], u[e]);
-              }
-            } else {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = SWIGLU ? sum(2 * nn + ch - 1, mi)[e] : sum(4 * ch + nn, mi)[e];
-            }
-            uint2 pk;
-            pk.x = pack_bf16(v[0], v[1]);
-            pk.y = pack_bf16(v[2], v[3]);
-            const int row = lane & 15;
-            *reinterpret_cast<uint2*>(stg + row * 128 + (((nn * 2 + (lane >> 5)) ^ ((row >> 1) & 7)) * 16) +
-                                      ((lane >> 4) & 1) * 8) = pk;
-          }
-          const bool pre = SAVE && ch > 0;
-          const int col = col_w + (SWIGLU ? 0 : ch * 64) + scol;
-          __bf16* C = static_cast<__bf16*>(pre ? OCC_PICK(cur, C2) : OCC_PICK(cur, C));
-          const long long pitch = pre ? 2ll * ldc : ldc;
-          const int c0 = pre ? 2 * ccol + (ch - 1) * first.N : ccol;
-          __bf16* dst = C + (cur.row_base + cur.m0 + wm * 64 + mi * 16) * pitch + c0 + col;
-#pragma unroll
-          for (int it = 0; it < 2; ++it) {
-            const int row = it * 8 + srow;
-            const u32x4 v = *reinterpret_cast<const u32x4*>(stg + row * 128 + (((lane & 7) ^ ((row >> 1) & 7)) * 16));
-            if (mi * 16 + row < rows_left && col < first.N) {
-              if constexpr (ONCE) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst + row * pitch));
-              else *reinterpret_cast<u32x4*>(dst + row * pitch) = v;
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-    }
+    store(std::false_type{});
     if (!more) break;   // uniform over the block
     cur = nxt;
+    if (!cur.half) continue;
+
+    // the block's last tile, a half one: its K tiles 0 and 1 and the weight rows of K tile 2 are on their way, K tile 0 has landed
+    nk = OCC_PICK(cur, K) / BK;
+    if (PARTS) {
+      parts = OCC_PICK(cur, ksplit);
+      edge = part_after(0);
+    }
+#pragma unroll
+    for (int ni = 0; ni < 8; ++ni)
+#pragma unroll
+      for (int mi = 0; mi < 4; ++mi) acc[ni][mi] = tot[PARTS ? ni : 0][mi] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) read_half_b(0, st, i);
+    half_step(k0, st, next(next(st)));
+    for (int kt = 0; kt < nk - 1; ++kt) {
+      const unsigned sn = next(st);
+      if (kt == nk - 3) {   // what is requested past the end is its first K tiles again
+        ld.ka = ld.kb = 0;
+        ld.kin = 0;
+      }
+      half_step(k1, sn, st);
+      finish_part(kt + 1);
+      half_step(k0, sn, st);
+      st = sn;
+    }
+    half_step(k1, next(st), st);
+    store(std::true_type{});
+    break;
   }
 #undef OCC_PICK
   wait_loads();   // the loads issued for a tile that does not exist must land before the block's LDS is released

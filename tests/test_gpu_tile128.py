@@ -145,6 +145,19 @@ def test_few_rows_have_the_bits_of_smaller_batches(T, part, d, f, E, S, k):
             assert np.array_equal(got, want), (name, train, np.mean(got != want))
 
 
+@pytest.mark.parametrize("T,d,f,E,S,k,D", [   # (one row tile per expert, on 256 CUs)
+    (800, 192, 320, 128, 0, 4, 4),    # gate/up 384 tiles: a round and 128, cut in 256 halves, every sixth past the columns; three K tiles
+    (800, 704, 192, 128, 0, 4, 4),    # down and dx 384; K of three tiles, and of two matrices
+    (800, 704, 320, 120, 1, 4, 4),    # up to 381 with the shared expert's in front
+])
+def test_last_tiles_in_halves(T, d, f, E, S, k, D):
+    test_tile128_products(T, d, f, E, S, k, D)
+
+
+def test_last_tiles_in_halves_with_k_in_parts():
+    test_few_rows_have_the_bits_of_smaller_batches(800, 100, 1024, 320, 118, 1, 3)   # 375 tiles, K in quarters
+
+
 @pytest.mark.parametrize("T,d,f,E,S,k,apart", [
     (140, 512, 256, 16, 4, 4, True),     # four K tiles of its own against the sixteen of the shared down projection
     (160, 1024, 512, 60, 4, 4, True),    # below 24 rows per expert
