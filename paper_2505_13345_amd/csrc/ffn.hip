@@ -1111,11 +1111,12 @@ static int k_parts(const GemmArgs& a, bool swiglu, int total_rows) {
 //    of 127 batches below 24 rows per expert 0.81 of the time apart on average (at worst 1.16), packed 0.88 (1.15).
 //    (64 + 4 experts, 155 tokens, d = 1024, f = 512: 46 us against 43; 60 + 1, 169 tokens, the same widths: 27 against 37.)
 //  - a down projection with scratch: apart, its K (S matrices long) is split over workgroups, joined it is one block's chain
-//    of about 0.75 us per K tile of 64.  Joined while what that costs (the chain's excess over a block's share of all tiles,
-//    or half the excess of the block with the most tiles, which runs on with more of the memory to itself) stays within 6 K
-//    tiles of what it saves, twice the work of `b` spread over 256 CUs: of 687 pairs it takes 272 of the 304 that gain 3 %
-//    or more and 20 that lose as much, at worst 1.13.
-//    (60 + 4 experts, 180 tokens, d = 512, f = 1088: 62 us against 36; 32 + 2, 517 tokens, 2048, 1408: 49 against 76.)
+//    of about 0.75 us per K tile of 64, and its block takes the fewer of the routed tiles (ffn_tile128.hip).  Joined while the
+//    chain's excess over a block's share of all tiles stays within 9 K tiles of what it saves, twice the work of `b` spread over
+//    256 CUs.  (90 batches of 150 - 1722 tokens, 8 - 128 experts, 1 - 4 shared ones, d = 512 - 4096, forward passes joined over
+//    apart: of the 65 taken 0.78 - 1.01, of the 25 not taken 0.94 - 1.30; the rule is nowhere more than 0.1 % off the better of the
+//    two but for two, 3 and 7 %.  60 + 4 experts, 300 tokens, d = 2048, f = 1408: 274 us against 293; 32 + 4, 461 tokens, 1024,
+//    1344: 156 against 129; 64 + 2, 1000 tokens, 2048, 1408: 292 against 322; 32 + 3, 1003 tokens, 2048, 704: 131 against 169.)
 static bool shares_launch(const GemmArgs& a, const GemmArgs& b, bool swiglu, int total_rows) {
   if (swiglu && streams_weights(a, total_rows))
     return (long long)b.ngroups * b.M * a.K > (a.Bp != nullptr ? 2 : 1) * 6144ll * a.ngroups;
@@ -1125,10 +1126,7 @@ static bool shares_launch(const GemmArgs& a, const GemmArgs& b, bool swiglu, int
   const long long tiles_a = groups > 0 ? groups * ((total_rows / groups + 127) / 128) * n_tiles : 0;   // evenly loaded experts
   const long long tiles_b = (b.M + 127) / 128 * n_tiles, tiles = tiles_a + tiles_b;
   const long long share = (tiles_a * a.K + tiles_b * b.K) / (tiles < 256 ? tiles : 256);
-  const long long most_b = (tiles_b + 255) / 256;   // tiles of the fullest block, those of `b` first
-  const long long fullest = most_b * b.K + ((tiles + 255) / 256 - most_b) * a.K;
-  const long long chain = b.K - share, last = (fullest - share) / 2;
-  return (chain > last ? chain : last) - tiles_b * b.K / 128 <= 6 * 64;
+  return b.K - share - tiles_b * b.K / 128 <= 9 * 64;
 }
 
 static int launch_preactivation_pair(const occult_cfg_t& c, const GemmArgs& a, const GemmArgs* b, int total_rows, int rows_b,

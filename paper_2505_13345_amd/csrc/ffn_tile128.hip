@@ -57,7 +57,9 @@ struct Tile {
 // their own (one wave per SIMD: there is room) and cost one addition per accumulator and part (500 tokens of 64 + 2 experts,
 // shared down projection in parts: 312 -> 318 us; 300 of 60 + 4, gate/up in quarters as well: 305 -> 325 us).
 // ONCE: the weights are requested, and the output stored, as not to be kept (launch_tile128).
-template <bool SWIGLU, bool SAVE, bool PARTS, bool ONCE>
+// ROUNDS: there may be more tiles than blocks.  A launch of a single round goes without the half tiles and what they take to set
+// up (each of its two launches 1.3 us shorter: forward of 300 tokens of 16 experts, d = f = 512, 43.5 us with, 41.2 without).
+template <bool SWIGLU, bool SAVE, bool PARTS, bool ONCE, bool ROUNDS>
 __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first, const GemmArgs second) {
   static_assert(SWIGLU || !SAVE, "pre-activations exist only with the fused activation");
   static_assert(!SAVE || !PARTS, "stored pre-activations are one sum over K");
@@ -99,8 +101,14 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
   const int cnt1 = __builtin_amdgcn_readfirstlane((total1 >> 3) + (xcd >= 8 - over1));
   const int lo1 = __builtin_amdgcn_readfirstlane(xcd * (total1 >> 3) + max(0, xcd - (8 - over1)));
   const int cnt2 = (total2 >> 3) + (xcd < over2), lo2 = xcd * (total2 >> 3) + min(xcd, over2);
-  const int whole = (cnt1 + cnt2) / stride * stride, left = cnt1 + cnt2 - whole;   // slots of whole rounds, and beyond
-  const bool halved = whole > 0 && 2 * left <= stride;   // so a block takes at most one half, as its last tile and not its first
+  // A tile of `second` with a longer K stands for `span` tiles of `first`: its block takes the next one so many rounds later.  (Shared
+  // down projection of two experts beside 64, K = 2816 against 1408, d = 2048: forward of 500 tokens 265 -> 253 us, where it
+  // now joins the launch, of 1000 tokens 303 -> 288)
+  const int span = ROUNDS && cnt2 <= stride ? second.span : 1;
+  const int slots = cnt1 + cnt2 * span;
+  const int whole = ROUNDS ? slots / stride * stride : 0, left = slots - whole;   // slots of whole rounds, and beyond
+  const bool halved = ROUNDS && whole > 0 && whole >= span * stride && 2 * left <= stride;  // so a block takes at most one half, as its last tile and not its first
+  auto slot_after = [&](int slot) { return slot + (slot < cnt2 ? span : 1) * stride; };
   auto tile_at = [&](int slot) {
     Tile t{};
     int second_half = 0;
@@ -116,8 +124,8 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
       t.m0 = within % mt2 * BM; t.n0 = within / mt2 * BN_OUT;
       t.rows = second.M;
       t.widx = second.w_base + t.group;
-    } else if (slot - cnt2 < cnt1) {
-      const int n = lo1 + slot - cnt2;
+    } else if (const int n1 = slot - cnt2 * (span == 1 ? 1 : min(slot / stride + 1, span)); n1 < cnt1) {   // (slots of `second` in the rounds up to this one)
+      const int n = lo1 + n1;
       for (int c0 = 0; c0 < first.ngroups; c0 += 64) {
         const int g = c0 + lane;
         const unsigned long long hit = __ballot(g < first.ngroups && n >= s_tpre[g] && n < s_tpre[g + 1]);
@@ -133,7 +141,7 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
       t.m0 = within % mt * BM; t.n0 = within / mt * BN_OUT;
       t.widx = first.grp_widx ? first.grp_widx[t.group] : first.w_base + t.group;
     }
-    t.half = __builtin_amdgcn_readfirstlane(t.half);
+    t.half = ROUNDS ? __builtin_amdgcn_readfirstlane(t.half) : 0;
     t.group = __builtin_amdgcn_readfirstlane(t.group);
     t.m0 = __builtin_amdgcn_readfirstlane(t.m0);
     t.n0 = __builtin_amdgcn_readfirstlane(t.n0 + second_half * (BN_OUT / 2));
@@ -156,7 +164,6 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
     long long kb;                     // byte offset of the K tile inside a token row (kt) and a weight row
     int kin, kseg;                    // K > kseg walks consecutive weight matrices
     long long ka, seg_step;
-    unsigned lds_b[2];                // where weight-row loads 0..3 and 4..7 go in a stage
   } ld;
   // tile row of this lane for index slot `lane` (0..31) of s_idx, clamped to the group
   auto idx_row = [&](const Tile& t, int r) { return t.row_base + min(t.m0 + r, t.rows - 1); };
@@ -166,9 +173,6 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
       load_to_lds_4(reinterpret_cast<const char*>(a_rows + idx_row(t, wave * 32 + (lane & 31))),
                     __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) int*)&s_idx[wave][0]));
   };
-  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
-  const unsigned lds_a = __builtin_amdgcn_readfirstlane(lds0 + wave * 4096);
-  const unsigned lds_b = __builtin_amdgcn_readfirstlane(lds0 + A_BYTES);
   auto start_loading = [&](const Tile& t) {   // the rows requested for t have landed
     const bool gather = OCC_PICK(t, a_rows) != nullptr;
     const unsigned lda = OCC_PICK(t, lda), ldb = OCC_PICK(t, ldb);
@@ -184,8 +188,9 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const unsigned chunk = (lane & 7) ^ ((i * 4 + (lane >> 4)) & 7);
-      // (a half tile's weight rows are loads 0..3 of the four waves; what the tile before requests of it beyond them are these again)
-      const int blk = t.half ? wave * 2 + ((i & 3) >> 1) : wave * 4 + (i >> 1);
+      // (a half tile's weight rows are loads 0..3 of the four waves, to where these go in any tile; what the tile before it
+      // requests beyond them are the same rows again)
+      const int blk = ROUNDS && t.half ? wave * 2 + ((i & 3) >> 1) : wave * 4 + (i >> 1);
       int ncol = t.n0 + (SWIGLU ? (blk >> 1) * 16 : blk * 16) + (i & 1) * 8 + lrow;
       if (ncol >= first.N) ncol = first.N - 1;
       ld.b_off[i] = ((unsigned)ncol * ldb + chunk * 8) * 2;   // host: a weight matrix is below 4 GiB
@@ -194,21 +199,21 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
     ld.a = static_cast<const char*>(OCC_PICK(t, A));
     ld.w_even = static_cast<const char*>(OCC_PICK(t, B)) + t.widx * stride_b * 2;
     ld.w_odd = SWIGLU ? static_cast<const char*>(OCC_PICK(t, B2)) + t.widx * stride_b * 2 : ld.w_even;
-    ld.lds_b[0] = lds_b + (t.half ? wave * 4096 : wave * 8192);
-    ld.lds_b[1] = ld.lds_b[0] + (t.half ? 16384 : 4096);   // a half tile: beyond its weight rows
     ld.ka = ld.kb = 0;
     ld.kin = 0;
     ld.kseg = OCC_PICK(t, kseg);
     ld.seg_step = (stride_b - ld.kseg) * 2;
   };
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+  const unsigned lds_a = __builtin_amdgcn_readfirstlane(lds0 + wave * 4096);
+  const unsigned lds_b = __builtin_amdgcn_readfirstlane(lds0 + A_BYTES + wave * 8192);
   constexpr int LOADS = 12;
   // load i (0..11) of the K tile being requested, into the stage at byte st; the last one moves on to the next K tile
   auto issue = [&](unsigned st, int i) {
     if (i < 8) {
       const char* w = (SWIGLU && (i & 2) ? ld.w_odd : ld.w_even) + ld.kb;
-      const unsigned to = ld.lds_b[i >> 2] + st + (i & 3) * 1024;
-      if constexpr (ONCE) load_to_lds_16_streaming(w, ld.b_off[i], to);
-      else load_to_lds_16(w, ld.b_off[i], to);
+      if constexpr (ONCE) load_to_lds_16_streaming(w, ld.b_off[i], lds_b + st + i * 1024);
+      else load_to_lds_16(w, ld.b_off[i], lds_b + st + i * 1024);
     } else load_to_lds_16(ld.a + ld.ka, ld.a_off[i - 8], lds_a + st + (i - 8) * 1024);
     if (i == LOADS - 1) {
       ld.ka += BK * 2;
@@ -286,9 +291,8 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
   // The same of a half tile: 4 groups.  Fragments of the weight rows in two sets, fb[4 * kk ..], so that all of the next step's
   // can be read meanwhile.  Step 0 requests the token rows of the K tile two ahead, step 1, behind the wait, the weight rows of
   // the one three ahead.
-  const char* half_b = smem + A_BYTES + wn * 8192;
-  auto read_half_b = [&](int kk, unsigned st, int i) {
-    fb[4 * kk + i] = *reinterpret_cast<const bf16x8*>(half_b + st + foff[kk] + i * 2048);
+  auto read_half_b = [&](int kk, unsigned st, int i) {   // (row blocks 2j and 2j + 1 of the wave tile came through one loading wave)
+    fb[4 * kk + i] = *reinterpret_cast<const bf16x8*>(frag_b + st + foff[kk] + (i >> 1) * 8192 + (i & 1) * 2048);
   };
   auto half_step = [&](auto kk_, unsigned st_next, unsigned st_load) {
     constexpr int kk = decltype(kk_)::value, LEAD = kk == 1 ? 4 : 0;   // products before the wait
@@ -392,7 +396,7 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
   __builtin_amdgcn_sched_barrier(0);
 
   while (true) {
-    slot += stride;
+    slot = slot_after(slot);
     Tile nxt = tile_at(slot);
     const bool more = nxt.valid;
     if (!more) nxt = cur;   // keeps everything derived from it addressable
@@ -431,7 +435,7 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
     store(std::false_type{});
     if (!more) break;   // uniform over the block
     cur = nxt;
-    if (!cur.half) continue;
+    if (!ROUNDS || !cur.half) continue;
 
     // the block's last tile, a half one: its K tiles 0 and 1 and the weight rows of K tile 2 are on their way, K tile 0 has landed
     nk = OCC_PICK(cur, K) / BK;
@@ -500,6 +504,8 @@ int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_
   long long blocks = ((t1 + 7) / 8 + (t2 + 7) / 8) * 8;   // one block per CU, a multiple of 8 so a block keeps its XCD
   const long long resident = cus >= 8 ? cus / 8 * 8 : 8;
   if (blocks > resident) blocks = resident;
+  const bool rounds = t1 + t2 > blocks;
+  second.span = b != nullptr && b->K > a.K ? (b->K + a.K / 2) / a.K : 1;
   const bool save = swiglu && a.C2 != nullptr, parts = a.ksplit > 1 || second.ksplit > 1;
   OCC_REQUIRE(!(save && parts) && (!parts || (a.ksplit >= 1 && (b == nullptr || second.ksplit >= 1))), OCCULT_EINVAL,
               "grouped GEMM: parts of K outside the 128-row tiles' range");
@@ -508,8 +514,10 @@ int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_
                     (long long)a.ngroups * a.N * a.K * (swiglu ? 4 : 2) > kOnceBytes;
 #define OCC_T128(SW, SAVE, PARTS)                                                                                        \
   do {                                                                                                                   \
-    if (once) hipLaunchKernelGGL((t128::grouped_gemm_bf16<SW, SAVE, PARTS, true>), grid, block, 0, s, a, second);        \
-    else hipLaunchKernelGGL((t128::grouped_gemm_bf16<SW, SAVE, PARTS, false>), grid, block, 0, s, a, second);            \
+    if (once && rounds) hipLaunchKernelGGL((t128::grouped_gemm_bf16<SW, SAVE, PARTS, true, true>), grid, block, 0, s, a, second); \
+    else if (once) hipLaunchKernelGGL((t128::grouped_gemm_bf16<SW, SAVE, PARTS, true, false>), grid, block, 0, s, a, second);     \
+    else if (rounds) hipLaunchKernelGGL((t128::grouped_gemm_bf16<SW, SAVE, PARTS, false, true>), grid, block, 0, s, a, second);   \
+    else hipLaunchKernelGGL((t128::grouped_gemm_bf16<SW, SAVE, PARTS, false, false>), grid, block, 0, s, a, second);              \
   } while (0)
   if (save) OCC_T128(true, true, false);
   else if (swiglu && parts) OCC_T128(true, false, true);

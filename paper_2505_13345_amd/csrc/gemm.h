@@ -37,6 +37,7 @@ struct GemmArgs {
   float* ws;                // small-tile kernel: [ksplit][M][N] partial sums
   int silu_rcp;             // 128-row tiles, SWIGLU: activation as the 256-row tiles compute it (hardware reciprocal)
   int rows_again;           // 128-row tiles: the rows of the product are read again soon (launch_tile128, kOnceRowsAgain)
+  int span;                 // 128-row tiles, second problem: tiles of the first that one of its tiles takes the time of (launch_tile128)
   int N;                    // output columns (for SWIGLU: columns of h)
   int K;
 };

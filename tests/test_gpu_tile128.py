@@ -149,6 +149,8 @@ def test_few_rows_have_the_bits_of_smaller_batches(T, part, d, f, E, S, k):
     (800, 192, 320, 128, 0, 4, 4),    # gate/up 384 tiles: a round and 128, cut in 256 halves, every sixth past the columns; three K tiles
     (800, 704, 192, 128, 0, 4, 4),    # down and dx 384; K of three tiles, and of two matrices
     (800, 704, 320, 120, 1, 4, 4),    # up to 381 with the shared expert's in front
+    (800, 704, 192, 100, 3, 4, 4),    # down: 300 and 21 shared, whose K is three times as long and which stand for three tiles each
+    (800, 704, 192, 160, 2, 5, 4),    # down: 480 and 21 that stand for two each; what is left of 522 in halves
 ])
 def test_last_tiles_in_halves(T, d, f, E, S, k, D):
     test_tile128_products(T, d, f, E, S, k, D)
