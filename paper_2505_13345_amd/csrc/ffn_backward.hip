@@ -177,6 +177,12 @@ extern "C" int occult_transpose_weights(const occult_cfg_t* cfg, const occult_we
   return launch_transposes(c, weights, w_down_t, w_gu_t, static_cast<hipStream_t>(stream));
 }
 
+// The memory-side cache.  Larger steps' rows do not outlast the products in it, and streaming the products' weights then only costs the
+// second reads of them: training steps of 97 - 239 rows per expert, streamed over not, 20 of up to 265 MB 0.91 - 0.99, 18 of 301 MB and more
+// with shared experts 1.00 - 1.04.  A little beyond it the weights decide, which the rows otherwise share it with: six times the rows'
+// bytes or more, 278 - 317 MB 0.94 - 0.97 (six steps), less, 279 - 293 MB 1.01 - 1.03 (three), 304 - 310 MB 0.98 - 1.03 (three).
+constexpr long long kRowsAgainBytes = 256ll << 20, kRowsAgainBytesFewer = 305ll << 20;
+
 extern "C" int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_plan_t* plan, const void* sfd_x,
                                           const void* x, const occult_weights_t* weights, const void* w_down_t,
                                           const void* w_gu_t, const void* epd_dy, const void* dy, void* epd_gu,
@@ -212,6 +218,10 @@ extern "C" int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_
   base.grp_offset = plan->exp_offset; base.grp_widx = plan->pos_expert; base.ngroups = c.E;
   sh.w_base = c.E; sh.ngroups = c.S; sh.M = c.T; sh.a_rows_total = c.T;
   const bool has_shared = c.S > 0;
+  // what the weight gradients read next: per routed row and per shared one h and [dg | du], the gradient at the output and the input
+  const long long rows_bytes = (long long)c.T * (c.k * (3ll * c.f + 2 * c.d) + (c.S > 0 ? c.S * 3ll * c.f + 2 * c.d : 0)) * elem_size(c);
+  const bool rows_again = rows_bytes <= kRowsAgainBytes ||
+                          (rows_bytes <= kRowsAgainBytesFewer && 3 * c.E * mat * elem_size(c) >= 6 * rows_bytes);
   OCC_REQUIRE(gu_saved == 0 || gu_saved == 1, OCCULT_EINVAL, "gu_saved=%d must be 0 or 1", gu_saved);
   if (!gu_saved) {   // g | u: the forward's first product without its SwiGLU epilogue, gate then up
     GemmArgs a = base, b = sh;
@@ -232,7 +242,7 @@ extern "C" int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_
   {   // dh = epd_dy W_down: contraction over d against the transposed down projection [f][d]
     GemmArgs a = base, b = sh;
     a.A = epd_dy; a.a_rows_total = n_epd;
-    a.rows_again = 1;   // by the weight gradients, as all that the next product reads and the forward kept
+    a.rows_again = rows_again;
     b.A = dy;
     a.lda = b.lda = a.ldb = b.ldb = a.kseg = b.kseg = a.K = b.K = c.d;
     a.B = b.B = w_down_t; a.b_group_stride = b.b_group_stride = mat;
@@ -251,7 +261,7 @@ extern "C" int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_
   {   // epd_dx = [dg | du] [W_gate^T | W_up^T]^T: one product over K = 2f; the shared experts' K walks their S matrices
     GemmArgs a = base, b = sh;
     a.A = epd_gu; a.lda = 2 * c.f; a.a_rows_total = n_epd;
-    a.rows_again = 1;
+    a.rows_again = rows_again;
     b.A = gu_shared; b.lda = c.S * 2 * c.f;
     b.ngroups = 1;
     a.B = b.B = w_gu_t; a.b_group_stride = b.b_group_stride = 2 * mat;

@@ -488,10 +488,11 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
 // 68.5 / 73.7, six in turn 463 / 441).  The shared experts' weights, which several row tiles read, go the same way: with 2 and
 // 4 of them a forward takes 0.78 - 0.98 up to 47 rows and 0.87 - 1.04 at 60 and 70.
 // The backward's products keep their weights out of the memory-side cache in larger batches too, up to the line of the small weight-gradient
-// tiles: these read the rows of all products next, and wait for memory at every group if the weights have taken their place
-// (1000 tokens of 64 + 2 experts, the three weight gradients 550 -> 400 us; training steps without -> with, d = 2048: f = 1408, 94 rows
-// 1685 -> 1580, with the forward's line 1526, 131 rows 1926 -> 1763, 188 rows 2105 -> 2105; f = 1024, 125 rows 1256 -> 1188, 188 rows
-// 1472 -> 1418; from 312 rows on 1 - 2 % slower: the rows of a step are then more than that cache holds).
+// tiles and while that cache holds the step's rows (ffn_backward.hip): these tiles read the rows of all products next, and wait for memory
+// at every group if the weights have taken their place (1000 tokens of 64 + 2 experts, the three weight gradients 550 -> 400 us).  35 training steps of
+// 80 - 230 rows per expert, with -> without the weights kept, one layer again and again / three in turn: 0.955 / 0.950 on average;
+// 64 + 2 experts, d = 2048, f = 1408, 100 rows 1651 -> 1521 / 1665 -> 1509 us, 130 rows 1814 -> 1637 / 1838 -> 1646, 180 rows
+// 2048 -> 1917 / 2070 -> 1900.  (With streamed weights and ordinary stores 0.962 / 0.967; with such stores alone 1.00.)
 constexpr long long kOnceRows = 96, kOnceRowsAgain = 240, kOnceBytes = 320ll << 20;
 int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, hipStream_t s) {
   const int bn_out = swiglu ? t128::BN / 2 : t128::BN;

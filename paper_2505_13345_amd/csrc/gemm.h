@@ -36,7 +36,7 @@ struct GemmArgs {
                             // y and writes its sums to ws; 128-row tiles: a block adds the parts in registers
   float* ws;                // small-tile kernel: [ksplit][M][N] partial sums
   int silu_rcp;             // 128-row tiles, SWIGLU: activation as the 256-row tiles compute it (hardware reciprocal)
-  int rows_again;           // 128-row tiles: the rows of the product are read again soon (launch_tile128, kOnceRowsAgain)
+  int rows_again;           // 128-row tiles: the rows of the product are read again soon and find place until then (launch_tile128)
   int span;                 // 128-row tiles, second problem: tiles of the first that one of its tiles takes the time of (launch_tile128)
   int N;                    // output columns (for SWIGLU: columns of h)
   int K;
