@@ -359,6 +359,15 @@ int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_plan_t* pla
                                void* epd_dh, void* epd_dx, void* gu_shared, void* dh_shared,
                                void* dx_shared, int gu_saved, occult_stream_t stream);
 
+/* The same call, with the same results, for experts whose weights are not trained: occult_expert_ffn_backward
+ * assumes that the weight gradients follow and, in batches of up to 240 rows per expert, keeps the rows that they
+ * read in the caches at the expense of its own weights; this one does not. */
+int occult_expert_ffn_backward_frozen(const occult_cfg_t* cfg, const occult_plan_t* plan, const void* sfd_x,
+                                      const void* x, const occult_weights_t* weights, const void* w_down_t,
+                                      const void* w_gu_t, const void* epd_dy, const void* dy, void* epd_gu,
+                                      void* epd_dh, void* epd_dx, void* gu_shared, void* dh_shared,
+                                      void* dx_shared, int gu_saved, occult_stream_t stream);
+
 /* Forward pass of a training step: occult_expert_ffn_ws that also keeps the pre-activations, so that
  * the backward pass need not recompute them: epd_gu [N_epd][2f] = [g | u] per EPD row and, with shared
  * experts, gu_shared [T][S*2f] = per shared expert [g | u] (rounded to cfg.dtype).  On 128- and 256-row

@@ -24,7 +24,7 @@ EXPORTS = [
     "occult_placement_greedy", "occult_plan_stats", "occult_router", "occult_dispatch_meta",
     "occult_similarity_gram", "occult_similarity_table", "occult_expert_ffn_ws_bytes", "occult_expert_ffn_ws",
     "occult_combine_backward", "occult_dispatch_backward", "occult_route_backward",
-    "occult_transpose_weights", "occult_expert_ffn_backward", "occult_expert_ffn_backward_weights",
+    "occult_transpose_weights", "occult_expert_ffn_backward", "occult_expert_ffn_backward_frozen", "occult_expert_ffn_backward_weights",
     "occult_pack_weights_bytes", "occult_pack_weights", "occult_expert_ffn_packed", "occult_expert_ffn_train",
     "occult_collaboration_stats", "occult_plan_static", "occult_combine_atomic",
     "occult_expert_ffn_backward_weights_ws_bytes", "occult_expert_ffn_backward_weights_ws", "occult_forward",
@@ -115,6 +115,7 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.occult_transpose_weights.argtypes = [cfgp, POINTER(occult_weights_t), c_void_p, c_void_p, c_void_p]
     lib.occult_expert_ffn_backward.argtypes = ([cfgp, planp, c_void_p, c_void_p, POINTER(occult_weights_t)] + [c_void_p] * 10
                                               + [c_int, c_void_p])
+    lib.occult_expert_ffn_backward_frozen.argtypes = lib.occult_expert_ffn_backward.argtypes
     lib.occult_expert_ffn_train.argtypes = [cfgp, planp, c_void_p, c_void_p, POINTER(occult_weights_t)] + [c_void_p] * 7 + [
         c_size_t, c_void_p]
     lib.occult_expert_ffn_backward_weights.argtypes = [cfgp, planp] + [c_void_p] * 11 + [c_int, c_void_p]
@@ -339,13 +340,14 @@ def occult_expert_ffn_train(cfg, plan, sfd_x, x, w_gate, w_up, w_down, epd_h, ep
 
 
 def occult_expert_ffn_backward(cfg, plan, sfd_x, x, w_gate, w_up, w_down_t, w_gu_t, epd_dy, dy, epd_gu, epd_dh, epd_dx,
-                               gu_shared=None, dh_shared=None, dx_shared=None, gu_saved=False, stream=None) -> None:
+                               gu_shared=None, dh_shared=None, dx_shared=None, gu_saved=False, stream=None,
+                               weights_follow=True) -> None:
+    lib = load_library()
     wts = occult_weights_t(_ptr(w_gate), _ptr(w_up), None)
-    _check(load_library().occult_expert_ffn_backward(ctypes.byref(cfg), ctypes.byref(plan), _ptr(sfd_x), _ptr(x),
-                                                     ctypes.byref(wts), _ptr(w_down_t), _ptr(w_gu_t), _ptr(epd_dy),
-                                                     _ptr(dy), _ptr(epd_gu), _ptr(epd_dh), _ptr(epd_dx), _ptr(gu_shared),
-                                                     _ptr(dh_shared), _ptr(dx_shared), int(bool(gu_saved)),
-                                                     _stream(stream)))
+    call = lib.occult_expert_ffn_backward if weights_follow else lib.occult_expert_ffn_backward_frozen
+    _check(call(ctypes.byref(cfg), ctypes.byref(plan), _ptr(sfd_x), _ptr(x), ctypes.byref(wts), _ptr(w_down_t), _ptr(w_gu_t),
+                _ptr(epd_dy), _ptr(dy), _ptr(epd_gu), _ptr(epd_dh), _ptr(epd_dx), _ptr(gu_shared), _ptr(dh_shared),
+                _ptr(dx_shared), int(bool(gu_saved)), _stream(stream)))
 
 
 def occult_expert_ffn_backward_weights(cfg, plan, sfd_x, x, epd_h, h_shared, epd_dy, dy, epd_gu, gu_shared, dw_gate,

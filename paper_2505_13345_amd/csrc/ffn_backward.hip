@@ -183,11 +183,11 @@ extern "C" int occult_transpose_weights(const occult_cfg_t* cfg, const occult_we
 // bytes or more, 278 - 317 MB 0.94 - 0.97 (six steps), less, 279 - 293 MB 1.01 - 1.03 (three), 304 - 310 MB 0.98 - 1.03 (three).
 constexpr long long kRowsAgainBytes = 256ll << 20, kRowsAgainBytesFewer = 305ll << 20;
 
-extern "C" int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_plan_t* plan, const void* sfd_x,
-                                          const void* x, const occult_weights_t* weights, const void* w_down_t,
-                                          const void* w_gu_t, const void* epd_dy, const void* dy, void* epd_gu,
-                                          void* epd_dh, void* epd_dx, void* gu_shared, void* dh_shared,
-                                          void* dx_shared, int gu_saved, occult_stream_t stream) {
+static int expert_ffn_backward_impl(const occult_cfg_t* cfg, const occult_plan_t* plan, const void* sfd_x, const void* x,
+                                    const occult_weights_t* weights, const void* w_down_t, const void* w_gu_t,
+                                    const void* epd_dy, const void* dy, void* epd_gu, void* epd_dh, void* epd_dx,
+                                    void* gu_shared, void* dh_shared, void* dx_shared, int gu_saved, bool weights_follow,
+                                    occult_stream_t stream) {
   int rc = check_cfg(cfg);
   if (rc) return rc;
   const occult_cfg_t c = *cfg;
@@ -220,8 +220,9 @@ extern "C" int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_
   const bool has_shared = c.S > 0;
   // what the weight gradients read next: per routed row and per shared one h and [dg | du], the gradient at the output and the input
   const long long rows_bytes = (long long)c.T * (c.k * (3ll * c.f + 2 * c.d) + (c.S > 0 ? c.S * 3ll * c.f + 2 * c.d : 0)) * elem_size(c);
-  const bool rows_again = rows_bytes <= kRowsAgainBytes ||
-                          (rows_bytes <= kRowsAgainBytesFewer && 3 * c.E * mat * elem_size(c) >= 6 * rows_bytes);
+  const bool rows_again = weights_follow &&
+                          (rows_bytes <= kRowsAgainBytes ||
+                           (rows_bytes <= kRowsAgainBytesFewer && 3 * c.E * mat * elem_size(c) >= 6 * rows_bytes));
   OCC_REQUIRE(gu_saved == 0 || gu_saved == 1, OCCULT_EINVAL, "gu_saved=%d must be 0 or 1", gu_saved);
   if (!gu_saved) {   // g | u: the forward's first product without its SwiGLU epilogue, gate then up
     GemmArgs a = base, b = sh;
@@ -274,4 +275,24 @@ extern "C" int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_
     if (rc) return rc;
   }
   return OCCULT_OK;
+}
+
+extern "C" int occult_expert_ffn_backward(const occult_cfg_t* cfg, const occult_plan_t* plan, const void* sfd_x,
+                                          const void* x, const occult_weights_t* weights, const void* w_down_t,
+                                          const void* w_gu_t, const void* epd_dy, const void* dy, void* epd_gu,
+                                          void* epd_dh, void* epd_dx, void* gu_shared, void* dh_shared,
+                                          void* dx_shared, int gu_saved, occult_stream_t stream) {
+  return expert_ffn_backward_impl(cfg, plan, sfd_x, x, weights, w_down_t, w_gu_t, epd_dy, dy, epd_gu, epd_dh, epd_dx, gu_shared,
+                                  dh_shared, dx_shared, gu_saved, true, stream);
+}
+
+// Nothing reads the rows again: streaming the weights up to 240 rows per expert would cost the second reads of them (forward and input
+// gradients of 130 - 230 rows per expert, weights streamed over kept, 1.01 - 1.08, 1.035 on average).
+extern "C" int occult_expert_ffn_backward_frozen(const occult_cfg_t* cfg, const occult_plan_t* plan, const void* sfd_x,
+                                                 const void* x, const occult_weights_t* weights, const void* w_down_t,
+                                                 const void* w_gu_t, const void* epd_dy, const void* dy, void* epd_gu,
+                                                 void* epd_dh, void* epd_dx, void* gu_shared, void* dh_shared,
+                                                 void* dx_shared, int gu_saved, occult_stream_t stream) {
+  return expert_ffn_backward_impl(cfg, plan, sfd_x, x, weights, w_down_t, w_gu_t, epd_dy, dy, epd_gu, epd_dh, epd_dx, gu_shared,
+                                  dh_shared, dx_shared, gu_saved, false, stream);
 }

@@ -45,6 +45,8 @@ class OccultLayer:
         # epd_gu and gu_shared hold the pre-activations of the present plan, rows and inputs: set by expert_ffn_train(),
         # cleared by every step that brings another plan, other rows or other outputs, and by the backward that overwrites them
         self.gu_saved = False
+        # whether weight gradients are to be expected after the next input gradients: they came after the last ones
+        self.weights_follow = True
         if with_ffn:
             ws_bytes = B.occult_expert_ffn_ws_bytes(self.cfg)
             if ws_bytes:
@@ -238,8 +240,10 @@ class OccultLayer:
         if gu_saved is None:   # pre-activations kept by expert_ffn_train() for this very batch
             gu_saved = self.gu_saved
         B.occult_expert_ffn_backward(self.cfg, self.plan, self.sfd_x, x, w_gate, w_up, self.w_down_t, self.w_gu_t,
-                                     epd_dy, dy, epd_gu, epd_dh, epd_dx, gu_sh, dh_sh, dx_sh, gu_saved)
+                                     epd_dy, dy, epd_gu, epd_dh, epd_dx, gu_sh, dh_sh, dx_sh, gu_saved,
+                                     weights_follow=self.weights_follow)
         self.gu_saved = False      # overwritten with [dg | du]
+        self.weights_follow = False
         return epd_dx, dx_sh
 
     def expert_ffn_backward_weights(self, x, dy, accumulate=False, use_ws=True):
@@ -259,6 +263,7 @@ class OccultLayer:
         B.occult_expert_ffn_backward_weights_ws(self.cfg, self.plan, self.sfd_x, x, self.epd_h, self.h_shared, self.epd_dy,
                                                 dy, self.epd_gu, getattr(self, "gu_shared", None), dw_gate, dw_up, dw_down,
                                                 ws, accumulate)
+        self.weights_follow = True
         return dw_gate, dw_up, dw_down
 
     def backward_input(self, x, w_gate, w_up, dy):

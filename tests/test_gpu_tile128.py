@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from inputs import workloads as wl
+from paper_2505_13345_amd import binding as B
 from paper_2505_13345_amd.layer import OccultLayer
 from tests.helpers import assert_one_rounding, require_gpu, say, to_dev
 
@@ -252,3 +253,58 @@ def test_weights_read_once_give_the_same_bits(T):
     for name in ("epd_h", "epd_y"):
         got, want = _bits(getattr(whole, name))[rows[:, 0]], _bits(getattr(small, name))[rows[:, 1]]
         assert np.array_equal(got, want), (name, np.mean(got != want))
+
+
+def _even_logits(T, E, k, gen, dev):
+    """Scores whose top k are k neighbouring experts, dealt out in turn: T * k / E rows in every group."""
+    lg = torch.rand((T, E), device=dev, generator=gen)
+    chosen = (torch.arange(T, device=dev)[:, None] * k + torch.arange(k, device=dev)[None]) % E
+    return lg.scatter_add_(1, chosen, torch.full((T, k), 2.0, device=dev))
+
+
+def test_input_gradients_alone_are_those_of_a_training_step(monkeypatch):
+    """130 rows per expert and weights larger than the memory-side cache: where weight gradients follow, the input gradients' products
+    stream their weights, alone they do not; the last tiles in halves, a shared one standing for two.  Every output is the same bits,
+    and the f64 product of its stored operands rounded once.  A layer expects weight gradients unless none followed the last time."""
+    T, d, f, E, S, k = 520, 2048, 2688, 32, 2, 8
+    say(f"input gradients alone T={T} d={d} f={f} E={E} S={S} k={k}")
+    dev = require_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(2)
+    rand = lambda *shape: torch.randn(shape, device=dev, generator=gen)
+    lg, x, dy = _even_logits(T, E, k, gen, dev), rand(T, d).bfloat16(), rand(T, d).bfloat16()
+    w = [torch.randn((E + S, *s), device=dev, generator=gen, dtype=torch.bfloat16).mul_(s[1] ** -0.5) for s in ((f, d), (f, d), (d, f))]
+    layer = OccultLayer(T, d, f, E, S, k, 4, "bf16")
+    layer.transpose_weights(*w)
+    follow, call = [], B.occult_expert_ffn_backward
+    monkeypatch.setattr(B, "occult_expert_ffn_backward", lambda *a, **kw: (follow.append(kw["weights_follow"]), call(*a, **kw)))
+    names = ("epd_dh", "epd_gu", "epd_dx", "dh_shared", "gu_shared", "dx_shared")
+    got = []
+    for step in range(4):
+        layer.forward(lg, x, *w, train=True)
+        layer.backward_input(x, w[0], w[1], dy)
+        if step < 2:
+            torch.cuda.synchronize()
+            got.append([getattr(layer, n).clone() for n in names])
+        else:
+            layer.expert_ffn_backward_weights(x, dy)
+    torch.cuda.synchronize()
+    assert follow == [True, False, False, True]
+    for name, a, b in zip(names, *got):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16)), name
+    off, expert = (layer.tables()[n].cpu().numpy() for n in ("exp_offset", "pos_expert"))
+    assert set(np.diff(off)) == {T * k // E}
+    dh, dgu, dx, dhs, dgus, dxs = got[0]
+    f64 = lambda t: t.double().cpu().numpy()
+    dx_ref = 0
+    for P, e in [(P, int(expert[P])) for P in range(E)] + [(None, E + s) for s in range(S)]:
+        wg, wu, wd = (t[e].double() for t in w)
+        if P is not None:
+            r = slice(off[P], off[P + 1])
+            assert_one_rounding(f64(dh[r]), f64(layer.epd_dy[r].double() @ wd), f"dh expert {e}")
+            assert_one_rounding(f64(dx[r]), f64(dgu[r, :f].double() @ wg + dgu[r, f:].double() @ wu), f"dx expert {e}")
+        else:
+            c = (e - E) * f
+            assert_one_rounding(f64(dhs[:, c:c + f]), f64(dy.double() @ wd), f"dh shared {e}")
+            dx_ref = dx_ref + dgus[:, 2 * c:2 * c + f].double() @ wg + dgus[:, 2 * c + f:2 * c + 2 * f].double() @ wu
+    assert_one_rounding(f64(dxs), f64(dx_ref), "dx shared")
