@@ -405,8 +405,10 @@ __global__ __launch_bounds__(kTPB) void plan_fill(const int32_t* __restrict__ id
 // two kinds routes all tokens for itself, four at a time: a chain of about 2 us, in place of a launch of that length, one of 6 us and the
 // gaps behind both.  The products read the rows of x that the plan's tables name as copies; same bits.
 // Which batches (us per pass, separate / this, three layers in turn; d = 2048 unless given):
-//  - up to 4 tokens, one round of routing: all.  1 token: 60 + 4 experts of f = 1408, k = 4 53.0 / 44.0, 64 of 1024, k = 8 47.0 / 37.4, 256 of
-//    512, d = 512 33.3 / 24.6; 4 tokens 75.2 / 65.0, 81.6 / 72.8, 36.9 / 27.2; pruned 92.7 / 84.0.
+//  - up to 4 tokens, one round of routing: all with up to 2560 workgroups that route, or 6 d.  1 token: 60 + 4 experts of f = 1408, k = 4
+//    53.0 / 44.0, 64 of 1024, k = 8 47.0 / 37.4, 256 of 512, d = 512 33.3 / 24.6; 4 tokens 75.2 / 65.0, 81.6 / 72.8, 36.9 / 27.2; pruned
+//    92.7 / 84.0.  4 tokens, 64 experts, k = 8: 2560 workgroups, d = 64 48.0 / 48.0, 256 67.2 / 65.2; 3072, d = 64 53.1 / 54.8, 256 76.7 / 78.2;
+//    4096, d = 64 62.9 / 68.5, 512 111 / 116, 1024 170 / 165, 2048 258 / 248; 6144, d = 1024 228 / 227, 2048 382 / 368.
 //  - more where the workgroups that route are few for what each of them streams (128 bytes per element of K), since every round of them
 //    over the CUs routes again: 8 tokens of 60 + 4 113 / 107, 64 + 2 135 / 125, 64 of 1024 116 / 110, d = 1024 and f = 704 53 / 45; 12 tokens
 //    139 / 131, d = 4096 330 / 320, 64 of 1024 139 / 138.  Past the line: d = 1024, f = 1408, k = 8, 8 tokens 94 / 96, d = 512 66 / 72; 16 tokens
@@ -643,7 +645,8 @@ static long long front_blocks(const occult_cfg_t& c) { return (long long)min_i(c
 
 bool fits_front(const occult_cfg_t& c) {
   if (c.T < 1 || c.T > kFrontTokens || c.k > kFrontSlots || (size_t)c.d * elem_size(c) / 16 > 64 * 8) return false;
-  return c.T <= 4 || (c.n_d == 0 && c.E <= 64 && 10 * front_blocks(c) <= 11ll * c.d);
+  if (c.T <= 4) return front_blocks(c) <= 2560 || front_blocks(c) <= 6ll * c.d;
+  return c.n_d == 0 && c.E <= 64 && 10 * front_blocks(c) <= 11ll * c.d;
 }
 
 int check_plan_dispatch_args(const occult_cfg_t* cfg, const int32_t* ids, const float* w, const occult_plan_t* plan, void* ws,

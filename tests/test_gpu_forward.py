@@ -1,5 +1,7 @@
 """layer.forward() is one call into the library: the same bits in every buffer as the five steps called one by one, for
 each kind of expert computation, and the errors of the steps."""
+import ctypes
+
 import pytest
 import torch
 
@@ -121,6 +123,45 @@ def test_forward_of_a_few_tokens(T, d, f, E, S, k, D, n_d, mode, packed):
     for name in ("plan_mem", "ids", "w", "sfd_x", "sfd_y", "y", "epd_h", "epd_y", "h_shared", "y_shared"):
         a, b = getattr(one, name), getattr(steps, name)
         assert a is None or torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+def _kernels_of(call):
+    """Kernel launches of a call, counted as the nodes of its graph."""
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    n = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("T,d,f,E,S,k,n_d,merged", [
+    (1, 256, 64, 60, 4, 4, 0, True), (4, 192, 64, 256, 1, 8, 2, True), (12, 1408, 384, 64, 1, 8, 0, True),
+    (13, 320, 64, 16, 2, 2, 0, False), (5, 128, 128, 65, 0, 3, 0, False), (5, 128, 128, 16, 0, 3, 2, False),
+    (12, 256, 384, 64, 0, 8, 0, False), (4, 64, 64, 16, 0, 9, 0, False), (1, 4160, 64, 16, 1, 2, 0, False),
+    # 2560 workgroups that route and one column block more; 6 d of them and more
+    (4, 64, 2560, 32, 0, 8, 0, True), (4, 64, 2624, 32, 0, 8, 0, False),
+    (4, 448, 2688, 32, 1, 8, 0, True), (4, 448, 2752, 32, 1, 8, 0, False),
+])
+def test_which_forward_passes_merge_their_first_launches(T, d, f, E, S, k, n_d, merged):
+    say(f"launches of forward T={T} d={d} f={f} E={E} S={S} k={k} n_d={n_d}")
+    dev = require_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(T + f)
+    bf = lambda *shape: torch.randn(shape, device=dev, generator=gen).mul_(0.05).to(torch.bfloat16)
+    x, w, lg = bf(T, d), (bf(E + S, f, d), bf(E + S, f, d), bf(E + S, d, f)), torch.randn((T, E), device=dev, generator=gen)
+    one, steps = (OccultLayer(T, d, f, E, S, k, 4 if E % 4 == 0 else 5, "bf16", n_d) for _ in range(2))
+    one.forward(lg, x, *w)
+    steps.route(lg)
+    steps.make_plan()
+    steps.dispatch(x)
+    steps.expert_ffn(x, *w)
+    steps.combine()
+    torch.cuda.synchronize()
+    assert torch.equal(one.y.view(torch.int16), steps.y.view(torch.int16))
+    launches = _kernels_of(lambda: one.forward(lg, x, *w))
+    assert launches == 3 if merged else launches > 3
 
 
 @pytest.mark.parametrize("S,one_call", [(0, True), (1, True), (0, False), (1, False)])
