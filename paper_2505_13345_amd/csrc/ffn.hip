@@ -1274,12 +1274,14 @@ static int expert_ffn_impl(const occult_cfg_t* cfg, const occult_plan_t* plan, c
   const int n_epd = c.T * c.k;
 
   const bool do1 = c.ffn_phase != 2, do2 = c.ffn_phase != 1;
+  const int once_rows = epd_gu != nullptr ? kOnceTrain : c.S > c.k ? kOnceForwardShared : kOnceForward;
 
   if (do1) {   // h = silu(x W_gate^T) * (x W_up^T); the S shared experts as S groups over the same T rows
     GemmArgs g1, a1;
     gate_up_products(c, x, weights, packed, epd_h, h_shared, &g1, &a1);
     g1.A = sfd_x; g1.a_rows = plan->epd_sfd_row; g1.a_rows_total = sfd_rows_max(c);
     g1.C2 = epd_gu;      // rows of 2f: [gate | up]
+    g1.once_rows = once_rows;
     a1.C2 = gu_shared;   // rows of S * 2f: per shared expert [gate | up]
     g1.grp_offset = plan->exp_offset; g1.grp_widx = plan->pos_expert;
     if (pairs_shared_with_routed(c)) {
@@ -1306,6 +1308,7 @@ static int expert_ffn_impl(const occult_cfg_t* cfg, const occult_plan_t* plan, c
     a2.C = y_shared; a2.ldc = c.d;
     g2.grp_offset = plan->exp_offset; g2.grp_widx = plan->pos_expert; g2.ngroups = c.E;
     g2.a_rows_total = n_epd;
+    g2.once_rows = once_rows;
     a2.w_base = c.E; a2.ngroups = 1; a2.M = c.T; a2.a_rows_total = c.T;
     if (pairs_shared_with_routed(c)) {
       a2.Bp = g2.Bp;

@@ -215,7 +215,7 @@ static int expert_ffn_backward_impl(const occult_cfg_t* cfg, const occult_plan_t
   // routed experts: groups = placement positions over the EPD rows; shared experts: S uniform groups over the T rows
   // of x, every token with weight 1
   GemmArgs base{}, sh{};
-  base.grp_offset = plan->exp_offset; base.grp_widx = plan->pos_expert; base.ngroups = c.E;
+  base.grp_offset = plan->exp_offset; base.grp_widx = plan->pos_expert; base.ngroups = c.E; base.once_rows = kOnceTrain;
   sh.w_base = c.E; sh.ngroups = c.S; sh.M = c.T; sh.a_rows_total = c.T;
   const bool has_shared = c.S > 0;
   // what the weight gradients read next: per routed row and per shared one h and [dg | du], the gradient at the output and the input
@@ -243,7 +243,7 @@ static int expert_ffn_backward_impl(const occult_cfg_t* cfg, const occult_plan_t
   {   // dh = epd_dy W_down: contraction over d against the transposed down projection [f][d]
     GemmArgs a = base, b = sh;
     a.A = epd_dy; a.a_rows_total = n_epd;
-    a.rows_again = rows_again;
+    if (rows_again) a.once_rows = kOnceRowsAgain;
     b.A = dy;
     a.lda = b.lda = a.ldb = b.ldb = a.kseg = b.kseg = a.K = b.K = c.d;
     a.B = b.B = w_down_t; a.b_group_stride = b.b_group_stride = mat;
@@ -262,7 +262,7 @@ static int expert_ffn_backward_impl(const occult_cfg_t* cfg, const occult_plan_t
   {   // epd_dx = [dg | du] [W_gate^T | W_up^T]^T: one product over K = 2f; the shared experts' K walks their S matrices
     GemmArgs a = base, b = sh;
     a.A = epd_gu; a.lda = 2 * c.f; a.a_rows_total = n_epd;
-    a.rows_again = rows_again;
+    if (rows_again) a.once_rows = kOnceRowsAgain;
     b.A = gu_shared; b.lda = c.S * 2 * c.f;
     b.ngroups = 1;
     a.B = b.B = w_gu_t; a.b_group_stride = b.b_group_stride = 2 * mat;

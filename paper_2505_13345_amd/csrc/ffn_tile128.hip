@@ -481,19 +481,22 @@ __global__ __launch_bounds__(256, 1) void grouped_gemm_bf16(const GemmArgs first
 // (us without / with: 64 experts, d = 2048, f = 1408, gate/up + down, 24 rows per expert 159 + 97 / 150 + 92, 47 rows
 // 169 + 106 / 163 + 96; 38 rows of f = 1024, 537 MB of gate/up 100 / 92, 268 MB of down 47 / 52; d = 1152, f = 704, 207 MB of gate/up
 // 44 / 55).  The line is put above the cache's size because it holds other tensors too; between 268 and 377 MB of weights
-// nothing was measured that would move it.  By rows, forward passes of three layers in turn / of one again and again, without -> with: f = 1408,
+// nothing was measured that would move it.  By rows (GemmArgs::once_rows), forward passes of three layers in turn / of one again and again, without -> with: f = 1408,
 // 64 + 2 experts, 75 rows 306 -> 303 / 303 -> 302, 94 rows 324 -> 320 / 312 -> 311, 112 rows 345 -> 366 / 334 -> 372; 60 + 4, 73 rows
 // 369 -> 366 / 369 -> 349, 100 rows 406 -> 399 / 400 -> 392; f = 1024, 64 experts, 75 rows 259 -> 233 / 261 -> 214, 100 rows 232 -> 243 /
 // 227 -> 250.  Below the line of bytes layers in turn gain by it what one layer loses (64 experts of 768 x 512, 47 rows, one layer
 // 68.5 / 73.7, six in turn 463 / 441).  The shared experts' weights, which several row tiles read, go the same way: with 2 and
-// 4 of them a forward takes 0.78 - 0.98 up to 47 rows and 0.87 - 1.04 at 60 and 70.
+// 4 of them a forward takes 0.78 - 0.98 up to 47 rows and 0.87 - 1.04 at 60 and 70.  Where these have more rows than the routed experts,
+// streaming loses beyond 72 (77 - 92 rows, streamed over kept, 2 - 4 shared experts, k = 1 and 2: 1.00 - 1.07); other
+// forward passes from 88 on (20 sizes of 72 - 88 rows 0.94 - 1.00, 10 of 90 - 95 rows 0.97 - 1.04, three layers in turn).  One that keeps its
+// pre-activations gains for the step behind it up to 95 rows (26 training steps 0.95 - 1.00).
 // The backward's products keep their weights out of the memory-side cache in larger batches too, up to the line of the small weight-gradient
 // tiles and while that cache holds the step's rows (ffn_backward.hip): these tiles read the rows of all products next, and wait for memory
 // at every group if the weights have taken their place (1000 tokens of 64 + 2 experts, the three weight gradients 550 -> 400 us).  35 training steps of
-// 80 - 230 rows per expert, with -> without the weights kept, one layer again and again / three in turn: 0.955 / 0.950 on average;
+// 80 - 230 rows per expert, streamed over kept, one layer again and again / three in turn: 0.955 / 0.950 on average, kept -> streamed
 // 64 + 2 experts, d = 2048, f = 1408, 100 rows 1651 -> 1521 / 1665 -> 1509 us, 130 rows 1814 -> 1637 / 1838 -> 1646, 180 rows
 // 2048 -> 1917 / 2070 -> 1900.  (With streamed weights and ordinary stores 0.962 / 0.967; with such stores alone 1.00.)
-constexpr long long kOnceRows = 96, kOnceRowsAgain = 240, kOnceBytes = 320ll << 20;
+constexpr long long kOnceBytes = 320ll << 20;
 int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_rows, hipStream_t s) {
   const int bn_out = swiglu ? t128::BN / 2 : t128::BN;
   const long long n_tiles = (a.N + bn_out - 1) / bn_out;
@@ -521,7 +524,7 @@ int launch_tile128(const GemmArgs& a, const GemmArgs* b, bool swiglu, int total_
   OCC_REQUIRE(!(save && parts) && (!parts || (a.ksplit >= 1 && (b == nullptr || second.ksplit >= 1))), OCCULT_EINVAL,
               "grouped GEMM: parts of K outside the 128-row tiles' range");
   const dim3 grid((unsigned)blocks), block(256);
-  const bool once = total_rows < (a.rows_again ? kOnceRowsAgain : kOnceRows) * a.ngroups &&
+  const bool once = total_rows < (long long)a.once_rows * a.ngroups &&
                     (long long)a.ngroups * a.N * a.K * (swiglu ? 4 : 2) > kOnceBytes;
 #define OCC_T128(SW, SAVE, PARTS)                                                                                        \
   do {                                                                                                                   \

@@ -36,7 +36,7 @@ struct GemmArgs {
                             // y and writes its sums to ws; 128-row tiles: a block adds the parts in registers
   float* ws;                // small-tile kernel: [ksplit][M][N] partial sums
   int silu_rcp;             // 128-row tiles, SWIGLU: activation as the 256-row tiles compute it (hardware reciprocal)
-  int rows_again;           // 128-row tiles: the rows of the product are read again soon and find place until then (launch_tile128)
+  int once_rows;            // 128-row tiles: rows per group below which large weights are read, and the output stored, as not to be kept
   int span;                 // 128-row tiles, second problem: tiles of the first that one of its tiles takes the time of (launch_tile128)
   int N;                    // output columns (for SWIGLU: columns of h)
   int K;
@@ -45,6 +45,10 @@ struct GemmArgs {
 // Launches C[rows][N] = A[rows][K] x B[group][N][K]^T group by group (cfg.dtype: bf16 on MFMA with f32
 // accumulation, or f32 matrix instructions); with `swiglu` the output is silu(A B^T) * (A B2^T).  `total_rows` = logical
 // rows over all groups.  Picks the tile shape from the rows per group.  Returns an OCCULT_* code.
+// GemmArgs::once_rows (figures at launch_tile128): a forward pass, one whose shared experts have more rows than the routed ones, and one
+// that keeps pre-activations; the input gradients, and those whose rows the weight gradients find in the caches
+constexpr int kOnceForward = 88, kOnceForwardShared = 72, kOnceTrain = 96, kOnceRowsAgain = 240;
+
 int launch_gemm(const occult_cfg_t& c, const GemmArgs& a, bool swiglu, int total_rows, hipStream_t s);
 
 // The same product for the routed experts (`a`, grouped rows) and, unless b is NULL, for the shared ones (`b`,
