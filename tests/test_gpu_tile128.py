@@ -150,7 +150,8 @@ def test_few_rows_have_the_bits_of_smaller_batches(T, part, d, f, E, S, k):
     (800, 192, 320, 128, 0, 4, 4),    # gate/up 384 tiles: a round and 128, cut in 256 halves, every sixth past the columns; three K tiles
     (800, 704, 192, 128, 0, 4, 4),    # down and dx 384; K of three tiles, and of two matrices
     (800, 704, 320, 120, 1, 4, 4),    # up to 381 with the shared expert's in front
-    (800, 704, 192, 100, 3, 4, 4),    # down: 300 and 21 shared, whose K is three times as long and which stand for three tiles each
+    (800, 704, 192, 100, 3, 4, 4),    # down: 300 and 21 shared, whose K is three times as long and which stand for three tiles each; none in halves
+    (800, 704, 192, 240, 3, 8, 4),    # down and dx: 720 and 21 that stand for three each; what is left of 783 in halves
     (800, 704, 192, 160, 2, 5, 4),    # down: 480 and 21 that stand for two each; what is left of 522 in halves
 ])
 def test_last_tiles_in_halves(T, d, f, E, S, k, D):
@@ -260,6 +261,45 @@ def _even_logits(T, E, k, gen, dev):
     lg = torch.rand((T, E), device=dev, generator=gen)
     chosen = (torch.arange(T, device=dev)[:, None] * k + torch.arange(k, device=dev)[None]) % E
     return lg.scatter_add_(1, chosen, torch.full((T, k), 2.0, device=dev))
+
+
+@pytest.mark.parametrize("E,S,D,train", [(64, 2, 4, False), (64, 2, 4, True), (70, 0, 2, False)])
+def test_streamed_weights_with_last_tiles_in_halves(E, S, D, train):
+    """500 tokens, 42 - 47 rows in every group, weights larger than the memory-side cache: both products stream them and have tiles in
+    halves, beside shared experts with a tile of the down projection standing for two (in parts of K, with the layer's scratch).
+    Every output is the f64 product of its stored operands rounded once."""
+    T, d, f, k = 500, 2048, 1408, 6
+    say(f"streamed weights and half tiles T={T} d={d} f={f} E={E} S={S} k={k} train={train}")
+    dev = require_gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(3)
+    lg, x = _even_logits(T, E, k, gen, dev), torch.randn((T, d), device=dev, generator=gen).bfloat16()
+    w = [torch.randn((E + S, *s), device=dev, generator=gen, dtype=torch.bfloat16).mul_(s[1] ** -0.5) for s in ((f, d), (f, d), (d, f))]
+    layer = OccultLayer(T, d, f, E, S, k, D, "bf16")
+    layer.forward(lg, x, *w, train=train)
+    torch.cuda.synchronize()
+    tab = layer.tables()
+    off, expert, src = (tab[n].cpu().numpy() for n in ("exp_offset", "pos_expert", "epd_sfd_row"))
+    assert set(np.diff(off)) <= {T * k // E, T * k // E + 1}
+    f64 = lambda t: t.double().cpu().numpy()
+
+    def check(tag, e, rows, h, gu):
+        g, u = rows.double() @ w[0][e].double().T, rows.double() @ w[1][e].double().T
+        assert_one_rounding(f64(h), f64(g / (1.0 + torch.exp(-g)) * u), f"h {tag}")
+        if gu is not None:
+            assert_one_rounding(f64(gu), f64(torch.cat([g, u], 1)), f"pre-activations {tag}")
+
+    for P in range(E):
+        r, e = slice(off[P], off[P + 1]), int(expert[P])
+        check(f"expert {e}", e, layer.sfd_x[torch.from_numpy(src[r]).long().to(dev)], layer.epd_h[r], layer.epd_gu[r] if train else None)
+        assert_one_rounding(f64(layer.epd_y[r]), f64(layer.epd_h[r].double() @ w[2][e].double().T), f"y expert {e}")
+    y = 0
+    for s in range(S):
+        h = layer.h_shared[:, s * f:(s + 1) * f]
+        check(f"shared {s}", E + s, x, h, layer.gu_shared[:, s * 2 * f:(s + 1) * 2 * f] if train else None)
+        y = y + h.double() @ w[2][E + s].double().T
+    if S:
+        assert_one_rounding(f64(layer.y_shared), f64(y), "y shared")
 
 
 def test_input_gradients_alone_are_those_of_a_training_step(monkeypatch):
