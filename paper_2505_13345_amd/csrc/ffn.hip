@@ -1113,10 +1113,11 @@ static int k_parts(const GemmArgs& a, bool swiglu, int total_rows) {
 //  - a down projection with scratch: apart, its K (S matrices long) is split over workgroups, joined it is one block's chain
 //    of about 0.75 us per K tile of 64, and its block takes the fewer of the routed tiles (ffn_tile128.hip).  Joined while the
 //    chain's excess over a block's share of all tiles stays within 9 K tiles of what it saves, twice the work of `b` spread over
-//    256 CUs.  (90 batches of 150 - 1722 tokens, 8 - 128 experts, 1 - 4 shared ones, d = 512 - 4096, forward passes joined over
-//    apart: of the 65 taken 0.78 - 1.01, of the 25 not taken 0.94 - 1.30; the rule is nowhere more than 0.1 % off the better of the
-//    two but for two, 3 and 7 %.  60 + 4 experts, 300 tokens, d = 2048, f = 1408: 274 us against 293; 32 + 4, 461 tokens, 1024,
-//    1344: 156 against 129; 64 + 2, 1000 tokens, 2048, 1408: 292 against 322; 32 + 3, 1003 tokens, 2048, 704: 131 against 169.)
+//    256 CUs.  (Forward passes joined over apart, 8 - 128 experts, 1 - 4 shared ones, d = 512 - 4096: of 90 batches of 150 - 1722 tokens
+//    from 24 rows per expert on the 69 taken 0.75 - 1.04, 0.90 on average, the 21 left apart 0.94 - 1.24; of 40 of 139 - 476 tokens
+//    below 24 rows the 31 taken 0.85 - 1.00, with packed weights, which the tiles do not read, 0.91 - 1.00, the 9 left 0.95 - 1.10 and
+//    0.99 - 1.12.  Joined / apart, d = 2048, f = 1408: 64 + 2 experts, 1000 tokens 311 / 358 us, 200 tokens 237 / 276, packed 238 / 259;
+//    left apart: 60 + 4, 300 tokens 276 / 295, its worst miss, 200 tokens packed 256 / 248; 64 + 4, 476 tokens, 1024, 896 154 / 143.)
 static bool shares_launch(const GemmArgs& a, const GemmArgs& b, bool swiglu, int total_rows) {
   if (swiglu && streams_weights(a, total_rows))
     return (long long)b.ngroups * b.M * a.K > (a.Bp != nullptr ? 2 : 1) * 6144ll * a.ngroups;
