@@ -235,7 +235,7 @@ def test_many_rows_have_the_bits_of_larger_batches(train):
 
 @pytest.mark.parametrize("T", [800, 1100])
 def test_weights_read_once_give_the_same_bits(T):
-    """Below 96 rows per expert, and with weights larger than the memory-side cache, the weights are requested as not to be
+    """Below 88 rows per expert, and with weights larger than the memory-side cache, the weights are requested as not to be
     kept: the rows of the first 500 tokens are those that the same tokens get in a batch of 800 or 1100."""
     d, f, E, k, part = 2048, 1408, 64, 6, 500
     say(f"weights read once: {part} and {T} tokens E={E} d={d} f={f}")
